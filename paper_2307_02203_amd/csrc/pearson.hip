@@ -6,7 +6,7 @@
 // The ensemble is member-major, so a member row is a contiguous stream over
 // vertices and every kernel below reads it with coalesced row segments.
 //
-// * pearson_gemv_kernel: one reference, FP32 FMA, four vertices per thread
+// * pearson_fp32_kernel: up to eight references, FP32 FMA, four vertices per thread
 //   (16-byte loads); bound by the 4 B/sample HBM stream.
 // * pearson_gemm_kernel: up to 64 references at once as a contraction over
 //   members on MFMA 32x32x16 bf16.  Standardised members are split into
@@ -35,42 +35,197 @@ __global__ void pearson_refcols_kernel(const float *__restrict__ x, const double
 }
 
 // ---------------------------------------------------------------- GEMV ----
-template <bool VEC>
-__global__ __launch_bounds__(256) void pearson_gemv_kernel(
-    const float *__restrict__ x, const double *__restrict__ mean,
-    const double *__restrict__ inv_std, int N, int64_t V, const float *__restrict__ zr,
-    float *__restrict__ out) {
-    const int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    if (v >= V) return;
-    float mu[4], sc[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
-    const float invN = 1.0f / (float)N;
-    for (int e = 0; e < 4; ++e) {
-        const int64_t ve = v + e < V ? v + e : V - 1;
-        mu[e] = (float)mean[ve];
-        sc[e] = (float)(inv_std[ve] / (double)N);
+// FP32 fields of up to R references in one read of the ensemble.  A workgroup
+// first forms the references' standardised columns in LDS (z[m][r], N strided
+// reads per reference from L2), so a call is one launch per eight references.
+//
+// A lane owns VW consecutive vertices and streams their member rows; eight rows
+// are in flight.  A row may start at any multiple of 4 bytes (V need not be a
+// multiple of 4), which the global loads allow; the last lane of a row steps back
+// to V - VW and leaves out what its neighbour stores.  R references cost R + 1
+// VALU per element, at R = 8 0.4 ms of VALU against 1.1 ms of HBM per 7 GB.
+//
+// S: the waves of a workgroup that share its vertices, each summing a contiguous
+// share of the members; their partial sums meet in LDS in wave order.  S = 1
+// keeps the plain sum over members.
+//
+// Measured against one launch per reference of 256 lanes x 4 vertices (scalar loads
+// when V % 4 != 0, the member loop never split): 5 references, 200 members, 37 x 29 x 11
+// vertices 398 -> 9.3 us (a serial chain of 200 loads in 12 workgroups before); one
+// reference, 1000 members, 1.76M vertices 1.109 ms both (6.35 TB/s, the HBM stream).
+template <int VW>
+struct row_vec;
+template <>
+struct row_vec<1> {
+    typedef float type;
+};
+template <>
+struct row_vec<4> {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+
+constexpr int kFp32Refs = 8;         // references per launch
+constexpr int kFp32Chunk = 1024;     // members of z in LDS at a time
+
+struct RefList {
+    int64_t v[kFp32Refs];
+};
+
+constexpr int fp32_waves(int S) { return S == 1 ? 4 : S; }
+
+template <int R, int VW, int S>
+__global__ __launch_bounds__(64 * fp32_waves(S)) void pearson_fp32_kernel(
+    const float *__restrict__ xr, const double *__restrict__ mean_r,
+    const double *__restrict__ inv_std_r, const float *__restrict__ x,
+    const double *__restrict__ mean, const double *__restrict__ inv_std, int N, int64_t V,
+    RefList refs, int n_ref, float *__restrict__ out) {
+    typedef typename row_vec<VW>::type row_t;
+    constexpr int T = 64 * fp32_waves(S);
+    constexpr int U = 8;  // member rows in flight
+    extern __shared__ __attribute__((aligned(16))) float s_z[];  // [min(N, kFp32Chunk)][R]
+    __shared__ float s_sum[S > 1 ? S : 1][S > 1 ? 64 * VW : 1];
+    __shared__ int64_t s_ref[R];
+    __shared__ double s_mu[R], s_is[R];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ph = S == 1 ? 0 : wave;  // this wave's share of the members
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (tid == r) {
+            const int64_t v = refs.v[r < n_ref ? r : n_ref - 1];
+            s_ref[r] = v;
+            s_mu[r] = mean_r[v];
+            s_is[r] = inv_std_r[v];
+        }
+    const int64_t g = (int64_t)blockIdx.x * (S == 1 ? T : 64) + (S == 1 ? tid : lane);
+    const int64_t v = g * VW;
+    const int64_t v0 = v < V - VW ? v : V - VW;  // V >= 8
+    float mu[VW], acc[R][VW];
+#pragma unroll
+    for (int e = 0; e < VW; ++e) {
+        mu[e] = (float)mean[v0 + e];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r][e] = 0.f;
     }
-    (void)invN;
-    if (VEC) {
-        const f32x4 *xp = reinterpret_cast<const f32x4 *>(x + v);
-        const int64_t row = V / 4;
-#pragma unroll 8
-        for (int m = 0; m < N; ++m) {
-            const f32x4 a = __builtin_nontemporal_load(xp + (int64_t)m * row);
-            const float z = zr[m];
-            acc[0] = fmaf(z, a[0] - mu[0], acc[0]);
-            acc[1] = fmaf(z, a[1] - mu[1], acc[1]);
-            acc[2] = fmaf(z, a[2] - mu[2], acc[2]);
-            acc[3] = fmaf(z, a[3] - mu[3], acc[3]);
+    const float *col = x + v0;
+    __syncthreads();
+    for (int c0 = 0; c0 < N; c0 += kFp32Chunk) {
+        const int n = min(N - c0, kFp32Chunk);
+        if (c0) __syncthreads();
+        for (int i = tid; i < n * R; i += T) {
+            const int r = i % R, m = c0 + i / R;
+            s_z[i] = (float)(((double)xr[(int64_t)m * V + s_ref[r]] - s_mu[r]) * s_is[r]);
+        }
+        __syncthreads();
+        const int m_lo = n * ph / S, m_hi = n * (ph + 1) / S;
+        auto add = [&](int m, const row_t &q) {
+#pragma unroll
+            for (int e = 0; e < VW; ++e) {
+                float a;
+                if constexpr (VW == 1)
+                    a = q - mu[0];
+                else
+                    a = q[e] - mu[e];
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[r][e] = fmaf(s_z[m * R + r], a, acc[r][e]);
+            }
+        };
+        int m = m_lo;
+        for (; m + U <= m_hi; m += U) {
+            row_t q[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                q[u] = __builtin_nontemporal_load(
+                    reinterpret_cast<const row_t *>(col + (int64_t)(c0 + m + u) * V));
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(m + u, q[u]);
+        }
+        for (; m < m_hi; ++m)
+            add(m, *reinterpret_cast<const row_t *>(col + (int64_t)(c0 + m) * V));
+    }
+    if constexpr (S > 1) {
+        // one reference at a time: wave partials to LDS, summed in wave order
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r) __syncthreads();
+#pragma unroll
+            for (int e = 0; e < VW; ++e) s_sum[ph][lane * VW + e] = acc[r][e];
+            __syncthreads();
+            for (int i = tid; i < 64 * VW; i += T) {
+                const int64_t gv = (int64_t)blockIdx.x * 64 * VW + (i / VW) * VW;  // lane's v
+                const int64_t vi = (gv < V - VW ? gv : V - VW) + i % VW;
+                float t = 0.f;
+                for (int p = 0; p < S; ++p) t += s_sum[p][i];
+                if (gv < V && vi >= gv && r < n_ref)
+                    out[(int64_t)r * V + vi] = t * (float)(inv_std[vi] / (double)N);
+            }
         }
     } else {
-        for (int m = 0; m < N; ++m) {
-            const float z = zr[m];
-            for (int e = 0; e < 4; ++e)
-                if (v + e < V) acc[e] = fmaf(z, x[(int64_t)m * V + v + e] - mu[e], acc[e]);
+        if (v >= V) return;
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+            if (v0 + e < v) continue;
+            const float sc = (float)(inv_std[v0 + e] / (double)N);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r < n_ref) out[(int64_t)r * V + v0 + e] = acc[r][e] * sc;
         }
     }
-    for (int e = 0; e < 4; ++e)
-        if (v + e < V) out[v + e] = acc[e] * sc[e];
+}
+
+struct Fp32Args {
+    const float *xr;
+    const double *mr, *ir;
+    const float *xq;
+    const double *mq, *iq;
+    int N;
+    int64_t V;
+};
+
+template <int R, int VW, int S>
+static void launch_fp32(const Fp32Args &a, const RefList &refs, int n_ref, float *out,
+                        hipStream_t st) {
+    const int64_t per_wg = (int64_t)(S == 1 ? 64 * fp32_waves(S) : 64) * VW;
+    const size_t lds = (size_t)(a.N < kFp32Chunk ? a.N : kFp32Chunk) * R * sizeof(float);
+    hipLaunchKernelGGL((pearson_fp32_kernel<R, VW, S>), dim3((unsigned)ceil_div(a.V, per_wg)),
+                       dim3(64 * fp32_waves(S)), lds, st, a.xr, a.mr, a.ir, a.xq, a.mq, a.iq, a.N,
+                       a.V, refs, n_ref, out);
+}
+
+// How the members are split: four vertices per lane fill the chip (eight waves on
+// each of 256 CUs) from 2^19 vertices on; below that 4 or 16 waves share a
+// workgroup's vertices, and under 2^15 vertices a lane also takes one vertex
+// instead of four.
+template <int R>
+static void launch_fp32_refs(const Fp32Args &a, const RefList &refs, int n_ref, float *out,
+                             hipStream_t st) {
+    if (a.V >= (1 << 19))
+        launch_fp32<R, 4, 1>(a, refs, n_ref, out, st);
+    else if (a.V >= (1 << 17))
+        launch_fp32<R, 4, 4>(a, refs, n_ref, out, st);
+    else if (a.V >= (1 << 15))
+        launch_fp32<R, 4, 16>(a, refs, n_ref, out, st);
+    else
+        launch_fp32<R, 1, 16>(a, refs, n_ref, out, st);
+}
+
+static int launch_pearson_fp32(const Fp32Args &a, const int64_t *ref_v, int n_ref, float *out,
+                               hipStream_t st) {
+    for (int r0 = 0; r0 < n_ref; r0 += kFp32Refs) {
+        const int n = n_ref - r0 < kFp32Refs ? n_ref - r0 : kFp32Refs;
+        RefList refs{};
+        for (int i = 0; i < n; ++i) refs.v[i] = ref_v[r0 + i];
+        float *o = out + (int64_t)r0 * a.V;
+        if (n == 1)
+            launch_fp32_refs<1>(a, refs, n, o, st);
+        else if (n == 2)
+            launch_fp32_refs<2>(a, refs, n, o, st);
+        else if (n <= 4)
+            launch_fp32_refs<4>(a, refs, n, o, st);
+        else
+            launch_fp32_refs<8>(a, refs, n, o, st);
+    }
+    return status_of_launch();
 }
 
 // ---------------------------------------------------------------- GEMM ----
@@ -556,32 +711,25 @@ int launch_pearson_field(const ndf_ensemble *e, int var_ref, int var_qry, const 
     const int N = e->n_members;
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
     const int kpad = (int)align_up((size_t)N, 16);
+    const float *xr = e->x + (int64_t)var_ref * N * V;
+    const float *xq = e->x + (int64_t)var_qry * N * V;
+    if (prec == NDF_PREC_FP32) {
+        const Fp32Args a{xr, e->mean + (int64_t)var_ref * V, e->inv_std + (int64_t)var_ref * V,
+                         xq, e->mean + (int64_t)var_qry * V, e->inv_std + (int64_t)var_qry * V,
+                         N, V};
+        return launch_pearson_fp32(a, ref_v, n_ref, out, st);
+    }
     char *w = (char *)ws;
     float *zr = (float *)w;
     w += align_up((size_t)n_ref * kpad * sizeof(float), 256);
     int64_t *refs = (int64_t *)w;
     w += align_up((size_t)n_ref * sizeof(int64_t), 256);
     if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
-    const float *xr = e->x + (int64_t)var_ref * N * V;
-    const float *xq = e->x + (int64_t)var_qry * N * V;
     hipLaunchKernelGGL(pearson_refcols_kernel, dim3(n_ref), dim3(256), 0, st, xr,
                        e->mean + (int64_t)var_ref * V, e->inv_std + (int64_t)var_ref * V, N, V,
                        refs, kpad, zr);
     const double *mq = e->mean + (int64_t)var_qry * V;
     const double *iq = e->inv_std + (int64_t)var_qry * V;
-    if (prec == NDF_PREC_FP32) {
-        const unsigned nb = (unsigned)ceil_div(ceil_div(V, 4), 256);
-        const bool vec = (V % 4) == 0;
-        for (int r = 0; r < n_ref; ++r) {
-            if (vec)
-                hipLaunchKernelGGL(pearson_gemv_kernel<true>, dim3(nb), dim3(256), 0, st, xq, mq,
-                                   iq, N, V, zr + (int64_t)r * kpad, out + (int64_t)r * V);
-            else
-                hipLaunchKernelGGL(pearson_gemv_kernel<false>, dim3(nb), dim3(256), 0, st, xq, mq,
-                                   iq, N, V, zr + (int64_t)r * kpad, out + (int64_t)r * V);
-        }
-        return status_of_launch();
-    }
     // split-bf16 MFMA contraction, references in groups of 64 (or one 32-block)
     const int n_ib = (int)ceil_div(n_ref, 64) * 2;
     uint16_t *frag = (uint16_t *)w;
