@@ -19,21 +19,6 @@
 
 namespace ndf {
 
-// z_ref rows in FP32, zero-padded to kpad members: ws layout float[n_ref][kpad].
-__global__ void pearson_refcols_kernel(const float *__restrict__ x, const double *__restrict__ mean,
-                                       const double *__restrict__ inv_std, int N, int64_t V,
-                                       const int64_t *__restrict__ refs, int kpad,
-                                       float *__restrict__ zr) {
-    const int r = blockIdx.x;
-    const int64_t v = refs[r];
-    const double mu = mean[v], is = inv_std[v];
-    for (int m = threadIdx.x; m < kpad; m += blockDim.x) {
-        float z = 0.f;
-        if (m < N) z = (float)(((double)x[(int64_t)m * V + v] - mu) * is);
-        zr[(int64_t)r * kpad + m] = z;
-    }
-}
-
 // ---------------------------------------------------------------- GEMV ----
 // FP32 fields of up to R references in one read of the ensemble.  A workgroup
 // first forms the references' standardised columns in LDS (z[m][r], N strided
@@ -232,21 +217,43 @@ static int launch_pearson_fp32(const Fp32Args &a, const int64_t *ref_v, int n_re
 // A operand (references) in MFMA order, ws layout:
 //   bf16 frag[ks][ib][part][lane][8], part 0 = hi, 1 = lo,
 //   lane l holds ref ib*32 + l%32, members ks*16 + 8*(l/32) + e.
-__global__ void pearson_afrag_kernel(const float *__restrict__ zr, int kpad, int n_ib,
-                                     int n_ref, uint16_t *__restrict__ frag) {
-    const int ks = blockIdx.x;
-    const int ib = blockIdx.y;
-    const int lane = threadIdx.x;  // 64
+// A lane gathers its eight members of its reference's column (strided rows of x),
+// standardises them in FP64 and splits the FP32 result; members past N and
+// references past n are zero.  The 64 references of two blocks come as a kernel
+// argument, so the operand takes one launch per 64 references (the list, the FP32
+// columns and the fragments were three: 12 us of a 64-reference call).
+constexpr int kFragRefs = 64;
+
+struct FragRefs {
+    int64_t v[kFragRefs];
+};
+
+__global__ __launch_bounds__(64) void pearson_afrag_kernel(
+    const float *__restrict__ x, const double *__restrict__ mean,
+    const double *__restrict__ inv_std, int N, int64_t V, FragRefs refs, int n, int ib0, int n_ib,
+    bf16x8 *__restrict__ frag) {
+    const int ks = blockIdx.x, ib = blockIdx.y, lane = threadIdx.x;
     const int r = ib * 32 + (lane & 31);
+    const int64_t v = refs.v[r];  // padded with a real vertex
+    const double mu = mean[v], is = inv_std[v];
+    float xv[8];
+#pragma unroll
     for (int e = 0; e < 8; ++e) {
         const int m = ks * 16 + 8 * (lane >> 5) + e;
-        const float z = (r < n_ref) ? zr[(int64_t)r * kpad + m] : 0.f;
-        const uint16_t hi = f2bf_bits(z);
-        const uint16_t lo = f2bf_bits(z - bf_bits2f(hi));
-        const int64_t base = (((int64_t)ks * n_ib + ib) * 2) * 64 * 8;
-        frag[base + lane * 8 + e] = hi;
-        frag[base + 64 * 8 + lane * 8 + e] = lo;
+        xv[e] = x[(int64_t)(m < N ? m : N - 1) * V + v];
     }
+    bf16x8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int m = ks * 16 + 8 * (lane >> 5) + e;
+        const float z = m < N && r < n ? (float)(((double)xv[e] - mu) * is) : 0.f;
+        const __bf16 h = f2bf(z);
+        hi[e] = h;
+        lo[e] = f2bf(z - (float)h);
+    }
+    bf16x8 *dst = frag + ((int64_t)ks * n_ib + ib0 + ib) * 2 * 64;
+    dst[lane] = hi;
+    dst[64 + lane] = lo;
 }
 
 // z = (x - mu) * sigma^-1 split into bf16 hi + lo: hi is z rounded, lo the
@@ -694,6 +701,8 @@ __global__ __launch_bounds__(256) void pearson_points_kernel(
 }
 
 // ------------------------------------------------------------ launchers ----
+// Room for the reference list, its FP32 columns and the fragments.  The kernels use
+// the fragments alone; the size stays what callers have laid out.
 size_t pearson_ws_bytes(int N, int n_ref, int prec) {
     const int kpad = (int)align_up((size_t)N, 16);
     size_t zr = align_up((size_t)n_ref * kpad * sizeof(float), 256);
@@ -713,32 +722,26 @@ int launch_pearson_field(const ndf_ensemble *e, int var_ref, int var_qry, const 
     const int kpad = (int)align_up((size_t)N, 16);
     const float *xr = e->x + (int64_t)var_ref * N * V;
     const float *xq = e->x + (int64_t)var_qry * N * V;
+    const double *mr = e->mean + (int64_t)var_ref * V, *ir = e->inv_std + (int64_t)var_ref * V;
+    const double *mq = e->mean + (int64_t)var_qry * V, *iq = e->inv_std + (int64_t)var_qry * V;
     if (prec == NDF_PREC_FP32) {
-        const Fp32Args a{xr, e->mean + (int64_t)var_ref * V, e->inv_std + (int64_t)var_ref * V,
-                         xq, e->mean + (int64_t)var_qry * V, e->inv_std + (int64_t)var_qry * V,
-                         N, V};
+        const Fp32Args a{xr, mr, ir, xq, mq, iq, N, V};
         return launch_pearson_fp32(a, ref_v, n_ref, out, st);
     }
-    char *w = (char *)ws;
-    float *zr = (float *)w;
-    w += align_up((size_t)n_ref * kpad * sizeof(float), 256);
-    int64_t *refs = (int64_t *)w;
-    w += align_up((size_t)n_ref * sizeof(int64_t), 256);
-    if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
-    hipLaunchKernelGGL(pearson_refcols_kernel, dim3(n_ref), dim3(256), 0, st, xr,
-                       e->mean + (int64_t)var_ref * V, e->inv_std + (int64_t)var_ref * V, N, V,
-                       refs, kpad, zr);
-    const double *mq = e->mean + (int64_t)var_qry * V;
-    const double *iq = e->inv_std + (int64_t)var_qry * V;
     // split-bf16 MFMA contraction, references in groups of 64 (or one 32-block)
     const int n_ib = (int)ceil_div(n_ref, 64) * 2;
-    uint16_t *frag = (uint16_t *)w;
-    hipLaunchKernelGGL(pearson_afrag_kernel, dim3(kpad / 16, n_ib), dim3(64), 0, st, zr, kpad,
-                       n_ib, n_ref, frag);
+    bf16x8 *frag = (bf16x8 *)ws;
+    for (int r0 = 0; r0 < n_ref; r0 += kFragRefs) {
+        const int n = n_ref - r0 < kFragRefs ? n_ref - r0 : kFragRefs;
+        FragRefs refs;
+        for (int i = 0; i < kFragRefs; ++i) refs.v[i] = ref_v[r0 + (i < n ? i : n - 1)];
+        hipLaunchKernelGGL(pearson_afrag_kernel, dim3(kpad / 16, 2), dim3(64), 0, st, xr, mr, ir, N,
+                           V, refs, n, r0 / 32, n_ib, frag);
+    }
     const unsigned nbx = (unsigned)ceil_div(V, 4 * kGemmVerts);
     // 8-byte accesses need every member row 8-byte aligned: V even
     const bool vec = (V % 2) == 0;
-    const bf16x8 *af = (const bf16x8 *)frag;
+    const bf16x8 *af = frag;
     if (n_ref > 64) {
         // one read of the ensemble per 256 references
         const dim3 g((unsigned)ceil_div(V, kWideVerts), (unsigned)ceil_div(n_ref, kWideRefs));
