@@ -548,60 +548,7 @@ __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
     }
 }
 
-// Every column's members in ascending (code, member) order: the sorted orders of
-// the neighbour search, built once per ensemble.  Workgroups stride over the
-// columns (one per wave for N <= 1024, else one per workgroup).
-template <int E>
-__device__ __forceinline__ void sort_column_e(const int32_t *__restrict__ c, int N,
-                                              uint16_t *__restrict__ o,
-                                              unsigned long long *xchg) {
-    const int tid = threadIdx.x;
-    unsigned long long k[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int m = E * tid + j;
-        k[j] = m < N ? (((unsigned long long)(uint32_t)c[m]) << 16) | (unsigned)m : ~0ull;
-    }
-    block_sort_regs<E>(k, xchg);
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int p = E * tid + j;
-        if (p < N) o[p] = (uint16_t)(k[j] & 0xffff);
-    }
-}
-
-// One wave sorts 64 E keys held E per lane (lane l holds keys E l .. E l + E - 1):
-// partners closer than E are in the lane's registers, all others are lane
-// shuffles; no LDS and no barrier.
-template <int E>
-__device__ __forceinline__ void wave_sort_regs(unsigned long long (&k)[E]) {
-    const int lane = threadIdx.x & 63;
-    constexpr int PT = 64 * E;
-    for (int size = 2; size <= PT; size <<= 1) {
-        for (int stride = size >> 1; stride >= E; stride >>= 1) {
-            const bool keep_min = ((E * lane & stride) == 0) == ((E * lane & size) == 0);
-#pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const unsigned long long o = __shfl_xor(k[j], stride / E, kWave);
-                k[j] = ((o < k[j]) == keep_min) ? o : k[j];
-            }
-        }
-#pragma unroll
-        for (int st = E / 2; st >= 1; st >>= 1) {
-            if (st >= size) continue;
-#pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const int jp = j ^ st;
-                if (jp < j) continue;
-                const bool up = ((E * lane + j) & size) == 0;
-                const unsigned long long a = k[j], b = k[jp];
-                const bool swap = (a > b) == up;
-                k[j] = swap ? b : a;
-                k[jp] = swap ? a : b;
-            }
-        }
-    }
-}
+constexpr int log2_int(int n) { return n <= 1 ? 0 : 1 + log2_int(n / 2); }
 
 // Ascending bitonic sort of 64 E 32-bit keys held E per lane, in the form whose
 // merge of two sorted halves starts by comparing element i with its mirror
@@ -611,7 +558,7 @@ __device__ __forceinline__ void wave_sort_regs(unsigned long long (&k)[E]) {
 template <int E>
 __device__ __forceinline__ void wave_sort_regs32(uint32_t (&k)[E]) {
     const int lane = threadIdx.x & 63;
-    constexpr int LE = E == 1 ? 0 : E == 2 ? 1 : E == 4 ? 2 : E == 8 ? 3 : 4;
+    constexpr int LE = log2_int(E);
     constexpr int LPT = 6 + LE;  // log2 of the key count
 #pragma unroll
     for (int ls = 1; ls <= LPT; ++ls) {
@@ -660,142 +607,219 @@ __device__ __forceinline__ void wave_sort_regs32(uint32_t (&k)[E]) {
     }
 }
 
-// Sorted member order of one column with 64 < N <= 1024 (E >= 2 per lane).  The
-// sort runs on 32-bit keys (code >> 2, member): codes lie in [0, 2^23], so
-// code >> 2 takes 22 bits and the member 10.  Samples whose codes agree above
-// the two lowest bits then sit in member order; where such neighbours exist,
-// odd-even transposition passes on the full (code, member) keys finish the
-// order, and a column that is still unsorted after four rounds (many near-equal
-// codes) is sorted again on full 64-bit keys.
+// Sorted member order of one column of N <= 64 E members by one wave, as a bucket
+// sort in LDS.  Codes spread over [0, 2^23], so 2 E 64 buckets of equal width hold one
+// or two samples each: every sample takes a place in its bucket from an LDS counter,
+// a scan of the counters gives the bucket starts, and the samples go to LDS in bucket
+// order, where lane l then holds positions E l .. E l + E - 1.  Their 32-bit keys
+//   (start of the bucket, code bits below the bucket, member)
+// order like (code, member), as the start grows with the bucket.  Odd-even passes
+// finish the buckets; a column with crowded buckets (repeated values, far outliers) is
+// still unsorted after kOddEven passes and goes through the full bitonic sort of the
+// same keys.
+constexpr int kOddEven = 8;  // passes (each both parities) before the full sort
+
 template <int E>
-__device__ __forceinline__ void wave_sort_column32(const int32_t *__restrict__ c, int N,
-                                                   uint16_t *__restrict__ o) {
-    static_assert(E >= 2, "pairs of one lane");
-    const int lane = threadIdx.x & 63;
-    uint32_t k[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int m = E * lane + j;
-        k[j] = m < N ? (((uint32_t)c[m] >> 2) << 10) | (uint32_t)m : 0xffffffffu;
-    }
-    wave_sort_regs32<E>(k);
-    // neighbours with equal code >> 2 (padding keys never tie with a sample)
-    bool tie = false;
-#pragma unroll
-    for (int j = 0; j + 1 < E; ++j) tie |= (k[j] >> 10) == (k[j + 1] >> 10) && k[j + 1] != 0xffffffffu;
-    const uint32_t nk = __shfl_down(k[0], 1, kWave);
-    if (lane < 63) tie |= (k[E - 1] >> 10) == (nk >> 10) && nk != 0xffffffffu;
-    if (!__any(tie)) {
-#pragma unroll
-        for (int j = 0; j < E; ++j) {
-            const int p = E * lane + j;
-            if (p < N) o[p] = (uint16_t)(k[j] & 0x3ff);
-        }
-        return;
-    }
-    unsigned long long f[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int m = (int)(k[j] & 0x3ff);
-        f[j] = k[j] == 0xffffffffu ? ~0ull
-                                   : (((unsigned long long)(uint32_t)c[m]) << 16) | (unsigned)m;
-    }
-    auto in_order = [&]() {
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j + 1 < E; ++j) bad |= f[j] > f[j + 1];
-        const unsigned long long nf = __shfl_down(f[0], 1, kWave);
-        if (lane < 63) bad |= f[E - 1] > nf;
-        return !__any(bad);
-    };
-    bool done = false;
-    for (int round = 0; round < 4 && !(done = in_order()); ++round) {
-#pragma unroll
-        for (int j = 0; j + 1 < E; j += 2) {  // pairs (2i, 2i + 1)
-            const unsigned long long a = f[j], b = f[j + 1];
-            f[j] = a < b ? a : b;
-            f[j + 1] = a < b ? b : a;
-        }
-        const unsigned long long nf = __shfl_down(f[0], 1, kWave);
-        const unsigned long long pf = __shfl_up(f[E - 1], 1, kWave);
-#pragma unroll
-        for (int j = 1; j + 1 < E; j += 2) {  // pairs (2i + 1, 2i + 2) inside a lane
-            const unsigned long long a = f[j], b = f[j + 1];
-            f[j] = a < b ? a : b;
-            f[j + 1] = a < b ? b : a;
-        }
-        // the pair across a lane boundary: the lower position keeps the minimum
-        if (lane < 63) f[E - 1] = f[E - 1] < nf ? f[E - 1] : nf;
-        if (lane > 0) f[0] = f[0] > pf ? f[0] : pf;
-    }
-    if (!done && !in_order()) wave_sort_regs<E>(f);
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int p = E * lane + j;
-        if (p < N) o[p] = (uint16_t)(f[j] & 0xffff);
-    }
+struct ColumnSort {
+    static constexpr int kLN = 6 + log2_int(E);          // log2 of the slots
+    // 2 buckets per slot; 8 at E = 32 so that start, code bits and member fit 32 bits
+    static constexpr int kLB = kLN <= 10 ? kLN + 1 : kLN + 2;
+    static constexpr int kLow = 23 - kLB;                // code bits inside a bucket
+    static constexpr int kWords = (1 << kLB) / 2;        // two 16-bit counters a word
+    static constexpr int kPer = kWords / 64;             // counter words per lane
+    static constexpr int kLds = kWords + 4;              // + the bucket of code 2^23
+    static_assert(2 * kLN + kLow <= 32, "key bits");
+    static_assert(kWords >= 64 * E, "the keys reuse the counters");
+};
+
+__device__ __forceinline__ void wave_lds_fence() {
+    // LDS operations of a wave complete in order; this only keeps the compiler from
+    // moving them across
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
+
+typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x8u __attribute__((ext_vector_type(8), aligned(2)));
 
 template <int E>
 __device__ __forceinline__ void wave_sort_column(const int32_t *__restrict__ c, int N,
-                                                 uint16_t *__restrict__ o) {
+                                                 uint16_t *__restrict__ o, uint32_t *lds) {
+    typedef ColumnSort<E> C;
     const int lane = threadIdx.x & 63;
-    unsigned long long k[E];
+    // members of this lane: four consecutive ones per load (E >= 4), else strided
+    auto member = [&](int j) {
+        return E >= 4 ? 256 * (j >> 2) + 4 * lane + (j & 3) : 64 * j + lane;
+    };
+    uint32_t code[E];
+    if constexpr (E >= 4) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int m = E * lane + j;
-        k[j] = m < N ? (((unsigned long long)(uint32_t)c[m]) << 16) | (unsigned)m : ~0ull;
+        for (int j = 0; j < E; j += 4) {
+            const int m = member(j);
+            i32x4u q = {0, 0, 0, 0};
+            if (m + 3 < N) {
+                q = *reinterpret_cast<const i32x4u *>(c + m);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (m + e < N) q[e] = c[m + e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) code[j + e] = (uint32_t)q[e];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < E; ++j) code[j] = member(j) < N ? (uint32_t)c[member(j)] : 0u;
     }
-    wave_sort_regs<E>(k);
+    // counters to zero
+    for (int i = lane; i < C::kLds / 4; i += 64)
+        reinterpret_cast<u32x4v *>(lds)[i] = u32x4v{0u, 0u, 0u, 0u};
+    wave_lds_fence();
+    // a place in the bucket (16-bit counters: at most 2048 samples)
+    uint32_t place[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-        const int p = E * lane + j;
-        if (p < N) o[p] = (uint16_t)(k[j] & 0xffff);
+        const uint32_t b = min(code[j] >> C::kLow, 1u << C::kLB);
+        if (member(j) < N) {
+            const uint32_t sh = (b & 1) * 16;
+            place[j] = (atomicAdd(&lds[b >> 1], 1u << sh) >> sh) & 0xffffu;
+        }
+    }
+    wave_lds_fence();
+    // exclusive scan over the buckets: lane l owns words kPer l .. kPer l + kPer - 1
+    uint32_t w[C::kPer], sum = 0;
+#pragma unroll
+    for (int i = 0; i < C::kPer; ++i) {
+        w[i] = lds[C::kPer * lane + i];
+        sum += (w[i] & 0xffffu) + (w[i] >> 16);
+    }
+    uint32_t run = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t t = __shfl_up(run, d, kWave);
+        if (lane >= d) run += t;
+    }
+    if (lane == 63) lds[C::kWords] = run;  // start of the bucket of code 2^23
+    run -= sum;
+#pragma unroll
+    for (int i = 0; i < C::kPer; ++i) {
+        const uint32_t lo = w[i] & 0xffffu, hi = w[i] >> 16;
+        lds[C::kPer * lane + i] = run | ((run + lo) << 16);
+        run += lo + hi;
+    }
+    wave_lds_fence();
+    uint32_t k[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        const uint32_t b = min(code[j] >> C::kLow, 1u << C::kLB);
+        const uint32_t start = (lds[b >> 1] >> ((b & 1) * 16)) & 0xffffu;
+        place[j] += start;
+        k[j] = (start << (C::kLow + C::kLN)) |
+               ((code[j] & ((1u << C::kLow) - 1)) << C::kLN) | (uint32_t)member(j);
+    }
+    wave_lds_fence();  // every start is read: the keys reuse the counters' LDS
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+        if (member(j) < N) lds[place[j]] = k[j];
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < E; ++j) k[j] = lds[E * lane + j];
+    wave_lds_fence();
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+        if (E * lane + j >= N) k[j] = 0xffffffffu;  // above every key: sorts last
+    int pass = 0;
+    for (;; ++pass) {
+        const uint32_t nk = __shfl_down(k[0], 1, kWave);
+        bool bad = lane < 63 && k[E - 1] > nk;
+#pragma unroll
+        for (int j = 0; j + 1 < E; ++j) bad |= k[j] > k[j + 1];
+        if (!__any(bad) || pass == kOddEven) {
+            if (__any(bad)) wave_sort_regs32<E>(k);
+            break;
+        }
+#pragma unroll
+        for (int j = 0; j + 1 < E; j += 2) {  // pairs (2i, 2i + 1) of a lane
+            const uint32_t a = k[j], b = k[j + 1];
+            k[j] = min(a, b);
+            k[j + 1] = max(a, b);
+        }
+        if constexpr (E == 1) {
+            // one key per lane: pairs (2l, 2l + 1), then (2l + 1, 2l + 2)
+            const uint32_t p = __shfl_xor(k[0], 1, kWave);
+            k[0] = lane & 1 ? max(k[0], p) : min(k[0], p);
+            const uint32_t up = __shfl_down(k[0], 1, kWave), dn = __shfl_up(k[0], 1, kWave);
+            if (lane & 1) {
+                if (lane < 63) k[0] = min(k[0], up);
+            } else if (lane > 0) {
+                k[0] = max(k[0], dn);
+            }
+        } else {
+            const uint32_t up = __shfl_down(k[0], 1, kWave), dn = __shfl_up(k[E - 1], 1, kWave);
+#pragma unroll
+            for (int j = 1; j + 1 < E; j += 2) {  // pairs (2i + 1, 2i + 2) of a lane
+                const uint32_t a = k[j], b = k[j + 1];
+                k[j] = min(a, b);
+                k[j + 1] = max(a, b);
+            }
+            // the pair across a lane boundary
+            if (lane < 63) k[E - 1] = min(k[E - 1], up);
+            if (lane > 0) k[0] = max(k[0], dn);
+        }
+    }
+    // positions E lane .. E lane + E - 1 of the order
+    constexpr uint32_t kMask = (1u << C::kLN) - 1;
+    if constexpr (E >= 8) {
+#pragma unroll
+        for (int j = 0; j < E; j += 8) {
+            const int p = E * lane + j;
+            if (p + 7 < N) {
+                u16x8u q;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) q[e] = (uint16_t)(k[j + e] & kMask);
+                *reinterpret_cast<u16x8u *>(o + p) = q;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (p + e < N) o[p + e] = (uint16_t)(k[j + e] & kMask);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+            if (E * lane + j < N) o[E * lane + j] = (uint16_t)(k[j] & kMask);
     }
 }
 
-__global__ __launch_bounds__(kKsgThreads) __attribute__((amdgpu_waves_per_eu(4))) void ksg_order_kernel(const int32_t *__restrict__ code,
+// One column per wave, N <= 64 E.  Bound by VALU issue (779 per column of 1000 members,
+// 70 % of the cycles) beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 ->
+// 3.31 ms (3.2 TB/s) against a register bitonic sort of every column.
+template <int E>
+__global__ __launch_bounds__(kKsgThreads) void ksg_order_kernel(const int32_t *__restrict__ code,
                                                                 int N, int64_t ncol,
                                                                 uint16_t *__restrict__ order) {
+    __shared__ __attribute__((aligned(16))) uint32_t s_lds[kKsgWaves][ColumnSort<E>::kLds];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t waves = (int64_t)gridDim.x * kKsgWaves;
+    for (int64_t v = (int64_t)blockIdx.x * kKsgWaves + wave; v < ncol; v += waves)
+        wave_sort_column<E>(code + v * N, N, order + v * N, s_lds[wave]);
+}
+
+// N > 2048 (no KSG call takes such columns): one column per workgroup, in LDS.
+__global__ __launch_bounds__(kKsgThreads) void ksg_order_block_kernel(
+    const int32_t *__restrict__ code, int N, int64_t ncol, uint16_t *__restrict__ order) {
     extern __shared__ unsigned long long s_x[];
-    const int P2 = pow2_ceil(N);
-    if (P2 <= 1024) {  // one column per wave
-        const int64_t waves = (int64_t)gridDim.x * kKsgWaves;
-        for (int64_t v = (int64_t)blockIdx.x * kKsgWaves + (threadIdx.x >> 6); v < ncol;
-             v += waves) {
-            const int32_t *c = code + v * N;
-            uint16_t *o = order + v * N;
-            if (P2 <= 64)
-                wave_sort_column<1>(c, N, o);
-            else if (P2 <= 128)
-                wave_sort_column32<2>(c, N, o);
-            else if (P2 <= 256)
-                wave_sort_column32<4>(c, N, o);
-            else if (P2 <= 512)
-                wave_sort_column32<8>(c, N, o);
-            else
-                wave_sort_column32<16>(c, N, o);
-        }
-        return;
-    }
-    const int P = max(P2, kKsgThreads);
+    const int P = pow2_ceil(N);
     for (int64_t v = blockIdx.x; v < ncol; v += gridDim.x) {
         const int32_t *c = code + v * N;
         uint16_t *o = order + v * N;
-        if (P <= kKsgThreads)
-            sort_column_e<1>(c, N, o, s_x);
-        else if (P <= 2 * kKsgThreads)
-            sort_column_e<2>(c, N, o, s_x);
-        else if (P <= 4 * kKsgThreads)
-            sort_column_e<4>(c, N, o, s_x);
-        else {
-            for (int m = threadIdx.x; m < P; m += kKsgThreads)
-                s_x[m] = m < N ? (((unsigned long long)(uint32_t)c[m]) << 16) | (unsigned)m : ~0ull;
-            __syncthreads();
-            block_bitonic_sort(s_x, P);
-            for (int p = threadIdx.x; p < N; p += kKsgThreads) o[p] = (uint16_t)(s_x[p] & 0xffff);
-            __syncthreads();
-        }
+        for (int m = threadIdx.x; m < P; m += kKsgThreads)
+            s_x[m] = m < N ? (((unsigned long long)(uint32_t)c[m]) << 16) | (unsigned)m : ~0ull;
+        __syncthreads();
+        block_bitonic_sort(s_x, P);
+        for (int p = threadIdx.x; p < N; p += kKsgThreads) o[p] = (uint16_t)(s_x[p] & 0xffff);
+        __syncthreads();
     }
 }
 
@@ -1030,11 +1054,26 @@ static void launch_field_k(dim3 g, size_t lds, hipStream_t st, const FieldArgs &
 int launch_ksg_orders(const ndf_ensemble *e, hipStream_t st) {
     const int N = e->n_members;
     const int64_t ncol = (int64_t)e->n_vars * e->nx * e->ny * e->nz;
-    const int P = p2(N) < kKsgThreads ? kKsgThreads : p2(N);
-    const size_t lds = (size_t)P * sizeof(unsigned long long);
-    hipLaunchKernelGGL(ksg_order_kernel, dim3((unsigned)ksg_grid(ncol, lds, kOrderWaves)),
-                       dim3(kKsgThreads), lds, st, e->code, N, ncol, e->order);
-    return status_of_launch();
+    if (N > 2048) {
+        const size_t lds = (size_t)p2(N) * sizeof(unsigned long long);
+        hipLaunchKernelGGL(ksg_order_block_kernel,
+                           dim3((unsigned)ksg_grid(ncol, lds, kOrderWaves)), dim3(kKsgThreads),
+                           lds, st, e->code, N, ncol, e->order);
+        return status_of_launch();
+    }
+    const int64_t wgs = ceil_div(ncol, kKsgWaves);
+    const int64_t cap = 256 * 8 * kOrderWaves;
+    const dim3 g((unsigned)(wgs < cap ? wgs : cap));
+#define NDF_ORDER_CASE(E)                                                                    \
+    if (N <= 64 * E) {                                                                       \
+        hipLaunchKernelGGL(ksg_order_kernel<E>, g, dim3(kKsgThreads), 0, st, e->code, N, ncol, \
+                           e->order);                                                        \
+        return status_of_launch();                                                           \
+    }
+    NDF_ORDER_CASE(1) NDF_ORDER_CASE(2) NDF_ORDER_CASE(4)
+    NDF_ORDER_CASE(8) NDF_ORDER_CASE(16) NDF_ORDER_CASE(32)
+#undef NDF_ORDER_CASE
+    return NDF_E_UNSUPPORTED;
 }
 
 int launch_ksg_field(const ndf_ensemble *e, int var_ref, int var_qry, const int64_t *ref_v,

@@ -46,3 +46,28 @@ def test_pearson_fp32_member_splits(dims, n_members, n_ref):
     for i, r in enumerate(refs):
         want = direct.pearson_field(np.ascontiguousarray(x[:, r]), np.ascontiguousarray(x[:, sub]))
         assert np.max(np.abs(got[i, sub] - want)) <= PEARSON_TOL
+
+
+# member counts on both sides of every slot count of the order kernel (64 E, E = 1 .. 32)
+# and of the workgroup path (N > 2048); columns from smooth to fully tied
+@pytest.mark.parametrize("n_members", [2, 3, 63, 64, 65, 127, 128, 129, 200, 255, 256, 257, 511,
+                                       512, 513, 1000, 1023, 1024, 1025, 2047, 2048, 2049, 4096])
+def test_stored_orders_are_the_stable_sort_of_the_codes(n_members):
+    dims = (5, 7, 2)
+    V = 70
+    rng = np.random.default_rng(n_members)
+    x = rng.standard_normal((n_members, V)).astype(np.float32)
+    x[:, 10:20] = rng.integers(0, 3, (n_members, 10))         # a few repeated values
+    x[:, 20:30] = rng.integers(0, 1 + n_members // 4, (n_members, 10))
+    x[:, 30:40] = rng.standard_cauchy((n_members, 10))        # far outliers: crowded buckets
+    x[:, 40] = 3.5                                            # constant
+    x[:, 41:45] = np.sort(x[:, 41:45], axis=0)
+    x[:, 45:48] = np.sort(x[:, 45:48], axis=0)[::-1]
+    x[:, 48:50] = np.linspace(-1, 1, n_members)[:, None]      # every bucket alike
+    x[-1, 50] = np.inf
+    x[0, 51] = np.nan
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=True)
+    ndf.ndf_prepare(e)
+    code = e.code[0].cpu().numpy()
+    order = e.order[0].cpu().numpy().astype(np.int64) & 0xffff
+    assert np.array_equal(order, np.argsort(code, axis=1, kind="stable"))
