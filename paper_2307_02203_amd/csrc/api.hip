@@ -24,7 +24,7 @@ int launch_ksg_field(const ndf_ensemble *e, int var_ref, int var_qry, const int6
 size_t ksg_pairs_ws_bytes(int N);
 int launch_ksg_orders(const ndf_ensemble *e, hipStream_t st);
 int launch_ksg_pairs(const ndf_ensemble *e, int var_a, int var_b, const int64_t *pairs, int64_t B,
-                     int k, float *out, int32_t *counts, double *H, hipStream_t st);
+                     int k, float *out, int32_t *counts, hipStream_t st);
 size_t ksg_points_ws_bytes(int N, int64_t B);
 int launch_ksg_points(const ndf_ensemble *e, int var_a, int var_b, const float *pos, int64_t B,
                       int k, float *out, int32_t *counts, void *ws, hipStream_t st);
@@ -34,7 +34,7 @@ using namespace ndf;
 
 // ------------------------------------------- field without allocation ----
 // Device scratch of the no-allocation KSG field call: the workspace of
-// launch_ksg_field (harmonic table, reference list, sorted reference columns)
+// launch_ksg_field (reference list, sorted reference columns)
 // for requests up to kKsgScratchBytes.  Every device holds its own copy for the
 // life of the process; host code reaches it only through the address that
 // hipGetSymbolAddress returns on that device (the array's name is not a device
@@ -249,7 +249,7 @@ int ndf_ksg_mi_pairs(const ndf_ensemble *ens, int32_t var_a, int32_t var_b,
     if (!pairs || !out || B < 1 || k < 1 || k >= ens->n_members) return NDF_E_ARG;
     if (k > 8 || ens->n_members > kMaxMembersKsg) return NDF_E_UNSUPPORTED;
     if (!ws || ws_bytes < ksg_pairs_ws_bytes(ens->n_members)) return NDF_E_WORKSPACE;
-    return launch_ksg_pairs(ens, var_a, var_b, pairs, B, k, out, counts, (double *)ws, S(stream));
+    return launch_ksg_pairs(ens, var_a, var_b, pairs, B, k, out, counts, S(stream));
 }
 
 int ndf_ksg_mi_points(const ndf_ensemble *ens, int32_t var_a, int32_t var_b, const float *pos,

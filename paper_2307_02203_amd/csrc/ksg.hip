@@ -8,31 +8,34 @@
 // and I = psi(k) + psi(N) - <psi(nx+1) + psi(ny+1)>, which with
 // psi(n) = H_{n-1} - gamma is H_{k-1} + H_{N-1} - <H_nx + H_ny>.
 //
-// GPU design (one workgroup of four 64-lane waves per pair, everything in LDS;
-// four waves share one pair's LDS so that a CU keeps enough waves in flight to
-// hide LDS latency):
-//  * the samples are kept in two orders, by x and by y; both come from the
+// GPU design (one workgroup per pair, four samples per thread, everything in LDS; a
+// pair of up to 256 members is one wave, of up to 2048 eight):
+//  * the samples are known in two orders, by x and by y; both come from the
 //    per-vertex sorted member orders that ndf_prepare stores (ties by member
 //    index), so no query sorts anything; without stored orders every column is
-//    sorted on the fly (ties by member index in x, by x position in y), which
-//    gives bit-identical results;
+//    sorted on the fly, which gives the same results;
+//  * for the neighbour search each order is split in two lists: the x order into the
+//    samples below and above the median y rank, the y order likewise by x rank;
 //  * the k nearest neighbours of a sample are found by walking outwards from its
-//    own position in one of the two orders, stopping on each side once the
+//    own position in its list of one order, stopping on each side once the
 //    distance along that coordinate reaches the current k-th distance (under the
-//    max-norm no later sample can be closer).  Each sample walks the order in
-//    which its 2k nearest codes are spread widest, i.e. where the strip the walk
-//    must cover holds the fewest samples; any choice gives the same exact result;
+//    max-norm no later sample can be closer); only a sample nearer to the other list
+//    (in the coordinate that splits them) than its k-th distance walks that list too.
+//    Each sample walks the order in which its nearest codes are spread widest, i.e.
+//    where the strip the walk must cover holds the fewest samples; any choice gives
+//    the same exact result;
 //  * the marginal counts are two lower bounds each, over the sorted x codes and
 //    over the sorted y codes; a bucket table of each order (built per pair in
 //    LDS) narrows every search to the few samples of one code bucket;
 //  * all distances and counts are exact int32, so the counts equal a brute-force
 //    evaluation bit for bit; the harmonic sum is FP64.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace ndf {
 
-constexpr int kKsgMaxN = 4096;
-constexpr int kKsgWaves = 4;
+constexpr int kKsgWaves = 4;  // of the sorting kernels
 constexpr int kKsgThreads = 64 * kKsgWaves;
 
 __device__ __forceinline__ int pow2_ceil(int n) {
@@ -62,41 +65,70 @@ __device__ void block_bitonic_sort(T *a, int P) {
     }
 }
 
-// Bucket tables of the marginal searches: T[b] = number of sorted codes below
-// b * 2^kTabShift for b = 0 .. kTabN - 1 (codes lie in [0, 2^23], so the last
-// entry is N).  A lower bound of v then only searches [T[b], T[b + 1]] with
-// b = v >> kTabShift: a handful of samples instead of all N.
-constexpr int kTabShift = 14;
-constexpr int kTabN = ((1 << 23) >> kTabShift) + 2;  // 514 entries
+// H[n] = 1 + 1/2 + ... + 1/n, summed in order in FP64 (a thread that summed it on the
+// GPU took 60 us for 1000 members in front of every call).
+constexpr int kKsgMaxN = 2048;
+struct Harmonic {
+    double v[kKsgMaxN + 1];
+    constexpr Harmonic() : v() {
+        double h = 0.0;
+        v[0] = 0.0;
+        for (int i = 1; i <= kKsgMaxN; ++i) {
+            h += 1.0 / (double)i;
+            v[i] = h;
+        }
+    }
+};
+static __device__ const Harmonic kHarmonic{};
 
+// Shape of the pair kernels with W waves: four samples per thread, up to 256 W members.
+// Bucket tables of the marginal searches: T[b] = number of sorted codes below
+// b << kShift for b = 0 .. kTab - 1 (codes lie in [0, 2^23], so the last entry is N).
+// A lower bound of v then only searches [T[b], T[b + 1]] with b = v >> kShift: a
+// handful of samples instead of all N.  The bucket width follows the sample count
+// (at 1000 members half and twice the width cost 5 and 1.6 %).
+constexpr int kPer = 4;  // samples per thread
+template <int W>
+struct Pair {
+    static constexpr int kT = 64 * W;                       // threads
+    static constexpr int kMax = kPer * kT;                  // members
+    static constexpr int kChunks = kMax / 64;
+    static constexpr int kShift = 16 - (W >= 8 ? 3 : W >= 4 ? 2 : W >= 2 ? 1 : 0);
+    static constexpr int kTab = ((1 << 23) >> kShift) + 2;  // W = 4: 514 entries
+};
+
+template <int W>
 __device__ __forceinline__ int tab_bucket(int v) {
-    return min(max(v, 0) >> kTabShift, kTabN - 2);
+    return min(max(v, 0), 1 << 23) >> Pair<W>::kShift;  // at most kTab - 2
 }
 
 // Table construction in three steps with a workgroup barrier between them:
 // every entry N (all threads) ...
+template <int W>
 __device__ __forceinline__ void tab_fill(uint16_t *T, int N) {
-    for (int i = threadIdx.x; i < kTabN; i += kKsgThreads) T[i] = (uint16_t)N;
+    for (int i = threadIdx.x; i < Pair<W>::kTab; i += Pair<W>::kT) T[i] = (uint16_t)N;
 }
 // ... the first position of every non-empty bucket of the sorted a[0..N) (all
 // threads) ...
-__device__ __forceinline__ void tab_scatter(const int2 *a, uint16_t *T, int N) {
-    for (int j = threadIdx.x; j < N; j += kKsgThreads) {
-        const int b = tab_bucket(a[j].x);
-        if (j == 0 || tab_bucket(a[j - 1].x) != b) T[b] = (uint16_t)j;
+template <int W>
+__device__ __forceinline__ void tab_scatter(const int *a, uint16_t *T, int N) {
+    for (int j = threadIdx.x; j < N; j += Pair<W>::kT) {
+        const int b = tab_bucket<W>(a[j]);
+        if (j == 0 || tab_bucket<W>(a[j - 1]) != b) T[b] = (uint16_t)j;
     }
 }
 // ... and a suffix minimum by one wave, so that an empty bucket takes the first
-// position of the next non-empty one (lane l owns entries kPer l .. kPer l + kPer - 1).
+// position of the next non-empty one (lane l owns entries kP l .. kP l + kP - 1).
+template <int W>
 __device__ __forceinline__ void tab_scan(uint16_t *T) {
-    constexpr int kPer = (kTabN + 63) / 64;
+    constexpr int kTab = Pair<W>::kTab, kP = (kTab + 63) / 64;
     const int lane = threadIdx.x & 63;
-    int v[kPer];
+    int v[kP];
     int run = 0xffff;
 #pragma unroll
-    for (int i = kPer - 1; i >= 0; --i) {
-        const int idx = lane * kPer + i;
-        if (idx < kTabN) run = min(run, (int)T[idx]);
+    for (int i = kP - 1; i >= 0; --i) {
+        const int idx = lane * kP + i;
+        if (idx < kTab) run = min(run, (int)T[idx]);
         v[i] = run;
     }
     int s = run;  // minimum over the chunks of this lane and all later ones
@@ -108,47 +140,50 @@ __device__ __forceinline__ void tab_scan(uint16_t *T) {
     int carry = __shfl_down(s, 1);
     if (lane == 63) carry = 0xffff;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int idx = lane * kPer + i;
-        if (idx < kTabN) T[idx] = (uint16_t)min(v[i], carry);
+    for (int i = 0; i < kP; ++i) {
+        const int idx = lane * kP + i;
+        if (idx < kTab) T[idx] = (uint16_t)min(v[i], carry);
     }
 }
 
-// Marginal counts of one sample with k-th distance eps > 0: entries of the sorted
-// x codes (xo[].x) and of the sorted y codes (yo[].x) strictly inside
-// (v - eps, v + eps), minus the sample itself.  Each of the four lower bounds
-// starts from its bucket range [T[b], T[b + 1]]; the searches advance in lockstep
-// from the widest range's step, so their LDS reads are in flight together, and a
-// probe is clamped into [0, N) and never advances past its range.
-__device__ __forceinline__ void marginal_counts(const int2 *xo, const int2 *yo,
-                                                const uint16_t *Tx, const uint16_t *Ty, int N,
-                                                int2 mxy, int eps, int &nx, int &ny) {
-    const int val[4] = {mxy.x + eps, mxy.x - eps + 1, mxy.y + eps, mxy.y - eps + 1};
+// Marginal counts of one sample (x, y) with k-th distance eps > 0: entries of the
+// sorted x codes xs and of the sorted y codes ys strictly inside (v - eps, v + eps),
+// minus the sample itself.  Each of the four lower bounds starts from its bucket
+// range [T[b], T[b + 1]]; the searches advance in lockstep from the widest range's
+// step, so their LDS reads are in flight together.  A probe stops at its range's end
+// (the entry before the end may lie at index -1, which is readable and moves nothing).
+template <int W>
+__device__ __forceinline__ void marginal_counts(const int *xs, const int *ys, const uint16_t *Tx,
+                                                const uint16_t *Ty, int x, int y, int eps, int &nx,
+                                                int &ny) {
+    const int val[4] = {x + eps, x - eps + 1, y + eps, y - eps + 1};
     int pos[4], hi[4], span = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const uint16_t *T = i < 2 ? Tx : Ty;
-        const int b = tab_bucket(val[i]);
-        pos[i] = T[b];
-        hi[i] = T[b + 1];
+        const uint16_t *T = (i < 2 ? Tx : Ty) + tab_bucket<W>(val[i]);
+        pos[i] = T[0];
+        hi[i] = T[1];
         span = max(span, hi[i] - pos[i]);
     }
     for (int st = span > 0 ? 1 << (31 - __clz(span)) : 0; st > 0; st >>= 1) {
-        int c[4];
+        int t[4], c[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = (i < 2 ? xo : yo)[min(pos[i] + st, N) - 1].x;
+        for (int i = 0; i < 4; ++i) {
+            t[i] = min(pos[i] + st, hi[i]);
+            c[i] = (i < 2 ? xs : ys)[t[i] - 1];
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (pos[i] + st <= hi[i] && c[i] < val[i]) pos[i] += st;
+        for (int i = 0; i < 4; ++i) pos[i] = c[i] < val[i] ? t[i] : pos[i];
     }
     nx = pos[0] - pos[1] - 1;
     ny = pos[2] - pos[3] - 1;
 }
 
-constexpr int kPad = 4;             // sentinel samples on each side of the x order
-constexpr int kFar = 1 << 29;       // sentinel x: its distance to any sample exceeds kUnset
-constexpr int kUnset = 1 << 28;     // k-th distance before k samples are seen: above any
-                                    // code difference (< 2^24), below any sentinel distance
+constexpr int kPad = 4;             // sentinel samples on each side of a list
+constexpr int kFar = 1 << 29;       // sentinel code: its distance to any sample exceeds kUnset
+constexpr int kUnset = (1 << 24) - 32;  // k-th distance before k samples are seen: above any
+                                    // code difference (<= 2^23), below any sentinel distance,
+                                    // and the greatest list distance of a walk start
 
 // v_med3_i32: the middle of three signed integers.  With lo <= hi it is d
 // clamped to [lo, hi] in one instruction (the compiler forms it only for
@@ -177,150 +212,311 @@ __device__ __forceinline__ void insert_k(int (&best)[K], int d) {
     best[0] = min(best[0], d);
 }
 
-// Neighbour search and counts for all samples of one pair.
-//   xo[p] = (x, y) in x order, yo[q] = (y, x) in y order, both with kPad
-//   sentinels on each side; yrank[p] = y-order position of x-order sample p;
-//   perm[p] = member of x-order sample p; epsL = N ints of LDS scratch;
-//   Tx, Ty = bucket tables of the x and y orders, every entry N on entry (Tx
-//   already built unless build_tx), every entry N again on return.
-// Returns the FP64 sum of H_nx + H_ny over all samples.
+// LDS of one pair.  The lists of the neighbour search live in `lists`: the x order's
+// two lists, then the y order's, each list between kPad sentinels,
+//   [pad | list 0: N / 2 | pad | pad | list 1: N - N / 2 | pad]   = N + 16 entries,
+// entry = (walked coordinate, other coordinate).  Before the lists are written the
+// region serves as scratch, and after the walks as the sorted codes xs[N], ys[N] of
+// the counts (from its second word on).
+struct PairLds {
+    int2 *lists;
+    int *eps;         // [N] y codes in y order, then walk starts, then k-th distances
+    uint16_t *yrank;  // [N] y rank of x-order sample p
+    uint16_t *other;  // [N] sample p's entry in the y order's lists, then its place in the
+                      // other list of its walk
+    uint16_t *Tx, *Ty;
+    uint16_t *perm;   // [N] members of the x order, where they are not stored (pairs mode)
+};
+
+constexpr int list_entries(int N) { return N + 4 * kPad; }
+
+// The bytes of `lists`: both orders' lists, or the exchange buffer of the sort.
+template <int W>
+__host__ __device__ inline size_t lists_bytes(int N) {
+    const size_t l = (size_t)2 * (N + 4 * kPad) * 8, x = (size_t)Pair<W>::kMax * 8;
+    return l > x ? l : x;
+}
+template <int W>
+__host__ __device__ inline size_t pair_lds_bytes(int N, bool perm) {
+    return lists_bytes<W>(N) + (size_t)N * 4 + (size_t)N * 4 + (size_t)Pair<W>::kTab * 4 + (perm ? (size_t)N * 2 : 0);
+}
+template <int W>
+__device__ __forceinline__ PairLds pair_lds(void *raw, int N) {
+    PairLds s;
+    s.lists = reinterpret_cast<int2 *>(raw);
+    s.eps = reinterpret_cast<int *>((char *)raw + lists_bytes<W>(N));
+    s.yrank = reinterpret_cast<uint16_t *>(s.eps + N);
+    s.other = s.yrank + N;
+    s.Tx = s.other + N;
+    s.Ty = s.Tx + Pair<W>::kTab;
+    s.perm = s.Ty + Pair<W>::kTab;
+    return s;
+}
+
+// One pair's samples as a thread holds them on entry: x-order sample p = tid + kT i has
+// code x[i] and the spread sx[i] of its nearest codes in x; y-order sample j = tid + kT i
+// has code y[i], the x code xj[i] and the x-order position pj[i].
+struct Samples {
+    int x[kPer], sx[kPer], y[kPer], xj[kPer], pj[kPer];
+};
+
+// Entry of the sample of rank r in its order's lists, q1 of the ranks below r being in
+// list 1 (clamped into the list, so that even unprepared orders stay in bounds).
+__device__ __forceinline__ int list_place(bool up, int r, int q1, int n0, int n1) {
+    return up ? kPad + n0 + 2 * kPad + min(q1, n1 - 1) : kPad + min(max(r - q1, 0), n0 - 1);
+}
+
+constexpr int kSpread = 16;  // the spread of a sample's 2 kSpread nearest codes predicts its
+                             // walk's strip (4 % fewer steps than with the k nearest)
+
+__device__ __forceinline__ int spread_at(const int *a, int p, int N) {
+    return a[min(p + kSpread, N - 1)] - a[max(p - kSpread, 0)];
+}
+
+// Exclusive prefix over the chunk counts c[0 .. C): lane l of every wave gets its own.
+template <int C>
+__device__ __forceinline__ int chunk_prefix(const int *c) {
+    const int lane = threadIdx.x & 63;
+    const int v = lane < C ? c[lane] : 0;
+    int s = v;
+#pragma unroll
+    for (int d = 1; d < C; d <<= 1) {
+        const int t = __shfl_up(s, d);
+        if (lane >= d) s += t;
+    }
+    return s - v;
+}
+
+__device__ __forceinline__ int mask_below(uint64_t m) {  // set bits below this lane
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+}
+
+constexpr int kRefill = 16;  // idle lanes that start new walks together
+
+// Neighbour search and counts for all samples of one pair.  Returns the FP64 sum of
+// H_nx + H_ny over all samples in every thread; perm[p] = member of x-order sample p
+// (read only for cnt).  Tx is built here from xs = (int *)lists when build_tx, else it
+// is already complete.
 //
-// Walk phase: first every sample's walk order and start position are computed
-// with all lanes busy.  Then the x order is dealt to the waves in chunks of 64
-// samples, round robin.  A lane walks one sample at a time; once 16 lanes of the
-// wave have finished, they take the wave's next unclaimed samples (handed out in
-// lane order from a wave-uniform counter), so short and long walks do not wait
-// for each other.
+// Lists: sample p's place in its half of the x order is the number of earlier samples
+// of the same half (a ballot per 64 samples and a prefix over the chunk counts); its
+// place in the other half is p minus that, so a change of lists needs no search.
+//
+// Walk phase: the x order is dealt to the waves in chunks of 64 samples, the middle
+// chunks first (the samples at the ends of an order have short walks, which then fill
+// the end of the phase).  A lane walks one sample at a time; once kRefill lanes of the
+// wave have finished, they change lists or take the wave's next unclaimed samples
+// (handed out in lane order from a wave-uniform counter), so short and long walks do
+// not wait for each other.
 // A walk takes 4 samples per side per step; a side stops once the farthest of
 // its 4 is at least the current k-th distance away along the walked coordinate
 // (always so for a sentinel, as the k-th distance starts at kUnset).  Samples
 // past that point never change the k smallest, so the overscan is harmless; a
 // block starts at most 3 samples past the last real one, and a stopped side
-// reads the 4 sentinels at its end, so reads stay within the padding.
-// Count phase: thread t takes samples t, t + 256, ... and counts the marginals
+// reads a block of sentinels, so reads stay within the lists.  A step has no branch:
+// a lane whose walk is over reads sentinels on both sides, which change nothing, and
+// which lanes still walk is a ballot of two comparisons, so the bookkeeping is scalar.
+// Walk start of a sample: entry of `lists` (13 bits) | the distance to the other list
+// in units of 32, rounded down (a list visited for nothing changes no result).
+// Count phase: thread t takes samples t, t + kT, ... and counts the marginals
 // by bucket table and binary search; the partial sums are combined in a fixed
-// order, so the FP64 total is reproducible.  Returns the total in every thread.
-template <int K>
-__device__ double ksg_points(const int2 *xo, const int2 *yo, const uint16_t *yrank, int N,
-                             const double *__restrict__ H, const uint16_t *perm,
-                             int32_t *__restrict__ cnt, int *epsL, uint16_t *Tx, uint16_t *Ty,
-                             bool build_tx) {
-    __shared__ double s_part[kKsgWaves];
+// order, so the FP64 total is reproducible.
+template <int K, int W>
+__device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
+                           const uint16_t *__restrict__ perm, int32_t *__restrict__ cnt,
+                           bool build_tx) {
+    typedef Pair<W> G;
+    constexpr int T = G::kT, C = G::kChunks;
+    __shared__ double s_part[W];
+    __shared__ int s_cy[C], s_cx[C];   // samples of the upper half per chunk of an order
+    __shared__ int s_edge[4];          // x at ranks n0 - 1, n0; y likewise
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // i-th sample of this wave (increasing in i)
-    auto sample = [&](int i) { return ((i >> 6) * kKsgWaves + wave) * 64 + (i & 63); };
-    int p = sample(lane);
-    bool active = false;
-    const int2 *A = xo;
-    const int2 *L = xo, *R = xo;  // next blocks: L[0..3] left (farthest first), R[0..3] right
-    int2 me = make_int2(0, 0);
+    const int n0 = N / 2, n1 = N - n0;
+    const int LY = list_entries(N);    // first entry of the y order's lists
+    const int H1 = n0 + 2 * kPad;      // a second list's offset from the first
+
+    // y codes in y order, y ranks, halves of the y order
+    uint64_t my[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int j = tid + T * i;
+        if (j < N) {
+            S.eps[j] = s.y[i];
+            S.yrank[s.pj[i]] = (uint16_t)j;
+            if (j == n0 - 1 || j == n0) {
+                s_edge[j - n0 + 1] = s.x[i];  // here j is a rank of the x order
+                s_edge[j - n0 + 3] = s.y[i];
+            }
+        }
+        my[i] = __ballot(j < N && s.pj[i] >= n0);
+        if (lane == 0) s_cy[i * W + wave] = __popcll(my[i]);
+    }
+    tab_fill<W>(S.Ty, N);
+    if (build_tx) tab_fill<W>(S.Tx, N);
+    __syncthreads();
+
+    // the y order's lists; the x order's halves
+    const int py = chunk_prefix<C>(s_cy);
+    int yv[kPer], jr[kPer];
+    uint64_t mx[kPer];
+    uint32_t in_y = 0;  // bit i: sample i walks the y order
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int p = tid + T * i;
+        const int q1 = __builtin_amdgcn_readlane(py, i * W + wave) + mask_below(my[i]);
+        if (p < N) {  // here p is a rank of the y order
+            const int at = LY + list_place(s.pj[i] >= n0, p, q1, n0, n1);
+            S.lists[at] = make_int2(s.y[i], s.xj[i]);
+            S.other[s.pj[i]] = (uint16_t)at;
+        }
+        jr[i] = p < N ? min((int)S.yrank[p], N - 1) : 0;
+        yv[i] = S.eps[jr[i]];
+        if (p < N && spread_at(S.eps, jr[i], N) > s.sx[i]) in_y |= 1u << i;
+        mx[i] = __ballot(p < N && jr[i] >= n0);
+        if (lane == 0) s_cx[i * W + wave] = __popcll(mx[i]);
+    }
+    tab_scatter<W>(S.eps, S.Ty, N);
+    if (build_tx) tab_scatter<W>(reinterpret_cast<const int *>(S.lists), S.Tx, N);
+    __syncthreads();
+
+    // the x order's lists, the sentinels, the walk starts
+    const int px = chunk_prefix<C>(s_cx);
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int p = tid + T * i;
+        const int q1 = __builtin_amdgcn_readlane(px, i * W + wave) + mask_below(mx[i]);
+        if (p < N) {
+            const bool up = jr[i] >= n0;
+            const int at = list_place(up, p, q1, n0, n1);
+            S.lists[at] = make_int2(s.x[i], yv[i]);
+            // own entry + entry of the other list = first entries of both + rank
+            int start = at, sum = 2 * kPad + H1 + p;
+            int gap = up ? yv[i] - s_edge[2] : s_edge[3] - yv[i];
+            if (in_y >> i & 1) {
+                start = S.other[p];
+                sum = 2 * (LY + kPad) + H1 + jr[i];
+                gap = p >= n0 ? s.x[i] - s_edge[0] : s_edge[1] - s.x[i];
+            }
+            S.other[p] = (uint16_t)min(max(sum - start, kPad), LY + LY - kPad);
+            S.eps[p] = (int)((uint32_t)start | (uint32_t)max(gap, 0) >> 5 << 13);
+        }
+    }
+    if (tid < 8 * kPad) {
+        // pads 0..3 of each order: left and right of the two lists
+        const int pad = (tid >> 2) & 3, u = tid & 3;
+        const int at = (tid >= 4 * kPad ? LY : 0) + u +
+                       (pad == 0 ? 0 : pad == 1 ? kPad + n0 : pad == 2 ? H1 : H1 + kPad + n1);
+        S.lists[at] = make_int2(pad & 1 ? kFar : -kFar, 0);
+    }
+    if (wave == 0) tab_scan<W>(S.Ty);
+    if (build_tx && wave == (W > 1 ? 1 : 0)) tab_scan<W>(S.Tx);
+    __syncthreads();
+
+    // ---- walks
+    typedef __attribute__((address_space(3))) const i32x2 lds_int2;
+    lds_int2 *const base = (lds_int2 *)reinterpret_cast<i32x2 *>(S.lists);
+    lds_int2 *const endL = base;                  // four sentinels: a finished left side
+    lds_int2 *const endR = base + H1 + kPad + n1; // ... and right side
+    const int nchunks = (N + 63) >> 6;
+    const int mine = 64 * ((nchunks - wave + W - 1) / W);  // this wave's share, whole chunks
+    // first sample of the wave's ci-th chunk, from the middle outwards; the partial
+    // chunk, the last one, comes last
+    auto chunk0 = [&](int ci) {
+        const int g = ci * W + wave, h = (g + 1) >> 1;
+        return 64 * (((nchunks - 1) >> 1) + (((g ^ nchunks) & 1) ? h : -h));
+    };
+    int p = 0, gap = 0;
+    i32x2 me = {0, 0};
+    lds_int2 *L = endL, *R = endR;
     int best[K];
 #pragma unroll
     for (int t = 0; t < K; ++t) best[t] = kUnset;
-
-    // Every sample's walk order and start position, with all lanes busy:
-    // epsL[p] = position | (walk in y order) << 16 until the walk of p ends.
-    for (int pp = tid; pp < N; pp += kKsgThreads) {
-        const int q = min((int)yrank[pp], N - 1);
-        // spread of the 32 nearest codes in each order: walk the sparser one (a
-        // wider window than the k nearest predicts the walk's strip better: 4 %
-        // fewer walk steps than with 2k on the synthetic ensembles)
-        constexpr int W = 16;
-        const int sx = xo[min(pp + W, N - 1)].x - xo[max(pp - W, 0)].x;
-        const int sy = yo[min(q + W, N - 1)].x - yo[max(q - W, 0)].x;
-        epsL[pp] = sy > sx ? (q | 0x10000) : pp;
-    }
-    tab_scatter(yo, Ty, N);
-    if (build_tx) tab_scatter(xo, Tx, N);
-    __syncthreads();
-    if (wave == 0)
-        tab_scan(Ty);
-    else if (wave == 1 && build_tx)
-        tab_scan(Tx);
-
-    auto start = [&](int pp) {
-        const int info = epsL[pp];
-        A = info >= 0x10000 ? yo : xo;
-        // a walk starts inside the sentinel-padded order, so it ends at a
-        // sentinel at the latest, whatever the data
-        const int pos = min(info & 0xffff, N - 1);
-        me = A[pos];  // the sample itself in its walk order: (walked, other)
-        L = A + pos - 4;
-        R = A + pos + 1;
+    int next = 0;  // first unclaimed sample of the wave
+    // the lanes of `idle` take the wave's next samples; returns those that got one
+    auto claim = [&](uint64_t idle) {
+        const int i = next + mask_below(idle), ci = next >> 6;
+        const int a0 = chunk0(ci), a1 = chunk0(ci + 1);
+        const int np = (i & 63) + ((i >> 6) == ci ? a0 : a1);
+        const uint64_t got = idle & __ballot(i < mine && np < N);
+        next += __popcll(idle);
+        if (__builtin_amdgcn_inverse_ballot_w64(got)) {
+            p = np;
+            const uint32_t info = (uint32_t)S.eps[p];
+            lds_int2 *at = base + (info & 0x1fff);
+            gap = (int)(info >> 13 << 5);
+            me = *at;
+            L = at - 4;
+            R = at + 1;
 #pragma unroll
-        for (int t = 0; t < K; ++t) best[t] = kUnset;
+            for (int t = 0; t < K; ++t) best[t] = kUnset;
+        }
+        return got;
     };
-
-    if (p < N) {
-        start(p);
-        active = true;
-    }
-    int next = 64;  // first unclaimed sample (wave-uniform)
-    bool more = sample(next) < N;
-    for (;;) {
-        if (active) {
-            // Both sides every step, no branches: a finished side reads the
-            // sentinel block at its end of the order, whose distances exceed
-            // every k-th distance, so it changes nothing.
-            int2 c[8];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                c[u] = L[u];
-                c[4 + u] = R[u];
+    uint64_t have = claim(~0ull), run = have;  // lanes with a sample; lanes still walking
+    while (have) {
+        const uint64_t fin = have & ~run;
+        // a batch of list changes and claims costs its instructions once for its lanes
+        if (__popcll(fin) >= kRefill || !run) {
+            // nearer to the other list than to the k-th neighbour: go on there
+            const uint64_t more = fin & __ballot(gap < best[K - 1]);
+            if (__builtin_amdgcn_inverse_ballot_w64(more)) {
+                R = base + S.other[p];
+                L = R - 4;
+                gap = kUnset;  // no third list
             }
+            const uint64_t done = fin & ~more;
+            if (__builtin_amdgcn_inverse_ballot_w64(done)) S.eps[p] = best[K - 1];
+            have &= ~done;
+            if (next < mine) have |= claim(done);
+            if (!have) break;
+        }
+        i32x2 c[8];
 #pragma unroll
-            for (int u = 3; u >= 0; --u)
-                insert_k<K>(best, max(me.x - c[u].x, absdiff_u32(me.y, c[u].y)));
+        for (int u = 0; u < 4; ++u) {
+            c[u] = L[u];
+            c[4 + u] = R[u];
+        }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                insert_k<K>(best, max(c[4 + u].x - me.x, absdiff_u32(me.y, c[4 + u].y)));
-            // a side goes on while its farthest sample is nearer than the k-th
-            // distance (never for a sentinel, never past the padding)
-            const bool al = (me.x - c[0].x) < best[K - 1];
-            const bool ar = (c[7].x - me.x) < best[K - 1];
-            L = al ? L - 4 : A - kPad;
-            R = ar ? R + 4 : A + N;
-            if (!al && !ar) {
-                epsL[p] = best[K - 1];
-                active = false;
-            }
-        }
-        const uint64_t idle = __ballot(!active);
-        if (!more) {
-            if (idle == ~0ull) break;
-            continue;
-        }
-        // refill once a quarter of the lanes is idle: the claim code runs with
-        // only the idle lanes on, so batching claims costs fewer issue slots than
-        // the short idle wait (measured: 51.3 ms refilling at every step, 50.5 ms
-        // at 16 idle lanes, 52.2 ms at 32)
-        if (__popcll(idle) < 16) continue;
-        if (!active) {
-            // rank of this lane among the idle ones
-            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
-                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0));
-            const int np = sample(next + rank);
-            if (np < N) {
-                p = np;
-                start(p);
-                active = true;
-            }
-        }
-        next = __builtin_amdgcn_readfirstlane(next + __popcll(idle));
-        more = sample(next) < N;
+        for (int u = 3; u >= 0; --u)
+            insert_k<K>(best, max(me.x - c[u].x, absdiff_u32(me.y, c[u].y)));
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            insert_k<K>(best, max(c[4 + u].x - me.x, absdiff_u32(me.y, c[4 + u].y)));
+        // a side goes on while its farthest sample is nearer than the k-th
+        // distance (never for a sentinel, never past the padding)
+        const bool al = (me.x - c[0].x) < best[K - 1];
+        const bool ar = (c[7].x - me.x) < best[K - 1];
+        L = al ? L - 4 : endL;
+        R = ar ? R + 4 : endR;
+        run = __ballot(al) | __ballot(ar);
     }
     __syncthreads();
 
+    // ---- counts, over the sorted codes
+    int *xs = reinterpret_cast<int *>(S.lists) + 1, *ys = xs + N;  // xs[-1] is readable
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int p = tid + T * i;
+        if (p < N) {
+            xs[p] = s.x[i];
+            ys[p] = s.y[i];
+        }
+    }
+    __syncthreads();
     double acc = 0.0;
-    for (int pp = tid; pp < N; pp += kKsgThreads) {
-        const int2 mxy = xo[pp];
-        const int eps = epsL[pp];
+    for (int i = 0; i < kPer; ++i) {
+        const int pp = tid + T * i;
+        if (pp >= N) break;
+        const int eps = S.eps[pp];
         int nx = 0, ny = 0;
-        if (eps > 0) marginal_counts(xo, yo, Tx, Ty, N, mxy, eps, nx, ny);
+        if (eps > 0)
+            marginal_counts<W>(xs, ys, S.Tx, S.Ty, xs[pp], ys[min((int)S.yrank[pp], N - 1)], eps,
+                               nx, ny);
         nx = min(max(nx, 0), N - 1);  // no-ops on sorted orders; keep H reads in bounds
         ny = min(max(ny, 0), N - 1);
-        acc += H[nx] + H[ny];
+        acc += kHarmonic.v[nx] + kHarmonic.v[ny];
         if (cnt) {
             const int m = perm[pp];
             cnt[m] = nx;
@@ -332,22 +528,19 @@ __device__ double ksg_points(const int2 *xo, const int2 *yo, const uint16_t *yra
     __syncthreads();
     double total = 0.0;
 #pragma unroll
-    for (int w = 0; w < kKsgWaves; ++w) total += s_part[w];
-    tab_fill(Ty, N);  // for the next pair (the counts above were the last readers)
-    if (build_tx) tab_fill(Tx, N);
+    for (int w = 0; w < W; ++w) total += s_part[w];
     return total;
 }
 
-// Ascending bitonic sort of 256 E keys held E per thread in registers (thread t
-// holds keys E t .. E t + E - 1).  Compare-exchange partners closer than E are in
-// the thread's own registers, partners up to 64 E apart are in the same wave
-// (lane shuffles), and only the strides of 64 E and more go through LDS (xchg,
-// 256 E keys), so a sort of 1024 keys takes 3 workgroup barriers instead of 55.
-template <int E>
-__device__ __forceinline__ void block_sort_regs(unsigned long long (&k)[E],
+// Ascending bitonic sort of kPer T keys held kPer per thread in registers (thread t
+// holds keys kPer t .. kPer t + kPer - 1).  Compare-exchange partners closer than kPer
+// are in the thread's own registers, partners up to 64 kPer apart are in the same wave
+// (lane shuffles), and only larger strides go through LDS (xchg, kPer T keys).
+template <int W>
+__device__ __forceinline__ void block_sort_regs(unsigned long long (&k)[kPer],
                                                 unsigned long long *xchg) {
     const int tid = threadIdx.x;
-    constexpr int PT = kKsgThreads * E;
+    constexpr int E = kPer, PT = Pair<W>::kMax;
     for (int size = 2; size <= PT; size <<= 1) {
         for (int stride = size >> 1; stride >= E; stride >>= 1) {
             const bool cross = stride >= 64 * E;
@@ -387,139 +580,62 @@ __device__ __forceinline__ void block_sort_regs(unsigned long long (&k)[E],
     __syncthreads();  // xchg may be reused by the caller
 }
 
-// The y order from a complete x order: (y, x position) keys sorted in
-// registers, written out as yo[q] = (y, x) with each sample's y rank.  The
-// exchange buffer of the sort is the yo region itself.
-template <int E>
-__device__ __forceinline__ void build_y_order_e(int2 *xo, int2 *yo, uint16_t *yrank, int N) {
+// m[i] = member of rank tid + kT i of a column: its stored order, or (order null) the
+// column sorted here by (code, member) through `scratch` (lists_bytes).
+template <int W>
+__device__ __forceinline__ void sorted_members(const int32_t *__restrict__ c,
+                                               const uint16_t *__restrict__ order, int N,
+                                               void *scratch, int (&m)[kPer]) {
     const int tid = threadIdx.x;
-    unsigned long long k[E];
+    constexpr int T = Pair<W>::kT;
+    if (order) {
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int p = E * tid + j;
-        k[j] = p < N ? (((unsigned long long)(uint32_t)xo[p].y) << 32) | (unsigned)p : ~0ull;
-    }
-    block_sort_regs<E>(k, reinterpret_cast<unsigned long long *>(yo));
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int q = E * tid + j;
-        if (q < N) {
-            const int p = (int)(k[j] & 0xffffffffu);
-            yo[q] = make_int2((int)(k[j] >> 32), xo[p].x);
-            yrank[p] = (uint16_t)q;
+        for (int i = 0; i < kPer; ++i) {  // in bounds even if never prepared
+            const int r = tid + T * i;
+            m[i] = r < N ? min((int)order[r], N - 1) : 0;
         }
+        return;
     }
-    if (tid < kPad) {
-        yo[-1 - tid] = make_int2(-kFar, 0);
-        yo[N + tid] = make_int2(kFar, 0);
+    unsigned long long k[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int r = kPer * tid + j;
+        k[j] = r < N ? (((unsigned long long)(uint32_t)c[r]) << 16) | (unsigned)r : ~0ull;
+    }
+    block_sort_regs<W>(k, reinterpret_cast<unsigned long long *>(scratch));
+    uint16_t *list = reinterpret_cast<uint16_t *>(scratch);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int r = kPer * tid + j;
+        if (r < N) list[r] = (uint16_t)(k[j] & 0xffff);
     }
     __syncthreads();
-}
-
-// The x order of a pair from its two code rows: (x code, member) keys sorted in
-// registers, written out as xo[p] = (x, y) and perm[p] = member (exchange buffer:
-// the yo region).
-template <int E>
-__device__ __forceinline__ void build_x_order_e(const int32_t *__restrict__ ca,
-                                                const int32_t *__restrict__ cb, int N, int2 *xo,
-                                                uint16_t *perm, int2 *yo) {
-    const int tid = threadIdx.x;
-    unsigned long long k[E];
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int m = E * tid + j;
-        k[j] = m < N ? (((unsigned long long)(uint32_t)ca[m]) << 16) | (unsigned)m : ~0ull;
-    }
-    block_sort_regs<E>(k, reinterpret_cast<unsigned long long *>(yo));
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const int p = E * tid + j;
-        if (p < N) {
-            const int m = (int)(k[j] & 0xffff);
-            perm[p] = (uint16_t)m;
-            xo[p] = make_int2((int)(k[j] >> 16), cb[m]);
-        }
-    }
+    for (int i = 0; i < kPer; ++i) m[i] = tid + T * i < N ? (int)list[tid + T * i] : 0;
     __syncthreads();
-}
-
-__device__ __forceinline__ void build_x_order(const int32_t *__restrict__ ca,
-                                              const int32_t *__restrict__ cb, int N, int P,
-                                              int2 *xo, uint16_t *perm, int2 *yo) {
-    if (P <= kKsgThreads)
-        build_x_order_e<1>(ca, cb, N, xo, perm, yo);
-    else if (P <= 2 * kKsgThreads)
-        build_x_order_e<2>(ca, cb, N, xo, perm, yo);
-    else if (P <= 4 * kKsgThreads)
-        build_x_order_e<4>(ca, cb, N, xo, perm, yo);
-    else {  // N > 1024: sort in LDS (8 keys per thread in registers would cost occupancy)
-        const int tid = threadIdx.x;
-        unsigned long long *keys = reinterpret_cast<unsigned long long *>(yo);
-        for (int m = tid; m < P; m += kKsgThreads)
-            keys[m] = m < N ? (((unsigned long long)(uint32_t)ca[m]) << 16) | (unsigned)m : ~0ull;
-        __syncthreads();
-        block_bitonic_sort(keys, P);
-        for (int p = tid; p < N; p += kKsgThreads) {
-            const int m = (int)(keys[p] & 0xffff);
-            perm[p] = (uint16_t)m;
-            xo[p] = make_int2((int)(keys[p] >> 16), cb[m]);
-        }
-        __syncthreads();
-    }
-}
-
-__device__ __forceinline__ void build_y_order(int2 *xo, int2 *yo, uint16_t *yrank, int N, int P) {
-    if (P <= kKsgThreads)
-        build_y_order_e<1>(xo, yo, yrank, N);
-    else if (P <= 2 * kKsgThreads)
-        build_y_order_e<2>(xo, yo, yrank, N);
-    else if (P <= 4 * kKsgThreads)
-        build_y_order_e<4>(xo, yo, yrank, N);
-    else {  // N > 1024: sort in LDS
-        const int tid = threadIdx.x;
-        unsigned long long *keys = reinterpret_cast<unsigned long long *>(yo);
-        for (int p = tid; p < P; p += kKsgThreads)
-            keys[p] = p < N ? (((unsigned long long)(uint32_t)xo[p].y) << 32) | (unsigned)p : ~0ull;
-        __syncthreads();
-        block_bitonic_sort(keys, P);
-        for (int q = tid; q < N; q += kKsgThreads) {
-            const unsigned long long key = keys[q];
-            const int p = (int)(key & 0xffffffffu);
-            yo[q] = make_int2((int)(key >> 32), xo[p].x);
-            yrank[p] = (uint16_t)q;
-        }
-        __syncthreads();
-        if (tid < kPad) {
-            yo[-1 - tid] = make_int2(-kFar, 0);
-            yo[N + tid] = make_int2(kFar, 0);
-        }
-        __syncthreads();
-    }
-}
-
-// Sentinels of the x order (written once per launch by each workgroup).
-__device__ __forceinline__ void ksg_sentinels(int2 *xy, int N) {
-    const int tid = threadIdx.x;
-    if (tid < kPad) {
-        xy[-1 - tid] = make_int2(-kFar, 0);
-        xy[N + tid] = make_int2(kFar, 0);
-    }
 }
 
 // ----------------------------------------------------------- field mode ----
-// Prologue: for each reference, its codes in ascending (code, member) order and
-// the member permutation; plus the harmonic table H[0..N] (sequential FP64 sum).
+// Prologue: for each reference (64 per launch, as a kernel argument), its codes in
+// ascending (code, member) order, the member permutation and its inverse, and its
+// entry of the reference list.
+constexpr int kSortRefs = 64;
+struct SortRefs {
+    int64_t v[kSortRefs];
+};
+
 __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
-                                    const uint16_t *__restrict__ order, int N,
-                                    const int64_t *__restrict__ refs, int32_t *__restrict__ xs,
-                                    uint16_t *__restrict__ perm, uint16_t *__restrict__ invp,
-                                    double *__restrict__ H) {
+                                    const uint16_t *__restrict__ order, int N, SortRefs rs,
+                                    int64_t *__restrict__ refs, int32_t *__restrict__ xs,
+                                    uint16_t *__restrict__ perm, uint16_t *__restrict__ invp) {
     extern __shared__ unsigned long long s_keys[];
     const int r = blockIdx.x;
     const int P = pow2_ceil(N);
-    const int32_t *c = code + refs[r] * N;
+    const int64_t v = rs.v[r];
+    const int32_t *c = code + v * N;
+    if (threadIdx.x == 0) refs[r] = v;
     if (order) {  // the column's stored order
-        const uint16_t *o = order + refs[r] * N;
+        const uint16_t *o = order + v * N;
         for (int p = threadIdx.x; p < N; p += kKsgThreads) {
             const int m = min((int)o[p], N - 1);  // in bounds even if never prepared
             xs[(int64_t)r * N + p] = c[m];
@@ -536,14 +652,6 @@ __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
             xs[(int64_t)r * N + p] = (int32_t)(s_keys[p] >> 16);
             perm[(int64_t)r * N + p] = (uint16_t)m;
             invp[(int64_t)r * N + m] = (uint16_t)p;
-        }
-    }
-    if (r == 0 && threadIdx.x == 0) {
-        double h = 0.0;
-        H[0] = 0.0;
-        for (int i = 1; i <= N; ++i) {
-            h += 1.0 / (double)i;
-            H[i] = h;
         }
     }
 }
@@ -823,51 +931,42 @@ __global__ __launch_bounds__(kKsgThreads) void ksg_order_block_kernel(
     }
 }
 
-// LDS plan of both kernels: xo (N + 2 kPad) int2 | yo (P + 2 kPad) int2, also the
-// sort keys and exchange buffer | perm N uint16 | yrank N uint16 | eps N int32 |
-// Tx, Ty kTabN uint16 each, with P = max(pow2_ceil(N), 256) (the register sort
-// always moves 256 E keys).
-__host__ __device__ inline size_t ksg_lds_bytes(int N, int P) {
-    return (size_t)(N + 2 * kPad) * 8 + (size_t)(P + 2 * kPad) * 8 + (size_t)N * 4 +
-           (size_t)N * 4 + (size_t)kTabN * 4;
-}
-
-template <int K>
-__global__ __launch_bounds__(kKsgThreads) __attribute__((amdgpu_waves_per_eu(6))) void ksg_field_kernel(
+template <int K, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void ksg_field_kernel(
     const int32_t *__restrict__ code_q, const int32_t *__restrict__ flags_r,
     const int32_t *__restrict__ flags_q, int N, int64_t V, const int64_t *__restrict__ refs,
     int n_ref, const int32_t *__restrict__ xs_all, const uint16_t *__restrict__ perm_all,
-    const double *__restrict__ H, float *__restrict__ out, int32_t *__restrict__ counts,
-    const int32_t *__restrict__ code_r, const uint16_t *__restrict__ order_q,
-    const uint16_t *__restrict__ invp_all) {
+    float *__restrict__ out, int32_t *__restrict__ counts, const int32_t *__restrict__ code_r,
+    const uint16_t *__restrict__ order_q, const uint16_t *__restrict__ invp_all) {
     extern __shared__ int4 s_raw[];
-    const int P = max(pow2_ceil(N), kKsgThreads);  // y-order region
-    int2 *xo = reinterpret_cast<int2 *>(s_raw) + kPad;
-    int2 *yo = xo + N + 2 * kPad;
-    uint16_t *perm = reinterpret_cast<uint16_t *>(yo + P + kPad);
-    uint16_t *yrank = perm + N;
-    int *epsL = reinterpret_cast<int *>(yrank + N);  // 4-byte aligned: N uint16 x 2
-    uint16_t *Tx = reinterpret_cast<uint16_t *>(epsL + N);
-    uint16_t *Ty = Tx + kTabN;
-    int *tmp = reinterpret_cast<int *>(yo);  // the query row in member order
+    constexpr int T = Pair<W>::kT;
+    const PairLds S = pair_lds<W>(s_raw, N);
     const int tid = threadIdx.x;
-    const double base = H[K - 1] + H[N - 1];
-    ksg_sentinels(xo, N);
-    tab_fill(Ty, N);
+    const double base = kHarmonic.v[K - 1] + kHarmonic.v[N - 1];
 
     for (int r = 0; r < n_ref; ++r) {
         const int32_t fr = flags_r[refs[r]];
+        const int32_t *xs = xs_all + (int64_t)r * N;
+        const uint16_t *invp = invp_all + (int64_t)r * N, *perm = perm_all + (int64_t)r * N;
+        const int32_t *cr = code_r + refs[r] * N;
+        // the reference's codes in its own order and its bucket table, shared by all
+        // its queries
+        Samples s;
+        int *xl = reinterpret_cast<int *>(S.lists);
         __syncthreads();
-        for (int p = tid; p < N; p += kKsgThreads) {
-            xo[p].x = xs_all[(int64_t)r * N + p];
-            perm[p] = perm_all[(int64_t)r * N + p];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int p = tid + T * i;
+            s.x[i] = p < N ? xs[p] : 0;
+            if (p < N) xl[p] = s.x[i];
         }
-        tab_fill(Tx, N);
+        tab_fill<W>(S.Tx, N);
         __syncthreads();
-        // the reference's bucket table, shared by all its queries
-        tab_scatter(xo, Tx, N);
+        tab_scatter<W>(xl, S.Tx, N);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) s.sx[i] = spread_at(xl, min(tid + T * i, N - 1), N);
         __syncthreads();
-        if (tid < 64) tab_scan(Tx);
+        if (tid < 64) tab_scan<W>(S.Tx);
         __syncthreads();
         for (int64_t q = blockIdx.x; q < V; q += gridDim.x) {
             const int32_t *cq = code_q + q * N;
@@ -878,64 +977,36 @@ __global__ __launch_bounds__(kKsgThreads) __attribute__((amdgpu_waves_per_eu(6))
                     out[(int64_t)r * V + q] = ((fr | fq) & NDF_FLAG_NONFINITE) ? __builtin_nanf("")
                                                                                 : 0.0f;
                 if (cnt)
-                    for (int i = tid; i < 2 * N; i += kKsgThreads) cnt[i] = 0;
+                    for (int i = tid; i < 2 * N; i += T) cnt[i] = 0;
                 continue;
             }
-            if (order_q) {
-                // both orders from stored ones: the query codes in x order, and the
-                // query's own sorted order for (y, x) and the y ranks
-                const uint16_t *oq = order_q + q * N;
-                const int32_t *cr = code_r + refs[r] * N;
-                const uint16_t *invp = invp_all + (int64_t)r * N;
-                for (int p = tid; p < N; p += kKsgThreads) xo[p].y = cq[perm[p]];
-                for (int j = tid; j < N; j += kKsgThreads) {
-                    const int m = min((int)oq[j], N - 1);  // in bounds even if never prepared
-                    yo[j] = make_int2(cq[m], cr[m]);
-                    yrank[min((int)invp[m], N - 1)] = (uint16_t)j;
-                }
-                if (tid < kPad) {
-                    yo[-1 - tid] = make_int2(-kFar, 0);
-                    yo[N + tid] = make_int2(kFar, 0);
-                }
-                __syncthreads();
-            } else {
-                // the query's codes: one coalesced row read, permuted into x order in LDS
-                for (int m = tid; m < N; m += kKsgThreads) tmp[m] = cq[m];
-                __syncthreads();
-                for (int p = tid; p < N; p += kKsgThreads) xo[p].y = tmp[perm[p]];
-                __syncthreads();
-                build_y_order(xo, yo, yrank, N, P);
+            int m[kPer];
+            sorted_members<W>(cq, order_q ? order_q + q * N : nullptr, N, S.lists, m);
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                s.y[i] = cq[m[i]];
+                s.xj[i] = cr[m[i]];
+                s.pj[i] = min((int)invp[m[i]], N - 1);
             }
-            const double acc =
-                ksg_points<K>(xo, yo, yrank, N, H, perm, cnt, epsL, Tx, Ty, false);
+            const double acc = ksg_pair<K, W>(S, s, N, perm, cnt, false);
             if (tid == 0) out[(int64_t)r * V + q] = (float)(base - acc / (double)N);
-            __syncthreads();
         }
     }
 }
 
 // ----------------------------------------------------------- pairs mode ----
-template <int K>
-__global__ __launch_bounds__(kKsgThreads) __attribute__((amdgpu_waves_per_eu(6))) void ksg_pairs_kernel(
+template <int K, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void ksg_pairs_kernel(
     const int32_t *__restrict__ code_a, const int32_t *__restrict__ code_b,
     const int32_t *__restrict__ flags_a, const int32_t *__restrict__ flags_b, int N, int64_t V,
-    const int64_t *__restrict__ pairs, int64_t B, const double *__restrict__ H,
-    float *__restrict__ out, int32_t *__restrict__ counts, const uint16_t *__restrict__ order_a,
+    const int64_t *__restrict__ pairs, int64_t B, float *__restrict__ out,
+    int32_t *__restrict__ counts, const uint16_t *__restrict__ order_a,
     const uint16_t *__restrict__ order_b) {
     extern __shared__ int4 s_raw[];
-    const int P = max(pow2_ceil(N), kKsgThreads);  // y-order region
-    int2 *xo = reinterpret_cast<int2 *>(s_raw) + kPad;
-    int2 *yo = xo + N + 2 * kPad;
-    uint16_t *perm = reinterpret_cast<uint16_t *>(yo + P + kPad);
-    uint16_t *yrank = perm + N;
-    int *epsL = reinterpret_cast<int *>(yrank + N);
-    uint16_t *Tx = reinterpret_cast<uint16_t *>(epsL + N);
-    uint16_t *Ty = Tx + kTabN;
+    constexpr int T = Pair<W>::kT;
+    const PairLds S = pair_lds<W>(s_raw, N);
     const int tid = threadIdx.x;
-    const double base = H[K - 1] + H[N - 1];
-    ksg_sentinels(xo, N);
-    tab_fill(Tx, N);
-    tab_fill(Ty, N);
+    const double base = kHarmonic.v[K - 1] + kHarmonic.v[N - 1];
 
     for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
         const int64_t va = pairs[2 * b], vb = pairs[2 * b + 1];
@@ -943,56 +1014,47 @@ __global__ __launch_bounds__(kKsgThreads) __attribute__((amdgpu_waves_per_eu(6))
         if (va < 0 || va >= V || vb < 0 || vb >= V) {  // out-of-range pair: NaN, no reads
             if (tid == 0) out[b] = __builtin_nanf("");
             if (cnt)
-                for (int i = tid; i < 2 * N; i += kKsgThreads) cnt[i] = -1;
+                for (int i = tid; i < 2 * N; i += T) cnt[i] = -1;
             continue;
         }
         const int32_t f = flags_a[va] | flags_b[vb];
         if (f & (NDF_FLAG_CONSTANT | NDF_FLAG_NONFINITE)) {
             if (tid == 0) out[b] = (f & NDF_FLAG_NONFINITE) ? __builtin_nanf("") : 0.0f;
             if (cnt)
-                for (int i = tid; i < 2 * N; i += kKsgThreads) cnt[i] = 0;
+                for (int i = tid; i < 2 * N; i += T) cnt[i] = 0;
             continue;
         }
         const int32_t *ca = code_a + va * N, *cb = code_b + vb * N;
-        if (order_a) {
-            // x order = a's stored order, y order = b's; epsL holds the inverse
-            // x permutation until the walk
-            const uint16_t *oa = order_a + va * N, *ob = order_b + vb * N;
-            for (int p = tid; p < N; p += kKsgThreads) {
-                const int m = min((int)oa[p], N - 1);  // in bounds even if never prepared
-                perm[p] = (uint16_t)m;
-                xo[p] = make_int2(ca[m], cb[m]);
-                epsL[m] = p;
+        Samples s;
+        int ma[kPer], mb[kPer];
+        const uint16_t *perm = order_a ? order_a + va * N : S.perm;
+        sorted_members<W>(ca, order_a ? order_a + va * N : nullptr, N, S.lists, ma);
+        if (cnt && !order_a)
+            for (int i = 0; i < kPer; ++i)
+                if (tid + T * i < N) S.perm[tid + T * i] = (uint16_t)ma[i];
+        sorted_members<W>(cb, order_b ? order_b + vb * N : nullptr, N, S.lists, mb);
+        // xs and the inverse x permutation in the lists' region until they are written
+        int *xl = reinterpret_cast<int *>(S.lists);
+        uint16_t *inv = reinterpret_cast<uint16_t *>(xl + N);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int p = tid + T * i;
+            s.x[i] = ca[ma[i]];
+            if (p < N) {
+                xl[p] = s.x[i];
+                inv[ma[i]] = (uint16_t)p;
             }
-            __syncthreads();
-            for (int j = tid; j < N; j += kKsgThreads) {
-                const int m = min((int)ob[j], N - 1);
-                yo[j] = make_int2(cb[m], ca[m]);
-                yrank[min(epsL[m], N - 1)] = (uint16_t)j;
-            }
-            if (tid < kPad) {
-                yo[-1 - tid] = make_int2(-kFar, 0);
-                yo[N + tid] = make_int2(kFar, 0);
-            }
-            __syncthreads();
-        } else {
-            build_x_order(ca, cb, N, P, xo, perm, yo);
-            build_y_order(xo, yo, yrank, N, P);
+            s.y[i] = cb[mb[i]];
+            s.xj[i] = ca[mb[i]];
         }
-        const double acc = ksg_points<K>(xo, yo, yrank, N, H, perm, cnt, epsL, Tx, Ty, true);
-        if (tid == 0) out[b] = (float)(base - acc / (double)N);
         __syncthreads();
-    }
-}
-
-__global__ void harmonic_kernel(int N, double *H) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double h = 0.0;
-        H[0] = 0.0;
-        for (int i = 1; i <= N; ++i) {
-            h += 1.0 / (double)i;
-            H[i] = h;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            s.sx[i] = spread_at(xl, min(tid + T * i, N - 1), N);
+            s.pj[i] = min((int)inv[mb[i]], N - 1);
         }
+        const double acc = ksg_pair<K, W>(S, s, N, perm, cnt, true);
+        if (tid == 0) out[b] = (float)(base - acc / (double)N);
     }
 }
 
@@ -1003,8 +1065,9 @@ static int p2(int n) {
     return p;
 }
 
-// Workspace: H[0..N] | refs | x codes in x order [n_ref][N] | x-order members
-// [n_ref][N] | inverse x permutation [n_ref][N].
+// Workspace: FP64 [N + 1] (unused: the harmonic numbers are a constant) | refs |
+// x codes in x order [n_ref][N] | x-order members [n_ref][N] | inverse x permutation
+// [n_ref][N].
 size_t ksg_field_ws_bytes(int N, int n_ref) {
     return align_up((size_t)(N + 1) * sizeof(double), 256) +
            align_up((size_t)n_ref * sizeof(int64_t), 256) +
@@ -1012,42 +1075,52 @@ size_t ksg_field_ws_bytes(int N, int n_ref) {
            2 * align_up((size_t)n_ref * N * sizeof(uint16_t), 256);
 }
 
-// Grid of a striding kernel: `waves` times as many workgroups as the CUs hold at
-// once given the LDS of one item (160 KB per CU), never more than there are
+// Grid of a striding kernel: `rounds` times as many workgroups of `waves` waves as the
+// CUs hold at once given the LDS of one item (160 KB per CU), never more than there are
 // items.  Items differ in cost (walk lengths) and CUs in speed, so a grid of
 // only resident workgroups ends with a tail of the slowest ones; a larger grid
 // lets the hardware hand the waiting workgroups to whichever CU frees up first
-// (measured on the KSG field: 59.9 ms with 1 wave of workgroups, 51.3 with 16,
-// 51.0 with 64).
-static int ksg_grid(int64_t items, size_t lds, int waves) {
+// (measured on a KSG field of 50 ms: 20 % longer with 1 round of workgroups than with
+// 16).  Every workgroup of a field first loads its reference and writes its register
+// spills once, so a field takes 16 rounds (1000 members x 1.76M vertices: the same time
+// as 64 with 1.3 GB less written); pairs take 64 (2^18 pairs: 0.7 % faster than 16).
+static int ksg_grid(int64_t items, size_t lds, int waves, int rounds) {
     int64_t per_cu = (int64_t)(163840 / (lds > 0 ? lds : 1));
-    per_cu = per_cu < 1 ? 1 : (per_cu > 8 ? 8 : per_cu);
-    const int64_t g = 256 * per_cu * waves;
+    const int64_t cap = 32 / waves;
+    per_cu = per_cu < 1 ? 1 : (per_cu > cap ? cap : per_cu);
+    const int64_t g = 256 * per_cu * rounds;
     return (int)(items < g ? items : g);
 }
-constexpr int kPairWaves = 64;  // workgroup waves of the field and pairs kernels
-constexpr int kOrderWaves = 16;  // of the sorted-order kernel
+constexpr int kFieldRounds = 16;
+constexpr int kPairRounds = 64;
+constexpr int kOrderRounds = 16;
 
-struct FieldArgs {
-    const int32_t *cq, *fr, *fq;
-    int N;
-    int64_t V;
-    const int64_t *refs;
-    int n_ref;
-    const int32_t *xs;
-    const uint16_t *perm;
-    const double *H;
-    float *out;
-    int32_t *counts;
-    const int32_t *cr;
-    const uint16_t *order_q, *invp;
-};
+// f(waves as a constant) for N members: one wave per 256
+template <typename F>
+static void with_pair_waves(int N, F f) {
+    if (N <= Pair<1>::kMax)
+        f(std::integral_constant<int, 1>{});
+    else if (N <= Pair<2>::kMax)
+        f(std::integral_constant<int, 2>{});
+    else if (N <= Pair<4>::kMax)
+        f(std::integral_constant<int, 4>{});
+    else
+        f(std::integral_constant<int, 8>{});
+}
 
-template <int K>
-static void launch_field_k(dim3 g, size_t lds, hipStream_t st, const FieldArgs &a) {
-    hipLaunchKernelGGL(ksg_field_kernel<K>, g, dim3(kKsgThreads), lds, st, a.cq, a.fr, a.fq, a.N,
-                       a.V, a.refs, a.n_ref, a.xs, a.perm, a.H, a.out, a.counts, a.cr, a.order_q,
-                       a.invp);
+// f(k as a constant), 1 <= k <= 8
+template <typename F>
+static void with_k(int k, F f) {
+    switch (k) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+        default: f(std::integral_constant<int, 8>{}); break;
+    }
 }
 
 // Sorted member orders of every column of every variable (ndf_prepare).
@@ -1057,12 +1130,12 @@ int launch_ksg_orders(const ndf_ensemble *e, hipStream_t st) {
     if (N > 2048) {
         const size_t lds = (size_t)p2(N) * sizeof(unsigned long long);
         hipLaunchKernelGGL(ksg_order_block_kernel,
-                           dim3((unsigned)ksg_grid(ncol, lds, kOrderWaves)), dim3(kKsgThreads),
+                           dim3((unsigned)ksg_grid(ncol, lds, kKsgWaves, kOrderRounds)), dim3(kKsgThreads),
                            lds, st, e->code, N, ncol, e->order);
         return status_of_launch();
     }
     const int64_t wgs = ceil_div(ncol, kKsgWaves);
-    const int64_t cap = 256 * 8 * kOrderWaves;
+    const int64_t cap = 256 * 8 * kOrderRounds;
     const dim3 g((unsigned)(wgs < cap ? wgs : cap));
 #define NDF_ORDER_CASE(E)                                                                    \
     if (N <= 64 * E) {                                                                       \
@@ -1079,10 +1152,9 @@ int launch_ksg_orders(const ndf_ensemble *e, hipStream_t st) {
 int launch_ksg_field(const ndf_ensemble *e, int var_ref, int var_qry, const int64_t *ref_v,
                      int n_ref, int k, float *out, int32_t *counts, void *ws, hipStream_t st) {
     const int N = e->n_members;
+    if (N > kKsgMaxN || k < 1 || k > 8) return NDF_E_UNSUPPORTED;
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
-    char *w = (char *)ws;
-    double *H = (double *)w;
-    w += align_up((size_t)(N + 1) * sizeof(double), 256);
+    char *w = (char *)ws + align_up((size_t)(N + 1) * sizeof(double), 256);
     int64_t *refs = (int64_t *)w;
     w += align_up((size_t)n_ref * sizeof(int64_t), 256);
     int32_t *xs = (int32_t *)w;
@@ -1090,56 +1162,57 @@ int launch_ksg_field(const ndf_ensemble *e, int var_ref, int var_qry, const int6
     uint16_t *perm = (uint16_t *)w;
     w += align_up((size_t)n_ref * N * sizeof(uint16_t), 256);
     uint16_t *invp = (uint16_t *)w;
-    if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
-    const int P = p2(N);
     const int32_t *cr = e->code + (int64_t)var_ref * V * N;
     const int32_t *cq = e->code + (int64_t)var_qry * V * N;
+    const int32_t *fr = e->flags + (int64_t)var_ref * V, *fq = e->flags + (int64_t)var_qry * V;
     const uint16_t *ordr = e->order ? e->order + (int64_t)var_ref * V * N : nullptr;
     const uint16_t *ordq = e->order ? e->order + (int64_t)var_qry * V * N : nullptr;
-    hipLaunchKernelGGL(ksg_sort_ref_kernel, dim3(n_ref), dim3(kKsgThreads), (size_t)P * 8, st, cr,
-                       ordr, N, refs, xs, perm, invp, H);
-    const size_t lds = ksg_lds_bytes(N, P < kKsgThreads ? kKsgThreads : P);
-    const dim3 g((unsigned)ksg_grid(V, lds, kPairWaves));
-    const FieldArgs a{cq, e->flags + (int64_t)var_ref * V, e->flags + (int64_t)var_qry * V,
-                      N, V, refs, n_ref, xs, perm, H, out, counts, cr, ordq, invp};
-    switch (k) {
-#define NDF_KSG_CASE(KK) \
-    case KK: launch_field_k<KK>(g, lds, st, a); break;
-        NDF_KSG_CASE(1) NDF_KSG_CASE(2) NDF_KSG_CASE(3) NDF_KSG_CASE(4)
-        NDF_KSG_CASE(5) NDF_KSG_CASE(6) NDF_KSG_CASE(7) NDF_KSG_CASE(8)
-#undef NDF_KSG_CASE
-        default: return NDF_E_UNSUPPORTED;
+    for (int r0 = 0; r0 < n_ref; r0 += kSortRefs) {
+        const int n = n_ref - r0 < kSortRefs ? n_ref - r0 : kSortRefs;
+        SortRefs rs{};
+        for (int i = 0; i < n; ++i) rs.v[i] = ref_v[r0 + i];
+        const int64_t o = (int64_t)r0 * N;
+        hipLaunchKernelGGL(ksg_sort_ref_kernel, dim3(n), dim3(kKsgThreads),
+                           ordr ? 0 : (size_t)p2(N) * 8, st, cr, ordr, N, rs, refs + r0, xs + o,
+                           perm + o, invp + o);
     }
+    with_pair_waves(N, [&](auto wc) {
+        constexpr int W = decltype(wc)::value;
+        const size_t lds = pair_lds_bytes<W>(N, false);
+        const dim3 g((unsigned)ksg_grid(V, lds, W, kFieldRounds));
+        with_k(k, [&](auto kc) {
+            constexpr int K = decltype(kc)::value;
+            hipLaunchKernelGGL((ksg_field_kernel<K, W>), g, dim3(64 * W), lds, st, cq, fr, fq, N, V,
+                               refs, n_ref, xs, perm, out, counts, cr, ordq, invp);
+        });
+    });
     return status_of_launch();
 }
 
+// The pairs kernels keep nothing in a workspace; its size stays what callers have laid out.
 size_t ksg_pairs_ws_bytes(int N) { return align_up((size_t)(N + 1) * sizeof(double), 256); }
 
 int launch_ksg_pairs(const ndf_ensemble *e, int var_a, int var_b, const int64_t *pairs, int64_t B,
-                     int k, float *out, int32_t *counts, double *H, hipStream_t st) {
+                     int k, float *out, int32_t *counts, hipStream_t st) {
     const int N = e->n_members;
+    if (N > kKsgMaxN || k < 1 || k > 8) return NDF_E_UNSUPPORTED;
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
-    const int P = p2(N);
-    hipLaunchKernelGGL(harmonic_kernel, dim3(1), dim3(64), 0, st, N, H);
-    const size_t lds = ksg_lds_bytes(N, P < kKsgThreads ? kKsgThreads : P);
-    const dim3 g((unsigned)ksg_grid(B, lds, kPairWaves));
     const int32_t *ca = e->code + (int64_t)var_a * V * N;
     const int32_t *cb = e->code + (int64_t)var_b * V * N;
     const int32_t *fa = e->flags + (int64_t)var_a * V;
     const int32_t *fb = e->flags + (int64_t)var_b * V;
     const uint16_t *oa = e->order ? e->order + (int64_t)var_a * V * N : nullptr;
     const uint16_t *ob = e->order ? e->order + (int64_t)var_b * V * N : nullptr;
-    switch (k) {
-#define NDF_KSG_CASE(KK)                                                                       \
-    case KK:                                                                                   \
-        hipLaunchKernelGGL(ksg_pairs_kernel<KK>, g, dim3(kKsgThreads), lds, st, ca, cb, fa, fb, N, V, \
-                           pairs, B, H, out, counts, oa, ob);                                     \
-        break;
-        NDF_KSG_CASE(1) NDF_KSG_CASE(2) NDF_KSG_CASE(3) NDF_KSG_CASE(4)
-        NDF_KSG_CASE(5) NDF_KSG_CASE(6) NDF_KSG_CASE(7) NDF_KSG_CASE(8)
-#undef NDF_KSG_CASE
-        default: return NDF_E_UNSUPPORTED;
-    }
+    with_pair_waves(N, [&](auto wc) {
+        constexpr int W = decltype(wc)::value;
+        const size_t lds = pair_lds_bytes<W>(N, counts && !oa);
+        const dim3 g((unsigned)ksg_grid(B, lds, W, kPairRounds));
+        with_k(k, [&](auto kc) {
+            constexpr int K = decltype(kc)::value;
+            hipLaunchKernelGGL((ksg_pairs_kernel<K, W>), g, dim3(64 * W), lds, st, ca, cb, fa, fb, N,
+                               V, pairs, B, out, counts, oa, ob);
+        });
+    });
     return status_of_launch();
 }
 

@@ -19,7 +19,7 @@
 namespace ndf {
 
 int launch_ksg_pairs(const ndf_ensemble *e, int var_a, int var_b, const int64_t *pairs, int64_t B,
-                     int k, float *out, int32_t *counts, double *H, hipStream_t st);
+                     int k, float *out, int32_t *counts, hipStream_t st);
 int launch_ksg_orders(const ndf_ensemble *e, hipStream_t st);
 size_t ksg_pairs_ws_bytes(int N);
 
@@ -114,7 +114,6 @@ int launch_ksg_points(const ndf_ensemble *e, int var_a, int var_b, const float *
     if (N > 64 * kPtsPerLane) return NDF_E_UNSUPPORTED;
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
     char *w = (char *)ws;
-    double *H = (double *)w;
     w += ksg_pairs_ws_bytes(N);
     int64_t *pairs = (int64_t *)w;
     w += align_up((size_t)B * 2 * sizeof(int64_t), 256);
@@ -142,7 +141,7 @@ int launch_ksg_points(const ndf_ensemble *e, int var_a, int var_b, const float *
     cols.order = order;
     const int s = launch_ksg_orders(&cols, st);
     if (s != NDF_OK) return s;
-    return launch_ksg_pairs(&cols, 0, 0, pairs, B, k, out, counts, H, st);
+    return launch_ksg_pairs(&cols, 0, 0, pairs, B, k, out, counts, st);
 }
 
 }  // namespace ndf

@@ -71,3 +71,52 @@ def test_stored_orders_are_the_stable_sort_of_the_codes(n_members):
     code = e.code[0].cpu().numpy()
     order = e.order[0].cpu().numpy().astype(np.int64) & 0xffff
     assert np.array_equal(order, np.argsort(code, axis=1, kind="stable"))
+
+
+def _ksg_columns(n_members, n_vertices, rng):
+    """Columns from independent to equal, with ties, outliers and monotone pairs."""
+    x = rng.standard_normal((n_members, n_vertices)).astype(np.float32)
+    x[:, 1] = x[:, 0] + 0.3 * x[:, 1]
+    x[:, 2] = x[:, 0]                                     # every distance tied in x and y
+    x[:, 3] = -x[:, 0]
+    x[:, 4] = rng.integers(0, 3, n_members)               # k-th distances of 0
+    x[:, 5] = rng.integers(0, 1 + n_members // 3, n_members)
+    x[:, 6] = rng.standard_cauchy(n_members)
+    x[:, 7] = 1.0                                         # constant
+    return x
+
+
+# member counts on both sides of every workgroup size (256, 512, 1024, 2048 members), of a
+# chunk of 64 samples and of the smallest k, stored orders and columns sorted on the fly
+@pytest.mark.parametrize("n_members,k", [(3, 2), (5, 4), (9, 8), (64, 1), (65, 4), (200, 3),
+                                         (255, 4), (256, 8), (257, 4), (511, 4), (513, 6),
+                                         (1000, 4), (1024, 2), (1025, 4), (2048, 4)])
+@pytest.mark.parametrize("orders", [True, False])
+def test_ksg_counts_at_every_workgroup_size(n_members, k, orders):
+    rng = np.random.default_rng(7 * n_members + k)
+    x = _ksg_columns(n_members, 12, rng)
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), 3, 2, 2, orders=orders)
+    ndf.ndf_prepare(e)
+    code = e.code[0].cpu().numpy().astype(np.int64)
+    refs = [0, 4, 6]
+    pairs = np.array([[a, b] for a in refs for b in range(12)])
+    mi, cnt = ndf.ksg_field(e, refs, k=k, counts=True)
+    pmi, pcnt = ndf.ksg_pairs(e, pairs, k=k, counts=True)
+    assert torch.equal(mi.reshape(-1), pmi)
+    assert torch.equal(cnt.reshape(-1, 2, n_members), pcnt)
+    cnt = cnt.cpu().numpy()
+    for i, r in enumerate(refs):
+        for v in range(12):
+            if v == 7:
+                assert mi[i, v] == 0.0
+                continue
+            dx = np.abs(code[r][:, None] - code[r][None])
+            dy = np.abs(code[v][:, None] - code[v][None])
+            d = np.maximum(dx, dy)
+            np.fill_diagonal(d, 1 << 40)
+            eps = np.partition(d, k - 1, axis=1)[:, k - 1:k]
+            own = (eps[:, 0] > 0).astype(np.int64)
+            assert np.array_equal(cnt[i, v, 0], (dx < eps).sum(1) - own)
+            assert np.array_equal(cnt[i, v, 1], (dy < eps).sum(1) - own)
+    want = direct.ksg_field(np.ascontiguousarray(x[:, 0]), x, k)
+    assert np.max(np.abs(mi[0].cpu().numpy() - want)) <= 1e-4
