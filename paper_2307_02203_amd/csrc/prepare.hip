@@ -7,27 +7,192 @@
 // multiply, divide) and round-half-even, so they are the same integers on any
 // conforming implementation; all later KSG distances are exact int32.
 //
-// One workgroup owns 64 consecutive vertices of one variable and reads their
-// members twice (sum / min / max, then centred squares and codes).  The ensemble
-// is member-major, so each member row contributes a 256-byte coalesced segment.
-// Codes are written vertex-major through an LDS transpose (64 members x 64
-// vertices per tile).  Each thread keeps 8 (first pass) or 16 (second pass) of
-// its member loads in flight; one load at a time left the kernel latency-bound at
-// 3.3 TB/s.  (Two vertices per thread with 8-byte loads measured slower: the
-// larger tile cut the resident workgroups per CU.)
+// Up to 1024 members (prepare_kernel) a workgroup reads its 32 vertices' members once
+// and keeps them in registers for both passes (sum / min / max, then centred squares and
+// codes); more members are read twice (prepare_long_kernel).  The ensemble
+// is member-major, so each member row contributes a coalesced segment; codes, and the
+// vertex-major copy of x where the caller wants one, leave through an LDS transpose.
 #include "common.hpp"
 
 #pragma clang fp contract(off)
 
 namespace ndf {
 
+// ------------------------------------------------------- up to 1024 members ----
+// Thread (vertex vl, phase ph) of eight waves holds members ph, ph + 16, ... (up to E, and
+// one of the last partial row) of vertex vl in registers, every load in flight at once;
+// two workgroups of eight waves per CU cover each other's load and coding phases.
+// Whole rows are guarded by uniform tests, so no load needs a clamped 64-bit address
+// (with one per load and lane the kernel spilled: 4.7 ms).  Bound by HBM: x read once,
+// codes written once, past the caches (non-temporal stores: 0.5 ms less), 14.1 GB for
+// 1000 members x 1.76M vertices in 3.14 ms, 4.5 TB/s, a large copy's rate (reading x twice
+// with 16 loads in flight: 21.1 GB in 5.24 ms).  One workgroup of eight waves with 168
+// registers is as fast; eight phases of 128 members each take 5.4 ms.
+constexpr int kRegV = 32;        // vertices per workgroup: 128-byte row segments
+constexpr int kRegPh = 16;       // member phases
+constexpr int kRegThreads = kRegV * kRegPh;
+typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Rows of the transpose tile: 16 J members of a vertex, padded by four words (the 32
+// vertices of a half wave fall into banks 4 apart).
+template <int J>
+constexpr int prep_row() {
+    return kRegPh * J + 4;
+}
+
+// dst[v][m] = tile for the members 16 J k .. of the workgroup's vertices: 4 J lanes per
+// vertex row, 16 bytes each, at any alignment.
+template <int J>
+__device__ __forceinline__ void prep_store(const int32_t *tile, int32_t *__restrict__ dst, int N,
+                                           int64_t V, int64_t v0, int m0) {
+    for (int i = threadIdx.x; i < kRegV * 4 * J; i += kRegThreads) {
+        const int row = i / (4 * J), c4 = i % (4 * J);
+        const int64_t v = v0 + row;
+        const int m = m0 + 4 * c4;
+        const int32_t *src = tile + row * prep_row<J>() + 4 * c4;
+        if (v >= V || m >= N) continue;
+        int32_t *d = dst + v * N + m;
+        if (m + 3 < N) {
+            const i32x4 q = *reinterpret_cast<const i32x4 *>(src);
+            __builtin_nontemporal_store((i32x4u)q, reinterpret_cast<i32x4u *>(d));
+        } else {
+            for (int e = 0; m + e < N; ++e) d[e] = src[e];
+        }
+    }
+}
+
+template <int E>
+__global__ __launch_bounds__(kRegThreads) __attribute__((amdgpu_waves_per_eu(4))) void
+prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict__ mean,
+               double *__restrict__ inv_std, int32_t *__restrict__ code,
+               int32_t *__restrict__ flags, int32_t *__restrict__ status,
+               float *__restrict__ xt) {
+    constexpr int J = E < 16 ? E : 16;  // rows of 16 members per transpose tile
+    constexpr int K = E / J + 1;        // tiles: E whole rows and a partial one
+    __shared__ __attribute__((aligned(16))) int32_t s_tile[kRegV * prep_row<J>()];
+    __shared__ double s_sum[kRegPh / 2][kRegV];
+    __shared__ float s_lo[kRegPh / 2][kRegV], s_hi[kRegPh / 2][kRegV];
+    __shared__ int s_bad[kRegPh / 2][kRegV];
+    const int var = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int vl = lane & 31, ph = 2 * wave + (lane >> 5);
+    const int64_t v0 = (int64_t)blockIdx.x * kRegV, v = v0 + vl;
+    const float *col = x + (int64_t)var * N * V + (v < V ? v : V - 1);
+
+    // every member once: NF whole rows of 16 members, and a row of the remaining ones
+    const int NF = N / kRegPh, rem = N % kRegPh;
+    const bool has = ph < rem;
+    const int64_t step = (int64_t)kRegPh * V;
+    col += (int64_t)(has || NF ? ph : 0) * V;
+    float a[E], al = 0.f;
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+        if (j < NF) a[j] = __builtin_nontemporal_load(col + j * step);
+    if (has) al = __builtin_nontemporal_load(col + NF * step);
+
+    // pass 1: sum, min, max, finiteness
+    double sum = 0.0;
+    float lo = INFINITY, hi = -INFINITY;
+    int bad = 0;
+    auto accumulate = [&](float q) {
+        sum += (double)q;
+        lo = fminf(lo, q);
+        hi = fmaxf(hi, q);
+        bad |= !isfinite(q);
+    };
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+        if (j < NF) accumulate(a[j]);
+    if (has) accumulate(al);
+    // the two phases of a wave, then the eight waves
+    sum += __shfl_xor(sum, 32);
+    lo = fminf(lo, __shfl_xor(lo, 32));
+    hi = fmaxf(hi, __shfl_xor(hi, 32));
+    bad |= __shfl_xor(bad, 32);
+    if (lane < 32) {
+        s_sum[wave][vl] = sum;
+        s_lo[wave][vl] = lo;
+        s_hi[wave][vl] = hi;
+        s_bad[wave][vl] = bad;
+    }
+    __syncthreads();
+    sum = 0.0;
+#pragma unroll
+    for (int p = 0; p < kRegPh / 2; ++p) {
+        sum += s_sum[p][vl];
+        lo = fminf(lo, s_lo[p][vl]);
+        hi = fmaxf(hi, s_hi[p][vl]);
+        bad |= s_bad[p][vl];
+    }
+    const double mu = sum / (double)N;
+    const bool flat = !(hi > lo);
+    const double dlo = (double)lo;
+    const double scale = flat ? 0.0 : 8388608.0 / ((double)hi - dlo);
+    __syncthreads();  // s_sum is reused
+
+    // pass 2: centred sum of squares; codes (and x) transposed through LDS into
+    // vertex-major rows, 16 J members at a time
+    double ss = 0.0;
+    int32_t *cv = code + (int64_t)var * V * N;
+    int32_t *tv = reinterpret_cast<int32_t *>(xt ? xt + (int64_t)var * V * N : nullptr);
+    int32_t *row = s_tile + vl * prep_row<J>() + ph;
+    auto encode = [&](float q) {
+        const double d = (double)q - mu;
+        ss += d * d;
+        return flat ? 0 : (int32_t)__builtin_rint(((double)q - dlo) * scale);
+    };
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int m0 = kRegPh * J * k;
+        if (m0 >= N) break;  // uniform
+        if (k) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < J; ++i)
+            if (J * k + i < E && J * k + i < NF) row[kRegPh * i] = encode(a[J * k + i]);
+        const bool tail = has && NF / J == k;
+        if (tail) row[kRegPh * (NF - J * k)] = encode(al);
+        __syncthreads();
+        prep_store<J>(s_tile, cv, N, V, v0, m0);
+        if (tv) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < J; ++i)
+                if (J * k + i < E && J * k + i < NF) row[kRegPh * i] = __float_as_int(a[J * k + i]);
+            if (tail) row[kRegPh * (NF - J * k)] = __float_as_int(al);
+            __syncthreads();
+            prep_store<J>(s_tile, tv, N, V, v0, m0);
+        }
+    }
+    ss += __shfl_xor(ss, 32);
+    if (lane < 32) s_sum[wave][vl] = ss;
+    __syncthreads();
+    if (tid < kRegV && v < V) {
+        double s2 = 0.0;
+#pragma unroll
+        for (int p = 0; p < kRegPh / 2; ++p) s2 += s_sum[p][vl];
+        const double var_pop = s2 / (double)N;
+        mean[(int64_t)var * V + v] = mu;
+        inv_std[(int64_t)var * V + v] = (var_pop > 0.0 && !flat) ? 1.0 / sqrt(var_pop) : 0.0;
+        flags[(int64_t)var * V + v] =
+            (bad ? NDF_FLAG_NONFINITE : 0) | (flat ? NDF_FLAG_CONSTANT : 0);
+        // every writer stores the same value, so the unordered stores agree
+        if (bad && status) *status = NDF_E_NONFINITE;
+    }
+}
+
+// --------------------------------------------------- more than 1024 members ----
+// One workgroup owns 64 consecutive vertices of one variable and reads their
+// members twice (sum / min / max, then centred squares and codes).  Each thread keeps 8
+// (first pass) or 16 (second pass) of its member loads in flight; one load at a time
+// left the kernel latency-bound at 3.3 TB/s.  (Two vertices per thread with 8-byte loads
+// measured slower: the larger tile cut the resident workgroups per CU.)
 constexpr int kPrepVW = 1;                    // consecutive vertices per thread (1 or 2)
 constexpr int kPrepG = 64;                    // vertex groups per workgroup
 constexpr int kPrepV = kPrepG * kPrepVW;      // vertices per workgroup
 constexpr int kPrepPh = 4;                    // member phases per vertex group
 constexpr int kPrepThreads = kPrepG * kPrepPh;
 
-__global__ __launch_bounds__(kPrepThreads) void prepare_kernel(
+__global__ __launch_bounds__(kPrepThreads) void prepare_long_kernel(
     const float *__restrict__ x, int N, int64_t V, double *__restrict__ mean,
     double *__restrict__ inv_std, int32_t *__restrict__ code, int32_t *__restrict__ flags,
     int32_t *__restrict__ status) {
@@ -268,18 +433,28 @@ int launch_status_clear(int32_t *status, hipStream_t st) {
 int launch_prepare(const ndf_ensemble *e, int32_t *status, hipStream_t st) {
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
     if (status) launch_status_clear(status, st);
+    const int N = e->n_members;
+    const dim3 rg((unsigned)ceil_div(V, kRegV), (unsigned)e->n_vars);
+    // the fewest registers that hold a thread's members: waves in flight against loads
+    // past the last member
+#define NDF_PREP_CASE(E)                                                                        \
+    if (N < kRegPh * (E + 1)) {                                                                 \
+        hipLaunchKernelGGL(prepare_kernel<E>, rg, dim3(kRegThreads), 0, st, e->x, N, V, e->mean, \
+                           e->inv_std, e->code, e->flags, status, e->xt);                       \
+        return status_of_launch();                                                              \
+    }
+    NDF_PREP_CASE(4) NDF_PREP_CASE(8) NDF_PREP_CASE(16)
+    NDF_PREP_CASE(32) NDF_PREP_CASE(48) NDF_PREP_CASE(64)
+#undef NDF_PREP_CASE
     dim3 grid((unsigned)ceil_div(V, kPrepV), (unsigned)e->n_vars);
-    hipLaunchKernelGGL(prepare_kernel, grid, dim3(kPrepThreads), 0, st, e->x, e->n_members, V,
-                       e->mean, e->inv_std, e->code, e->flags, status);
+    hipLaunchKernelGGL(prepare_long_kernel, grid, dim3(kPrepThreads), 0, st, e->x, N, V, e->mean,
+                       e->inv_std, e->code, e->flags, status);
     if (e->xt) {
-        dim3 tg((unsigned)ceil_div(V, 64), (unsigned)ceil_div(e->n_members, 64),
-                (unsigned)e->n_vars);
-        if (V % 4 == 0 && e->n_members % 4 == 0)
-            hipLaunchKernelGGL(transpose_kernel<true>, tg, dim3(256), 0, st, e->x, e->n_members, V,
-                               e->xt);
+        dim3 tg((unsigned)ceil_div(V, 64), (unsigned)ceil_div(N, 64), (unsigned)e->n_vars);
+        if (V % 4 == 0 && N % 4 == 0)
+            hipLaunchKernelGGL(transpose_kernel<true>, tg, dim3(256), 0, st, e->x, N, V, e->xt);
         else
-            hipLaunchKernelGGL(transpose_kernel<false>, tg, dim3(256), 0, st, e->x, e->n_members,
-                               V, e->xt);
+            hipLaunchKernelGGL(transpose_kernel<false>, tg, dim3(256), 0, st, e->x, N, V, e->xt);
     }
     return status_of_launch();
 }

@@ -120,3 +120,43 @@ def test_ksg_counts_at_every_workgroup_size(n_members, k, orders):
             assert np.array_equal(cnt[i, v, 1], (dy < eps).sum(1) - own)
     want = direct.ksg_field(np.ascontiguousarray(x[:, 0]), x, k)
     assert np.max(np.abs(mi[0].cpu().numpy() - want)) <= 1e-4
+
+
+# member counts on both sides of every register count of the one-read kernel (16 E members
+# for E = 4 .. 64) and of the two-read path, vertex counts around its 32-vertex tiles
+@pytest.mark.parametrize("n_members,dims", [(2, (2, 2, 2)), (5, (3, 11, 1 + 1)), (63, (4, 4, 2)),
+                                            (64, (5, 13, 3)), (65, (31, 2, 3)), (128, (8, 8, 5)),
+                                            (129, (7, 3, 2)), (255, (9, 7, 2)), (257, (3, 3, 7)),
+                                            (512, (5, 5, 5)), (513, (2, 33, 2)), (768, (4, 9, 2)),
+                                            (769, (3, 5, 3)), (1000, (7, 9, 3)), (1023, (3, 3, 3)),
+                                            (1024, (6, 6, 2)), (1025, (5, 7, 2)), (2050, (3, 4, 3))])
+def test_prepare_at_every_register_count(n_members, dims):
+    V = dims[0] * dims[1] * dims[2]
+    rng = np.random.default_rng(n_members)
+    x = (rng.standard_normal((n_members, V)) * 3.0 + 40.0).astype(np.float32)
+    x[:, 1] = -7.25
+    x[n_members // 2, 2] = np.nan
+    x[0, 3] = np.inf
+    x[-1, 4] = 1e6
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=False, transposed=True)
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    ndf.ndf_prepare(e, ws)
+    assert ndf.status_word(ws) == ndf.NDF_E_NONFINITE
+    flags = np.zeros(V, dtype=np.int32)
+    flags[1] = ndf.NDF_FLAG_CONSTANT
+    flags[2:4] = ndf.NDF_FLAG_NONFINITE
+    if n_members == 2:  # one finite value left: its range is zero
+        flags[2] |= ndf.NDF_FLAG_CONSTANT
+    assert np.array_equal(e.flags[0].cpu().numpy(), flags)
+    assert np.array_equal(e.xt[0].cpu().numpy(), x.T, equal_nan=True)
+    ok = flags == 0
+    d = x.T[ok].astype(np.float64)
+    lo, hi = d.min(1, keepdims=True), d.max(1, keepdims=True)
+    assert np.array_equal(e.code[0].cpu().numpy()[ok], np.rint((d - lo) * (8388608.0 / (hi - lo))))
+    assert np.all(e.code[0].cpu().numpy()[1] == 0) and e.inv_std[0, 1].item() == 0.0
+    # FP64 sums of at most 2050 terms: (N + 2) 2^-53 of sum |x| on either side
+    tol = 2 * (n_members + 2) * 2.0 ** -53
+    mean = e.mean[0].cpu().numpy()[ok]
+    assert np.max(np.abs(mean - d.mean(1)) / np.abs(d).mean(1)) <= tol
+    var = ((d - d.mean(1, keepdims=True)) ** 2).mean(1)
+    assert np.max(np.abs(e.inv_std[0].cpu().numpy()[ok] * np.sqrt(var) - 1.0)) <= 4 * tol
