@@ -303,6 +303,23 @@ __device__ __forceinline__ bf16x8 ff_chunk(int kb, int h, const float (&p)[3]) {
     return r;
 }
 
+// Copy COUNT elements into LDS with every load of a thread issued before its
+// first store (a loop over i = tid, tid + THREADS, ... waits for each load in turn:
+// some twenty L2 round trips per workgroup before its first tile).  Loads past
+// COUNT read element COUNT - 1 and are not stored, so no load sits behind a branch.
+template <int COUNT, int THREADS, typename T>
+__device__ __forceinline__ void stage_lds(T *__restrict__ dst, const T *__restrict__ src,
+                                          int tid) {
+    constexpr int kIt = (COUNT + THREADS - 1) / THREADS;
+    T v[kIt];
+#pragma unroll
+    for (int j = 0; j < kIt; ++j) v[j] = src[min(tid + j * THREADS, COUNT - 1)];
+#pragma unroll
+    for (int j = 0; j < kIt; ++j)
+        if (COUNT % THREADS == 0 || tid + j * THREADS < COUNT)
+            dst[tid + j * THREADS] = v[j];
+}
+
 size_t net_train_ws_bytes(const ndf_net_config *c, int64_t B);
 size_t net_infer_ws_bytes(const ndf_net_config *c, int64_t n_ref, int prec);
 size_t net_infer_lat_ws_bytes(int64_t n_ref);

@@ -425,20 +425,23 @@ __global__ __launch_bounds__(kThreads) void head_fwd_kernel(
 
 // Mean of the per-block sums; a non-finite loss (a NaN or infinite target or
 // output) sets the call's status word, which stops the optimiser step.
-__global__ void loss_reduce_kernel(const double *__restrict__ partial, int n, int64_t B,
-                                   float *__restrict__ loss, int32_t *__restrict__ status) {
-    __shared__ double s[64];
+// One wave.
+__device__ __forceinline__ void loss_reduce(const double *__restrict__ partial, int n, int64_t B,
+                                            float *__restrict__ loss,
+                                            int32_t *__restrict__ status) {
     double t = 0.0;
-    for (int i = threadIdx.x; i < n; i += 64) t += partial[i];
-    s[threadIdx.x] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double a = 0.0;
-        for (int i = 0; i < 64; ++i) a += s[i];
-        const float l = (float)(a / (double)B);
+    for (int i = threadIdx.x & 63; i < n; i += 64) t += partial[i];
+    t = wave_sum_f64(t);
+    if ((threadIdx.x & 63) == 0) {
+        const float l = (float)(t / (double)B);
         loss[0] = l;
         if (!isfinite(l)) status[0] = NDF_E_NONFINITE;
     }
+}
+
+__global__ void loss_reduce_kernel(const double *__restrict__ partial, int n, int64_t B,
+                                   float *__restrict__ loss, int32_t *__restrict__ status) {
+    loss_reduce(partial, n, B, loss, status);
 }
 
 // dPre5 = gy w6 (masked by d2 > 0);  gw6 += sum_b gy d2;  gb6 += sum_b gy
@@ -633,13 +636,28 @@ struct TrainFrags {
     bf16x8 *t[5];
 };
 
+// With G the gradient (n floats, 256-byte aligned) and the status word are cleared too:
+// one launch in front of the forward kernel instead of three.
+constexpr int kPackBlocks = 64;
+
 __global__ void pack_train_kernel(const float *__restrict__ P, int64_t w1, int64_t w2,
-                                  int64_t w3, int64_t w4, int64_t w5, int kin1, TrainFrags F) {
+                                  int64_t w3, int64_t w4, int64_t w5, int kin1, TrainFrags F,
+                                  float *__restrict__ G, int64_t n, int32_t *__restrict__ status) {
+    if (blockIdx.x >= kPackBlocks) {
+        const int64_t n4 = n / 4, step = (int64_t)(gridDim.x - kPackBlocks) * blockDim.x;
+        const int64_t t0 = (int64_t)(blockIdx.x - kPackBlocks) * blockDim.x + threadIdx.x;
+        for (int64_t i = t0; i < n4; i += step)
+            reinterpret_cast<f32x4 *>(G)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int64_t i = 4 * n4 + t0; i < n; i += step) G[i] = 0.f;
+        return;
+    }
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = NDF_OK;
     const int64_t wo[5] = {w1, w2, w3, w4, w5};
     // forward: W1 (128 x kin1) and W2..W5; adjoint: W1^T (the 32 grid inputs only:
     // no gradient flows into the Fourier features) and W2^T..W5^T
     const int n1 = kH * kin1, nf = n1 + 4 * kH * kH, na = kH * kK0 + 4 * kH * kH;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nf + na; t += gridDim.x * blockDim.x) {
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nf + na;
+         t += kPackBlocks * blockDim.x) {
         const bool adj = t >= nf;
         int u = adj ? t - nf : t;
         const int m1 = adj ? kH * kK0 : n1;
@@ -680,6 +698,9 @@ struct FusedArgs {
     float *y;       // [B] or null
     float *dh0;     // [2 B][32] FP32, rows q B + pair
     double *partial;
+    int n_partial;  // workgroups of the forward kernel
+    float *loss;
+    int32_t *status;
 };
 
 __device__ __forceinline__ int64_t slab_chunk(int64_t blk, int nkb, int kb, int lane) {
@@ -730,7 +751,7 @@ __device__ __forceinline__ void mma_block(const bf16x8 *__restrict__ wf, int ob,
 // 2 kb + h (8 FP32 features per cell, trilinear over 8 corners).
 template <bool POS>
 __device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, int kb, int h, int64_t v,
-                                            const float (&p)[3]) {
+                                            const float (&p)[3], bool few) {
     const int l = 2 * kb + h;
     int R[3];
     level_dims(A.g, l, R);
@@ -742,18 +763,35 @@ __device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, int kb, int h, i
     else
         corners_R32<true>(A.g, R, v, idx, w, hm);
     const f32x4 *grid = reinterpret_cast<const f32x4 *>(A.P + (h ? A.grid[2 * kb + 1] : A.grid[2 * kb]));
+    // A corner of weight 0 adds nothing, and on a level of the vertex grid's size only one
+    // corner of eight has weight.  With many waves in flight the others are skipped; a
+    // branch around each read waits for it before the next is issued, so with few waves
+    // (`few`, uniform) they read the last weighted corner's cell instead.
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        // a corner of weight 0 adds nothing: on a level of the vertex grid's size
-        // only one corner of eight has weight, so most lanes skip the other reads
-        if (w[c] == 0.f) continue;
-        const f32x4 c0 = grid[(int64_t)idx[c] * 2], c1 = grid[(int64_t)idx[c] * 2 + 1];
+    auto add = [&](float wc, const f32x4 &c0, const f32x4 &c1) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            s0[i] = fmaf(w[c], c0[i], s0[i]);
-            s1[i] = fmaf(w[c], c1[i], s1[i]);
+            s0[i] = fmaf(wc, c0[i], s0[i]);
+            s1[i] = fmaf(wc, c1[i], s1[i]);
         }
+    };
+    if (few) {
+        int some = idx[0];
+#pragma unroll
+        for (int c = 1; c < 8; ++c) some = w[c] != 0.f ? idx[c] : some;
+        f32x4 c0[8], c1[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int64_t at = 2 * (int64_t)(w[c] != 0.f ? idx[c] : some);
+            c0[c] = grid[at];
+            c1[c] = grid[at + 1];
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) add(w[c], c0[c], c1[c]);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+            if (w[c] != 0.f) add(w[c], grid[2 * (int64_t)idx[c]], grid[2 * (int64_t)idx[c] + 1]);
     }
     bf16x8 t;
 #pragma unroll
@@ -767,6 +805,14 @@ __device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, int kb, int h, i
 __device__ __forceinline__ u32x4 as_u(const bf16x8 &v) { return __builtin_bit_cast(u32x4, v); }
 __device__ __forceinline__ bf16x8 as_b(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
 
+// First tile of a wave; the next ones follow at gridDim.x kTW.  Up to one tile per wave
+// the tiles are dealt to the workgroups first (few tiles then run on many CUs), else a
+// workgroup's waves take neighbouring tiles (their slabs are neighbours in memory).
+__device__ __forceinline__ int64_t first_tile(int64_t T, int wave) {
+    return T <= (int64_t)gridDim.x * kTW ? blockIdx.x + (int64_t)gridDim.x * wave
+                                         : (int64_t)blockIdx.x * kTW + wave;
+}
+
 // Forward of 32 pairs per wave; with targets also the loss partial sums, gy and
 // the first gradient da5 = gy w6 (masked by d2 > 0).
 template <bool POS, bool FF>
@@ -778,9 +824,9 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
     __shared__ __attribute__((aligned(16))) float s_w6[kH];
     __shared__ double s_part[kTW];
     const int tid = threadIdx.x;
-    for (int i = tid; i < 4 * KB1 * 64; i += kTThreads) s_w1[i] = A.wf[0][i];
-    for (int L = 0; L < 4; ++L)
-        for (int i = tid; i < kFragH; i += kTThreads) s_w[L][i] = A.wf[L + 1][i];
+    stage_lds<4 * KB1 * 64, kTThreads>(s_w1, A.wf[0], tid);
+#pragma unroll
+    for (int L = 0; L < 4; ++L) stage_lds<kFragH, kTThreads>(s_w[L], A.wf[L + 1], tid);
     for (int i = tid; i < 5 * kH; i += kTThreads) s_b[i / kH][i % kH] = A.b[i / kH][i % kH];
     for (int i = tid; i < kH; i += kTThreads) s_w6[i] = A.w6[i];
     __syncthreads();
@@ -790,9 +836,9 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
     const int64_t V = (int64_t)A.g.nx * A.g.ny * A.g.nz;
     const float b6 = A.b6[0];
     const float inv_b = 1.f / (float)A.B;
+    const bool few = T <= 2 * (int64_t)gridDim.x;  // at most two waves of a CU gather
     double loss_part = 0.0;
-    for (int64_t tile = (int64_t)blockIdx.x * kTW + wave; tile < T;
-         tile += (int64_t)gridDim.x * kTW) {
+    for (int64_t tile = first_tile(T, wave); tile < T; tile += (int64_t)gridDim.x * kTW) {
         int h4 = 4 * h;
         asm volatile("" : "+v"(h4));
         const int64_t pair = tile * 32 + jl;
@@ -813,7 +859,7 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
             }
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                a[kb][q] = gather_h0<POS>(A, kb, h, v, p);
+                a[kb][q] = gather_h0<POS>(A, kb, h, v, p, few);
                 A.h0[slab_chunk(2 * tile + q, KB1, kb, lane)] = as_u(a[kb][q]);
             }
             if (FF) {  // the raw position and its Fourier features
@@ -1006,15 +1052,15 @@ __global__ __launch_bounds__(kTThreads) void train_bwd_kernel(FusedArgs A) {
     __shared__ bf16x8 s_t1[kFrag1];
     __shared__ bf16x8 s_t[4][kFragH];  // W2^T .. W5^T
     const int tid = threadIdx.x;
-    for (int i = tid; i < kFrag1; i += kTThreads) s_t1[i] = A.wt[0][i];
-    for (int L = 0; L < 4; ++L)
-        for (int i = tid; i < kFragH; i += kTThreads) s_t[L][i] = A.wt[L + 1][i];
+    stage_lds<kFrag1, kTThreads>(s_t1, A.wt[0], tid);
+#pragma unroll
+    for (int L = 0; L < 4; ++L) stage_lds<kFragH, kTThreads>(s_t[L], A.wt[L + 1], tid);
+    if (blockIdx.x == 0 && tid < 64) loss_reduce(A.partial, A.n_partial, A.B, A.loss, A.status);
     __syncthreads();
 
     const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, jl = lane & 31;
     const int64_t T = ceil_div(A.B, 32);
-    for (int64_t tile = (int64_t)blockIdx.x * kTW + wave; tile < T;
-         tile += (int64_t)gridDim.x * kTW) {
+    for (int64_t tile = first_tile(T, wave); tile < T; tile += (int64_t)gridDim.x * kTW) {
         const int64_t pair = tile * 32 + jl;
         const bool ok = pair < A.B;
         bf16x8 x[8][2], y[8][2];
@@ -1305,9 +1351,12 @@ static FusedWS carve_fused(const ndf_net_config *c, void *ws, int64_t B) {
     return t;
 }
 
+// One workgroup per 32-pair tile up to one per CU (a workgroup's 140 KB of weights fill a
+// CU's LDS), then more tiles per workgroup, and two rounds of workgroups once every wave
+// of one round has two tiles.
 static unsigned fused_blocks(int64_t B) {
-    const int64_t b = ceil_div(ceil_div(B, 32), kTW);
-    return (unsigned)(b < kFusedBlocksMax ? (b > 0 ? b : 1) : kFusedBlocksMax);
+    const int64_t T = ceil_div(B, 32);
+    return (unsigned)(T < 256 ? T : T <= 256 * kTW ? 256 : kFusedBlocksMax);
 }
 
 static FusedArgs fused_args(const ndf_net_config *c, const NetOffsets &o, const float *P,
@@ -1343,12 +1392,14 @@ static FusedArgs fused_args(const ndf_net_config *c, const NetOffsets &o, const 
     return a;
 }
 
-static void fused_forward(const ndf_net_config *c, const NetOffsets &o, const float *P,
-                          const int64_t *pairs, const float *pos, const float *targets, int64_t B,
-                          const FusedWS &t, float *y, hipStream_t st) {
-    hipLaunchKernelGGL(pack_train_kernel, dim3(64), dim3(256), 0, st, P, o.W1[0], o.W2[0],
-                       o.W3[0], o.W4, o.W5, enc_in(c), t.fr);
-    const FusedArgs a = fused_args(c, o, P, pairs, pos, targets, B, t, y);
+// G, status: the gradient and the status word to clear first (null: neither).
+static void fused_forward(const ndf_net_config *c, const NetOffsets &o, const FusedArgs &a,
+                          const FusedWS &t, float *G, int32_t *status, hipStream_t st) {
+    const float *P = a.P, *pos = a.pos;
+    const int64_t B = a.B;
+    const unsigned zero = G ? gs_blocks(o.total / 4) : 0;
+    hipLaunchKernelGGL(pack_train_kernel, dim3(kPackBlocks + zero), dim3(256), 0, st, P, o.W1[0],
+                       o.W2[0], o.W3[0], o.W4, o.W5, enc_in(c), t.fr, G, o.total, status);
     const dim3 g(fused_blocks(B)), b(kTThreads);
     if (c->fourier) {
         if (pos)
@@ -1368,13 +1419,11 @@ static int fused_grad(const ndf_net_config *c, const float *P, const int64_t *pa
                       void *ws, hipStream_t st) {
     const NetOffsets o = net_offsets(c);
     const FusedWS t = carve_fused(c, ws, B);
-    launch_status_clear(t.status, st);
-    hipLaunchKernelGGL(fill_kernel, dim3(gs_blocks(o.total)), dim3(kThreads), 0, st, G, o.total,
-                       0.f);
-    fused_forward(c, o, P, pairs, pos, targets, B, t, nullptr, st);
-    hipLaunchKernelGGL(loss_reduce_kernel, dim3(1), dim3(64), 0, st, t.partial,
-                       (int)fused_blocks(B), B, loss, t.status);
-    const FusedArgs a = fused_args(c, o, P, pairs, pos, targets, B, t, nullptr);
+    FusedArgs a = fused_args(c, o, P, pairs, pos, targets, B, t, nullptr);
+    a.n_partial = (int)fused_blocks(B);
+    a.loss = loss;
+    a.status = t.status;
+    fused_forward(c, o, a, t, G, t.status, st);
     hipLaunchKernelGGL(train_bwd_kernel, dim3(fused_blocks(B)), dim3(kTThreads), 0, st, a);
     const int64_t rows = 2 * B;
     hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)grid_bwd_blocks(rows)), dim3(kThreads), 0,
@@ -1448,7 +1497,9 @@ int launch_net_forward(const ndf_net_config *c, const float *params, const int64
                        const float *pos, int64_t B, float *y, void *ws, hipStream_t st) {
     const NetOffsets o = net_offsets(c);
     if (fused_path(c)) {
-        fused_forward(c, o, params, pairs, pos, nullptr, B, carve_fused(c, ws, B), y, st);
+        const FusedWS t = carve_fused(c, ws, B);
+        fused_forward(c, o, fused_args(c, o, params, pairs, pos, nullptr, B, t, y), t, nullptr,
+                      nullptr, st);
         return status_of_launch();
     }
     TrainWS t = carve(ws, B);
