@@ -1,18 +1,19 @@
 // Training kernels of the learned dependence field (Sec. 4, Eq. 3; Sec. 4.3).
 //
-// One step over B vertex pairs runs the network row-wise: the R = 2B positions
-// (all first endpoints, then all second endpoints) go through the grid lookup
-// and the encoder, the two latents of a pair are multiplied, and the decoder
-// gives Phi.  The mean L1 loss is differentiated by hand:
+// The mean L1 loss is differentiated by hand:
 //   forward   grid gather -> [X W^T + b, ReLU] x2 -> X W3^T + b3 -> product
 //             -> [X W^T + b, ReLU] x2 -> w6 . d2 + b6
 //   adjoint   dY W (masked by the forward ReLU), dW += dY^T X, db += sum dY,
 //             the product rule across the merge, FP32 atomic scatter into the
 //             grid levels with the trilinear weights.
 // Layer products run on MFMA 32x32x16 bf16 with FP32 accumulate: activations
-// and weights are rounded to bf16 as they enter the MFMA; everything stored
-// (activations, gradients, parameters, Adam moments) is FP32.
+// and weights are rounded to bf16 as they enter the MFMA; latents, parameters, parameter
+// gradients and Adam moments are FP32.
 //
+// Networks with an encoder MLP run in the fused kernels below ("fused step").  A
+// grid-only network (no encoder MLP) runs row-wise, layer by layer: the R = 2B positions
+// (all first endpoints, then all second endpoints) go through the grid lookup, the two
+// feature rows of a pair are multiplied, and the decoder gives Phi:
 //  rows_mma_kernel  Y[rows][NOUT] = epilogue(X[rows][KIN] A^T), A staged once per
 //                   workgroup in LDS in MFMA operand order (A = W forward,
 //                   A = W^T for the data adjoint); 64 rows per wave and tile.
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void grid_bwd_kernel(float *__restrict__ 
 }
 
 // ----------------------------------------------------- row-wise MFMA ----
-enum { EPI_BIAS = 0, EPI_BIAS_RELU = 1, EPI_MASK = 2, EPI_PLAIN = 3 };
+enum { EPI_BIAS_RELU = 0, EPI_MASK = 1, EPI_PLAIN = 2 };
 
 __device__ __forceinline__ bf16x8 load_row8(const float *__restrict__ X, int64_t rows, int64_t r,
                                             int ld, int k0) {
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(kThreads) void rows_mma_kernel(
         const int ob = i >> 5, il = i & 31, kb = k >> 4, hh = (k >> 3) & 1, e = k & 7;
         sa[((ob * KB + kb) * 64 + hh * 32 + il) * 8 + e] = f2bf(wv);
     }
-    if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU)
+    if (EPI == EPI_BIAS_RELU)
         for (int i = threadIdx.x; i < NOUT; i += kThreads) s_bias[i] = bias[i];
     __syncthreads();
 
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void rows_mma_kernel(
                     f32x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = acc[ob][jb][4 * gq + e];
-                    if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) {
+                    if (EPI == EPI_BIAS_RELU) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] += s_bias[i0 + e];
                     }
@@ -545,10 +546,7 @@ GridOffs grid_offs(const NetOffsets &o) {
     return g;
 }
 
-void encode_merge_layer4(const ndf_net_config *c, const NetOffsets &o, const float *P, int64_t B,
-                         const TrainWS &t, hipStream_t st);
-
-// Forward pass into the workspace; with targets also the loss and gy.
+// Forward pass of a grid-only network into the workspace; with targets also the loss and gy.
 void forward(const ndf_net_config *c, const NetOffsets &o, const float *P, const int64_t *pairs,
              const float *pos, const float *targets, int64_t B, const TrainWS &t,
              hipStream_t st) {
@@ -557,48 +555,20 @@ void forward(const ndf_net_config *c, const NetOffsets &o, const float *P, const
     const GridOffs go = grid_offs(o);
     hipLaunchKernelGGL(grid_fwd_kernel, dim3((unsigned)ceil_div(R * kL, kThreads)), dim3(kThreads),
                        0, st, P, go, g, c->n_enc, pairs, pos, B, t.H0);
-    if (c->grid_only) {
-        // the grid features are the latents: merge them and decode (W4 is [128][32])
-        hipLaunchKernelGGL(merge_fwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st,
-                           t.H0, B, t.M, kK0);
-        hipLaunchKernelGGL((rows_mma_kernel<kK0, kH, EPI_BIAS_RELU>), dim3(mma_blocks(B)),
-                           dim3(kThreads), 0, st, t.M, B, P + o.W4, kK0, 1, P + o.b4, nullptr,
-                           t.D1);
-    } else {
-        encode_merge_layer4(c, o, P, B, t, st);
-    }
+    // the grid features are the latents: merge them and decode (W4 is [128][32])
+    hipLaunchKernelGGL(merge_fwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st, t.H0,
+                       B, t.M, kK0);
+    hipLaunchKernelGGL((rows_mma_kernel<kK0, kH, EPI_BIAS_RELU>), dim3(mma_blocks(B)),
+                       dim3(kThreads), 0, st, t.M, B, P + o.W4, kK0, 1, P + o.b4, nullptr, t.D1);
     hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_BIAS_RELU>), dim3(mma_blocks(B)),
                        dim3(kThreads), 0, st, t.D1, B, P + o.W5, kH, 1, P + o.b5, nullptr, t.D2);
     hipLaunchKernelGGL(head_fwd_kernel, dim3((unsigned)ceil_div(B, kThreads)), dim3(kThreads), 0,
                        st, t.D2, P + o.w6, P + o.b6, targets, B, t.y, t.gy, t.partial);
 }
 
-// Encoder layers of both endpoints, the latent product and decoder layer 4.
-void encode_merge_layer4(const ndf_net_config *c, const NetOffsets &o, const float *P, int64_t B,
-                         const TrainWS &t, hipStream_t st) {
-    const int64_t R = 2 * B;
-    const int n_enc = c->n_enc;
-    for (int e = 0; e < n_enc; ++e) {
-        const int64_t r0 = n_enc == 1 ? 0 : e * B, rows = n_enc == 1 ? R : B;
-        hipLaunchKernelGGL((rows_mma_kernel<kK0, kH, EPI_BIAS_RELU>), dim3(mma_blocks(rows)),
-                           dim3(kThreads), 0, st, t.H0 + r0 * kK0, rows, P + o.W1[e], kK0, 1,
-                           P + o.b1[e], nullptr, t.H1 + r0 * kH);
-        hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_BIAS_RELU>), dim3(mma_blocks(rows)),
-                           dim3(kThreads), 0, st, t.H1 + r0 * kH, rows, P + o.W2[e], kH, 1,
-                           P + o.b2[e], nullptr, t.H2 + r0 * kH);
-        hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_BIAS>), dim3(mma_blocks(rows)),
-                           dim3(kThreads), 0, st, t.H2 + r0 * kH, rows, P + o.W3[e], kH, 1,
-                           P + o.b3[e], nullptr, t.E + r0 * kH);
-    }
-    hipLaunchKernelGGL(merge_fwd_kernel, dim3(gs_blocks(B * kH / 4)), dim3(kThreads), 0, st, t.E, B,
-                       t.M, kH);
-    hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_BIAS_RELU>), dim3(mma_blocks(B)),
-                       dim3(kThreads), 0, st, t.M, B, P + o.W4, kH, 1, P + o.b4, nullptr, t.D1);
-}
-
 // ========================================================== fused step ====
 // The step of a network with one encoder shared by both endpoints (the
-// symmetric pair encoding of Sec. 4.1) runs in four kernels: a forward kernel
+// symmetric pair encoding of Sec. 4.1) runs in four kernels after a packing one: a forward kernel
 // (grid gather, encoder for both endpoints, latent product, decoder, head, the
 // L1 loss and its gradient), a backward kernel (the data adjoint from the head
 // back to dL/dh0), the grid scatter (grid_bwd_kernel) and one kernel for every
@@ -611,7 +581,13 @@ void encode_merge_layer4(const ndf_net_config *c, const NetOffsets &o, const flo
 // = 16 bytes = row lane % 32, features feat_perm(kb, lane / 32, e) for layer
 // outputs (the order the MFMA accumulators pack into) and feat_nat for the grid
 // features h0.  Every store and load of a slab is a coalesced 16-byte access.
-// Numerics are those of the layer-by-layer kernels: bf16 operands into every
+// With two encoders (cross-variable fields) the weights of both and the decoder exceed a
+// CU's LDS, so the forward and the backward kernel each become an encoder and a decoder
+// kernel: the encoder kernels take 64 rows of one endpoint per wave (both MFMA column
+// blocks, its encoder's weights in LDS), the decoder kernels 32 pairs.  Slab block of pair
+// block t and endpoint e: 2 t + e with a shared encoder, e T + t with two (an encoder's
+// slabs are then one range for the weight gradients).
+// Numerics are those of a layer-by-layer evaluation: bf16 operands into every
 // MFMA, FP32 accumulators, FP32 latents into the product; the stored operands
 // of the weight gradients are the same bf16 values the MFMAs take, and bias
 // gradients sum those bf16 values (a bias is the weight of a constant input 1).
@@ -626,65 +602,74 @@ constexpr int kFragH = 4 * 8 * 64;     // bf16x8 per 128 x 128 layer fragment se
 constexpr int kFrag1 = 4 * 2 * 64;     // W1 (128 x 32), and W1^T (32 x 128): 8 x 64
 constexpr int kFrag1F = 4 * 7 * 64;    // W1 with Fourier features (128 x 112)
 
-// Packed weights of one step: forward A fragments of W1..W5 (W[o][k], lane l
+// Packed weights of one step.  Matrices: W1, W2, W3 of each encoder, then W4, W5 (index
+// 3 e + l, 3 n_enc + l).  f: forward A fragments (W[o][k], lane l
 // of fragment (ob, kb) holds row 32 ob + l % 32, inputs 8 (l / 32) + 16 kb + e in
-// the order of the layer's input), then the adjoint's A fragments of
-// W1^T..W5^T (row = the layer's input k, inputs = its outputs o in the packed
-// gradient's order feat_perm).
+// the order of the layer's input); t: the adjoint's A fragments of the
+// transposed matrices (row = the layer's input k, inputs = its outputs o in the packed
+// gradient's order feat_perm; of W1 the 32 grid inputs only, since no gradient flows
+// into the Fourier features).
+constexpr int kMaxMats = 8;
+
 struct TrainFrags {
-    bf16x8 *f[5];
-    bf16x8 *t[5];
+    bf16x8 *f[kMaxMats];
+    bf16x8 *t[kMaxMats];
 };
 
 // With G the gradient (n floats, 256-byte aligned) and the status word are cleared too:
 // one launch in front of the forward kernel instead of three.
-constexpr int kPackBlocks = 64;
+constexpr int kPackBlocks = 16;  // per matrix
 
-__global__ void pack_train_kernel(const float *__restrict__ P, int64_t w1, int64_t w2,
-                                  int64_t w3, int64_t w4, int64_t w5, int kin1, TrainFrags F,
-                                  float *__restrict__ G, int64_t n, int32_t *__restrict__ status) {
-    if (blockIdx.x >= kPackBlocks) {
-        const int64_t n4 = n / 4, step = (int64_t)(gridDim.x - kPackBlocks) * blockDim.x;
-        const int64_t t0 = (int64_t)(blockIdx.x - kPackBlocks) * blockDim.x + threadIdx.x;
+struct PackArgs {
+    int64_t w[kMaxMats];  // offsets of the matrices in P
+    int n_enc, kin1;
+    TrainFrags F;
+};
+
+__global__ void pack_train_kernel(const float *__restrict__ P, PackArgs A, float *__restrict__ G,
+                                  int64_t n, int32_t *__restrict__ status) {
+    const int n_mat = 3 * A.n_enc + 2, pack = kPackBlocks * n_mat;
+    if ((int)blockIdx.x >= pack) {
+        const int64_t n4 = n / 4, step = (int64_t)(gridDim.x - pack) * blockDim.x;
+        const int64_t t0 = (int64_t)(blockIdx.x - pack) * blockDim.x + threadIdx.x;
         for (int64_t i = t0; i < n4; i += step)
             reinterpret_cast<f32x4 *>(G)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int64_t i = 4 * n4 + t0; i < n; i += step) G[i] = 0.f;
         return;
     }
     if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = NDF_OK;
-    const int64_t wo[5] = {w1, w2, w3, w4, w5};
-    // forward: W1 (128 x kin1) and W2..W5; adjoint: W1^T (the 32 grid inputs only:
-    // no gradient flows into the Fourier features) and W2^T..W5^T
-    const int n1 = kH * kin1, nf = n1 + 4 * kH * kH, na = kH * kK0 + 4 * kH * kH;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nf + na;
-         t += kPackBlocks * blockDim.x) {
-        const bool adj = t >= nf;
-        int u = adj ? t - nf : t;
-        const int m1 = adj ? kH * kK0 : n1;
-        const int L = u < m1 ? 0 : 1 + (u - m1) / (kH * kH);
-        if (L > 0) u = (u - m1) % (kH * kH);
-        const int KIN = L == 0 ? kin1 : kH;
-        const int e = u & 7, lane = (u >> 3) & 63, fi = u >> 9;
+    const int L = blockIdx.x / kPackBlocks;
+    const bool first = L < 3 * A.n_enc && L % 3 == 0;  // a W1
+    const int KIN = first ? A.kin1 : kH, KB = KIN / 16;
+    const int nf = kH * KIN, na = kH * (first ? kK0 : kH);
+    const float *W = P + A.w[L];
+    __bf16 *df = reinterpret_cast<__bf16 *>(A.F.f[L]), *dt = reinterpret_cast<__bf16 *>(A.F.t[L]);
+    for (int u = (blockIdx.x % kPackBlocks) * blockDim.x + threadIdx.x; u < nf + na;
+         u += kPackBlocks * blockDim.x) {
+        const bool adj = u >= nf;
+        const int v = adj ? u - nf : u;
+        const int e = v & 7, lane = (v >> 3) & 63, fi = v >> 9;
         const int h = lane >> 5, il = lane & 31;
-        float v;
         if (!adj) {
-            const int KB = KIN / 16, ob = fi / KB, kb = fi % KB;
-            const int k = L == 0 ? feat_nat(kb, h, e) : feat_perm(kb, h, e);
-            v = P[wo[L] + (int64_t)(32 * ob + il) * KIN + k];
+            const int ob = fi / KB, kb = fi % KB;
+            const int k = first ? feat_nat(kb, h, e) : feat_perm(kb, h, e);
+            df[v] = f2bf(W[(int64_t)(32 * ob + il) * KIN + k]);
         } else {
             const int mb = fi / 8, kb = fi % 8;
-            v = P[wo[L] + (int64_t)feat_perm(kb, h, e) * KIN + 32 * mb + il];
+            dt[v] = f2bf(W[(int64_t)feat_perm(kb, h, e) * KIN + 32 * mb + il]);
         }
-        __bf16 *dst = reinterpret_cast<__bf16 *>(adj ? F.t[L] : F.f[L]);
-        dst[u] = f2bf(v);
     }
 }
 
 struct FusedArgs {
     const float *P;
-    int64_t grid[kL];  // offsets of the (single) encoder's grid levels in P
+    int64_t grid[kL];  // offsets of the (first) encoder's grid levels in P
     const bf16x8 *wf[5], *wt[5];
     const float *b[5], *w6, *b6;
+    // two encoders: the second one's grid levels, W1..W3 and b1..b3
+    int64_t grid1[kL];
+    const bf16x8 *wf1[3], *wt1[3];
+    const float *b1[3];
     GridGeom g;
     const int64_t *pairs;
     const float *pos;
@@ -750,8 +735,8 @@ __device__ __forceinline__ void mma_block(const bf16x8 *__restrict__ wf, int ob,
 // Grid features of one endpoint for k-block kb: lane half h gathers level
 // 2 kb + h (8 FP32 features per cell, trilinear over 8 corners).
 template <bool POS>
-__device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, int kb, int h, int64_t v,
-                                            const float (&p)[3], bool few) {
+__device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, const int64_t (&goff)[kL], int kb,
+                                            int h, int64_t v, const float (&p)[3], bool few) {
     const int l = 2 * kb + h;
     int R[3];
     level_dims(A.g, l, R);
@@ -762,7 +747,7 @@ __device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, int kb, int h, i
         corners_pos32<true>(R, p, idx, w, hm);
     else
         corners_R32<true>(A.g, R, v, idx, w, hm);
-    const f32x4 *grid = reinterpret_cast<const f32x4 *>(A.P + (h ? A.grid[2 * kb + 1] : A.grid[2 * kb]));
+    const f32x4 *grid = reinterpret_cast<const f32x4 *>(A.P + (h ? goff[2 * kb + 1] : goff[2 * kb]));
     // A corner of weight 0 adds nothing, and on a level of the vertex grid's size only one
     // corner of eight has weight.  With many waves in flight the others are skipped; a
     // branch around each read waits for it before the next is issued, so with few waves
@@ -805,6 +790,100 @@ __device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, int kb, int h, i
 __device__ __forceinline__ u32x4 as_u(const bf16x8 &v) { return __builtin_bit_cast(u32x4, v); }
 __device__ __forceinline__ bf16x8 as_b(const u32x4 &v) { return __builtin_bit_cast(bf16x8, v); }
 
+// Decoder of 32 pairs from the packed latent product b: W4, W5, the head
+// y = w6 . d2 + b6; with targets gy, da5 and this lane's |y - t|, which is returned.
+__device__ __forceinline__ double decode_pairs(const FusedArgs &A, int64_t tile,
+                                               const bf16x8 *__restrict__ w4,
+                                               const bf16x8 *__restrict__ w5,
+                                               const float *__restrict__ s_b4,
+                                               const float *__restrict__ s_b5,
+                                               const float *__restrict__ s_w6, bf16x8 (&b)[8][2],
+                                               bf16x8 (&a)[8][2], int lane, int h4) {
+    const int h = lane >> 5, jl = lane & 31;
+    const int64_t pair = tile * 32 + jl;
+    const bool ok = pair < A.B;
+    const float b6 = A.b6[0], inv_b = 1.f / (float)A.B;
+    double loss_part = 0.0;
+    f32x16 acc[2];
+    // layer 4: ReLU (pair rows)
+#pragma unroll
+    for (int ob = 0; ob < 4; ++ob) {
+        mma_block<8, 1>(w4, ob, s_b4 + h4, b, acc, lane);
+        u32x4 c0, c1;
+        pack_block(acc[0], c0, c1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            c0[i] = relu_bf16x2(c0[i]);
+            c1[i] = relu_bf16x2(c1[i]);
+        }
+        a[2 * ob][0] = as_b(c0);
+        a[2 * ob + 1][0] = as_b(c1);
+        A.d1[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
+        A.d1[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // layer 5: ReLU, and the head y = w6 . d2 + b6 in FP32
+    float part = 0.f;
+#pragma unroll
+    for (int ob = 0; ob < 4; ++ob) {
+        mma_block<8, 1>(w5, ob, s_b5 + h4, a, acc, lane);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 wv = *reinterpret_cast<const f32x4 *>(s_w6 + h4 + 32 * ob + 8 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                acc[0][4 * g + i] = relu_f32(acc[0][4 * g + i]);
+                part = fmaf(wv[i], acc[0][4 * g + i], part);
+            }
+        }
+        u32x4 c0, c1;
+        pack_block(acc[0], c0, c1);
+        b[2 * ob][0] = as_b(c0);
+        b[2 * ob + 1][0] = as_b(c1);
+        A.d2[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
+        A.d2[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const float y = part + __shfl_xor(part, 32, 64) + b6;
+    if (A.y && h == 0 && ok) A.y[pair] = y;
+    if (A.targets) {
+        const float r = ok ? y - A.targets[pair] : 0.f;
+        const float gyv = (r > 0.f ? 1.f : (r < 0.f ? -1.f : 0.f)) * inv_b;
+        if (h == 0) {
+            A.gy[tile * 32 + jl] = gyv;
+            loss_part = ok ? fabs((double)r) : 0.0;
+        }
+        // da5 = gy w6 where d2 > 0, in the packed order of d2
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const u32x4 dd = as_u(b[j][0]);
+            u32x4 c;
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2) {
+                const int f0 = feat_perm(j, 0, 2 * e2) + h4;
+                c[e2] = relu_mask2(pack_bf16x2(gyv * s_w6[f0], gyv * s_w6[f0 + 1]), dd[e2]);
+            }
+            A.da5[slab_chunk(tile, 8, j, lane)] = c;
+        }
+    }
+    return loss_part;
+}
+
+// Per-workgroup loss partial sum (with targets).
+__device__ __forceinline__ void store_loss_part(const FusedArgs &A, double loss_part,
+                                                double *s_part) {
+    if (A.targets) {
+        loss_part = wave_sum_f64(loss_part);
+        if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = loss_part;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double t = 0.0;
+            for (int w = 0; w < kTW; ++w) t += s_part[w];
+            A.partial[blockIdx.x] = t;
+        }
+    }
+}
+
 // First tile of a wave; the next ones follow at gridDim.x kTW.  Up to one tile per wave
 // the tiles are dealt to the workgroups first (few tiles then run on many CUs), else a
 // workgroup's waves take neighbouring tiles (their slabs are neighbours in memory).
@@ -834,8 +913,6 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
     const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, jl = lane & 31;
     const int64_t T = ceil_div(A.B, 32);
     const int64_t V = (int64_t)A.g.nx * A.g.ny * A.g.nz;
-    const float b6 = A.b6[0];
-    const float inv_b = 1.f / (float)A.B;
     const bool few = T <= 2 * (int64_t)gridDim.x;  // at most two waves of a CU gather
     double loss_part = 0.0;
     for (int64_t tile = first_tile(T, wave); tile < T; tile += (int64_t)gridDim.x * kTW) {
@@ -859,7 +936,7 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
             }
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                a[kb][q] = gather_h0<POS>(A, kb, h, v, p, few);
+                a[kb][q] = gather_h0<POS>(A, A.grid, kb, h, v, p, few);
                 A.h0[slab_chunk(2 * tile + q, KB1, kb, lane)] = as_u(a[kb][q]);
             }
             if (FF) {  // the raw position and its Fourier features
@@ -940,78 +1017,9 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
             A.m[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
             __builtin_amdgcn_sched_barrier(0);
         }
-        // layer 4: ReLU (pair rows)
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-            mma_block<8, 1>(s_w[2], ob, s_b[3] + h4, b, acc, lane);
-            u32x4 c0, c1;
-            pack_block(acc[0], c0, c1);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                c0[i] = relu_bf16x2(c0[i]);
-                c1[i] = relu_bf16x2(c1[i]);
-            }
-            a[2 * ob][0] = as_b(c0);
-            a[2 * ob + 1][0] = as_b(c1);
-            A.d1[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
-            A.d1[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        // layer 5: ReLU, and the head y = w6 . d2 + b6 in FP32
-        float part = 0.f;
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-            mma_block<8, 1>(s_w[3], ob, s_b[4] + h4, a, acc, lane);
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x4 wv = *reinterpret_cast<const f32x4 *>(s_w6 + h4 + 32 * ob + 8 * g);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[0][4 * g + i] = relu_f32(acc[0][4 * g + i]);
-                    part = fmaf(wv[i], acc[0][4 * g + i], part);
-                }
-            }
-            u32x4 c0, c1;
-            pack_block(acc[0], c0, c1);
-            b[2 * ob][0] = as_b(c0);
-            b[2 * ob + 1][0] = as_b(c1);
-            A.d2[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
-            A.d2[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        const float y = part + __shfl_xor(part, 32, 64) + b6;
-        if (A.y && h == 0 && ok) A.y[pair] = y;
-        if (A.targets) {
-            const float r = ok ? y - A.targets[pair] : 0.f;
-            const float gyv = (r > 0.f ? 1.f : (r < 0.f ? -1.f : 0.f)) * inv_b;
-            if (h == 0) {
-                A.gy[tile * 32 + jl] = gyv;
-                loss_part += ok ? fabs((double)r) : 0.0;
-            }
-            // da5 = gy w6 where d2 > 0, in the packed order of d2
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const u32x4 dd = as_u(b[j][0]);
-                u32x4 c;
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const int f0 = feat_perm(j, 0, 2 * e2) + h4;
-                    c[e2] = relu_mask2(pack_bf16x2(gyv * s_w6[f0], gyv * s_w6[f0 + 1]), dd[e2]);
-                }
-                A.da5[slab_chunk(tile, 8, j, lane)] = c;
-            }
-        }
+        loss_part += decode_pairs(A, tile, s_w[2], s_w[3], s_b[3], s_b[4], s_w6, b, a, lane, h4);
     }
-    if (A.targets) {
-        loss_part = wave_sum_f64(loss_part);
-        if (lane == 0) s_part[wave] = loss_part;
-        __syncthreads();
-        if (tid == 0) {
-            double t = 0.0;
-            for (int w = 0; w < kTW; ++w) t += s_part[w];
-            A.partial[blockIdx.x] = t;
-        }
-    }
+    store_loss_part(A, loss_part, s_part);
 }
 
 // One encoder adjoint layer for both endpoints: out = pack(W^T in) masked by the
@@ -1045,6 +1053,47 @@ __device__ __forceinline__ void adj_masked_layer(const bf16x8 *__restrict__ wt,
     }
 }
 
+// W5^T of 32 pairs: y = d(d1) masked by d1 > 0 from da5 (x, read here), stored as da4.
+__device__ __forceinline__ void adj_layer5(const FusedArgs &A, int64_t tile,
+                                           const bf16x8 *__restrict__ w5t, bf16x8 (&x)[8][2],
+                                           bf16x8 (&y)[8][2], int lane) {
+    f32x16 acc[2];
+#pragma unroll
+    for (int kb = 0; kb < 8; ++kb) x[kb][0] = as_b(A.da5[slab_chunk(tile, 8, kb, lane)]);
+    // W5^T: d(d1), masked by d1 > 0 -> da4
+#pragma unroll
+    for (int ob = 0; ob < 4; ++ob) {
+        mma_block<8, 1>(w5t, ob, nullptr, x, acc, lane);
+        u32x4 c0, c1;
+        pack_block(acc[0], c0, c1);
+        const u32x4 m0 = A.d1[slab_chunk(tile, 8, 2 * ob, lane)];
+        const u32x4 m1 = A.d1[slab_chunk(tile, 8, 2 * ob + 1, lane)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            c0[i] = relu_mask2(c0[i], m0[i]);
+            c1[i] = relu_mask2(c1[i], m1[i]);
+        }
+        y[2 * ob][0] = as_b(c0);
+        y[2 * ob + 1][0] = as_b(c1);
+        A.da4[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
+        A.da4[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// dL/dh0 of one row (32 features: level g = 0..3, features 4 h + i).
+__device__ __forceinline__ void store_dh0(const FusedArgs &A, int64_t row, const f32x16 &acc,
+                                          int h) {
+    float *dst = A.dh0 + row * kK0 + 4 * h;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        f32x4 t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = acc[4 * g + i];
+        *reinterpret_cast<f32x4 *>(dst + 8 * g) = t;
+    }
+}
+
 // Data adjoint of 32 pairs per wave: da5 -> da4 -> dlat (both endpoints) -> da2
 // -> da1 -> dL/dh0 (FP32, rows q B + pair, for the grid scatter).  Every G slab
 // is stored for the weight gradients.
@@ -1064,28 +1113,8 @@ __global__ __launch_bounds__(kTThreads) void train_bwd_kernel(FusedArgs A) {
         const int64_t pair = tile * 32 + jl;
         const bool ok = pair < A.B;
         bf16x8 x[8][2], y[8][2];
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) x[kb][0] = as_b(A.da5[slab_chunk(tile, 8, kb, lane)]);
         f32x16 acc[2];
-        // W5^T: d(d1), masked by d1 > 0 -> da4
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) {
-            mma_block<8, 1>(s_t[3], ob, nullptr, x, acc, lane);
-            u32x4 c0, c1;
-            pack_block(acc[0], c0, c1);
-            const u32x4 m0 = A.d1[slab_chunk(tile, 8, 2 * ob, lane)];
-            const u32x4 m1 = A.d1[slab_chunk(tile, 8, 2 * ob + 1, lane)];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                c0[i] = relu_mask2(c0[i], m0[i]);
-                c1[i] = relu_mask2(c1[i], m1[i]);
-            }
-            y[2 * ob][0] = as_b(c0);
-            y[2 * ob + 1][0] = as_b(c1);
-            A.da4[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
-            A.da4[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        adj_layer5(A, tile, s_t[3], x, y, lane);
         // W4^T: dm, then the product rule: dlat_A = dm lat_B, dlat_B = dm lat_A
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {
@@ -1121,22 +1150,263 @@ __global__ __launch_bounds__(kTThreads) void train_bwd_kernel(FusedArgs A) {
         mma_block<8, 2>(s_t1, 0, nullptr, x, acc, lane);
         if (ok) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                float *dst = A.dh0 + ((int64_t)q * A.B + pair) * kK0 + 4 * h;
+            for (int q = 0; q < 2; ++q) store_dh0(A, (int64_t)q * A.B + pair, acc[q], h);
+        }
+    }
+}
+
+// ------------------------------------------------------- two encoders ----
+// Bound by the slabs' HBM stream like the shared-encoder kernels, plus the latents read back
+// (32 KB per pair block in each direction).  A step of 2^16 pairs of the 250 x 352 x 20 grid:
+// 165 us in these four kernels, 0.62 ms with packing, scatter, weight gradients and Adam
+// over 37.8M parameters (0.21 ms); one kernel per layer with FP32 activations in HBM took
+// 1.40 ms.
+// One ReLU (MASKED: adjoint) layer of 64 rows: out = relu(W in + b), or W^T in masked by
+// the forward activation hm > 0; stored as slab blocks blk[q] where st[q].
+template <int KB, bool MASKED>
+__device__ __forceinline__ void rows64_layer(const bf16x8 *__restrict__ wf,
+                                             const float *__restrict__ bias_h,
+                                             const u32x4 *__restrict__ hm,
+                                             u32x4 *__restrict__ slab, const int64_t (&blk)[2],
+                                             const bool (&st)[2], const bf16x8 (&in)[8][2],
+                                             bf16x8 (&out)[8][2], int lane) {
+    f32x16 acc[2];
+#pragma unroll
+    for (int ob = 0; ob < 4; ++ob) {
+        mma_block<KB, 2>(wf, ob, bias_h, in, acc, lane);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            u32x4 c0, c1;
+            pack_block(acc[q], c0, c1);
+            const int64_t i0 = slab_chunk(blk[q], 8, 2 * ob, lane),
+                          i1 = slab_chunk(blk[q], 8, 2 * ob + 1, lane);
+            u32x4 m0, m1;
+            if (MASKED) {  // blk[q] is a real block even where nothing is stored
+                m0 = hm[i0];
+                m1 = hm[i1];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                c0[i] = MASKED ? relu_mask2(c0[i], m0[i]) : relu_bf16x2(c0[i]);
+                c1[i] = MASKED ? relu_mask2(c1[i], m1[i]) : relu_bf16x2(c1[i]);
+            }
+            out[2 * ob][q] = as_b(c0);
+            out[2 * ob + 1][q] = as_b(c1);
+            if (st[q]) {
+                slab[i0] = c0;
+                slab[i1] = c1;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The two 32-pair blocks of a wave's tile of one endpoint: q = 1 of the last tile may lie
+// past the last block (it then repeats the last one and stores nothing).
+__device__ __forceinline__ void rows64_blocks(int64_t tile, int64_t T, int e, int64_t (&pb)[2],
+                                              int64_t (&blk)[2], bool (&st)[2]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        st[q] = 2 * tile + q < T;
+        pb[q] = st[q] ? 2 * tile + q : T - 1;
+        blk[q] = e * T + pb[q];
+    }
+}
+
+// Encoder forward: blockIdx.y = endpoint = encoder, 64 rows per wave.
+template <bool POS>
+__global__ __launch_bounds__(kTThreads) void train_enc_fwd_kernel(FusedArgs A) {
+    __shared__ bf16x8 s_w1[kFrag1];
+    __shared__ bf16x8 s_w[2][kFragH];
+    __shared__ __attribute__((aligned(16))) float s_b[3][kH];
+    const int tid = threadIdx.x, e = blockIdx.y;
+    stage_lds<kFrag1, kTThreads>(s_w1, e ? A.wf1[0] : A.wf[0], tid);
+    stage_lds<kFragH, kTThreads>(s_w[0], e ? A.wf1[1] : A.wf[1], tid);
+    stage_lds<kFragH, kTThreads>(s_w[1], e ? A.wf1[2] : A.wf[2], tid);
+    if (tid < kH) {
+        s_b[0][tid] = (e ? A.b1[0] : A.b[0])[tid];
+        s_b[1][tid] = (e ? A.b1[1] : A.b[1])[tid];
+        s_b[2][tid] = (e ? A.b1[2] : A.b[2])[tid];
+    }
+    int64_t goff[kL];
+#pragma unroll
+    for (int l = 0; l < kL; ++l) goff[l] = e ? A.grid1[l] : A.grid[l];
+    __syncthreads();
+
+    const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, jl = lane & 31;
+    const int64_t T = ceil_div(A.B, 32), T2 = ceil_div(T, 2);
+    const int64_t V = (int64_t)A.g.nx * A.g.ny * A.g.nz;
+    const bool few = T2 <= 2 * (int64_t)gridDim.x;
+    for (int64_t tile = first_tile(T2, wave); tile < T2; tile += (int64_t)gridDim.x * kTW) {
+        int h4 = 4 * h;
+        asm volatile("" : "+v"(h4));
+        int64_t pb[2], blk[2];
+        bool st[2];
+        rows64_blocks(tile, T, e, pb, blk, st);
+        bf16x8 a[8][2], b[8][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int64_t pair = pb[q] * 32 + jl;
+            int64_t v = 0;
+            float p[3] = {0.f, 0.f, 0.f};
+            if (pair < A.B) {
+                if (POS) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) p[c] = A.pos[(2 * pair + e) * 3 + c];
+                } else {
+                    v = A.pairs[2 * pair + e];
+                    v = v < 0 ? 0 : (v >= V ? V - 1 : v);  // out-of-range pairs are clamped
+                }
+            }
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                a[kb][q] = gather_h0<POS>(A, goff, kb, h, v, p, few);
+                if (st[q]) A.h0[slab_chunk(blk[q], 2, kb, lane)] = as_u(a[kb][q]);
+            }
+        }
+        rows64_layer<2, false>(s_w1, s_b[0] + h4, nullptr, A.h1, blk, st, a, b, lane);
+        rows64_layer<8, false>(s_w[0], s_b[1] + h4, nullptr, A.h2, blk, st, b, a, lane);
+        f32x16 acc[2];
+#pragma unroll
+        for (int ob = 0; ob < 4; ++ob) {  // the latents, FP32
+            mma_block<8, 2>(s_w[1], ob, s_b[2] + h4, a, acc, lane);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     f32x4 t;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) t[i] = acc[q][4 * g + i];
-                    *reinterpret_cast<f32x4 *>(dst + 8 * g) = t;
+                    if (st[q]) A.lat[(blk[q] * 4 + ob) * 256 + g * 64 + lane] = t;
                 }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// The FP32 latents of pair block t, output block ob, of both endpoints.
+__device__ __forceinline__ void load_latents(const FusedArgs &A, int64_t t, int64_t T, int ob,
+                                             int lane, f32x16 (&lat)[2]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 v = A.lat[((q * T + t) * 4 + ob) * 256 + g * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lat[q][4 * g + i] = v[i];
+        }
+}
+
+// Decoder forward of 32 pairs per wave: the latent product, W4, W5, the head, and with
+// targets the loss partial sums, gy and da5.
+__global__ __launch_bounds__(kTThreads) void train_dec_fwd_kernel(FusedArgs A) {
+    __shared__ bf16x8 s_w[2][kFragH];
+    __shared__ __attribute__((aligned(16))) float s_b[2][kH];
+    __shared__ __attribute__((aligned(16))) float s_w6[kH];
+    __shared__ double s_part[kTW];
+    const int tid = threadIdx.x;
+    stage_lds<kFragH, kTThreads>(s_w[0], A.wf[3], tid);
+    stage_lds<kFragH, kTThreads>(s_w[1], A.wf[4], tid);
+    if (tid < kH) {
+        s_b[0][tid] = A.b[3][tid];
+        s_b[1][tid] = A.b[4][tid];
+        s_w6[tid] = A.w6[tid];
+    }
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6, h = lane >> 5;
+    const int64_t T = ceil_div(A.B, 32);
+    double loss_part = 0.0;
+    for (int64_t tile = first_tile(T, wave); tile < T; tile += (int64_t)gridDim.x * kTW) {
+        int h4 = 4 * h;
+        asm volatile("" : "+v"(h4));
+        bf16x8 a[8][2], b[8][2];
+#pragma unroll
+        for (int ob = 0; ob < 4; ++ob) {
+            f32x16 lat[2], mm;
+            load_latents(A, tile, T, ob, lane, lat);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mm[r] = lat[0][r] * lat[1][r];
+            u32x4 c0, c1;
+            pack_block(mm, c0, c1);
+            b[2 * ob][0] = as_b(c0);
+            b[2 * ob + 1][0] = as_b(c1);
+            A.m[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
+            A.m[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
+        }
+        loss_part += decode_pairs(A, tile, s_w[0], s_w[1], s_b[0], s_b[1], s_w6, b, a, lane, h4);
+    }
+    store_loss_part(A, loss_part, s_part);
+}
+
+// Decoder adjoint of 32 pairs per wave: da5 -> da4 -> dlat of both endpoints.
+__global__ __launch_bounds__(kTThreads) void train_dec_bwd_kernel(FusedArgs A) {
+    __shared__ bf16x8 s_t[2][kFragH];  // W4^T, W5^T
+    const int tid = threadIdx.x;
+    stage_lds<kFragH, kTThreads>(s_t[0], A.wt[3], tid);
+    stage_lds<kFragH, kTThreads>(s_t[1], A.wt[4], tid);
+    if (blockIdx.x == 0 && tid < 64) loss_reduce(A.partial, A.n_partial, A.B, A.loss, A.status);
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6;
+    const int64_t T = ceil_div(A.B, 32);
+    for (int64_t tile = first_tile(T, wave); tile < T; tile += (int64_t)gridDim.x * kTW) {
+        bf16x8 x[8][2], y[8][2];
+        adj_layer5(A, tile, s_t[1], x, y, lane);
+        f32x16 acc[2];
+#pragma unroll
+        for (int ob = 0; ob < 4; ++ob) {
+            mma_block<8, 1>(s_t[0], ob, nullptr, y, acc, lane);
+            f32x16 lat[2];
+            load_latents(A, tile, T, ob, lane, lat);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                f32x16 d;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) d[r] = acc[0][r] * lat[1 - q][r];
+                u32x4 c0, c1;
+                pack_block(d, c0, c1);
+                A.dlat[slab_chunk(q * T + tile, 8, 2 * ob, lane)] = c0;
+                A.dlat[slab_chunk(q * T + tile, 8, 2 * ob + 1, lane)] = c1;
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// Encoder adjoint: blockIdx.y = endpoint = encoder, 64 rows per wave: dlat -> da2 -> da1
+// -> dL/dh0.
+__global__ __launch_bounds__(kTThreads) void train_enc_bwd_kernel(FusedArgs A) {
+    __shared__ bf16x8 s_t1[kFrag1];
+    __shared__ bf16x8 s_t[2][kFragH];  // W2^T, W3^T
+    const int tid = threadIdx.x, e = blockIdx.y;
+    stage_lds<kFrag1, kTThreads>(s_t1, e ? A.wt1[0] : A.wt[0], tid);
+    stage_lds<kFragH, kTThreads>(s_t[0], e ? A.wt1[1] : A.wt[1], tid);
+    stage_lds<kFragH, kTThreads>(s_t[1], e ? A.wt1[2] : A.wt[2], tid);
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6, h = lane >> 5, jl = lane & 31;
+    const int64_t T = ceil_div(A.B, 32), T2 = ceil_div(T, 2);
+    for (int64_t tile = first_tile(T2, wave); tile < T2; tile += (int64_t)gridDim.x * kTW) {
+        int64_t pb[2], blk[2];
+        bool st[2];
+        rows64_blocks(tile, T, e, pb, blk, st);
+        bf16x8 x[8][2], y[8][2];
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) x[kb][q] = as_b(A.dlat[slab_chunk(blk[q], 8, kb, lane)]);
+        rows64_layer<8, true>(s_t[1], nullptr, A.h2, A.da2, blk, st, x, y, lane);
+        rows64_layer<8, true>(s_t[0], nullptr, A.h1, A.da1, blk, st, y, x, lane);
+        f32x16 acc[2];
+        mma_block<8, 2>(s_t1, 0, nullptr, x, acc, lane);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int64_t pair = pb[q] * 32 + jl;
+            if (st[q] && pair < A.B) store_dh0(A, e * A.B + pair, acc[q], h);
         }
     }
 }
 
 // Weight and bias gradients of every layer in one launch: workgroup ranges
-// [wg0[L], wg0[L + 1]) take layer L (0..4 = W1..W5, 5 = the head w6, b6), each
+// [wg0[L], wg0[L + 1]) take layer L (the packed matrices, then the head w6, b6), each
 // workgroup a strided share of its layer's 64-row slab pairs.  A slab pair of
 // G (the layer's output gradient) and X (its input) is loaded with 16-byte
 // reads (4 rows x 8 features per thread), transposed in registers and written
@@ -1145,13 +1415,14 @@ __global__ __launch_bounds__(kTThreads) void train_bwd_kernel(FusedArgs A) {
 // f < 128 sum the bf16 G column f for the bias.  One atomic flush per workgroup
 // at the end.
 struct WgradArgs {
-    const u32x4 *g[5], *x[5];
-    int kin1;  // inputs of W1 (32, or 112 with Fourier features)
-    int64_t nslab[6];
-    float *dW[6], *db[6];
+    int n_mat;  // matrices; layer n_mat is the head
+    const u32x4 *g[kMaxMats], *x[kMaxMats];
+    int kin[kMaxMats];  // inputs (W1: 32, or 112 with Fourier features)
+    int64_t nslab[kMaxMats + 1];
+    float *dW[kMaxMats + 1], *db[kMaxMats + 1];
     const u32x4 *d2;
     const float *gy;
-    int wg0[7];
+    int wg0[kMaxMats + 2];
 };
 
 constexpr int kWgLD = 64 + 8;  // bf16 per LDS feature row (64 rows + pad)
@@ -1206,26 +1477,27 @@ __global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
     __shared__ float s_gy[64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, jl = lane & 31;
     int L = 0;
-    while (L < 5 && (int)blockIdx.x >= A.wg0[L + 1]) ++L;
+    while (L < A.n_mat && (int)blockIdx.x >= A.wg0[L + 1]) ++L;
+    const bool head = L == A.n_mat;
     const int part = (int)blockIdx.x - A.wg0[L], nparts = A.wg0[L + 1] - A.wg0[L];
     const int64_t nslab = A.nslab[L];
     if (2 * (int64_t)part >= nslab) return;
-    const int kin = L == 0 ? A.kin1 : kH;
+    const int kin = head ? kH : A.kin[L];
     const int xkb = kin / 16, xcb = (kin + 31) / 32;
     const int ob = wave & 3, cb0 = 2 * (wave >> 2);
     // this thread's block
     const int u = tid & 255, sl = u >> 7, kb = (u >> 4) & 7, hh = (u >> 3) & 1,
               r0 = 4 * (u & 7);
     const bool is_g = tid < 256;
-    const bool active = L == 5 ? (is_g ? tid < 64 : true) : (is_g || kb < xkb);
-    const u32x4 *src = L == 5 ? A.d2 : (is_g ? A.g[L] : A.x[L]);
+    const bool active = head ? (is_g ? tid < 64 : true) : (is_g || kb < xkb);
+    const u32x4 *src = head ? A.d2 : (is_g ? A.g[L] : A.x[L]);
     const int nkb = is_g ? 8 : xkb;
-    const bool nat = !is_g && L == 0;
+    const bool nat = !is_g && kin != kH;  // a W1: h0 in natural order
     u32x4 c[4];
     float gyv = 0.f;
     auto fetch = [&](int64_t sp) {
         if (!active) return;
-        if (L == 5 && is_g) {
+        if (head && is_g) {
             const int64_t r = 2 * sp * 32 + tid;
             gyv = r < nslab * 32 ? A.gy[r] : 0.f;
         } else {
@@ -1241,14 +1513,14 @@ __global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
     fetch(part);
     for (int64_t sp = part; 2 * sp < nslab; sp += nparts) {
         if (active) {
-            if (L == 5 && is_g)
+            if (head && is_g)
                 s_gy[tid] = gyv;
             else
-                write4(c, kb, hh, r0, sl, nat, is_g && L != 5 ? s_g : s_x);
+                write4(c, kb, hh, r0, sl, nat, is_g && !head ? s_g : s_x);
         }
         __syncthreads();
         if (2 * (sp + nparts) < nslab) fetch(sp + nparts);
-        if (L == 5) {
+        if (head) {
             // dw6[k] = sum_rows gy d2[row][k] (thread k), db6 = sum_rows gy (thread 128)
             if (tid < kH) {
                 const __bf16 *xr = s_x + tid * kWgLD;
@@ -1284,9 +1556,9 @@ __global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
         }
         __syncthreads();
     }
-    if (L == 5) {
-        if (tid < kH) unsafeAtomicAdd(A.dW[5] + tid, bsum);
-        else if (tid == kH) unsafeAtomicAdd(A.db[5], bsum);
+    if (head) {
+        if (tid < kH) unsafeAtomicAdd(A.dW[L] + tid, bsum);
+        else if (tid == kH) unsafeAtomicAdd(A.db[L], bsum);
         return;
     }
 #pragma unroll
@@ -1303,7 +1575,9 @@ __global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
 }
 
 // ------------------------------------------------------- fused host ----
-static bool fused_path(const ndf_net_config *c) { return c->n_enc == 1 && !c->grid_only; }
+static bool fused_path(const ndf_net_config *c) { return !c->grid_only; }
+
+static int n_mats(const ndf_net_config *c) { return 3 * c->n_enc + 2; }
 
 struct FusedWS {
     int32_t *status;
@@ -1329,8 +1603,11 @@ static FusedWS carve_fused(const ndf_net_config *c, void *ws, int64_t B) {
     };
     t.status = (int32_t *)take(kStatusBytes);
     const int kb1 = enc_in(c) / 16;
-    for (int L = 0; L < 5; ++L) t.fr.f[L] = (bf16x8 *)take((L == 0 ? 4 * kb1 * 64 : kFragH) * 16);
-    for (int L = 0; L < 5; ++L) t.fr.t[L] = (bf16x8 *)take((L == 0 ? kFrag1 : kFragH) * 16);
+    auto first = [&](int L) { return L < 3 * c->n_enc && L % 3 == 0; };  // a W1
+    for (int L = 0; L < n_mats(c); ++L)
+        t.fr.f[L] = (bf16x8 *)take((first(L) ? 4 * kb1 * 64 : kFragH) * 16);
+    for (int L = 0; L < n_mats(c); ++L)
+        t.fr.t[L] = (bf16x8 *)take((first(L) ? kFrag1 : kFragH) * 16);
     const size_t slab = 8 * 64 * 16;  // 128 features x 32 rows, bf16
     t.h0 = (u32x4 *)take(2 * T * kb1 * 64 * 16);
     t.h1 = (u32x4 *)take(2 * T * slab);
@@ -1359,6 +1636,13 @@ static unsigned fused_blocks(int64_t B) {
     return (unsigned)(T < 256 ? T : T <= 256 * kTW ? 256 : kFusedBlocksMax);
 }
 
+// Workgroups per encoder of the encoder kernels (64 rows per wave): as fused_blocks, the
+// two encoders sharing the CUs.
+static unsigned enc_blocks(int64_t B) {
+    const int64_t T2 = ceil_div(ceil_div(B, 32), 2);
+    return (unsigned)(T2 < 128 ? T2 : T2 <= 128 * kTW ? 128 : 256);
+}
+
 static FusedArgs fused_args(const ndf_net_config *c, const NetOffsets &o, const float *P,
                             const int64_t *pairs, const float *pos, const float *targets,
                             int64_t B, const FusedWS &t, float *y) {
@@ -1366,8 +1650,19 @@ static FusedArgs fused_args(const ndf_net_config *c, const NetOffsets &o, const 
     a.P = P;
     for (int l = 0; l < kL; ++l) a.grid[l] = o.grid[0][l];
     for (int L = 0; L < 5; ++L) {
-        a.wf[L] = t.fr.f[L];
-        a.wt[L] = t.fr.t[L];
+        const int i = L < 3 ? L : 3 * (c->n_enc - 1) + L;
+        a.wf[L] = t.fr.f[i];
+        a.wt[L] = t.fr.t[i];
+    }
+    if (c->n_enc == 2) {
+        for (int l = 0; l < kL; ++l) a.grid1[l] = o.grid[1][l];
+        for (int L = 0; L < 3; ++L) {
+            a.wf1[L] = t.fr.f[3 + L];
+            a.wt1[L] = t.fr.t[3 + L];
+        }
+        a.b1[0] = P + o.b1[1];
+        a.b1[1] = P + o.b2[1];
+        a.b1[2] = P + o.b3[1];
     }
     a.b[0] = P + o.b1[0];
     a.b[1] = P + o.b2[0];
@@ -1398,8 +1693,28 @@ static void fused_forward(const ndf_net_config *c, const NetOffsets &o, const Fu
     const float *P = a.P, *pos = a.pos;
     const int64_t B = a.B;
     const unsigned zero = G ? gs_blocks(o.total / 4) : 0;
-    hipLaunchKernelGGL(pack_train_kernel, dim3(kPackBlocks + zero), dim3(256), 0, st, P, o.W1[0],
-                       o.W2[0], o.W3[0], o.W4, o.W5, enc_in(c), t.fr, G, o.total, status);
+    PackArgs pk{};
+    pk.n_enc = c->n_enc;
+    pk.kin1 = enc_in(c);
+    pk.F = t.fr;
+    for (int e = 0; e < c->n_enc; ++e) {
+        pk.w[3 * e] = o.W1[e];
+        pk.w[3 * e + 1] = o.W2[e];
+        pk.w[3 * e + 2] = o.W3[e];
+    }
+    pk.w[3 * c->n_enc] = o.W4;
+    pk.w[3 * c->n_enc + 1] = o.W5;
+    hipLaunchKernelGGL(pack_train_kernel, dim3(kPackBlocks * n_mats(c) + zero), dim3(256), 0, st, P,
+                       pk, G, o.total, status);
+    if (c->n_enc == 2) {
+        const dim3 ge(enc_blocks(B), 2);
+        if (pos)
+            hipLaunchKernelGGL(train_enc_fwd_kernel<true>, ge, dim3(kTThreads), 0, st, a);
+        else
+            hipLaunchKernelGGL(train_enc_fwd_kernel<false>, ge, dim3(kTThreads), 0, st, a);
+        hipLaunchKernelGGL(train_dec_fwd_kernel, dim3(fused_blocks(B)), dim3(kTThreads), 0, st, a);
+        return;
+    }
     const dim3 g(fused_blocks(B)), b(kTThreads);
     if (c->fourier) {
         if (pos)
@@ -1424,39 +1739,52 @@ static int fused_grad(const ndf_net_config *c, const float *P, const int64_t *pa
     a.loss = loss;
     a.status = t.status;
     fused_forward(c, o, a, t, G, t.status, st);
-    hipLaunchKernelGGL(train_bwd_kernel, dim3(fused_blocks(B)), dim3(kTThreads), 0, st, a);
+    const int n_enc = c->n_enc;
+    if (n_enc == 2) {
+        hipLaunchKernelGGL(train_dec_bwd_kernel, dim3(fused_blocks(B)), dim3(kTThreads), 0, st, a);
+        hipLaunchKernelGGL(train_enc_bwd_kernel, dim3(enc_blocks(B), 2), dim3(kTThreads), 0, st, a);
+    } else {
+        hipLaunchKernelGGL(train_bwd_kernel, dim3(fused_blocks(B)), dim3(kTThreads), 0, st, a);
+    }
     const int64_t rows = 2 * B;
     hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)grid_bwd_blocks(rows)), dim3(kThreads), 0,
-                       st, G, grid_offs(o), grid_geom(c), 1, pairs, pos, B, (int64_t)0, rows,
+                       st, G, grid_offs(o), grid_geom(c), n_enc, pairs, pos, B, (int64_t)0, rows,
                        t.dh0);
     WgradArgs w{};
     const int64_t T = ceil_div(B, 32);
-    const u32x4 *gs[5] = {t.da1, t.da2, t.dlat, t.da4, t.da5};
-    const u32x4 *xs[5] = {t.h0, t.h1, t.h2, t.m, t.d1};
-    const int64_t ns[6] = {2 * T, 2 * T, 2 * T, T, T, T};
-    float *dws[6] = {G + o.W1[0], G + o.W2[0], G + o.W3[0], G + o.W4, G + o.W5, G + o.w6};
-    float *dbs[6] = {G + o.b1[0], G + o.b2[0], G + o.b3[0], G + o.b4, G + o.b5, G + o.b6};
+    const int64_t te = n_enc == 2 ? T : 2 * T;  // slabs per encoder
+    int acc_wg = 0, L = 0;
     // workgroups per layer in proportion to the bytes it reads (per decoder slab:
     // W1 20 KB, W2 and W3 32, W4 and W5 16, the head 8), 511 in all, one round at
     // two workgroups per CU; at most one per slab pair
-    const int share[6] = {82, 132, 132, 66, 66, 33};
-    int acc_wg = 0;
-    for (int L = 0; L < 6; ++L) {
-        if (L < 5) {
-            w.g[L] = gs[L];
-            w.x[L] = xs[L];
+    auto layer = [&](int share, const u32x4 *g, const u32x4 *x, int kin, int64_t nslab, float *dW,
+                     float *db) {
+        if (g) {
+            w.g[L] = g;
+            w.x[L] = x;
+            w.kin[L] = kin;
         }
-        w.nslab[L] = ns[L];
-        w.dW[L] = dws[L];
-        w.db[L] = dbs[L];
+        w.nslab[L] = nslab;
+        w.dW[L] = dW;
+        w.db[L] = db;
         w.wg0[L] = acc_wg;
-        const int64_t pairs_l = ceil_div(ns[L], 2);
-        acc_wg += (int)(pairs_l < share[L] ? pairs_l : share[L]);
+        const int64_t pairs_l = ceil_div(nslab, 2);
+        acc_wg += (int)(pairs_l < share ? pairs_l : share);
+        ++L;
+    };
+    const int64_t s8 = te * 8 * 64, s1 = te * (enc_in(c) / 16) * 64;  // chunks per encoder
+    for (int e = 0; e < n_enc; ++e) {
+        layer(82 / n_enc, t.da1 + e * s8, t.h0 + e * s1, enc_in(c), te, G + o.W1[e], G + o.b1[e]);
+        layer(132 / n_enc, t.da2 + e * s8, t.h1 + e * s8, kH, te, G + o.W2[e], G + o.b2[e]);
+        layer(132 / n_enc, t.dlat + e * s8, t.h2 + e * s8, kH, te, G + o.W3[e], G + o.b3[e]);
     }
-    w.wg0[6] = acc_wg;
+    layer(66, t.da4, t.m, kH, T, G + o.W4, G + o.b4);
+    layer(66, t.da5, t.d1, kH, T, G + o.W5, G + o.b5);
+    layer(33, nullptr, nullptr, kH, T, G + o.w6, G + o.b6);
+    w.n_mat = L - 1;
+    w.wg0[L] = acc_wg;
     w.d2 = t.d2;
     w.gy = t.gy;
-    w.kin1 = enc_in(c);
     hipLaunchKernelGGL(wgrad_all_kernel, dim3((unsigned)acc_wg), dim3(512), 0, st, w);
     return status_of_launch();
 }
@@ -1534,57 +1862,16 @@ int launch_net_grad(const ndf_net_config *c, const float *P, const int64_t *pair
                        st, t.dA, B, P + o.W5, 1, kH, nullptr, t.D1, t.dB);
     const GridGeom g = grid_geom(c);
     const GridOffs go = grid_offs(o);
-    const int n_enc = c->n_enc;
-    if (c->grid_only) {
-        // W4 [128][32] on the merged grid features; the product rule gives the
-        // grid features' gradient directly
-        hipLaunchKernelGGL(wgrad_kernel<kK0>, dim3(wgrad_blocks(B)), dim3(kThreads), 0, st, t.dB,
-                           t.M, B, G + o.W4, G + o.b4);
-        hipLaunchKernelGGL((rows_mma_kernel<kH, kK0, EPI_PLAIN>), dim3(mma_blocks(B)),
-                           dim3(kThreads), 0, st, t.dB, B, P + o.W4, 1, kK0, nullptr, nullptr,
-                           t.dA);
-        hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st,
-                           t.dA, t.H0, B, t.dH0, kK0);
-        for (int e = 0; e < n_enc; ++e) {
-            const int64_t r0 = n_enc == 1 ? 0 : e * B, rows = n_enc == 1 ? R : B;
-            const int64_t gb = grid_bwd_blocks(rows);
-            hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)gb),
-                               dim3(kThreads), 0, st, G, go, g, n_enc, pairs, pos, B, r0, rows,
-                               t.dH0);
-        }
-        return status_of_launch();
-    }
-    hipLaunchKernelGGL(wgrad_kernel<kH>, dim3(wgrad_blocks(B)), dim3(kThreads), 0, st, t.dB, t.M, B,
-                       G + o.W4, G + o.b4);
-    hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_PLAIN>), dim3(mma_blocks(B)), dim3(kThreads), 0,
-                       st, t.dB, B, P + o.W4, 1, kH, nullptr, nullptr, t.dA);
-    // product rule across the merge: dE[b] = dM[b] * E[B+b], dE[B+b] = dM[b] * E[b]
-    hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kH / 4)), dim3(kThreads), 0, st, t.dA,
-                       t.E, B, t.dB, kH);
-    // encoder adjoint(s): with a shared encoder both branches accumulate into one set
-    for (int e = 0; e < n_enc; ++e) {
-        const int64_t r0 = n_enc == 1 ? 0 : e * B, rows = n_enc == 1 ? R : B;
-        float *dE = t.dB + r0 * kH, *dP2 = t.dA + r0 * kH, *dP1 = t.dB + r0 * kH;
-        hipLaunchKernelGGL(wgrad_kernel<kH>, dim3(wgrad_blocks(rows)), dim3(kThreads), 0, st, dE,
-                           t.H2 + r0 * kH, rows, G + o.W3[e], G + o.b3[e]);
-        hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_MASK>), dim3(mma_blocks(rows)),
-                           dim3(kThreads), 0, st, dE, rows, P + o.W3[e], 1, kH, nullptr,
-                           t.H2 + r0 * kH, dP2);
-        hipLaunchKernelGGL(wgrad_kernel<kH>, dim3(wgrad_blocks(rows)), dim3(kThreads), 0, st, dP2,
-                           t.H1 + r0 * kH, rows, G + o.W2[e], G + o.b2[e]);
-        hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_MASK>), dim3(mma_blocks(rows)),
-                           dim3(kThreads), 0, st, dP2, rows, P + o.W2[e], 1, kH, nullptr,
-                           t.H1 + r0 * kH, dP1);
-        hipLaunchKernelGGL(wgrad_kernel<kK0>, dim3(wgrad_blocks(rows)), dim3(kThreads), 0, st, dP1,
-                           t.H0 + r0 * kK0, rows, G + o.W1[e], G + o.b1[e]);
-        hipLaunchKernelGGL((rows_mma_kernel<kH, kK0, EPI_PLAIN>), dim3(mma_blocks(rows)),
-                           dim3(kThreads), 0, st, dP1, rows, P + o.W1[e], 1, kK0, nullptr, nullptr,
-                           t.dH0 + r0 * kK0);
-        const int64_t gb = grid_bwd_blocks(rows);
-        hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)gb),
-                           dim3(kThreads), 0, st, G, go, g, n_enc, pairs, pos, B, r0, rows,
-                           t.dH0);
-    }
+    // W4 [128][32] on the merged grid features; the product rule gives the
+    // grid features' gradient directly
+    hipLaunchKernelGGL(wgrad_kernel<kK0>, dim3(wgrad_blocks(B)), dim3(kThreads), 0, st, t.dB, t.M,
+                       B, G + o.W4, G + o.b4);
+    hipLaunchKernelGGL((rows_mma_kernel<kH, kK0, EPI_PLAIN>), dim3(mma_blocks(B)), dim3(kThreads),
+                       0, st, t.dB, B, P + o.W4, 1, kK0, nullptr, nullptr, t.dA);
+    hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st, t.dA,
+                       t.H0, B, t.dH0, kK0);
+    hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)grid_bwd_blocks(R)), dim3(kThreads), 0, st,
+                       G, go, g, c->n_enc, pairs, pos, B, (int64_t)0, R, t.dH0);
     return status_of_launch();
 }
 

@@ -1,14 +1,21 @@
 """GPU parity of the size-dependent branches of the launchers at the sizes where
 they can go wrong (both sides of every dispatch line, ragged remainders, the
 smallest and largest member counts), against the FP64 oracle."""
+import sys
+
 import numpy as np
 import pytest
 import torch
 
+import gen
 from oracle import direct
+from oracle import ndf_net as nn
 from paper_2307_02203_amd import ndf
 
 pytestmark = pytest.mark.gpu
+
+sys.path.insert(0, __file__.rsplit("/", 1)[0])
+from floors import TRAIN_OPS, check_grad_floor  # noqa: E402
 
 PEARSON_TOL = 1e-5  # the FP32 path's bar on every configured ensemble
 
@@ -160,3 +167,36 @@ def test_prepare_at_every_register_count(n_members, dims):
     assert np.max(np.abs(mean - d.mean(1)) / np.abs(d).mean(1)) <= tol
     var = ((d - d.mean(1, keepdims=True)) ** 2).mean(1)
     assert np.max(np.abs(e.inv_std[0].cpu().numpy()[ok] * np.sqrt(var) - 1.0)) <= 4 * tol
+
+
+# pair counts around a 32-pair tile, a 64-row encoder tile and one tile per workgroup
+# (256 shared, 128 per encoder), one and two encoders
+@pytest.mark.parametrize("n_enc", [1, 2])
+@pytest.mark.parametrize("B", [1, 31, 33, 64, 65, 200, 8225])
+def test_training_kernels_at_tile_edges(n_enc, B):
+    cfg = gen.CONFIGS["tiny"]
+    lay = gen.NetLayout.for_grid(cfg.nx, cfg.ny, cfg.nz, n_enc=n_enc)
+    flat = gen.make_net_params(lay, seed=2340, grid_scale=0.5, bias_scale=0.1)
+    c = ndf.net_config(cfg.nx, cfg.ny, cfg.nz, lay.res, n_enc=n_enc)
+    net = nn.Net(flat, (cfg.nx, cfg.ny, cfg.nz), lay.res, 8, 128, n_enc)
+    P = torch.from_numpy(flat).cuda()
+    pairs = gen.random_pairs(cfg.n_vertices, B, seed=B)
+    pairs_t = torch.as_tensor(pairs, device="cuda")
+    y, _ = nn.forward(net, pairs[:, 0], pairs[:, 1])
+    t = y + 1.0  # residual -1 everywhere, far from the L1 kink
+    _, g_o, _ = nn.loss_and_grad(net, pairs[:, 0], pairs[:, 1], t)
+    _, g_e, _ = nn.loss_and_grad(net, pairs[:, 0], pairs[:, 1], t, TRAIN_OPS)
+    ws = torch.empty(ndf.train_ws_bytes(c, B), dtype=torch.uint8, device="cuda")
+    g = torch.full_like(P, 7.0)
+    loss = torch.empty(1, device="cuda")
+    ndf.ndf_net_grad(c, P, pairs_t, torch.as_tensor(t, dtype=torch.float32, device="cuda"), g,
+                     loss, ws)
+    assert abs(loss.item() - 1.0) <= 1e-2
+    check_grad_floor(lay, g.cpu().numpy().astype(np.float64), g_o.flat, g_e.flat,
+                     f"grad n_enc={n_enc} B={B}")
+    # a pair's output does not depend on the batch around it
+    out = torch.empty(B, device="cuda")
+    ndf.ndf_net_forward(c, P, pairs_t, out, ws)
+    half = torch.empty(max(1, B // 2), device="cuda")
+    ndf.ndf_net_forward(c, P, pairs_t[:len(half)].contiguous(), half, ws)
+    assert torch.equal(out[:len(half)], half)
