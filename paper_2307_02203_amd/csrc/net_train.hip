@@ -30,9 +30,15 @@ struct GridOffs {
 };
 
 __device__ __forceinline__ int64_t grid_off(const GridOffs &go, int e, int l) {
-    const int64_t a = l == 0 ? go.off[0][0] : (l == 1 ? go.off[0][1] : (l == 2 ? go.off[0][2] : go.off[0][3]));
-    const int64_t b = l == 0 ? go.off[1][0] : (l == 1 ? go.off[1][1] : (l == 2 ? go.off[1][2] : go.off[1][3]));
-    return e ? b : a;
+    // each offset is read before the choice, which else becomes one of addresses and
+    // moves the struct to scratch memory
+    int64_t r = 0;
+#pragma unroll
+    for (int i = 0; i < 2 * kL; ++i) {
+        const int64_t o = go.off[i / kL][i % kL];
+        r |= e * kL + l == i ? o : 0;
+    }
+    return r;
 }
 
 // ------------------------------------------------------------- helpers ----
@@ -133,16 +139,16 @@ __global__ __launch_bounds__(kThreads) void grid_bwd_kernel(float *__restrict__ 
                                                             GridGeom g, int n_enc,
                                                             const int64_t *__restrict__ pairs,
                                                             const float *__restrict__ pos,
-                                                            int64_t B, int64_t row0, int64_t rows,
+                                                            int64_t B,
                                                             const float *__restrict__ dH0) {
     const int lane = threadIdx.x & 63, i = lane >> 4, dx = (lane >> 3) & 1, f = lane & 7;
-    const int64_t items = rows * kL;
+    const int64_t items = 2 * B * kL;
     const int64_t waves = (int64_t)gridDim.x * (kThreads / 64);
     for (int64_t w0 = ((int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * 4;
          w0 < items; w0 += waves * 4) {
         const int64_t it = w0 + i;
         if (it >= items) continue;
-        const int64_t n = row0 + it / kL;
+        const int64_t n = it / kL;
         const int l = (int)(it % kL);
         const int e = (n_enc == 2 && n >= B) ? 1 : 0;
         int idx[8];
@@ -165,6 +171,384 @@ __global__ __launch_bounds__(kThreads) void grid_bwd_kernel(float *__restrict__ 
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             if (wc[c] != 0.f) unsafeAtomicAdd(gl + (int64_t)ic[c] * kF, wc[c] * d);
+    }
+}
+
+// ---------------------------------------------------- sorted grid scatter ----
+// Large batches add to every cell of the coarser levels many times (2^18 pairs: 154, 38
+// and 9 times on the 250 x 352 x 20 grid's three coarser levels).  The rows are therefore
+// sorted by the spatial tile of the data grid they lie in (grid_sort_count_kernel,
+// grid_sort_place_kernel), and a workgroup takes up to TilePlan::rows rows of one tile
+// (grid_tile_kernel): the tile's cells of those levels are boxes that fit in LDS, where
+// the rows' contributions are summed; one global atomic per touched cell and feature
+// remains.  Hashed levels (no box) and the finest one (a cell is hit about
+// once) are added to directly by a wave of their own, as grid_bwd_kernel does for small
+// batches.  Added directly, the batch is bound by the L2 atomics (one level 0.25 ns per
+// row) and on small grids by the adds to one cell, which follow each other: 2^18 pairs of
+// 250 x 352 x 20 vertices took 466 us, now 142 (sort 27, tiles 115; at positions 623 and
+// 262), of 37 x 29 x 11 1363 and 125, 150000 pairs of 16 x 14 x 5 2467 and 80.
+constexpr int kSortWgs = 64;        // workgroups (row ranges) of the sort
+constexpr int kSortThreads = 1024;
+constexpr int kMaxTiles = 4096;     // tiles of all encoders
+constexpr int64_t kMinSorted = 4096;  // rows below which the sort's launches cost more
+constexpr size_t kTileLds = 70 * 1024;  // boxes of a tile (two workgroups per CU)
+
+struct TilePlan {
+    int t[3];             // tile edges in data-grid vertices
+    int nt[3];            // tiles per axis
+    uint32_t m[3];        // ceil(2^32 / t)
+    int n_tiles;          // of one encoder
+    int box[kL - 1][3];   // cells of a tile's box per axis
+    int off[kL - 1];      // the box's first cell in LDS
+    int cells;            // of all boxes
+    int rows;             // rows of a workgroup, at most
+    int boxed;            // levels 0 .. boxed - 1 have boxes (at most kL - 1)
+};
+
+// A sorted row: data-grid coordinates of its vertex, or its position.
+struct __attribute__((aligned(16))) SortedRow {
+    int n;
+    int x, y, z;  // vertex (i, j, k), or the bits of the position's floats
+};
+
+__device__ __forceinline__ void vertex_ijk(const GridGeom &g, int64_t v64, int (&c)[3]) {
+    const uint32_t v = (uint32_t)v64;
+    const uint32_t t = (uint32_t)(((uint64_t)v * g.mx) >> 40);  // v / nx
+    const uint32_t k = (uint32_t)(((uint64_t)t * g.my) >> 40);  // t / ny
+    c[0] = (int)(v - t * (uint32_t)g.nx);
+    c[1] = (int)(t - k * (uint32_t)g.ny);
+    c[2] = (int)k;
+}
+
+// Row n as a sorted entry and its tile (encoder e's tiles follow encoder e - 1's).
+__device__ __forceinline__ int row_tile(const GridGeom &g, const TilePlan &tp, int n_enc,
+                                        const int64_t *pairs, const float *pos, int64_t B,
+                                        int64_t n, SortedRow &r) {
+    int c[3];
+    r.n = (int)n;
+    if (pos) {
+        const float *p = row_pos(pos, B, n);
+        const int nn[3] = {g.nx, g.ny, g.nz};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float hn = 0.5f * (float)(nn[a] - 1);
+            c[a] = min((int)fminf(fmaxf(fmaf(p[a], hn, hn), 0.f), (float)(nn[a] - 1)), nn[a] - 1);
+        }
+        r.x = __float_as_int(p[0]);
+        r.y = __float_as_int(p[1]);
+        r.z = __float_as_int(p[2]);
+    } else {
+        int64_t v = row_vertex(pairs, B, n);
+        const int64_t V = (int64_t)g.nx * g.ny * g.nz;
+        v = v < 0 ? 0 : (v >= V ? V - 1 : v);  // out-of-range pairs are clamped
+        vertex_ijk(g, v, c);
+        r.x = c[0];
+        r.y = c[1];
+        r.z = c[2];
+    }
+    int ti[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) ti[a] = (int)(((uint64_t)(uint32_t)c[a] * tp.m[a]) >> 32);
+    const int e = (n_enc == 2 && n >= B) ? 1 : 0;
+    return e * tp.n_tiles + ti[0] + tp.nt[0] * (ti[1] + tp.nt[1] * ti[2]);
+}
+
+// Workgroup w counts the rows of its range per tile: hist[w][tile].
+__global__ __launch_bounds__(kSortThreads) void grid_sort_count_kernel(
+    GridGeom g, TilePlan tp, int n_enc, const int64_t *__restrict__ pairs,
+    const float *__restrict__ pos, int64_t B, int *__restrict__ hist) {
+    __shared__ int s_n[kMaxTiles];
+    const int tiles = n_enc * tp.n_tiles;
+    for (int i = threadIdx.x; i < tiles; i += kSortThreads) s_n[i] = 0;
+    __syncthreads();
+    const int64_t rows = 2 * B, lo = rows * blockIdx.x / kSortWgs,
+                  hi = rows * (blockIdx.x + 1) / kSortWgs;
+    for (int64_t n = lo + threadIdx.x; n < hi; n += kSortThreads) {
+        SortedRow r;
+        atomicAdd(&s_n[row_tile(g, tp, n_enc, pairs, pos, B, n, r)], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < tiles; i += kSortThreads)
+        hist[(int64_t)blockIdx.x * tiles + i] = s_n[i];
+}
+
+// Exclusive scan of v over the workgroup's threads (kSortThreads), total in `total`.
+__device__ __forceinline__ int block_scan(int v, int *s_w, int &total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int s = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int t = __shfl_up(s, d);
+        if (lane >= d) s += t;
+    }
+    if (lane == 63) s_w[w] = s;
+    __syncthreads();
+    int base = 0;
+    total = 0;
+    for (int i = 0; i < kSortThreads / 64; ++i) {
+        base += i < w ? s_w[i] : 0;
+        total += s_w[i];
+    }
+    __syncthreads();
+    return base + s - v;
+}
+
+// Workgroup w places the rows of its range: tile starts from all counts, then the rows of
+// earlier ranges, then an LDS counter.  Workgroup 0 also writes the work list of
+// grid_tile_kernel: list[0].x = entries, list[1 + i] = (tile, first row, end row, -).
+__global__ __launch_bounds__(kSortThreads) void grid_sort_place_kernel(
+    GridGeom g, TilePlan tp, int n_enc, const int64_t *__restrict__ pairs,
+    const float *__restrict__ pos, int64_t B, const int *__restrict__ hist,
+    SortedRow *__restrict__ out, int4 *__restrict__ list) {
+    __shared__ int s_at[kMaxTiles];
+    __shared__ int s_w[kSortThreads / 64];
+    const int tiles = n_enc * tp.n_tiles;
+    int start0 = 0, item0 = 0;
+    for (int t0 = 0; t0 < tiles; t0 += kSortThreads) {
+        const int t = t0 + threadIdx.x;
+        int all = 0, before = 0;
+        if (t < tiles) {
+#pragma unroll 16
+            for (int w = 0; w < kSortWgs; ++w) {
+                const int h = hist[(int64_t)w * tiles + t];
+                all += h;
+                before += w < (int)blockIdx.x ? h : 0;
+            }
+        }
+        int sum, items;
+        const int start = start0 + block_scan(all, s_w, sum);
+        if (t < tiles) s_at[t] = start + before;
+        start0 += sum;
+        if (blockIdx.x == 0) {  // uniform
+            const int n_item = (all + tp.rows - 1) / tp.rows;
+            const int item = item0 + block_scan(n_item, s_w, items);
+            for (int i = 0; i < n_item; ++i)
+                list[1 + item + i] = make_int4(t, start + i * tp.rows,
+                                               start + min(all, (i + 1) * tp.rows), 0);
+            item0 += items;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) list[0] = make_int4(item0, 0, 0, 0);
+    __syncthreads();
+    const int64_t rows = 2 * B, lo = rows * blockIdx.x / kSortWgs,
+                  hi = rows * (blockIdx.x + 1) / kSortWgs;
+    for (int64_t n = lo + threadIdx.x; n < hi; n += kSortThreads) {
+        SortedRow r;
+        const int t = row_tile(g, tp, n_enc, pairs, pos, B, n, r);
+        out[atomicAdd(&s_at[t], 1)] = r;
+    }
+}
+
+// Base cell and fraction of a sorted row on a level along axis a: the arithmetic of
+// corners_R32 and corners_pos32, so the same weights bit for bit.
+template <bool POS>
+__device__ __forceinline__ void axis_cell(const GridGeom &g, int R, int a, int c, int &b,
+                                          float &f) {
+    if (POS) {
+        const float hr = 0.5f * (float)(R - 1);
+        const float x = fminf(fmaxf(fmaf(__int_as_float(c), hr, hr), 0.f), (float)(R - 1));
+        b = min(max((int)x, 0), R - 2);
+        f = x - (float)b;
+    } else {
+        const int n1 = (a == 0 ? g.nx : a == 1 ? g.ny : g.nz) - 1;
+        const uint32_t p = (uint32_t)c * (uint32_t)(R - 1);
+        const uint32_t q = (uint32_t)(((uint64_t)p * g.md[a]) >> 40);
+        const uint32_t rem = p - q * (uint32_t)n1;
+        b = min((int)q, R - 2);
+        f = (float)((int)q - b) + (float)rem * g.inv[a];
+    }
+}
+
+// Rows [lo, hi) of one tile on a level without a box, by one wave: kAhead rows in turn per
+// lane group, their loads in flight together; rows of one cell that follow each other
+// are summed before the global atomics.  PAIR: a group is (x-neighbour, feature), so an
+// instruction adds four 64-byte runs, as in grid_bwd_kernel; else (vertices of a level of
+// the data grid's size, one corner each) a group is the feature.
+template <bool POS, bool PAIR>
+__device__ __forceinline__ void tile_direct(float *__restrict__ gl, const GridGeom &g,
+                                            const int (&R)[3], uint32_t hm, int l,
+                                            const SortedRow *__restrict__ rows, int lo, int hi,
+                                            const float *__restrict__ dH0) {
+    constexpr int kGroup = PAIR ? 16 : 8, kRows = 64 / kGroup, kAhead = 8, kC = PAIR ? 4 : 8;
+    const int lane = threadIdx.x & 63, f = lane & 7, dx = PAIR ? (lane >> 3) & 1 : 0;
+    auto add = [&](const int (&b)[3], const float (&v)[kC]) {
+#pragma unroll
+        for (int c = 0; c < kC; ++c) {
+            const int x = PAIR ? dx : c & 1, y = PAIR ? c & 1 : (c >> 1) & 1,
+                      z = PAIR ? c >> 1 : c >> 2;
+            if (v[c] != 0.f)
+                unsafeAtomicAdd(gl + (int64_t)cell_index<true>(b[0] + x, b[1] + y, b[2] + z, R, hm) * kF + f,
+                                v[c]);
+        }
+    };
+    for (int i0 = lo + lane / kGroup * kAhead; i0 < hi; i0 += kRows * kAhead) {
+        SortedRow r[kAhead];
+        float d[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) r[u] = rows[min(i0 + u, hi - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) d[u] = dH0[(int64_t)r[u].n * kK0 + l * kF + f];
+        int at[3] = {-1, -1, -1};  // cell of the rows in `sum`
+        float sum[kC] = {};
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (i0 + u >= hi) break;
+            const int rc[3] = {r[u].x, r[u].y, r[u].z};
+            int b[3];
+            float w[3];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) axis_cell<POS>(g, R[a], a, rc[a], b[a], w[a]);
+            if (b[0] != at[0] || b[1] != at[1] || b[2] != at[2]) {
+                add(at, sum);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) at[a] = b[a];
+#pragma unroll
+                for (int c = 0; c < kC; ++c) sum[c] = 0.f;
+            }
+#pragma unroll
+            for (int c = 0; c < kC; ++c) {
+                const int x = PAIR ? dx : c & 1, y = PAIR ? c & 1 : (c >> 1) & 1,
+                          z = PAIR ? c >> 1 : c >> 2;
+                const float wc = (x ? w[0] : 1.f - w[0]) * (y ? w[1] : 1.f - w[1]) *
+                                 (z ? w[2] : 1.f - w[2]);
+                if (wc != 0.f) sum[c] += wc * d[u];
+            }
+        }
+        add(at, sum);
+    }
+}
+
+// A workgroup takes one item (rows of one tile), wave l level l.  A boxed level's LDS box
+// belongs to that wave alone, so a row is one read, add and write of 64 words, lane =
+// (corner, feature), with no atomics: LDS float atomics take four cycles a lane (256 a row
+// and level, measured; the kernel with them took 665 us for 2^18 pairs), the chain of
+// read, add and write about half.  The cells, fractions and dL/dh0 of 64 rows are
+// computed and loaded at once, a row per lane, and pass through LDS, from where every
+// lane reads the row's at one address (through scalar registers, lane by lane, a row took
+// 430 cycles); the next 64 rows' loads are in flight meanwhile.
+constexpr int kBatch = 64;
+
+struct TileStage {
+    f32x4 row[kBatch];   // entry of the box (int bits), fractions
+    float d[kBatch][kF];
+};
+
+template <bool POS>
+__global__ __launch_bounds__(64 * kL) void grid_tile_kernel(
+    float *__restrict__ grad, GridOffs go, GridGeom g, TilePlan tp,
+    const SortedRow *__restrict__ rows, const int4 *__restrict__ list,
+    const float *__restrict__ dH0) {
+    extern __shared__ f32x4 s_tile[];  // TileStage[boxed] | [cells][8]
+    if ((int)blockIdx.x >= list[0].x) return;
+    const int4 item = list[1 + blockIdx.x];
+    const int e = item.x >= tp.n_tiles ? 1 : 0, tile = item.x - e * tp.n_tiles;
+    const int ti[3] = {tile % tp.nt[0], tile / tp.nt[0] % tp.nt[1], tile / (tp.nt[0] * tp.nt[1])};
+    const int nn[3] = {g.nx, g.ny, g.nz};
+    const int lane = threadIdx.x & 63, f = lane & 7;
+    const int l = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int R[3], box[3], o[3];  // level sizes; the box's edges and first cell
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        R[a] = 0;
+#pragma unroll
+        for (int i = 0; i < kL; ++i) {
+            const int r = g.R[i][a];
+            R[a] |= l == i ? r : 0;
+        }
+    }
+    float *gl = grad + grid_off(go, e, l);
+    if (l >= tp.boxed) {
+        const uint32_t hm = level_hmask(g, l);
+        if (!POS && R[0] == nn[0] && R[1] == nn[1] && R[2] == nn[2])
+            tile_direct<POS, false>(gl, g, R, hm, l, rows, item.y, item.z, dH0);
+        else
+            tile_direct<POS, true>(gl, g, R, hm, l, rows, item.y, item.z, dH0);
+        return;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        box[a] = l == 0 ? tp.box[0][a] : l == 1 ? tp.box[1][a] : tp.box[2][a];
+        o[a] = max(min((int)((int64_t)ti[a] * tp.t[a] * (R[a] - 1) / (nn[a] - 1)), R[a] - box[a]), 0);
+    }
+    const int cells = box[0] * box[1] * box[2];
+    TileStage &S = reinterpret_cast<TileStage *>(s_tile)[l];
+    float *acc = reinterpret_cast<float *>(reinterpret_cast<TileStage *>(s_tile) + tp.boxed) +
+                 (l == 0 ? tp.off[0] : l == 1 ? tp.off[1] : tp.off[2]) * kF;
+    for (int i = lane; i < cells * kF; i += 64) acc[i] = 0.f;
+    // this lane's corner: weight factor s_a f_a + t_a per axis, offset in the box
+    const int dx = (lane >> 3) & 1, dy = (lane >> 4) & 1, dz = lane >> 5;
+    const float sx = dx ? 1.f : -1.f, sy = dy ? 1.f : -1.f, sz = dz ? 1.f : -1.f;
+    const float tx = dx ? 0.f : 1.f, ty = dy ? 0.f : 1.f, tz = dz ? 0.f : 1.f;
+    float *const mine = acc + (dx + box[0] * (dy + box[1] * dz)) * kF + f;
+
+    const int last = item.z - 1;
+    auto load_d = [&](int n, f32x4 &a, f32x4 &b) {
+        const f32x4 *p = reinterpret_cast<const f32x4 *>(dH0 + (int64_t)n * kK0 + l * kF);
+        a = p[0];
+        b = p[1];
+    };
+    SortedRow r = rows[min(item.y + lane, last)];
+    SortedRow r1 = rows[min(item.y + kBatch + lane, last)];
+    f32x4 d0, d1;
+    load_d(r.n, d0, d1);
+    for (int i0 = item.y; i0 < item.z; i0 += kBatch) {
+        const int rc[3] = {r.x, r.y, r.z};
+        int b[3];
+        float w[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) axis_cell<POS>(g, R[a], a, rc[a], b[a], w[a]);
+        const int lx = b[0] - o[0], ly = b[1] - o[1], lz = b[2] - o[2];
+        const bool real = i0 + lane < item.z;
+        const bool in = (uint32_t)lx < (uint32_t)(box[0] - 1) &&
+                        (uint32_t)ly < (uint32_t)(box[1] - 1) &&
+                        (uint32_t)lz < (uint32_t)(box[2] - 1);
+        if (real && !in) {  // a position's rounding at a tile's edge: added to directly
+            for (int c = 0; c < 8; ++c) {
+                const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
+                const float wc = (cx ? w[0] : 1.f - w[0]) * (cy ? w[1] : 1.f - w[1]) *
+                                 (cz ? w[2] : 1.f - w[2]);
+                float *at = gl + (int64_t)(b[0] + cx + R[0] * (b[1] + cy + R[1] * (b[2] + cz))) * kF;
+                if (wc != 0.f)
+                    for (int k = 0; k < kF; ++k) unsafeAtomicAdd(at + k, wc * (k < 4 ? d0[k] : d1[k - 4]));
+            }
+        }
+        const bool use = real && in;  // else a row of zeros
+        const int at = use ? (lx + box[0] * (ly + box[1] * lz)) * kF : 0;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        S.row[lane] = f32x4{__int_as_float(at), w[0], w[1], w[2]};
+        *reinterpret_cast<f32x4 *>(&S.d[lane][0]) = use ? d0 : zero;
+        *reinterpret_cast<f32x4 *>(&S.d[lane][4]) = use ? d1 : zero;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // the next batch
+        r = r1;
+        load_d(r.n, d0, d1);
+        r1 = rows[min(i0 + 2 * kBatch + lane, last)];
+        const int n = min(item.z - i0, kBatch);
+        for (int j0 = 0; j0 < n; j0 += 8) {
+            float wd[8];
+            int where[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const f32x4 q = S.row[j0 + j];
+                where[j] = __float_as_int(q[0]);
+                const float wc = fmaf(sx, q[1], tx) * fmaf(sy, q[2], ty) * fmaf(sz, q[3], tz);
+                // a corner of weight 0 adds nothing, also where dL/dh0 is no number
+                const int m = wc != 0.f ? -1 : 0;
+                wd[j] = __int_as_float(__float_as_int(wc * S.d[j0 + j][f]) & m);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) mine[where[j]] += wd[j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    // one global atomic per touched cell and feature, x-neighbours in one run
+    for (int i = lane; i < cells * kF; i += 64) {
+        const float v = acc[i];
+        const int c = i >> 3, x = c % box[0], yz = c / box[0], y = yz % box[1], z = yz / box[1];
+        if (v != 0.f)
+            unsafeAtomicAdd(gl + (int64_t)((o[0] + x) + R[0] * ((o[1] + y) + R[1] * (o[2] + z))) * kF + f, v);
     }
 }
 
@@ -530,9 +914,13 @@ unsigned mma_blocks(int64_t rows) {
     int64_t b = ceil_div(ceil_div(rows, 64), 4);
     return (unsigned)(b < 1024 ? (b > 0 ? b : 1) : 1024);
 }
-int64_t grid_bwd_blocks(int64_t rows) {
-    const int64_t b = ceil_div(rows * kL, 4 * (kThreads / 64));  // 4 items per wave
-    return b < 8192 ? (b > 0 ? b : 1) : 8192;
+// dL/dh0 of 2 B rows added to the grid levels directly.
+void scatter_direct(float *G, const GridOffs &go, const GridGeom &g, int n_enc,
+                    const int64_t *pairs, const float *pos, int64_t B, const float *dh0,
+                    hipStream_t st) {
+    const int64_t b = ceil_div(2 * B * kL, 4 * (kThreads / 64));  // 4 items per wave
+    hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)(b < 8192 ? b : 8192)), dim3(kThreads), 0,
+                       st, G, go, g, n_enc, pairs, pos, B, dh0);
 }
 unsigned wgrad_blocks(int64_t rows) {
     int64_t b = ceil_div(rows, 64);
@@ -1636,6 +2024,128 @@ static unsigned fused_blocks(int64_t B) {
     return (unsigned)(T < 256 ? T : T <= 256 * kTW ? 256 : kFusedBlocksMax);
 }
 
+// Bytes the sorted scatter needs beside the gradient: rows, work list, counts.
+static size_t tile_scratch(int64_t rows, int64_t tiles, int rows_wg, size_t *list, size_t *hist) {
+    *list = align_up((size_t)rows * sizeof(SortedRow), 256);
+    *hist = *list + align_up((size_t)(tiles + rows / rows_wg + 1) * sizeof(int4), 256);
+    return *hist + (size_t)tiles * kSortWgs * sizeof(int);
+}
+
+// How the grid gradient of `rows` rows is added up: true and a plan for the sorted scatter
+// where it is the faster one by this model (us; measured on grids of 16 x 14 x 5 to
+// 400 x 400 x 11).  Directly, a level takes 0.25 ns per row (0.45 in tables far beyond the
+// L2s; 0.15 at vertices of a level of the data grid's size, where a row has one corner)
+// and, since adds to one cell follow each other, 150 ns per row and cell.  Sorted: the sort 12 us and 0.023 ns per row, a boxed row
+// 0.106 us in a workgroup's chain (512 workgroups run at once) and 1/32 ns per cell of
+// every workgroup's boxes, beside which the levels without boxes are added to.  Tiles of
+// three depths and nearly square footprints are tried for the one to three coarsest dense
+// levels, as far as their boxes stay within kTileLds and the lists within `scratch` bytes.
+static bool tile_plan(const ndf_net_config *c, const GridGeom &g, int64_t rows, bool vertices,
+                      size_t scratch, TilePlan &best) {
+    if (rows < kMinSorted || rows >= (1ll << 31)) return false;
+    const int n[3] = {c->nx, c->ny, c->nz};
+    const double nr = (double)rows;
+    double direct[kL], cost = 0.0;
+    for (int l = 0; l < kL; ++l) {
+        const int *R = g.R[l];
+        const bool one = vertices && R[0] == n[0] && R[1] == n[1] && R[2] == n[2];
+        const double cells = g.hmask[l] ? g.hmask[l] + 1.0 : (double)R[0] * R[1] * R[2];
+        direct[l] = nr * (one ? 0.15e-3 + 0.02 / cells
+                              : (cells > 1 << 19 ? 0.45e-3 : 0.25e-3) + 0.15 / cells);
+        cost += direct[l];
+    }
+    const int64_t even = ceil_div(rows, 512);  // rows of a workgroup if all tiles were one
+    const int rows_wg = (int)(even < 128 ? 128 : even > 1024 ? 1024 : align_up((size_t)even, 64));
+    bool found = false;
+    constexpr int kSizes[] = {4, 6, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64, 96, 400};
+    constexpr int kN = sizeof(kSizes) / sizeof(kSizes[0]);
+    const int depth[3] = {n[2], n[2] < 32 ? n[2] : 32, n[2] < 16 ? n[2] : 16};
+    for (int boxed = 1; boxed < kL && !g.hmask[boxed - 1]; ++boxed) {  // levels 0 .. boxed - 1
+        double left = 0.0;
+        for (int l = boxed; l < kL; ++l) left += direct[l];
+        for (int zi = 0; zi < 3; ++zi) {
+            if (zi && depth[zi] == depth[zi - 1]) continue;
+            for (int k = 0; k < 2 * kN; ++k) {
+                const int tx = kSizes[k / 2], ty = k & 1 ? (k > 1 ? kSizes[k / 2 - 1] : tx) : tx;
+                TilePlan p{};
+                const int t[3] = {tx < n[0] ? tx : n[0], ty < n[1] ? ty : n[1], depth[zi]};
+                int64_t tiles = c->n_enc;
+                for (int a = 0; a < 3; ++a) {
+                    p.t[a] = t[a];
+                    p.nt[a] = (int)ceil_div(n[a], t[a]);
+                    p.m[a] = (uint32_t)(((1ull << 32) + t[a] - 1) / t[a]);
+                    tiles *= p.nt[a];
+                }
+                int64_t cells = 0;
+                for (int l = 0; l < boxed; ++l) {
+                    p.off[l] = (int)cells;
+                    int64_t nl = 1;
+                    for (int a = 0; a < 3; ++a) {
+                        // base cells of a tile's span, and the last one's neighbour
+                        const int64_t span =
+                            (int64_t)(t[a] - (vertices ? 1 : 0)) * (g.R[l][a] - 1) / (n[a] - 1) + 3;
+                        p.box[l][a] = (int)(span < g.R[l][a] ? span : g.R[l][a]);
+                        nl *= p.box[l][a];
+                    }
+                    cells += nl;
+                }
+                if (cells * kF * 4 > (int64_t)kTileLds) break;
+                size_t list, hist;
+                if (tiles > kMaxTiles || tile_scratch(rows, tiles, rows_wg, &list, &hist) > scratch)
+                    continue;
+                p.n_tiles = (int)(tiles / c->n_enc);
+                p.cells = (int)cells;
+                p.rows = rows_wg;
+                p.boxed = boxed;
+                const double per = nr / (double)tiles;
+                const double wgs = (double)tiles * (double)ceil_div((int64_t)per + 1, rows_wg);
+                const double chain = per < rows_wg ? per : rows_wg;
+                const double box = 0.106 * chain * (wgs > 512.0 ? wgs / 512.0 + 0.5 : 1.0) +
+                                   (double)cells * wgs / 32e3;
+                const double us = 12.0 + 0.023e-3 * nr + (box > left ? box : left);
+                if (us < cost) {
+                    cost = us;
+                    best = p;
+                    found = true;
+                }
+            }
+        }
+    }
+    return found;
+}
+
+// The grid gradient from dL/dh0; scratch: the FP32 latents' region, free by then.
+static void scatter_grid(const ndf_net_config *c, const NetOffsets &o, const int64_t *pairs,
+                         const float *pos, int64_t B, float *G, const float *dh0, void *scratch,
+                         size_t scratch_bytes, hipStream_t st) {
+    const GridGeom g = grid_geom(c);
+    const GridOffs go = grid_offs(o);
+    const int64_t rows = 2 * B;
+    TilePlan tp;
+    if (!tile_plan(c, g, rows, pos == nullptr, scratch_bytes, tp)) {
+        scatter_direct(G, go, g, c->n_enc, pairs, pos, B, dh0, st);
+        return;
+    }
+    const int tiles = c->n_enc * tp.n_tiles;
+    const int64_t items = tiles + rows / tp.rows;  // at most
+    size_t list_at, hist_at;
+    tile_scratch(rows, tiles, tp.rows, &list_at, &hist_at);
+    SortedRow *sorted = (SortedRow *)scratch;
+    int4 *list = (int4 *)((char *)scratch + list_at);
+    int *hist = (int *)((char *)scratch + hist_at);
+    hipLaunchKernelGGL(grid_sort_count_kernel, dim3(kSortWgs), dim3(kSortThreads), 0, st, g, tp,
+                       c->n_enc, pairs, pos, B, hist);
+    hipLaunchKernelGGL(grid_sort_place_kernel, dim3(kSortWgs), dim3(kSortThreads), 0, st, g, tp,
+                       c->n_enc, pairs, pos, B, hist, sorted, list);
+    const size_t lds = tp.boxed * sizeof(TileStage) + (size_t)tp.cells * kF * sizeof(float);
+    if (pos)
+        hipLaunchKernelGGL(grid_tile_kernel<true>, dim3((unsigned)items), dim3(64 * kL), lds,
+                           st, G, go, g, tp, sorted, list, dh0);
+    else
+        hipLaunchKernelGGL(grid_tile_kernel<false>, dim3((unsigned)items), dim3(64 * kL), lds,
+                           st, G, go, g, tp, sorted, list, dh0);
+}
+
 // Workgroups per encoder of the encoder kernels (64 rows per wave): as fused_blocks, the
 // two encoders sharing the CUs.
 static unsigned enc_blocks(int64_t B) {
@@ -1746,10 +2256,7 @@ static int fused_grad(const ndf_net_config *c, const float *P, const int64_t *pa
     } else {
         hipLaunchKernelGGL(train_bwd_kernel, dim3(fused_blocks(B)), dim3(kTThreads), 0, st, a);
     }
-    const int64_t rows = 2 * B;
-    hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)grid_bwd_blocks(rows)), dim3(kThreads), 0,
-                       st, G, grid_offs(o), grid_geom(c), n_enc, pairs, pos, B, (int64_t)0, rows,
-                       t.dh0);
+    scatter_grid(c, o, pairs, pos, B, G, t.dh0, t.lat, (size_t)((char *)t.m - (char *)t.lat), st);
     WgradArgs w{};
     const int64_t T = ceil_div(B, 32);
     const int64_t te = n_enc == 2 ? T : 2 * T;  // slabs per encoder
@@ -1870,8 +2377,7 @@ int launch_net_grad(const ndf_net_config *c, const float *P, const int64_t *pair
                        0, st, t.dB, B, P + o.W4, 1, kK0, nullptr, nullptr, t.dA);
     hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st, t.dA,
                        t.H0, B, t.dH0, kK0);
-    hipLaunchKernelGGL(grid_bwd_kernel, dim3((unsigned)grid_bwd_blocks(R)), dim3(kThreads), 0, st,
-                       G, go, g, c->n_enc, pairs, pos, B, (int64_t)0, R, t.dH0);
+    scatter_direct(G, go, g, c->n_enc, pairs, pos, B, t.dH0, st);
     return status_of_launch();
 }
 

@@ -200,3 +200,55 @@ def test_training_kernels_at_tile_edges(n_enc, B):
     half = torch.empty(max(1, B // 2), device="cuda")
     ndf.ndf_net_forward(c, P, pairs_t[:len(half)].contiguous(), half, ws)
     assert torch.equal(out[:len(half)], half)
+
+
+# batches whose grid gradient is added up tile by tile, on both sides of a workgroup's 128
+# to 1024 rows, against the sum over 2^i batches too small for that
+@pytest.mark.parametrize("dims,B,n_enc,at,hashmap,what", [
+    ((16, 14, 5), 2048, 1, False, 0, "random"), ((16, 14, 5), 8000, 2, False, 0, "ends"),
+    ((37, 29, 11), 16000, 1, False, 0, "one"), ((37, 29, 11), 65408, 1, False, 0, "random"),
+    ((12, 12, 4), 7996, 1, True, 0, "random"), ((37, 29, 11), 15992, 2, True, 0, "outside"),
+    ((90, 70, 10), 16000, 2, True, 0, "random"), ((90, 70, 10), 31872, 1, False, 12, "random"),
+    ((150, 150, 24), 63936, 1, False, 0, "random"), ((2, 2, 2), 7992, 1, False, 0, "random")])
+def test_training_grid_gradient_by_tiles(dims, B, n_enc, at, hashmap, what):
+    rng = np.random.default_rng(B)
+    V = dims[0] * dims[1] * dims[2]
+    lay = gen.NetLayout.for_grid(*dims, n_enc=n_enc, log2_hashmap=hashmap)
+    flat = gen.make_net_params(lay, seed=2341, grid_scale=0.5, bias_scale=0.1)
+    c = ndf.net_config(*dims, lay.res, n_enc=n_enc, log2_hashmap=hashmap)
+    P = torch.from_numpy(flat).cuda()
+    if at:
+        p = rng.uniform(-1.0, 1.0, (B, 2, 3))
+        if what == "outside":
+            p *= 1.5
+            p[::97, 1, 1] = np.nan
+        where = torch.as_tensor(p.astype(np.float32), device="cuda")
+    else:
+        v = rng.integers(0, V, (B, 2))
+        if what == "one":
+            v[:] = (V // 2, V // 3)
+        if what == "ends":
+            v = rng.choice([0, 1, V - 2, V - 1], (B, 2))
+        where = torch.as_tensor(v, device="cuda")
+    grad = ndf.ndf_net_grad_at if at else ndf.ndf_net_grad
+    ws = torch.empty(ndf.train_ws_bytes(c, B), dtype=torch.uint8, device="cuda")
+    loss = torch.empty(1, device="cuda")
+
+    def run(w):
+        g = torch.full_like(P, 7.0)
+        t = torch.full((len(w),), 1e3, device="cuda")  # one residual sign for every pair
+        grad(c, P, w, t, g, loss, ws)
+        return g.double()
+
+    got = run(where)
+    # 2^i batches of equal size: their BF16 operands are scaled by a power of two, so the
+    # rows' gradients are the same numbers and only the order of the FP32 sums differs.
+    # As many as B can be cut into: equal rows ("one") round alike, and 2000 of them added
+    # one after the other to a cell are off by up to 3e-5 themselves.
+    chunks = min(B & -B, 256)
+    want = sum(run(w.contiguous()) for w in where.chunk(chunks)) / chunks
+    for name, _shape in lay.tensors():
+        a, b = (lay.view(x.cpu().numpy(), name).ravel() for x in (got, want))
+        # at most 2^17 adds per cell, rounding errors that add up at random (sqrt(2^17)
+        # 2^-24 of sum |x|) and sum |x| up to four times |sum x|
+        assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b), name
