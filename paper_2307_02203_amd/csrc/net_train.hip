@@ -996,7 +996,9 @@ constexpr int kFrag1F = 4 * 7 * 64;    // W1 with Fourier features (128 x 112)
 // the order of the layer's input); t: the adjoint's A fragments of the
 // transposed matrices (row = the layer's input k, inputs = its outputs o in the packed
 // gradient's order feat_perm; of W1 the 32 grid inputs only, since no gradient flows
-// into the Fourier features).
+// into the Fourier features).  With two encoders every layer's inputs are in the order
+// feat_nat (operand<true>) and biases are added last, as in the layer-by-layer kernels:
+// every activation and gradient is then the same number bit for bit, whichever run.
 constexpr int kMaxMats = 8;
 
 struct TrainFrags {
@@ -1028,6 +1030,7 @@ __global__ void pack_train_kernel(const float *__restrict__ P, PackArgs A, float
     if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = NDF_OK;
     const int L = blockIdx.x / kPackBlocks;
     const bool first = L < 3 * A.n_enc && L % 3 == 0;  // a W1
+    const bool nat = A.n_enc == 2;
     const int KIN = first ? A.kin1 : kH, KB = KIN / 16;
     const int nf = kH * KIN, na = kH * (first ? kK0 : kH);
     const float *W = P + A.w[L];
@@ -1040,11 +1043,12 @@ __global__ void pack_train_kernel(const float *__restrict__ P, PackArgs A, float
         const int h = lane >> 5, il = lane & 31;
         if (!adj) {
             const int ob = fi / KB, kb = fi % KB;
-            const int k = first ? feat_nat(kb, h, e) : feat_perm(kb, h, e);
+            const int k = first || nat ? feat_nat(kb, h, e) : feat_perm(kb, h, e);
             df[v] = f2bf(W[(int64_t)(32 * ob + il) * KIN + k]);
         } else {
             const int mb = fi / 8, kb = fi % 8;
-            dt[v] = f2bf(W[(int64_t)feat_perm(kb, h, e) * KIN + 32 * mb + il]);
+            const int o = nat ? feat_nat(kb, h, e) : feat_perm(kb, h, e);
+            dt[v] = f2bf(W[(int64_t)o * KIN + 32 * mb + il]);
         }
     }
 }
@@ -1090,6 +1094,22 @@ __device__ __forceinline__ void pack_block(const f32x16 &acc, u32x4 &c0, u32x4 &
     }
 }
 
+// A packed chunk as the next layer's operand: as it is (inputs in the order feat_perm), or
+// (NAT) in the order feat_nat, which exchanges the second four features of lanes 0-31
+// with the first four of lanes 32-63.
+template <bool NAT>
+__device__ __forceinline__ bf16x8 operand(u32x4 c) {
+    if (NAT) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const auto r = __builtin_amdgcn_permlane32_swap(c[i], c[2 + i], false, false);
+            c[i] = r[0];
+            c[2 + i] = r[1];
+        }
+    }
+    return __builtin_bit_cast(bf16x8, c);
+}
+
 // Keep the halves of g whose forward activation (bf16 pair h, a ReLU output, so
 // +0 or positive) is non-zero: the ReLU derivative on packed pairs.
 __device__ __forceinline__ uint32_t relu_mask2(uint32_t g, uint32_t h) {
@@ -1098,15 +1118,15 @@ __device__ __forceinline__ uint32_t relu_mask2(uint32_t g, uint32_t h) {
     return g & (lo | hi);
 }
 
-// acc[q] = bias (or 0) + W-block ob x in[.][q] over KB k-blocks.
-template <int KB, int NQ>
+// acc[q] = bias (or 0) + W-block ob x in[.][q] over KB k-blocks; NAT adds the bias last.
+template <int KB, int NQ, bool NAT = false>
 __device__ __forceinline__ void mma_block(const bf16x8 *__restrict__ wf, int ob,
                                           const float *__restrict__ bias_h,
                                           const bf16x8 (&in)[8][2], f32x16 (&acc)[2], int lane) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-        if (bias_h) bv = *reinterpret_cast<const f32x4 *>(bias_h + 32 * ob + 8 * g);
+        if (bias_h && !NAT) bv = *reinterpret_cast<const f32x4 *>(bias_h + 32 * ob + 8 * g);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -1117,6 +1137,16 @@ __device__ __forceinline__ void mma_block(const bf16x8 *__restrict__ wf, int ob,
         const bf16x8 a = wf[(ob * KB + kb) * 64 + lane];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) acc[q] = mfma32(a, in[kb][q], acc[q]);
+    }
+    if (bias_h && NAT) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 bv = *reinterpret_cast<const f32x4 *>(bias_h + 32 * ob + 8 * g);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) acc[q][4 * g + i] += bv[i];
+        }
     }
 }
 
@@ -1180,6 +1210,7 @@ __device__ __forceinline__ bf16x8 as_b(const u32x4 &v) { return __builtin_bit_ca
 
 // Decoder of 32 pairs from the packed latent product b: W4, W5, the head
 // y = w6 . d2 + b6; with targets gy, da5 and this lane's |y - t|, which is returned.
+template <bool NAT>
 __device__ __forceinline__ double decode_pairs(const FusedArgs &A, int64_t tile,
                                                const bf16x8 *__restrict__ w4,
                                                const bf16x8 *__restrict__ w5,
@@ -1196,7 +1227,7 @@ __device__ __forceinline__ double decode_pairs(const FusedArgs &A, int64_t tile,
     // layer 4: ReLU (pair rows)
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
-        mma_block<8, 1>(w4, ob, s_b4 + h4, b, acc, lane);
+        mma_block<8, 1, NAT>(w4, ob, s_b4 + h4, b, acc, lane);
         u32x4 c0, c1;
         pack_block(acc[0], c0, c1);
 #pragma unroll
@@ -1204,8 +1235,8 @@ __device__ __forceinline__ double decode_pairs(const FusedArgs &A, int64_t tile,
             c0[i] = relu_bf16x2(c0[i]);
             c1[i] = relu_bf16x2(c1[i]);
         }
-        a[2 * ob][0] = as_b(c0);
-        a[2 * ob + 1][0] = as_b(c1);
+        a[2 * ob][0] = operand<NAT>(c0);
+        a[2 * ob + 1][0] = operand<NAT>(c1);
         A.d1[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
         A.d1[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
         __builtin_amdgcn_sched_barrier(0);
@@ -1214,7 +1245,7 @@ __device__ __forceinline__ double decode_pairs(const FusedArgs &A, int64_t tile,
     float part = 0.f;
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
-        mma_block<8, 1>(w5, ob, s_b5 + h4, a, acc, lane);
+        mma_block<8, 1, NAT>(w5, ob, s_b5 + h4, a, acc, lane);
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const f32x4 wv = *reinterpret_cast<const f32x4 *>(s_w6 + h4 + 32 * ob + 8 * g);
@@ -1405,7 +1436,7 @@ __global__ __launch_bounds__(kTThreads) void train_fwd_kernel(FusedArgs A) {
             A.m[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
             __builtin_amdgcn_sched_barrier(0);
         }
-        loss_part += decode_pairs(A, tile, s_w[2], s_w[3], s_b[3], s_b[4], s_w6, b, a, lane, h4);
+        loss_part += decode_pairs<false>(A, tile, s_w[2], s_w[3], s_b[3], s_b[4], s_w6, b, a, lane, h4);
     }
     store_loss_part(A, loss_part, s_part);
 }
@@ -1442,12 +1473,13 @@ __device__ __forceinline__ void adj_masked_layer(const bf16x8 *__restrict__ wt,
 }
 
 // W5^T of 32 pairs: y = d(d1) masked by d1 > 0 from da5 (x, read here), stored as da4.
+template <bool NAT>
 __device__ __forceinline__ void adj_layer5(const FusedArgs &A, int64_t tile,
                                            const bf16x8 *__restrict__ w5t, bf16x8 (&x)[8][2],
                                            bf16x8 (&y)[8][2], int lane) {
     f32x16 acc[2];
 #pragma unroll
-    for (int kb = 0; kb < 8; ++kb) x[kb][0] = as_b(A.da5[slab_chunk(tile, 8, kb, lane)]);
+    for (int kb = 0; kb < 8; ++kb) x[kb][0] = operand<NAT>(A.da5[slab_chunk(tile, 8, kb, lane)]);
     // W5^T: d(d1), masked by d1 > 0 -> da4
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
@@ -1461,8 +1493,8 @@ __device__ __forceinline__ void adj_layer5(const FusedArgs &A, int64_t tile,
             c0[i] = relu_mask2(c0[i], m0[i]);
             c1[i] = relu_mask2(c1[i], m1[i]);
         }
-        y[2 * ob][0] = as_b(c0);
-        y[2 * ob + 1][0] = as_b(c1);
+        y[2 * ob][0] = operand<NAT>(c0);
+        y[2 * ob + 1][0] = operand<NAT>(c1);
         A.da4[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
         A.da4[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
         __builtin_amdgcn_sched_barrier(0);
@@ -1502,7 +1534,7 @@ __global__ __launch_bounds__(kTThreads) void train_bwd_kernel(FusedArgs A) {
         const bool ok = pair < A.B;
         bf16x8 x[8][2], y[8][2];
         f32x16 acc[2];
-        adj_layer5(A, tile, s_t[3], x, y, lane);
+        adj_layer5<false>(A, tile, s_t[3], x, y, lane);
         // W4^T: dm, then the product rule: dlat_A = dm lat_B, dlat_B = dm lat_A
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {
@@ -1561,7 +1593,7 @@ __device__ __forceinline__ void rows64_layer(const bf16x8 *__restrict__ wf,
     f32x16 acc[2];
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob) {
-        mma_block<KB, 2>(wf, ob, bias_h, in, acc, lane);
+        mma_block<KB, 2, true>(wf, ob, bias_h, in, acc, lane);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             u32x4 c0, c1;
@@ -1578,8 +1610,8 @@ __device__ __forceinline__ void rows64_layer(const bf16x8 *__restrict__ wf,
                 c0[i] = MASKED ? relu_mask2(c0[i], m0[i]) : relu_bf16x2(c0[i]);
                 c1[i] = MASKED ? relu_mask2(c1[i], m1[i]) : relu_bf16x2(c1[i]);
             }
-            out[2 * ob][q] = as_b(c0);
-            out[2 * ob + 1][q] = as_b(c1);
+            out[2 * ob][q] = operand<true>(c0);
+            out[2 * ob + 1][q] = operand<true>(c1);
             if (st[q]) {
                 slab[i0] = c0;
                 slab[i1] = c1;
@@ -1657,7 +1689,7 @@ __global__ __launch_bounds__(kTThreads) void train_enc_fwd_kernel(FusedArgs A) {
         f32x16 acc[2];
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {  // the latents, FP32
-            mma_block<8, 2>(s_w[1], ob, s_b[2] + h4, a, acc, lane);
+            mma_block<8, 2, true>(s_w[1], ob, s_b[2] + h4, a, acc, lane);
 #pragma unroll
             for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -1716,12 +1748,12 @@ __global__ __launch_bounds__(kTThreads) void train_dec_fwd_kernel(FusedArgs A) {
             for (int r = 0; r < 16; ++r) mm[r] = lat[0][r] * lat[1][r];
             u32x4 c0, c1;
             pack_block(mm, c0, c1);
-            b[2 * ob][0] = as_b(c0);
-            b[2 * ob + 1][0] = as_b(c1);
+            b[2 * ob][0] = operand<true>(c0);
+            b[2 * ob + 1][0] = operand<true>(c1);
             A.m[slab_chunk(tile, 8, 2 * ob, lane)] = c0;
             A.m[slab_chunk(tile, 8, 2 * ob + 1, lane)] = c1;
         }
-        loss_part += decode_pairs(A, tile, s_w[0], s_w[1], s_b[0], s_b[1], s_w6, b, a, lane, h4);
+        loss_part += decode_pairs<true>(A, tile, s_w[0], s_w[1], s_b[0], s_b[1], s_w6, b, a, lane, h4);
     }
     store_loss_part(A, loss_part, s_part);
 }
@@ -1738,7 +1770,7 @@ __global__ __launch_bounds__(kTThreads) void train_dec_bwd_kernel(FusedArgs A) {
     const int64_t T = ceil_div(A.B, 32);
     for (int64_t tile = first_tile(T, wave); tile < T; tile += (int64_t)gridDim.x * kTW) {
         bf16x8 x[8][2], y[8][2];
-        adj_layer5(A, tile, s_t[1], x, y, lane);
+        adj_layer5<true>(A, tile, s_t[1], x, y, lane);
         f32x16 acc[2];
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {
@@ -1780,7 +1812,7 @@ __global__ __launch_bounds__(kTThreads) void train_enc_bwd_kernel(FusedArgs A) {
 #pragma unroll
         for (int kb = 0; kb < 8; ++kb)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) x[kb][q] = as_b(A.dlat[slab_chunk(blk[q], 8, kb, lane)]);
+            for (int q = 0; q < 2; ++q) x[kb][q] = operand<true>(A.dlat[slab_chunk(blk[q], 8, kb, lane)]);
         rows64_layer<8, true>(s_t[1], nullptr, A.h2, A.da2, blk, st, x, y, lane);
         rows64_layer<8, true>(s_t[0], nullptr, A.h1, A.da1, blk, st, y, x, lane);
         f32x16 acc[2];
