@@ -10,7 +10,7 @@
 #include "net.hpp"
 
 namespace ndf {
-int launch_prepare(const ndf_ensemble *e, int32_t *status, hipStream_t st);
+int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStream_t st);
 size_t pearson_ws_bytes(int N, int n_ref, int prec);
 int launch_pearson_field(const ndf_ensemble *e, int var_ref, int var_qry, const int64_t *ref_v,
                          int n_ref, float *out, int prec, void *ws, hipStream_t st);
@@ -165,8 +165,9 @@ int ndf_prepare(const ndf_ensemble *ens, void *ws, size_t ws_bytes, void *stream
     int s = check_ensemble(ens, true);
     if (s != NDF_OK) return s;
     if (ws && ws_bytes < kStatusBytes) return NDF_E_WORKSPACE;
-    s = launch_prepare(ens, (int32_t *)ws, S(stream));
-    if (s == NDF_OK && ens->order) s = launch_ksg_orders(ens, S(stream));
+    bool sorted;
+    s = launch_prepare(ens, (int32_t *)ws, &sorted, S(stream));
+    if (s == NDF_OK && ens->order && !sorted) s = launch_ksg_orders(ens, S(stream));
     return s;
 }
 

@@ -31,7 +31,7 @@
 //    evaluation bit for bit; the harmonic sum is FP64.
 #include <type_traits>
 
-#include "common.hpp"
+#include "order.hpp"
 
 namespace ndf {
 
@@ -656,262 +656,27 @@ __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
     }
 }
 
-constexpr int log2_int(int n) { return n <= 1 ? 0 : 1 + log2_int(n / 2); }
+// Waves per SIMD the registers are held to: of E = 16 four waves cover the LDS latencies
+// better than three of 144 registers (3.31 -> 2.95 ms); five and more spill (12 ms).
+constexpr int order_waves(int E) { return E == 16 ? 4 : 1; }
 
-// Ascending bitonic sort of 64 E 32-bit keys held E per lane, in the form whose
-// merge of two sorted halves starts by comparing element i with its mirror
-// i ^ (size - 1): every comparator then puts the minimum at the lower index, so a
-// pair in one lane is one v_min and one v_max, and a pair across lanes one lane
-// shuffle plus a min or max.
+// One column per wave, N <= 64 E.  Bound by VALU issue (779 per column of 1000 members)
+// and LDS beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 -> 2.95 ms
+// (3.6 TB/s) against a register bitonic sort of every column.  Holding the place in the
+// code's word and reading the counters twice took fewer registers, but more LDS: 3.3 ms.
 template <int E>
-__device__ __forceinline__ void wave_sort_regs32(uint32_t (&k)[E]) {
-    const int lane = threadIdx.x & 63;
-    constexpr int LE = log2_int(E);
-    constexpr int LPT = 6 + LE;  // log2 of the key count
-#pragma unroll
-    for (int ls = 1; ls <= LPT; ++ls) {
-        const int size = 1 << ls;
-        if (size <= E) {
-#pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const int jp = j ^ (size - 1);
-                if (jp > j) {
-                    const uint32_t a = k[j], b = k[jp];
-                    k[j] = min(a, b);
-                    k[jp] = max(a, b);
-                }
-            }
-        } else {
-            // partner of (lane, j) is (lane ^ (size / E - 1), E - 1 - j)
-            const bool lower = ((E * lane) & (size >> 1)) == 0;
-            uint32_t t[E];
-#pragma unroll
-            for (int j = 0; j < E; ++j) t[j] = __shfl_xor(k[E - 1 - j], size / E - 1, kWave);
-#pragma unroll
-            for (int j = 0; j < E; ++j) k[j] = lower ? min(k[j], t[j]) : max(k[j], t[j]);
-        }
-#pragma unroll
-        for (int ls2 = ls - 2; ls2 >= 0; --ls2) {
-            const int stride = 1 << ls2;
-            if (stride >= E) {
-                const bool lower = ((E * lane) & stride) == 0;
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const uint32_t o = __shfl_xor(k[j], stride / E, kWave);
-                    k[j] = lower ? min(k[j], o) : max(k[j], o);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const int jp = j ^ stride;
-                    if (jp > j) {
-                        const uint32_t a = k[j], b = k[jp];
-                        k[j] = min(a, b);
-                        k[jp] = max(a, b);
-                    }
-                }
-            }
-        }
-    }
-}
-
-// Sorted member order of one column of N <= 64 E members by one wave, as a bucket
-// sort in LDS.  Codes spread over [0, 2^23], so 2 E 64 buckets of equal width hold one
-// or two samples each: every sample takes a place in its bucket from an LDS counter,
-// a scan of the counters gives the bucket starts, and the samples go to LDS in bucket
-// order, where lane l then holds positions E l .. E l + E - 1.  Their 32-bit keys
-//   (start of the bucket, code bits below the bucket, member)
-// order like (code, member), as the start grows with the bucket.  Odd-even passes
-// finish the buckets; a column with crowded buckets (repeated values, far outliers) is
-// still unsorted after kOddEven passes and goes through the full bitonic sort of the
-// same keys.
-constexpr int kOddEven = 8;  // passes (each both parities) before the full sort
-
-template <int E>
-struct ColumnSort {
-    static constexpr int kLN = 6 + log2_int(E);          // log2 of the slots
-    // 2 buckets per slot; 8 at E = 32 so that start, code bits and member fit 32 bits
-    static constexpr int kLB = kLN <= 10 ? kLN + 1 : kLN + 2;
-    static constexpr int kLow = 23 - kLB;                // code bits inside a bucket
-    static constexpr int kWords = (1 << kLB) / 2;        // two 16-bit counters a word
-    static constexpr int kPer = kWords / 64;             // counter words per lane
-    static constexpr int kLds = kWords + 4;              // + the bucket of code 2^23
-    static_assert(2 * kLN + kLow <= 32, "key bits");
-    static_assert(kWords >= 64 * E, "the keys reuse the counters");
-};
-
-__device__ __forceinline__ void wave_lds_fence() {
-    // LDS operations of a wave complete in order; this only keeps the compiler from
-    // moving them across
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x8u __attribute__((ext_vector_type(8), aligned(2)));
-
-template <int E>
-__device__ __forceinline__ void wave_sort_column(const int32_t *__restrict__ c, int N,
-                                                 uint16_t *__restrict__ o, uint32_t *lds) {
-    typedef ColumnSort<E> C;
-    const int lane = threadIdx.x & 63;
-    // members of this lane: four consecutive ones per load (E >= 4), else strided
-    auto member = [&](int j) {
-        return E >= 4 ? 256 * (j >> 2) + 4 * lane + (j & 3) : 64 * j + lane;
-    };
-    uint32_t code[E];
-    if constexpr (E >= 4) {
-#pragma unroll
-        for (int j = 0; j < E; j += 4) {
-            const int m = member(j);
-            i32x4u q = {0, 0, 0, 0};
-            if (m + 3 < N) {
-                q = *reinterpret_cast<const i32x4u *>(c + m);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (m + e < N) q[e] = c[m + e];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) code[j + e] = (uint32_t)q[e];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < E; ++j) code[j] = member(j) < N ? (uint32_t)c[member(j)] : 0u;
-    }
-    // counters to zero
-    for (int i = lane; i < C::kLds / 4; i += 64)
-        reinterpret_cast<u32x4v *>(lds)[i] = u32x4v{0u, 0u, 0u, 0u};
-    wave_lds_fence();
-    // a place in the bucket (16-bit counters: at most 2048 samples)
-    uint32_t place[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const uint32_t b = min(code[j] >> C::kLow, 1u << C::kLB);
-        if (member(j) < N) {
-            const uint32_t sh = (b & 1) * 16;
-            place[j] = (atomicAdd(&lds[b >> 1], 1u << sh) >> sh) & 0xffffu;
-        }
-    }
-    wave_lds_fence();
-    // exclusive scan over the buckets: lane l owns words kPer l .. kPer l + kPer - 1
-    uint32_t w[C::kPer], sum = 0;
-#pragma unroll
-    for (int i = 0; i < C::kPer; ++i) {
-        w[i] = lds[C::kPer * lane + i];
-        sum += (w[i] & 0xffffu) + (w[i] >> 16);
-    }
-    uint32_t run = sum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(run, d, kWave);
-        if (lane >= d) run += t;
-    }
-    if (lane == 63) lds[C::kWords] = run;  // start of the bucket of code 2^23
-    run -= sum;
-#pragma unroll
-    for (int i = 0; i < C::kPer; ++i) {
-        const uint32_t lo = w[i] & 0xffffu, hi = w[i] >> 16;
-        lds[C::kPer * lane + i] = run | ((run + lo) << 16);
-        run += lo + hi;
-    }
-    wave_lds_fence();
-    uint32_t k[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-        const uint32_t b = min(code[j] >> C::kLow, 1u << C::kLB);
-        const uint32_t start = (lds[b >> 1] >> ((b & 1) * 16)) & 0xffffu;
-        place[j] += start;
-        k[j] = (start << (C::kLow + C::kLN)) |
-               ((code[j] & ((1u << C::kLow) - 1)) << C::kLN) | (uint32_t)member(j);
-    }
-    wave_lds_fence();  // every start is read: the keys reuse the counters' LDS
-#pragma unroll
-    for (int j = 0; j < E; ++j)
-        if (member(j) < N) lds[place[j]] = k[j];
-    wave_lds_fence();
-#pragma unroll
-    for (int j = 0; j < E; ++j) k[j] = lds[E * lane + j];
-    wave_lds_fence();
-#pragma unroll
-    for (int j = 0; j < E; ++j)
-        if (E * lane + j >= N) k[j] = 0xffffffffu;  // above every key: sorts last
-    int pass = 0;
-    for (;; ++pass) {
-        const uint32_t nk = __shfl_down(k[0], 1, kWave);
-        bool bad = lane < 63 && k[E - 1] > nk;
-#pragma unroll
-        for (int j = 0; j + 1 < E; ++j) bad |= k[j] > k[j + 1];
-        if (!__any(bad) || pass == kOddEven) {
-            if (__any(bad)) wave_sort_regs32<E>(k);
-            break;
-        }
-#pragma unroll
-        for (int j = 0; j + 1 < E; j += 2) {  // pairs (2i, 2i + 1) of a lane
-            const uint32_t a = k[j], b = k[j + 1];
-            k[j] = min(a, b);
-            k[j + 1] = max(a, b);
-        }
-        if constexpr (E == 1) {
-            // one key per lane: pairs (2l, 2l + 1), then (2l + 1, 2l + 2)
-            const uint32_t p = __shfl_xor(k[0], 1, kWave);
-            k[0] = lane & 1 ? max(k[0], p) : min(k[0], p);
-            const uint32_t up = __shfl_down(k[0], 1, kWave), dn = __shfl_up(k[0], 1, kWave);
-            if (lane & 1) {
-                if (lane < 63) k[0] = min(k[0], up);
-            } else if (lane > 0) {
-                k[0] = max(k[0], dn);
-            }
-        } else {
-            const uint32_t up = __shfl_down(k[0], 1, kWave), dn = __shfl_up(k[E - 1], 1, kWave);
-#pragma unroll
-            for (int j = 1; j + 1 < E; j += 2) {  // pairs (2i + 1, 2i + 2) of a lane
-                const uint32_t a = k[j], b = k[j + 1];
-                k[j] = min(a, b);
-                k[j + 1] = max(a, b);
-            }
-            // the pair across a lane boundary
-            if (lane < 63) k[E - 1] = min(k[E - 1], up);
-            if (lane > 0) k[0] = max(k[0], dn);
-        }
-    }
-    // positions E lane .. E lane + E - 1 of the order
-    constexpr uint32_t kMask = (1u << C::kLN) - 1;
-    if constexpr (E >= 8) {
-#pragma unroll
-        for (int j = 0; j < E; j += 8) {
-            const int p = E * lane + j;
-            if (p + 7 < N) {
-                u16x8u q;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) q[e] = (uint16_t)(k[j + e] & kMask);
-                *reinterpret_cast<u16x8u *>(o + p) = q;
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (p + e < N) o[p + e] = (uint16_t)(k[j + e] & kMask);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < E; ++j)
-            if (E * lane + j < N) o[E * lane + j] = (uint16_t)(k[j] & kMask);
-    }
-}
-
-// One column per wave, N <= 64 E.  Bound by VALU issue (779 per column of 1000 members,
-// 70 % of the cycles) beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 ->
-// 3.31 ms (3.2 TB/s) against a register bitonic sort of every column.
-template <int E>
-__global__ __launch_bounds__(kKsgThreads) void ksg_order_kernel(const int32_t *__restrict__ code,
+__global__ __launch_bounds__(kKsgThreads, order_waves(E)) void ksg_order_kernel(const int32_t *__restrict__ code,
                                                                 int N, int64_t ncol,
                                                                 uint16_t *__restrict__ order) {
     __shared__ __attribute__((aligned(16))) uint32_t s_lds[kKsgWaves][ColumnSort<E>::kLds];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t waves = (int64_t)gridDim.x * kKsgWaves;
     for (int64_t v = (int64_t)blockIdx.x * kKsgWaves + wave; v < ncol; v += waves)
-        wave_sort_column<E>(code + v * N, N, order + v * N, s_lds[wave]);
+    {
+        uint32_t c[E];
+        load_codes<E>(code + v * N, N, c);
+        wave_sort_codes<E>(c, N, order + v * N, s_lds[wave]);
+    }
 }
 
 // N > 2048 (no KSG call takes such columns): one column per workgroup, in LDS.

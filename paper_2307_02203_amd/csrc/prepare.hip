@@ -12,7 +12,7 @@
 // codes); more members are read twice (prepare_long_kernel).  The ensemble
 // is member-major, so each member row contributes a coalesced segment; codes, and the
 // vertex-major copy of x where the caller wants one, leave through an LDS transpose.
-#include "common.hpp"
+#include "order.hpp"
 
 #pragma clang fp contract(off)
 
@@ -31,7 +31,6 @@ namespace ndf {
 constexpr int kRegV = 32;        // vertices per workgroup: 128-byte row segments
 constexpr int kRegPh = 16;       // member phases
 constexpr int kRegThreads = kRegV * kRegPh;
-typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Rows of the transpose tile: 16 J members of a vertex, padded by four words (the 32
 // vertices of a half wave fall into banks 4 apart).
@@ -61,15 +60,18 @@ __device__ __forceinline__ void prep_store(const int32_t *tile, int32_t *__restr
     }
 }
 
-template <int E>
+template <int E, int OE>
 __global__ __launch_bounds__(kRegThreads) __attribute__((amdgpu_waves_per_eu(4))) void
 prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict__ mean,
                double *__restrict__ inv_std, int32_t *__restrict__ code,
                int32_t *__restrict__ flags, int32_t *__restrict__ status,
-               float *__restrict__ xt) {
+               float *__restrict__ xt, uint16_t *__restrict__ order) {
     constexpr int J = E < 16 ? E : 16;  // rows of 16 members per transpose tile
     constexpr int K = E / J + 1;        // tiles: E whole rows and a partial one
-    __shared__ __attribute__((aligned(16))) int32_t s_tile[kRegV * prep_row<J>()];
+    constexpr int kCols = kRegV / (kRegThreads / 64);  // columns a wave sorts
+    constexpr int kSort = OE ? (kRegThreads / 64) * ColumnSort<OE ? OE : 1>::kLds : 0;
+    constexpr int kTile = kRegV * prep_row<J>();
+    __shared__ __attribute__((aligned(16))) int32_t s_tile[kTile > kSort ? kTile : kSort];
     __shared__ double s_sum[kRegPh / 2][kRegV];
     __shared__ float s_lo[kRegPh / 2][kRegV], s_hi[kRegPh / 2][kRegV];
     __shared__ int s_bad[kRegPh / 2][kRegV];
@@ -141,6 +143,7 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
         ss += d * d;
         return flat ? 0 : (int32_t)__builtin_rint(((double)q - dlo) * scale);
     };
+    uint32_t sc[kCols][OE ? OE : 1];  // the codes of this wave's columns, as they are sorted
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int m0 = kRegPh * J * k;
@@ -153,6 +156,25 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
         if (tail) row[kRegPh * (NF - J * k)] = encode(al);
         __syncthreads();
         prep_store<J>(s_tile, cv, N, V, v0, m0);
+        if constexpr (OE >= 4) {
+            if (4 * k < OE) {
+#pragma unroll
+                for (int c = 0; c < kCols; ++c) {
+                    const i32x4 q = *reinterpret_cast<const i32x4 *>(
+                        s_tile + (kCols * wave + c) * prep_row<J>() + 4 * lane);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sc[c][4 * k + e] = (uint32_t)q[e];
+                }
+            }
+        } else if constexpr (OE > 0) {
+            if (k == 0) {
+#pragma unroll
+                for (int c = 0; c < kCols; ++c)
+#pragma unroll
+                    for (int j = 0; j < OE; ++j)
+                        sc[c][j] = (uint32_t)s_tile[(kCols * wave + c) * prep_row<J>() + 64 * j + lane];
+            }
+        }
         if (tv) {
             __syncthreads();
 #pragma unroll
@@ -177,6 +199,17 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
             (bad ? NDF_FLAG_NONFINITE : 0) | (flat ? NDF_FLAG_CONSTANT : 0);
         // every writer stores the same value, so the unordered stores agree
         if (bad && status) *status = NDF_E_NONFINITE;
+    }
+    if constexpr (OE > 0) {
+        uint16_t *ov = order + (int64_t)var * V * N;
+        uint32_t *lds = reinterpret_cast<uint32_t *>(s_tile) + wave * ColumnSort<OE>::kLds;
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) {
+            const int64_t vc = v0 + kCols * wave + c;
+            if (vc >= V) break;  // uniform
+            wave_sort_codes<OE>(sc[c], N, ov + vc * N, lds);
+            wave_lds_fence();
+        }
     }
 }
 
@@ -430,22 +463,33 @@ int launch_status_clear(int32_t *status, hipStream_t st) {
     return status_of_launch();
 }
 
-int launch_prepare(const ndf_ensemble *e, int32_t *status, hipStream_t st) {
+int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStream_t st) {
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
     if (status) launch_status_clear(status, st);
     const int N = e->n_members;
     const dim3 rg((unsigned)ceil_div(V, kRegV), (unsigned)e->n_vars);
     // the fewest registers that hold a thread's members: waves in flight against loads
-    // past the last member
-#define NDF_PREP_CASE(E)                                                                        \
-    if (N < kRegPh * (E + 1)) {                                                                 \
-        hipLaunchKernelGGL(prepare_kernel<E>, rg, dim3(kRegThreads), 0, st, e->x, N, V, e->mean, \
-                           e->inv_std, e->code, e->flags, status, e->xt);                       \
-        return status_of_launch();                                                              \
+    // past the last member.  Up to 512 members the columns are sorted here too, from codes
+    // kept in registers (450 members of 1.76M vertices 2.82 -> 2.62 ms, 250 members 1.40 ->
+    // 1.30); with more the codes of a wave's four columns spill (1000 members 7.74 ms
+    // against 6.08 with a kernel of its own).
+    *sorted = false;
+#define NDF_PREP_LAUNCH(E, OE)                                                                   \
+    hipLaunchKernelGGL((prepare_kernel<E, OE>), rg, dim3(kRegThreads), 0, st, e->x, N, V, e->mean, \
+                       e->inv_std, e->code, e->flags, status, e->xt, e->order)
+#define NDF_PREP_CASE(E, OE)                                                                     \
+    if (N < kRegPh * (E + 1)) {                                                                  \
+        *sorted = OE && e->order && N <= 64 * OE;                                                     \
+        if (*sorted)                                                                             \
+            NDF_PREP_LAUNCH(E, OE);                                                              \
+        else                                                                                     \
+            NDF_PREP_LAUNCH(E, 0);                                                               \
+        return status_of_launch();                                                               \
     }
-    NDF_PREP_CASE(4) NDF_PREP_CASE(8) NDF_PREP_CASE(16)
-    NDF_PREP_CASE(32) NDF_PREP_CASE(48) NDF_PREP_CASE(64)
+    NDF_PREP_CASE(4, 1) NDF_PREP_CASE(8, 2) NDF_PREP_CASE(16, 4)
+    NDF_PREP_CASE(32, 8) NDF_PREP_CASE(48, 0) NDF_PREP_CASE(64, 0)
 #undef NDF_PREP_CASE
+#undef NDF_PREP_LAUNCH
     dim3 grid((unsigned)ceil_div(V, kPrepV), (unsigned)e->n_vars);
     hipLaunchKernelGGL(prepare_long_kernel, grid, dim3(kPrepThreads), 0, st, e->x, N, V, e->mean,
                        e->inv_std, e->code, e->flags, status);
