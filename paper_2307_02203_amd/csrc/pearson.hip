@@ -378,6 +378,113 @@ __global__ __launch_bounds__(256) void pearson_gemm_kernel(
         }
 }
 
+// The same tile and the same sums for grids whose waves do not fill the chip: there a wave
+// waits a memory latency per k-step (1.9 us), so kDeep k-steps of x and two of the
+// reference fragments are in flight, in one wave per workgroup (a step then takes 0.6 us;
+// two k-steps in flight 0.7, six 0.6).  No load is behind a branch: rows past
+// the last member read member N - 1 (the reference operand is zero there), columns past
+// the last vertex a real vertex's (never stored).
+constexpr int kDeep = 4;
+
+template <int NIB, bool VEC>
+__global__ __launch_bounds__(64) void pearson_gemm_deep_kernel(
+    const float *__restrict__ x, const double *__restrict__ mean,
+    const double *__restrict__ inv_std, int N, int64_t V, const bf16x8 *__restrict__ afrag,
+    int n_ib_total, int n_ref, float *__restrict__ out) {
+    const int lane = threadIdx.x, h = lane >> 5, jl = lane & 31;
+    const int ib0 = blockIdx.y * NIB;
+    const int64_t v0 = (int64_t)blockIdx.x * kGemmVerts + 2 * jl;
+    float mu[2], is[2];
+    int64_t vr[2];  // the column read
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        vr[t] = VEC ? (v0 < V ? v0 : V - 2) + t : (v0 + t < V ? v0 + t : V - 1);
+        mu[t] = (float)mean[vr[t]];
+        is[t] = (float)inv_std[vr[t]];
+    }
+    f32x16 acc[NIB][2];
+#pragma unroll
+    for (int i = 0; i < NIB; ++i)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][t][r] = 0.f;
+
+    auto load = [&](int ks, float (&xv)[8][2]) {
+        const int m0 = ks * 16 + 8 * h;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float *row = x + (int64_t)min(m0 + e, N - 1) * V;
+            if (VEC) {
+                const f32x2 a = *reinterpret_cast<const f32x2 *>(row + vr[0]);
+                xv[e][0] = a[0];
+                xv[e][1] = a[1];
+            } else {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) xv[e][t] = row[vr[t]];
+            }
+        }
+    };
+    const int ksteps = (N + 15) / 16;
+    auto frags = [&](int ks, bf16x8 (&f)[NIB][2]) {
+        const int k = min(ks, ksteps - 1);
+#pragma unroll
+        for (int i = 0; i < NIB; ++i)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                f[i][p] = afrag[(((int64_t)k * n_ib_total + ib0 + i) * 2 + p) * 64 + lane];
+    };
+    float xv[kDeep][8][2];
+    bf16x8 f[2][NIB][2];
+#pragma unroll
+    for (int d = 0; d < kDeep; ++d) load(d, xv[d]);
+#pragma unroll
+    for (int d = 0; d < 2; ++d) frags(d, f[d]);
+    for (int ks0 = 0; ks0 < ksteps; ks0 += kDeep) {
+#pragma unroll
+        for (int d = 0; d < kDeep; ++d) {
+            const int ks = ks0 + d;
+            if (ks >= ksteps) break;  // uniform
+            bf16x8 bhi[2], blo[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    __bf16 hb, lb;
+                    split_z(xv[d][e][t], mu[t], is[t], hb, lb);
+                    bhi[t][e] = hb;
+                    blo[t][e] = lb;
+                }
+            load(ks + kDeep, xv[d]);
+#pragma unroll
+            for (int i = 0; i < NIB; ++i)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    acc[i][t] = mfma32(f[d & 1][i][0], bhi[t], acc[i][t]);
+                    acc[i][t] = mfma32(f[d & 1][i][0], blo[t], acc[i][t]);
+                    acc[i][t] = mfma32(f[d & 1][i][1], bhi[t], acc[i][t]);
+                }
+            frags(ks + 2, f[d & 1]);
+        }
+    }
+    const float invN = 1.0f / (float)N;
+#pragma unroll
+    for (int i = 0; i < NIB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int ref = (ib0 + i) * 32 + d_row(r, lane);
+            if (ref >= n_ref) continue;
+            float *o = out + (int64_t)ref * V + v0;
+            if (VEC && v0 < V) {
+                *reinterpret_cast<f32x2 *>(o) = f32x2{acc[i][0][r] * invN, acc[i][1][r] * invN};
+            } else if (!VEC) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    if (v0 + t < V) o[t] = acc[i][t][r] * invN;
+            }
+        }
+}
+
 // Many references in one read of the ensemble: a workgroup of four waves takes
 // 128 vertices and 256 references, wave w the references 64 w .. 64 w + 63 for
 // all 128 vertices (four 32-vertex tiles, 128 accumulators: the reference
@@ -715,6 +822,16 @@ size_t pearson_ws_bytes(int N, int n_ref, int prec) {
     return zr + refs;
 }
 
+// Whether a call's waves of 32 references x 64 vertices are few enough for the kernel that
+// hides latencies within a wave: about one per SIMD.  Both give the same bits.  1000
+// members, us: 11803 vertices, 64 references (370 waves) 119 -> 40, 100 (740) 58 -> 46, 256
+// (1480) 71 against 84; 65600 vertices, 32 references (1025) 73 -> 58, 64 (2050) 98
+// against 100; 131072 vertices, 1 reference (2048) 88 against 104.
+constexpr int64_t kDeepWaves = 1088;
+static bool pearson_deep(int64_t V, int n_ref) {
+    return ceil_div(V, kGemmVerts) * ceil_div(n_ref, 32) <= kDeepWaves;
+}
+
 int launch_pearson_field(const ndf_ensemble *e, int var_ref, int var_qry, const int64_t *ref_v,
                          int n_ref, float *out, int prec, void *ws, hipStream_t st) {
     const int N = e->n_members;
@@ -742,7 +859,15 @@ int launch_pearson_field(const ndf_ensemble *e, int var_ref, int var_qry, const 
     // 8-byte accesses need every member row 8-byte aligned: V even
     const bool vec = (V % 2) == 0;
     const bf16x8 *af = frag;
-    if (n_ref > 64) {
+    if (pearson_deep(V, n_ref)) {
+        const dim3 g((unsigned)ceil_div(V, kGemmVerts), (unsigned)ceil_div(n_ref, 32));
+        if (vec)
+            hipLaunchKernelGGL((pearson_gemm_deep_kernel<1, true>), g, dim3(64), 0, st, xq, mq, iq,
+                               N, V, af, n_ib, n_ref, out);
+        else
+            hipLaunchKernelGGL((pearson_gemm_deep_kernel<1, false>), g, dim3(64), 0, st, xq, mq, iq,
+                               N, V, af, n_ib, n_ref, out);
+    } else if (n_ref > 64) {
         // one read of the ensemble per 256 references
         const dim3 g((unsigned)ceil_div(V, kWideVerts), (unsigned)ceil_div(n_ref, kWideRefs));
         hipLaunchKernelGGL(pearson_gemm_wide_kernel, g, dim3(256), 0, st, xq, mq, iq, N, V, af,

@@ -57,6 +57,33 @@ def test_pearson_fp32_member_splits(dims, n_members, n_ref):
 
 # member counts on both sides of every slot count of the order kernel (64 E, E = 1 .. 32)
 # and of the workgroup path (N > 2048); columns from smooth to fully tied
+# grids and reference counts on both sides of the line between the kernels (1088 waves of 32
+# references x 64 vertices), even and odd vertex counts around a tile, member counts around
+# a k-step (16) and the k-steps in flight (4)
+@pytest.mark.parametrize("dims,n_members,n_ref",
+                         [((2, 2, 2), 2, 1), ((3, 3, 3), 15, 2), ((4, 4, 4), 16, 32),
+                          ((5, 13, 1 + 1), 17, 33), ((7, 9, 2 + 1), 63, 64), ((8, 8, 2), 64, 65),
+                          ((37, 29, 11), 65, 100), ((37, 29, 11), 81, 193), ((129, 90, 6), 33, 32),
+                          ((129, 90, 6), 20, 33)])
+def test_pearson_split_bf16_small_grids(dims, n_members, n_ref):
+    x, e = _ensemble(n_members, dims, seed=n_members + n_ref)
+    V = x.shape[1]
+    x[n_members // 2, V - 1] = np.nan
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=False)
+    ndf.ndf_prepare(e)
+    refs = np.linspace(0, V - 2, n_ref).astype(np.int64)
+    got = ndf.pearson_field(e, list(refs), prec=ndf.NDF_PREC_SPLIT_BF16).cpu().numpy()
+    assert np.all(np.isnan(got[:, V - 1]) | (got[:, V - 1] == 0.0))
+    z = x[:, :V - 1].astype(np.float64)
+    z = (z - z.mean(0)) / z.std(0)
+    for r, v in enumerate(refs):
+        want = (z[:, v:v + 1] * z).mean(0)
+        # hi + lo carries 2^-16 of |z| on either side and lo lo is dropped; FP32 sums of N
+        # terms and FP32 moments
+        tol = (3 * 2.0 ** -16 + (n_members + 8) * 2.0 ** -24) * np.abs(z[:, v:v + 1] * z).mean(0)
+        assert np.all(np.abs(got[r, :V - 1] - want) <= tol), (r, v)
+
+
 @pytest.mark.parametrize("n_members", [2, 3, 63, 64, 65, 127, 128, 129, 200, 255, 256, 257, 511,
                                        512, 513, 1000, 1023, 1024, 1025, 2047, 2048, 2049, 4096])
 def test_stored_orders_are_the_stable_sort_of_the_codes(n_members):
