@@ -1514,10 +1514,14 @@ static void launch_calibrate(const ndf_net_config *c, const QLayout &q, char *Q,
                  nullptr, st);
 }
 
-static unsigned infer_blocks(int64_t nq) {
-    const int64_t tiles = ceil_div(nq, 64);
-    const int64_t b = ceil_div(tiles, kInferWaves);
-    return (unsigned)(b < 256 ? (b > 0 ? b : 1) : 256);  // one resident workgroup per CU
+// Workgroups of a launch over nq queries, each for `refs` references that a tile can be
+// split over: one per CU, and with little work one per tile (and reference), so that few
+// tiles run on many CUs, though every workgroup then stages the weights (from L2) for one.
+// Dealt eight to a workgroup's waves, 11803 vertices ran on 24 CUs: one BF16 field 17.4 ->
+// 11.7 us, 16 of them 117 -> 46, 9 E4M3 cross fields 86 -> 45; no size measured slower.
+static unsigned infer_blocks(int64_t nq, int refs = 1) {
+    const int64_t items = ceil_div(nq, 64) * refs;
+    return (unsigned)(items < 256 ? (items > 0 ? items : 1) : 256);
 }
 
 size_t net_latent_cache_bytes(const ndf_net_config *c) {
@@ -1586,7 +1590,7 @@ static void decode_cached(const ndf_net_config *c, const QLayout &q, const char 
     const InferArgs a1 = make_args(c, q, Q, c->n_enc - 1);
     for (int r0 = 0; r0 < n_ref; r0 += kMultiRefs) {
         const int n = n_ref - r0 < kMultiRefs ? n_ref - r0 : kMultiRefs;
-        hipLaunchKernelGGL(infer_cached_kernel<false>, dim3(infer_blocks(a1.V)),
+        hipLaunchKernelGGL(infer_cached_kernel<false>, dim3(infer_blocks(a1.V, n)),
                            dim3(kInferThreads), 0, st, a1, (const u32x4 *)cache, a1.V,
                            lat + (int64_t)r0 * kH, n, out + (int64_t)r0 * a1.V, a1.V);
     }
@@ -1630,8 +1634,8 @@ int launch_infer_field(const ndf_net_config *c, const void *qp, int prec, const 
         const InferArgs8 a8 = make_args8(c, q, Q, c->n_enc - 1);
         for (int r0 = 0; r0 < n_ref; r0 += kMultiRefs) {
             const int n = n_ref - r0 < kMultiRefs ? n_ref - r0 : kMultiRefs;
-            hipLaunchKernelGGL(infer_cached_fp8_kernel, dim3(infer_blocks(V)), dim3(kInferThreads),
-                               0, st, a8, (const u32x4 *)cache, V, lat + (int64_t)r0 * kH, n,
+            hipLaunchKernelGGL(infer_cached_fp8_kernel, dim3(infer_blocks(V, n)),
+                               dim3(kInferThreads), 0, st, a8, (const u32x4 *)cache, V, lat + (int64_t)r0 * kH, n,
                                out + (int64_t)r0 * V, V);
         }
         return status_of_launch();

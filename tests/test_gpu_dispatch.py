@@ -196,6 +196,31 @@ def test_prepare_at_every_register_count(n_members, dims):
     assert np.max(np.abs(e.inv_std[0].cpu().numpy()[ok] * np.sqrt(var) - 1.0)) <= 4 * tol
 
 
+# one tile and more, references around the launch's 16 and the parts a tile is split into
+@pytest.mark.parametrize("dims,n_ref", [((2, 2, 2), 2), ((4, 4, 4), 17), ((5, 13, 2), 9),
+                                        ((16, 14, 5), 33), ((37, 29, 11), 16), ((81, 29, 7), 5)])
+def test_fields_do_not_depend_on_the_launch(dims, n_ref):
+    V = dims[0] * dims[1] * dims[2]
+    lay = gen.NetLayout.for_grid(*dims)
+    c = ndf.net_config(*dims, lay.res)
+    P = torch.from_numpy(gen.make_net_params(lay, seed=2342, grid_scale=0.5, bias_scale=0.1)).cuda()
+    refs = [int(v) for v in np.linspace(0, V - 1, n_ref)]
+
+    def field(q, r, prec):
+        out = torch.full((len(r), V), 7.0, device="cuda")
+        ws = torch.empty(ndf.infer_ws_bytes(c, len(r), prec), dtype=torch.uint8, device="cuda")
+        ndf.ndf_infer_field(c, q, prec, r, out, ws)
+        return out
+
+    # a field's bits are the same alone and among others (E4M3: from two references on)
+    for prec, n in ((ndf.NDF_PREC_BF16, 1), (ndf.NDF_PREC_FP8_E4M3, 2)):
+        q = torch.empty(ndf.ndf_net_qparam_bytes(c, prec), dtype=torch.uint8, device="cuda")
+        ndf.ndf_net_quantize(c, P, prec, q)
+        whole = field(q, refs, prec)
+        for r in range(0, n_ref - n + 1):
+            assert torch.equal(field(q, refs[r:r + n], prec), whole[r:r + n]), (prec, r)
+
+
 # pair counts around a 32-pair tile, a 64-row encoder tile and one tile per workgroup
 # (256 shared, 128 per encoder), one and two encoders
 @pytest.mark.parametrize("n_enc", [1, 2])
