@@ -533,7 +533,7 @@ def _rooflines(med, N, V):
                          / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s"},
         "pearson_b64": {"bound": "hbm", "achieved": 4.0 * N * V / (med["pearson_b64"] * 1e-3)
                         / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s"},
-        # x read twice (moments, then codes) + int32 codes written: 12 B per sample
+        # x read once + int32 codes and their uint16 order written: 10 B per sample
         "prepare_moments_codes": None,
         "ndf_field": {"bound": "mfma", "achieved": 2.0 * NDF_MAC * V / (med["ndf_field"] * 1e-3)
                       / 1e12, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s"},

@@ -956,11 +956,11 @@ void forward(const ndf_net_config *c, const NetOffsets &o, const float *P, const
 
 // ========================================================== fused step ====
 // The step of a network with one encoder shared by both endpoints (the
-// symmetric pair encoding of Sec. 4.1) runs in four kernels after a packing one: a forward kernel
-// (grid gather, encoder for both endpoints, latent product, decoder, head, the
+// symmetric pair encoding of Sec. 4.1) runs in these kernels after a packing one: a forward
+// kernel (grid gather, encoder for both endpoints, latent product, decoder, head, the
 // L1 loss and its gradient), a backward kernel (the data adjoint from the head
-// back to dL/dh0), the grid scatter (grid_bwd_kernel) and one kernel for every
-// weight and bias gradient.  A wave takes 32 pairs: the first endpoints are
+// back to dL/dh0), the grid scatter (grid_bwd_kernel, or grid_tile_kernel after a sort)
+// and one kernel for every weight and bias gradient.  A wave takes 32 pairs: the first endpoints are
 // MFMA column block q = 0, the second endpoints q = 1, so both share every
 // weight fragment and the latent product is register-local; the decoder runs
 // on the pair rows (q = 0).
