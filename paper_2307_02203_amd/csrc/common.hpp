@@ -65,11 +65,6 @@ __device__ __forceinline__ void data_cell(const float *p, int nx, int ny, int nz
     }
 }
 
-// Copies the host list ref_v[n_ref] of reference vertices into device memory dst
-// through kernel arguments (64 per launch) instead of a pageable host copy, which
-// would make the host wait for the stream; stream-ordered like any launch.
-int put_refs(const int64_t *ref_v, int n_ref, int64_t *dst, hipStream_t st);
-
 // Bytes at the start of a workspace that hold the int32 device status word
 // (NDF_OK, or NDF_E_NONFINITE once a call has met a non-finite input or loss).
 constexpr size_t kStatusBytes = 256;

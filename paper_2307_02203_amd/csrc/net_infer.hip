@@ -17,6 +17,8 @@
 // Latents are rounded to bf16 before the product, and the product of two bf16
 // numbers is exact in FP32, so Phi(p, q) and Phi(q, p) of a self field are
 // computed identically.
+#include <type_traits>
+
 #include "net.hpp"
 
 namespace ndf {
@@ -273,6 +275,17 @@ int launch_net_quantize(const ndf_net_config *c, const float *P, int prec, void 
 }
 
 // ------------------------------------------------------- fused kernel ----
+// The vertices of the latent mode (MODE 1), 256 per launch, as a kernel argument (a list in
+// device memory took a launch of its own, 5 us, in front of every call); the other modes
+// take the vertices or positions in order.
+constexpr int kLatRefs = 256;
+struct RefVerts {
+    int64_t v[kLatRefs];
+};
+struct NoVerts {};
+template <int MODE>
+using QueryList = std::conditional_t<MODE == 1, RefVerts, NoVerts>;
+
 struct InferArgs {
     const uint16_t *grid[kL];   // bf16 [cells][8] of the query encoder
     const bf16x8 *w[5];         // A fragments W1..W5
@@ -402,6 +415,14 @@ __device__ __forceinline__ void dense_layer(const bf16x8 *__restrict__ wf,
     }
 }
 
+template <int MODE>
+__device__ __forceinline__ int64_t query_vertex(const QueryList<MODE> &ql, int64_t n) {
+    if constexpr (MODE == 1)
+        return ql.v[n];
+    else
+        return n;
+}
+
 // Work of the field and latent kernels: workgroup b owns the contiguous tiles
 // [ntiles b / G, ntiles (b + 1) / G) (neighbouring tiles share grid corners in
 // L2), and its waves claim them one at a time from an LDS counter, so a wave that
@@ -429,7 +450,7 @@ __device__ __forceinline__ void await_flag(int *flag) {
 }
 
 // MODE 0: field (out[v] = Phi(ref, v) for v < nq); MODE 1: latents of the
-// vertices in qlist (lat_out[n][128], bf16-rounded values stored as FP32);
+// vertices in ql (lat_out[n][128], bf16-rounded values stored as FP32);
 // MODE 2: latents of vertices 0 .. nq-1 into the query-latent cache (out);
 // MODE 3: field at the continuous positions qpos[n][3] in [-1, 1]^3.
 // HASH: some grid level is a hash table (compiled out when every level is dense).
@@ -468,7 +489,7 @@ __device__ __forceinline__ void wave_max_into(const bf16x8 (&v)[8][2], const boo
 // s_w[3]; field modes only, shared grid or separate grids alike.
 template <int MODE, bool HASH, bool SEP = false, bool GO = false, bool FF = false>
 __global__ __launch_bounds__(kInferThreads) void infer_kernel(InferArgs A,
-                                                              const int64_t *__restrict__ qlist,
+                                                              const QueryList<MODE> ql,
                                                               int64_t nq,
                                                               const float *__restrict__ ref_lat,
                                                               float *__restrict__ out,
@@ -609,7 +630,7 @@ __global__ __launch_bounds__(kInferThreads) void infer_kernel(InferArgs A,
             const int64_t n = row0 + q * 32 + jl;
             ok[q] = n < nq;
             vq[q] = ok[q] && MODE != 3 ? (MODE == 4 ? cal_vertex(n, nq, A.V)
-                                                    : (qlist ? qlist[n] : n))
+                                                    : query_vertex<MODE>(ql, n))
                                       : 0;
 #pragma unroll
             for (int a = 0; a < 3; ++a) pq[q][a] = MODE == 3 && ok[q] ? qpos[3 * n + a] : 0.f;
@@ -929,10 +950,10 @@ __device__ __forceinline__ void dense_layer_fp8(
 }
 
 // MODE 0: field (out[v] = Phi(ref, v)); MODE 1: latents of the vertices in
-// qlist (FP32); MODE 3: field at the continuous positions qpos[n][3].
+// ql (FP32); MODE 3: field at the continuous positions qpos[n][3].
 template <int MODE, bool HASH, bool FF = false>
 __global__ __launch_bounds__(kInferThreads) void infer_fp8_kernel(InferArgs8 A,
-                                                                  const int64_t *__restrict__ qlist,
+                                                                  const QueryList<MODE> ql,
                                                                   int64_t nq,
                                                                   const float *__restrict__ ref_lat,
                                                                   float *__restrict__ out,
@@ -1046,7 +1067,7 @@ __global__ __launch_bounds__(kInferThreads) void infer_fp8_kernel(InferArgs8 A,
         for (int q = 0; q < 2; ++q) {
             const int64_t n = row0 + q * 32 + jl;
             ok[q] = n < nq;
-            vq[q] = ok[q] && MODE != 3 ? (qlist ? qlist[n] : n) : 0;
+            vq[q] = ok[q] && MODE != 3 ? query_vertex<MODE>(ql, n) : 0;
 #pragma unroll
             for (int a = 0; a < 3; ++a) pq[q][a] = MODE == 3 && ok[q] ? qpos[3 * n + a] : 0.f;
         }
@@ -1502,7 +1523,7 @@ static bool any_hashed(const ndf_net_config *c) {
 // queries spread evenly over the grid), run through the BF16 layers.
 template <int MODE>
 static void run_infer(const ndf_net_config *c, bool sep, dim3 g, const InferArgs &a,
-                      const int64_t *ql, int64_t nq, const float *rl, float *out,
+                      const QueryList<MODE> &ql, int64_t nq, const float *rl, float *out,
                       const float *qpos, hipStream_t st);
 
 static void launch_calibrate(const ndf_net_config *c, const QLayout &q, char *Q, hipStream_t st) {
@@ -1510,7 +1531,7 @@ static void launch_calibrate(const ndf_net_config *c, const QLayout &q, char *Q,
     hipLaunchKernelGGL(zero_i32_kernel, dim3(1), dim3(64), 0, st, amax, 4);
     const InferArgs a = fused_args(c, q, Q, 0);
     const dim3 g(kCalRefs);
-    run_infer<4>(c, c->n_enc == 2, g, a, nullptr, (int64_t)kCalQueries, nullptr, (float *)amax,
+    run_infer<4>(c, c->n_enc == 2, g, a, {}, (int64_t)kCalQueries, nullptr, (float *)amax,
                  nullptr, st);
 }
 
@@ -1533,7 +1554,7 @@ size_t net_latent_cache_bytes(const ndf_net_config *c) {
 // whose reference latent comes from encoder 0) and input embedding.
 template <int MODE>
 static void run_infer(const ndf_net_config *c, bool sep, dim3 g, const InferArgs &a,
-                      const int64_t *ql, int64_t nq, const float *rl, float *out,
+                      const QueryList<MODE> &ql, int64_t nq, const float *rl, float *out,
                       const float *qpos, hipStream_t st) {
     const dim3 b(kInferThreads);
     const bool hash = any_hashed(c);
@@ -1557,9 +1578,9 @@ static void run_infer(const ndf_net_config *c, bool sep, dim3 g, const InferArgs
 }
 
 template <int MODE>
-static void run_infer8(const ndf_net_config *c, dim3 g, const InferArgs8 &a, const int64_t *ql,
-                       int64_t nq, const float *rl, float *out, const float *qpos,
-                       hipStream_t st) {
+static void run_infer8(const ndf_net_config *c, dim3 g, const InferArgs8 &a,
+                       const QueryList<MODE> &ql, int64_t nq, const float *rl, float *out,
+                       const float *qpos, hipStream_t st) {
     const dim3 b(kInferThreads);
     const bool hash = any_hashed(c);
 #define NDF_IK8(H, F) \
@@ -1577,7 +1598,7 @@ static void run_infer8(const ndf_net_config *c, dim3 g, const InferArgs8 &a, con
 int launch_infer_latents(const ndf_net_config *c, const void *qp, void *cache, hipStream_t st) {
     const QLayout q = qlayout(c);
     const InferArgs a = make_args(c, q, (const char *)qp, c->n_enc - 1);
-    run_infer<2>(c, false, dim3(infer_blocks(a.V)), a, nullptr, a.V, nullptr, (float *)cache,
+    run_infer<2>(c, false, dim3(infer_blocks(a.V)), a, {}, a.V, nullptr, (float *)cache,
                  nullptr, st);
     return status_of_launch();
 }
@@ -1596,11 +1617,32 @@ static void decode_cached(const ndf_net_config *c, const QLayout &q, const char 
     }
 }
 
-// Reference latents lat[n][128] of the vertices refs[n] (device) with encoder 0.
+// Reference latents lat[n_ref][128] of the vertices ref_v[n_ref] (host) with encoder 0:
+// run(list, count, latents) per kLatRefs of them.
+template <typename F>
+static void each_ref_list(const int64_t *ref_v, int n_ref, float *lat, F run) {
+    for (int r0 = 0; r0 < n_ref; r0 += kLatRefs) {
+        const int n = n_ref - r0 < kLatRefs ? n_ref - r0 : kLatRefs;
+        RefVerts list{};
+        for (int i = 0; i < n; ++i) list.v[i] = ref_v[r0 + i];
+        run(list, n, lat + (int64_t)r0 * kH);
+    }
+}
+
 static void ref_latents(const ndf_net_config *c, const QLayout &q, const char *Q,
-                        const int64_t *refs, int n, float *lat, hipStream_t st) {
+                        const int64_t *ref_v, int n_ref, float *lat, hipStream_t st) {
     const InferArgs a0 = make_args(c, q, Q, 0);
-    run_infer<1>(c, false, dim3(infer_blocks(n)), a0, refs, (int64_t)n, nullptr, lat, nullptr, st);
+    each_ref_list(ref_v, n_ref, lat, [&](const RefVerts &list, int n, float *l) {
+        run_infer<1>(c, false, dim3(infer_blocks(n)), a0, list, (int64_t)n, nullptr, l, nullptr, st);
+    });
+}
+
+static void ref_latents8(const ndf_net_config *c, const QLayout &q, const char *Q,
+                         const int64_t *ref_v, int n_ref, float *lat, hipStream_t st) {
+    const InferArgs8 a0 = make_args8(c, q, Q, 0);
+    each_ref_list(ref_v, n_ref, lat, [&](const RefVerts &list, int n, float *l) {
+        run_infer8<1>(c, dim3(infer_blocks(n)), a0, list, (int64_t)n, nullptr, l, nullptr, st);
+    });
 }
 
 int launch_infer_field_cached(const ndf_net_config *c, const void *qp, const int64_t *ref_v,
@@ -1608,9 +1650,7 @@ int launch_infer_field_cached(const ndf_net_config *c, const void *qp, const int
     const QLayout q = qlayout(c);
     const char *Q = (const char *)qp;
     float *lat = (float *)ws;
-    int64_t *refs = (int64_t *)((char *)ws + align_up((size_t)n_ref * kH * sizeof(float), 256));
-    if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
-    ref_latents(c, q, Q, refs, n_ref, lat, st);
+    ref_latents(c, q, Q, ref_v, n_ref, lat, st);
     decode_cached(c, q, Q, cache, lat, n_ref, out, st);
     return status_of_launch();
 }
@@ -1622,21 +1662,19 @@ int launch_infer_field(const ndf_net_config *c, const void *qp, int prec, const 
     const QLayout q = qlayout(c);
     const char *Q = (const char *)qp;
     float *lat = (float *)ws;
-    int64_t *refs = (int64_t *)((char *)ws + align_up((size_t)n_ref * kH * sizeof(float), 256));
     const int64_t V = (int64_t)c->nx * c->ny * c->nz;
     if (prec == NDF_PREC_FP8_E4M3 && n_ref >= 2 && !c->grid_only) {
         // the BF16 query latents once into the workspace, then every reference's
         // decoder in E4M3, kMultiRefs references per pass over the cache
-        if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
         void *cache = (char *)ws + net_infer_lat_ws_bytes(n_ref);
-        ref_latents(c, q, Q, refs, n_ref, lat, st);
+        ref_latents(c, q, Q, ref_v, n_ref, lat, st);
         if (launch_infer_latents(c, qp, cache, st) != NDF_OK) return NDF_E_HIP;
         const InferArgs8 a8 = make_args8(c, q, Q, c->n_enc - 1);
         for (int r0 = 0; r0 < n_ref; r0 += kMultiRefs) {
             const int n = n_ref - r0 < kMultiRefs ? n_ref - r0 : kMultiRefs;
             hipLaunchKernelGGL(infer_cached_fp8_kernel, dim3(infer_blocks(V, n)),
-                               dim3(kInferThreads), 0, st, a8, (const u32x4 *)cache, V, lat + (int64_t)r0 * kH, n,
-                               out + (int64_t)r0 * V, V);
+                               dim3(kInferThreads), 0, st, a8, (const u32x4 *)cache, V,
+                               lat + (int64_t)r0 * kH, n, out + (int64_t)r0 * V, V);
         }
         return status_of_launch();
     }
@@ -1645,7 +1683,7 @@ int launch_infer_field(const ndf_net_config *c, const void *qp, int prec, const 
         InferArgs8 a = make_args8(c, q, Q, 0);
         for (int r = 0; r < n_ref; ++r) {
             a.fuse_ref = ref_v[r];
-            run_infer8<0>(c, dim3(infer_blocks(V)), a, nullptr, V, nullptr, out + (int64_t)r * V,
+            run_infer8<0>(c, dim3(infer_blocks(V)), a, {}, V, nullptr, out + (int64_t)r * V,
                           nullptr, st);
         }
         return status_of_launch();
@@ -1660,7 +1698,7 @@ int launch_infer_field(const ndf_net_config *c, const void *qp, int prec, const 
             const dim3 g(infer_blocks(a.V)), b(kInferThreads);
             float *o = out + (int64_t)r * a.V;
 #define NDF_GO_FIELD(H, S) \
-    hipLaunchKernelGGL((infer_kernel<0, H, S, true>), g, b, 0, st, a, nullptr, a.V, nullptr, o, nullptr)
+    hipLaunchKernelGGL((infer_kernel<0, H, S, true>), g, b, 0, st, a, NoVerts{}, a.V, nullptr, o, nullptr)
             if (hash && sep) NDF_GO_FIELD(true, true);
             else if (hash) NDF_GO_FIELD(true, false);
             else if (sep) NDF_GO_FIELD(false, true);
@@ -1673,9 +1711,8 @@ int launch_infer_field(const ndf_net_config *c, const void *qp, int prec, const 
         // the query latents once into the workspace, then every reference decoded
         // from them, kMultiRefs references per pass over the cache (bit for bit
         // the fused single-reference field)
-        if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
         void *cache = (char *)ws + net_infer_lat_ws_bytes(n_ref);
-        ref_latents(c, q, Q, refs, n_ref, lat, st);
+        ref_latents(c, q, Q, ref_v, n_ref, lat, st);
         if (launch_infer_latents(c, qp, cache, st) != NDF_OK) return NDF_E_HIP;
         decode_cached(c, q, Q, cache, lat, n_ref, out, st);
         return status_of_launch();
@@ -1685,19 +1722,17 @@ int launch_infer_field(const ndf_net_config *c, const void *qp, int prec, const 
         const bool sep = c->n_enc == 2;
         for (int r = 0; r < n_ref; ++r) {
             const InferArgs a = fused_args(c, q, Q, ref_v[r]);
-            run_infer<0>(c, sep, dim3(infer_blocks(a.V)), a, nullptr, a.V, nullptr,
+            run_infer<0>(c, sep, dim3(infer_blocks(a.V)), a, {}, a.V, nullptr,
                          out + (int64_t)r * a.V, nullptr, st);
         }
         return status_of_launch();
     }
     // FP8 with two encoders: reference latents with encoder 0 (p1), then one pass
     // per reference with the query encoder (p2)
-    if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
-    const InferArgs8 a0 = make_args8(c, q, Q, 0);
-    run_infer8<1>(c, dim3(infer_blocks(n_ref)), a0, refs, (int64_t)n_ref, nullptr, lat, nullptr, st);
+    ref_latents8(c, q, Q, ref_v, n_ref, lat, st);
     const InferArgs8 a1 = make_args8(c, q, Q, c->n_enc - 1);
     for (int r = 0; r < n_ref; ++r)
-        run_infer8<0>(c, dim3(infer_blocks(V)), a1, nullptr, V, lat + (int64_t)r * kH,
+        run_infer8<0>(c, dim3(infer_blocks(V)), a1, {}, V, lat + (int64_t)r * kH,
                       out + (int64_t)r * V, nullptr, st);
     return status_of_launch();
 }
@@ -1710,7 +1745,6 @@ int launch_infer_points(const ndf_net_config *c, const void *qp, int prec, const
     const QLayout q = qlayout(c);
     const char *Q = (const char *)qp;
     float *lat = (float *)ws;
-    int64_t *refs = (int64_t *)((char *)ws + align_up((size_t)n_ref * kH * sizeof(float), 256));
     if (c->grid_only) {  // BF16, one fused pass per reference
         if (prec != NDF_PREC_BF16) return NDF_E_UNSUPPORTED;
         const bool sep = c->n_enc == 2;
@@ -1719,7 +1753,7 @@ int launch_infer_points(const ndf_net_config *c, const void *qp, int prec, const
             const dim3 g(infer_blocks(n)), b(kInferThreads);
             float *o = out + (int64_t)r * n;
 #define NDF_GO_POINTS(H, S) \
-    hipLaunchKernelGGL((infer_kernel<3, H, S, true>), g, b, 0, st, a, nullptr, n, nullptr, o, pos)
+    hipLaunchKernelGGL((infer_kernel<3, H, S, true>), g, b, 0, st, a, NoVerts{}, n, nullptr, o, pos)
             if (hash && sep) NDF_GO_POINTS(true, true);
             else if (hash) NDF_GO_POINTS(true, false);
             else if (sep) NDF_GO_POINTS(false, true);
@@ -1733,33 +1767,30 @@ int launch_infer_points(const ndf_net_config *c, const void *qp, int prec, const
             InferArgs8 a = make_args8(c, q, Q, 0);
             for (int r = 0; r < n_ref; ++r) {
                 a.fuse_ref = ref_v[r];
-                run_infer8<3>(c, dim3(infer_blocks(n)), a, nullptr, n, nullptr,
+                run_infer8<3>(c, dim3(infer_blocks(n)), a, {}, n, nullptr,
                               out + (int64_t)r * n, pos, st);
             }
         } else {
             for (int r = 0; r < n_ref; ++r) {
                 const InferArgs a = fused_args(c, q, Q, ref_v[r]);
-                run_infer<3>(c, false, dim3(infer_blocks(n)), a, nullptr, n, nullptr,
+                run_infer<3>(c, false, dim3(infer_blocks(n)), a, {}, n, nullptr,
                              out + (int64_t)r * n, pos, st);
             }
         }
         return status_of_launch();
     }
-    if (put_refs(ref_v, n_ref, refs, st) != NDF_OK) return NDF_E_HIP;
     if (prec == NDF_PREC_FP8_E4M3) {
-        const InferArgs8 a0 = make_args8(c, q, Q, 0);
-        run_infer8<1>(c, dim3(infer_blocks(n_ref)), a0, refs, (int64_t)n_ref, nullptr, lat, nullptr,
-                      st);
+        ref_latents8(c, q, Q, ref_v, n_ref, lat, st);
         const InferArgs8 a1 = make_args8(c, q, Q, c->n_enc - 1);
         for (int r = 0; r < n_ref; ++r)
-            run_infer8<3>(c, dim3(infer_blocks(n)), a1, nullptr, n, lat + (int64_t)r * kH,
+            run_infer8<3>(c, dim3(infer_blocks(n)), a1, {}, n, lat + (int64_t)r * kH,
                           out + (int64_t)r * n, pos, st);
         return status_of_launch();
     }
-    ref_latents(c, q, Q, refs, n_ref, lat, st);
+    ref_latents(c, q, Q, ref_v, n_ref, lat, st);
     const InferArgs a1 = make_args(c, q, Q, c->n_enc - 1);
     for (int r = 0; r < n_ref; ++r)
-        run_infer<3>(c, false, dim3(infer_blocks(n)), a1, nullptr, n, lat + (int64_t)r * kH,
+        run_infer<3>(c, false, dim3(infer_blocks(n)), a1, {}, n, lat + (int64_t)r * kH,
                      out + (int64_t)r * n, pos, st);
     return status_of_launch();
 }
@@ -1769,11 +1800,8 @@ int launch_infer_difference(const ndf_net_config *c, const void *qp, int64_t ref
     const QLayout q = qlayout(c);
     const char *Q = (const char *)qp;
     float *lat = (float *)ws;
-    int64_t *refs = (int64_t *)((char *)ws + align_up((size_t)2 * kH * sizeof(float), 256));
     const int64_t both[2] = {ref_a, ref_b};
-    if (put_refs(both, 2, refs, st) != NDF_OK) return NDF_E_HIP;
-    const InferArgs a0 = make_args(c, q, Q, 0);
-    run_infer<1>(c, false, dim3(1), a0, refs, (int64_t)2, nullptr, lat, nullptr, st);
+    ref_latents(c, q, Q, both, 2, lat, st);
     const InferArgs a1 = make_args(c, q, Q, c->n_enc - 1);
     hipLaunchKernelGGL(infer_cached_kernel<true>, dim3(infer_blocks(a1.V)), dim3(kInferThreads), 0,
                        st, a1, (const u32x4 *)cache, a1.V, lat, 2, out, a1.V);
