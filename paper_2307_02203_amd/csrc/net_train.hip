@@ -191,7 +191,7 @@ constexpr int kSortWgs = 64;        // workgroups (row ranges) of the sort
 constexpr int kSortThreads = 1024;
 constexpr int kMaxTiles = 4096;     // tiles of all encoders
 constexpr int64_t kMinSorted = 4096;  // rows below which the sort's launches cost more
-constexpr size_t kTileLds = 70 * 1024;  // boxes of a tile (two workgroups per CU)
+constexpr size_t kTileLds = 55 * 1024;  // boxes of a tile; with the stages 64 KB of LDS
 
 struct TilePlan {
     int t[3];             // tile edges in data-grid vertices
@@ -432,6 +432,7 @@ struct TileStage {
     f32x4 row[kBatch];   // entry of the box (int bits), fractions
     float d[kBatch][kF];
 };
+static_assert(kTileLds + (kL - 1) * sizeof(TileStage) <= 64 * 1024, "LDS of a launch");
 
 template <bool POS>
 __global__ __launch_bounds__(64 * kL) void grid_tile_kernel(
