@@ -1892,7 +1892,7 @@ __device__ __forceinline__ void write4(const u32x4 (&c)[4], int kb, int h, int r
 // columns 64 (w / 4) .. + 63 (two 32-column blocks).  Threads t < 256 stage G
 // (the head: t < 64 stage gy), t >= 256 stage X, four rows of one 8-feature
 // block each; the next slab pair's loads are in flight while the MFMAs run.
-__global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
+__global__ __launch_bounds__(512, 4) void wgrad_all_kernel(WgradArgs A) {
     __shared__ __attribute__((aligned(16))) __bf16 s_g[kH * kWgLD];
     __shared__ __attribute__((aligned(16))) __bf16 s_x[kH * kWgLD];
     __shared__ float s_gy[64];
@@ -1942,13 +1942,14 @@ __global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
         __syncthreads();
         if (2 * (sp + nparts) < nslab) fetch(sp + nparts);
         if (head) {
-            // dw6[k] = sum_rows gy d2[row][k] (thread k), db6 = sum_rows gy (thread 128)
+            // dw6[k] = sum_rows gy d2[row][k] (thread k), db6 = sum_rows gy (thread kH + row:
+            // equal addends round alike, so one thread over all rows was 1e-5 off)
             if (tid < kH) {
                 const __bf16 *xr = s_x + tid * kWgLD;
 #pragma unroll 8
                 for (int r = 0; r < 64; ++r) bsum = fmaf(s_gy[r], (float)xr[r], bsum);
-            } else if (tid == kH) {
-                for (int r = 0; r < 64; ++r) bsum += s_gy[r];
+            } else if (wave == 2) {
+                bsum += s_gy[lane];
             }
         } else {
             if (cb0 < xcb) {
@@ -1979,7 +1980,11 @@ __global__ __launch_bounds__(512) void wgrad_all_kernel(WgradArgs A) {
     }
     if (head) {
         if (tid < kH) unsafeAtomicAdd(A.dW[L] + tid, bsum);
-        else if (tid == kH) unsafeAtomicAdd(A.db[L], bsum);
+        if (wave == 2) {
+#pragma unroll
+            for (int d = 32; d; d >>= 1) bsum += __shfl_xor(bsum, d);
+            if (lane == 0) unsafeAtomicAdd(A.db[L], bsum);
+        }
         return;
     }
 #pragma unroll
