@@ -599,7 +599,8 @@ def _ksg_roofline(ms, N, V):
 # kernel sources; reported only while every source still matches.
 _PMC_TRAFFIC = {
     "ksg_field": ("profiles/pmc_ksg_field_paper_1760000v_1000m.txt",
-                  ["paper_2307_02203_amd/csrc/ksg.hip"]),
+                  ["paper_2307_02203_amd/csrc/ksg.hip",
+                   "paper_2307_02203_amd/csrc/ksg_lists.hpp"]),
     "ndf_field": ("profiles/pmc_infer_bf16_paper_1760000v.txt",
                   ["paper_2307_02203_amd/csrc/net_infer.hip",
                    "paper_2307_02203_amd/csrc/net.hpp"]),

@@ -31,6 +31,7 @@
 //    evaluation bit for bit; the harmonic sum is FP64.
 #include <type_traits>
 
+#include "ksg_lists.hpp"
 #include "order.hpp"
 
 namespace ndf {
@@ -179,12 +180,6 @@ __device__ __forceinline__ void marginal_counts(const int *xs, const int *ys, co
     ny = pos[2] - pos[3] - 1;
 }
 
-constexpr int kPad = 4;             // sentinel samples on each side of a list
-constexpr int kFar = 1 << 29;       // sentinel code: its distance to any sample exceeds kUnset
-constexpr int kUnset = (1 << 24) - 32;  // k-th distance before k samples are seen: above any
-                                    // code difference (<= 2^23), below any sentinel distance,
-                                    // and the greatest list distance of a walk start
-
 // v_med3_i32: the middle of three signed integers.  With lo <= hi it is d
 // clamped to [lo, hi] in one instruction (the compiler forms it only for
 // constant bounds).  Operands are plain VALU results, so the asm needs no wait
@@ -212,9 +207,7 @@ __device__ __forceinline__ void insert_k(int (&best)[K], int d) {
     best[0] = min(best[0], d);
 }
 
-// LDS of one pair.  The lists of the neighbour search live in `lists`: the x order's
-// two lists, then the y order's, each list between kPad sentinels,
-//   [pad | list 0: N / 2 | pad | pad | list 1: N - N / 2 | pad]   = N + 16 entries,
+// LDS of one pair.  The lists of the neighbour search live in `lists` (ksg_lists.hpp),
 // entry = (walked coordinate, other coordinate).  Before the lists are written the
 // region serves as scratch, and after the walks as the sorted codes xs[N], ys[N] of
 // the counts (from its second word on).
@@ -222,18 +215,16 @@ struct PairLds {
     int2 *lists;
     int *eps;         // [N] y codes in y order, then walk starts, then k-th distances
     uint16_t *yrank;  // [N] y rank of x-order sample p
-    uint16_t *other;  // [N] sample p's entry in the y order's lists, then its place in the
+    uint16_t *other;  // [N] sample p's place in the y order's lists, then its place in the
                       // other list of its walk
     uint16_t *Tx, *Ty;
     uint16_t *perm;   // [N] members of the x order, where they are not stored (pairs mode)
 };
 
-constexpr int list_entries(int N) { return N + 4 * kPad; }
-
 // The bytes of `lists`: both orders' lists, or the exchange buffer of the sort.
 template <int W>
 __host__ __device__ inline size_t lists_bytes(int N) {
-    const size_t l = (size_t)2 * (N + 4 * kPad) * 8, x = (size_t)Pair<W>::kMax * 8;
+    const size_t l = (size_t)2 * list_entries(N) * 8, x = (size_t)Pair<W>::kMax * 8;
     return l > x ? l : x;
 }
 template <int W>
@@ -259,12 +250,6 @@ __device__ __forceinline__ PairLds pair_lds(void *raw, int N) {
 struct Samples {
     int x[kPer], sx[kPer], y[kPer], xj[kPer], pj[kPer];
 };
-
-// Entry of the sample of rank r in its order's lists, q1 of the ranks below r being in
-// list 1 (clamped into the list, so that even unprepared orders stay in bounds).
-__device__ __forceinline__ int list_place(bool up, int r, int q1, int n0, int n1) {
-    return up ? kPad + n0 + 2 * kPad + min(q1, n1 - 1) : kPad + min(max(r - q1, 0), n0 - 1);
-}
 
 constexpr int kSpread = 16;  // the spread of a sample's 2 kSpread nearest codes predicts its
                              // walk's strip (4 % fewer steps than with the k nearest)
@@ -317,8 +302,7 @@ constexpr int kRefill = 16;  // idle lanes that start new walks together
 // reads a block of sentinels, so reads stay within the lists.  A step has no branch:
 // a lane whose walk is over reads sentinels on both sides, which change nothing, and
 // which lanes still walk is a ballot of two comparisons, so the bookkeeping is scalar.
-// Walk start of a sample: entry of `lists` (13 bits) | the distance to the other list
-// in units of 32, rounded down (a list visited for nothing changes no result).
+// Where a walk starts and ends, and why it cannot leave the lists: ksg_lists.hpp.
 // Count phase: thread t takes samples t, t + kT, ... and counts the marginals
 // by bucket table and binary search; the partial sums are combined in a fixed
 // order, so the FP64 total is reproducible.
@@ -335,7 +319,6 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n0 = N / 2, n1 = N - n0;
     const int LY = list_entries(N);    // first entry of the y order's lists
-    const int H1 = n0 + 2 * kPad;      // a second list's offset from the first
 
     // y codes in y order, y ranks, halves of the y order
     uint64_t my[kPer];
@@ -368,7 +351,7 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
         const int q1 = __builtin_amdgcn_readlane(py, i * W + wave) + mask_below(my[i]);
         if (p < N) {  // here p is a rank of the y order
             const int at = LY + list_place(s.pj[i] >= n0, p, q1, n0, n1);
-            S.lists[at] = make_int2(s.y[i], s.xj[i]);
+            S.lists[kPad + at] = make_int2(s.y[i], s.xj[i]);
             S.other[s.pj[i]] = (uint16_t)at;
         }
         jr[i] = p < N ? min((int)S.yrank[p], N - 1) : 0;
@@ -390,25 +373,23 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
         if (p < N) {
             const bool up = jr[i] >= n0;
             const int at = list_place(up, p, q1, n0, n1);
-            S.lists[at] = make_int2(s.x[i], yv[i]);
-            // own entry + entry of the other list = first entries of both + rank
-            int start = at, sum = 2 * kPad + H1 + p;
+            S.lists[kPad + at] = make_int2(s.x[i], yv[i]);
+            int start = at, sum = place_sum(0, n0, p);
             int gap = up ? yv[i] - s_edge[2] : s_edge[3] - yv[i];
             if (in_y >> i & 1) {
                 start = S.other[p];
-                sum = 2 * (LY + kPad) + H1 + jr[i];
+                sum = place_sum(LY, n0, jr[i]);
                 gap = p >= n0 ? s.x[i] - s_edge[0] : s_edge[1] - s.x[i];
             }
-            S.other[p] = (uint16_t)min(max(sum - start, kPad), LY + LY - kPad);
-            S.eps[p] = (int)((uint32_t)start | (uint32_t)max(gap, 0) >> 5 << 13);
+            S.other[p] = (uint16_t)walk_other(sum - start, LY);
+            S.eps[p] = (int)pack_start(start, gap);
         }
     }
     if (tid < 8 * kPad) {
         // pads 0..3 of each order: left and right of the two lists
         const int pad = (tid >> 2) & 3, u = tid & 3;
-        const int at = (tid >= 4 * kPad ? LY : 0) + u +
-                       (pad == 0 ? 0 : pad == 1 ? kPad + n0 : pad == 2 ? H1 : H1 + kPad + n1);
-        S.lists[at] = make_int2(pad & 1 ? kFar : -kFar, 0);
+        const int at = pad_place(pad, tid >= 4 * kPad ? LY : 0, n0, n1) + u;
+        S.lists[at] = make_int2(pad_code(pad), 0);
     }
     if (wave == 0) tab_scan<W>(S.Ty);
     if (build_tx && wave == (W > 1 ? 1 : 0)) tab_scan<W>(S.Tx);
@@ -418,7 +399,7 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
     typedef __attribute__((address_space(3))) const i32x2 lds_int2;
     lds_int2 *const base = (lds_int2 *)reinterpret_cast<i32x2 *>(S.lists);
     lds_int2 *const endL = base;                  // four sentinels: a finished left side
-    lds_int2 *const endR = base + H1 + kPad + n1; // ... and right side
+    lds_int2 *const endR = base + pad_place(3, 0, n0, n1);  // ... and right side
     const int nchunks = (N + 63) >> 6;
     const int mine = 64 * ((nchunks - wave + W - 1) / W);  // this wave's share, whole chunks
     // first sample of the wave's ci-th chunk, from the middle outwards; the partial
@@ -444,9 +425,10 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
         if (__builtin_amdgcn_inverse_ballot_w64(got)) {
             p = np;
             const uint32_t info = (uint32_t)S.eps[p];
-            lds_int2 *at = base + (info & 0x1fff);
-            gap = (int)(info >> 13 << 5);
+            lds_int2 *at = base + kPad + walk_place(start_place(info), LY);
+            gap = start_gap(info);
             me = *at;
+            me.x = walk_code(me.x);
             L = at - 4;
             R = at + 1;
 #pragma unroll
@@ -462,7 +444,7 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
             // nearer to the other list than to the k-th neighbour: go on there
             const uint64_t more = fin & __ballot(gap < best[K - 1]);
             if (__builtin_amdgcn_inverse_ballot_w64(more)) {
-                R = base + S.other[p];
+                R = base + kPad + S.other[p];
                 L = R - 4;
                 gap = kUnset;  // no third list
             }

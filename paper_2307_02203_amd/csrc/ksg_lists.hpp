@@ -1,0 +1,76 @@
+// Layout of the neighbour search's lists and the bounds of a walk over them (ksg.hip), in
+// plain C++ so that a host program can run the same arithmetic.
+//
+// A pair's lists are the x order's two, then the y order's two, each list between kPad
+// sentinels:
+//   [pad | list 0: n0 = N / 2 | pad | pad | list 1: n1 = N - n0 | pad] = list_entries(N)
+// entries per order.  A walk reads blocks of kPad entries outwards, a side at a time, and
+// goes on while the farthest one of its block is nearer than the k-th distance, which is at
+// most kUnset.  The blocks of a side are kPad apart, so exactly one of them has its farthest
+// entry in the outermost sentinels of its side; a code in [0, 2^23] is at least kUnset away
+// from those, so the walk ends there at the latest, with every read inside the region, for
+// any place that walk_place or walk_other returns and whatever the entries between hold.
+#pragma once
+#include <stdint.h>
+
+namespace ndf {
+
+constexpr int kPad = 4;             // sentinel samples on each side of a list
+constexpr int kFar = 1 << 29;       // sentinel code: its distance to any sample exceeds kUnset
+constexpr int kUnset = (1 << 24) - 32;  // k-th distance before k samples are seen: above any
+                                    // code difference (<= 2^23), below any sentinel distance,
+                                    // and the greatest list distance of a walk start
+constexpr int kTopCode = 1 << 23;   // codes lie in [0, kTopCode]
+static_assert(kFar - kTopCode >= kUnset, "a sentinel ends a walk");
+
+__host__ __device__ constexpr int list_entries(int N) { return N + 4 * kPad; }
+__host__ __device__ constexpr int clamp_int(int v, int lo, int hi) {
+    return v < lo ? lo : v > hi ? hi : v;
+}
+
+// Places count entries from the first list's first.  Place of the sample of rank r in its
+// order's lists, q1 of the ranks below r being in list 1 (clamped into the list, so that
+// even unprepared orders stay in bounds).
+__host__ __device__ inline int list_place(bool up, int r, int q1, int n0, int n1) {
+    return up ? n0 + 2 * kPad + (q1 < n1 - 1 ? q1 : n1 - 1) : clamp_int(r - q1, 0, n0 - 1);
+}
+// A sample's place in one list plus the place where it would stand in the order's other
+// list, r samples of the order being below it; `first`: the order's first entry.
+__host__ __device__ constexpr int place_sum(int first, int n0, int r) {
+    return 2 * first + n0 + 2 * kPad + r;
+}
+
+// Pad `pad` (0..3: left and right of list 0, left and right of list 1) of an order that
+// starts at entry `first`: its first entry, and the sentinels' code.
+__host__ __device__ inline int pad_place(int pad, int first, int n0, int n1) {
+    return first + (pad == 0   ? 0
+                    : pad == 1 ? kPad + n0
+                    : pad == 2 ? n0 + 2 * kPad
+                               : n0 + 3 * kPad + n1);
+}
+__host__ __device__ inline int pad_code(int pad) { return pad & 1 ? kFar : -kFar; }
+
+// The place a walk starts at (its own sample's) and the one it goes on at in the other
+// list: no-ops on prepared orders.  In an order that is no permutation a sample without an
+// entry leaves what its word held before, which must not lead out of the lists (a negative
+// place is a large unsigned one).
+__host__ __device__ constexpr uint32_t min_u32(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__host__ __device__ constexpr int walk_place(uint32_t at, int entries) {
+    return (int)min_u32(at, (uint32_t)(2 * entries - 2 * kPad - 1));
+}
+__host__ __device__ constexpr int walk_other(int at, int entries) {
+    return (int)min_u32((uint32_t)at, (uint32_t)(2 * entries - 2 * kPad));
+}
+// The walked code of a walk's own sample: a no-op on a sample's entry, else in the range
+// from which every sentinel is far.
+__host__ __device__ constexpr int walk_code(int c) { return clamp_int(c, 0, kTopCode); }
+
+// A walk start as one word: place (13 bits) and the distance to the other list in units of
+// 32, rounded down (a list visited for nothing changes no result).
+__host__ __device__ constexpr uint32_t pack_start(int place, int gap) {
+    return (uint32_t)place | (uint32_t)(gap > 0 ? gap : 0) >> 5 << 13;
+}
+__host__ __device__ constexpr uint32_t start_place(uint32_t s) { return s & 0x1fff; }
+__host__ __device__ constexpr int start_gap(uint32_t s) { return (int)(s >> 13 << 5); }
+
+}  // namespace ndf
