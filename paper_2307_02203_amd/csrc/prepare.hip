@@ -31,6 +31,9 @@ namespace ndf {
 constexpr int kRegV = 32;        // vertices per workgroup: 128-byte row segments
 constexpr int kRegPh = 16;       // member phases
 constexpr int kRegThreads = kRegV * kRegPh;
+// Workgroups along x, the rest along z: a launch takes fewer than 2^32 threads per axis,
+// which 16 per vertex reach at 2^28 vertices.
+constexpr int64_t kRegGridX = 1 << 22;
 
 // Rows of the transpose tile: 16 J members of a vertex, padded by four words (the 32
 // vertices of a half wave fall into banks 4 apart).
@@ -78,7 +81,8 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
     const int var = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int vl = lane & 31, ph = 2 * wave + (lane >> 5);
-    const int64_t v0 = (int64_t)blockIdx.x * kRegV, v = v0 + vl;
+    const int64_t v0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * kRegV, v = v0 + vl;
+    if (v0 >= V) return;  // uniform: past the last tile of a grid with several z
     const float *col = x + (int64_t)var * N * V + (v < V ? v : V - 1);
 
     // every member once: NF whole rows of 16 members, and a row of the remaining ones
@@ -467,7 +471,9 @@ int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStre
     const int64_t V = (int64_t)e->nx * e->ny * e->nz;
     if (status) launch_status_clear(status, st);
     const int N = e->n_members;
-    const dim3 rg((unsigned)ceil_div(V, kRegV), (unsigned)e->n_vars);
+    const int64_t tiles = ceil_div(V, kRegV);
+    const dim3 rg((unsigned)(tiles < kRegGridX ? tiles : kRegGridX), (unsigned)e->n_vars,
+                  (unsigned)ceil_div(tiles, kRegGridX));
     // the fewest registers that hold a thread's members: waves in flight against loads
     // past the last member.  Up to 512 members the columns are sorted here too, from codes
     // kept in registers (450 members of 1.76M vertices 2.82 -> 2.62 ms, 250 members 1.40 ->
