@@ -270,7 +270,12 @@ int ndf_net_init(const ndf_net_config *cfg, float *params, float *opt_state, uin
  * atomic scatter into the grids).  pairs int64[B][2] (device), targets
  * float[B]; loss_out float[1] (device).  The workspace's status word becomes
  * NDF_E_NONFINITE when the loss is not finite (a NaN or infinite target or
- * output). */
+ * output).  Two encoders: besides ndf_workspace_bytes(NDF_OP_TRAIN, ...) the
+ * training and forward calls accept a workspace that holds the layers' rows
+ * alone, 7176 bytes per pair and 8 per 256 pairs (thirteen arrays and the status
+ * word, each rounded up to 256 bytes), which is less below 224 pairs; they then
+ * run layer by layer, three to six times slower, with the gradient of
+ * ndf_train_step right behind those bytes. */
 int ndf_net_grad(const ndf_net_config *cfg, const float *params, const int64_t *pairs,
                  const float *targets, int64_t B, float *grad_out, float *loss_out,
                  void *ws, size_t ws_bytes, void *stream);

@@ -268,9 +268,10 @@ int ndf_net_grad(const ndf_net_config *cfg, const float *params, const int64_t *
     int s = check_net_config(cfg);
     if (s != NDF_OK) return s;
     if (!params || !pairs || !targets || !grad_out || !loss_out || B < 1) return NDF_E_ARG;
-    if (!ws || ws_bytes < net_train_ws_bytes(cfg, B)) return NDF_E_WORKSPACE;
+    const size_t plan = net_train_plan_bytes(cfg, B, ws_bytes);
+    if (!ws || !plan) return NDF_E_WORKSPACE;
     return launch_net_grad(cfg, params, pairs, nullptr, targets, B, grad_out, loss_out, ws,
-                           S(stream));
+                           plan, S(stream));
 }
 
 int ndf_net_grad_at(const ndf_net_config *cfg, const float *params, const float *pos,
@@ -279,9 +280,10 @@ int ndf_net_grad_at(const ndf_net_config *cfg, const float *params, const float 
     int s = check_net_config(cfg);
     if (s != NDF_OK) return s;
     if (!params || !pos || !targets || !grad_out || !loss_out || B < 1) return NDF_E_ARG;
-    if (!ws || ws_bytes < net_train_ws_bytes(cfg, B)) return NDF_E_WORKSPACE;
+    const size_t plan = net_train_plan_bytes(cfg, B, ws_bytes);
+    if (!ws || !plan) return NDF_E_WORKSPACE;
     return launch_net_grad(cfg, params, nullptr, pos, targets, B, grad_out, loss_out, ws,
-                           S(stream));
+                           plan, S(stream));
 }
 
 int ndf_net_forward(const ndf_net_config *cfg, const float *params, const int64_t *pairs,
@@ -289,8 +291,9 @@ int ndf_net_forward(const ndf_net_config *cfg, const float *params, const int64_
     int s = check_net_config(cfg);
     if (s != NDF_OK) return s;
     if (!params || !pairs || !y || B < 1) return NDF_E_ARG;
-    if (!ws || ws_bytes < net_train_ws_bytes(cfg, B)) return NDF_E_WORKSPACE;
-    return launch_net_forward(cfg, params, pairs, nullptr, B, y, ws, S(stream));
+    const size_t plan = net_train_plan_bytes(cfg, B, ws_bytes);
+    if (!ws || !plan) return NDF_E_WORKSPACE;
+    return launch_net_forward(cfg, params, pairs, nullptr, B, y, ws, plan, S(stream));
 }
 
 int ndf_net_forward_at(const ndf_net_config *cfg, const float *params, const float *pos,
@@ -298,8 +301,9 @@ int ndf_net_forward_at(const ndf_net_config *cfg, const float *params, const flo
     int s = check_net_config(cfg);
     if (s != NDF_OK) return s;
     if (!params || !pos || !y || B < 1) return NDF_E_ARG;
-    if (!ws || ws_bytes < net_train_ws_bytes(cfg, B)) return NDF_E_WORKSPACE;
-    return launch_net_forward(cfg, params, nullptr, pos, B, y, ws, S(stream));
+    const size_t plan = net_train_plan_bytes(cfg, B, ws_bytes);
+    if (!ws || !plan) return NDF_E_WORKSPACE;
+    return launch_net_forward(cfg, params, nullptr, pos, B, y, ws, plan, S(stream));
 }
 
 int ndf_train_step(const ndf_net_config *cfg, float *params, float *opt_state, int64_t step,
@@ -310,11 +314,11 @@ int ndf_train_step(const ndf_net_config *cfg, float *params, float *opt_state, i
     if (!params || !opt_state || !pairs || !targets || !loss_out || B < 1 || step < 1 ||
         !(lr >= 0.f) || !isfinite(lr))
         return NDF_E_ARG;
-    const size_t pbytes = (size_t)net_offsets(cfg).total * sizeof(float);
-    if (!ws || ws_bytes < net_train_ws_bytes(cfg, B) + align_up(pbytes, 256))
-        return NDF_E_WORKSPACE;
-    float *grad = (float *)((char *)ws + net_train_ws_bytes(cfg, B));
-    s = launch_net_grad(cfg, params, pairs, nullptr, targets, B, grad, loss_out, ws, S(stream));
+    const size_t pbytes = align_up((size_t)net_offsets(cfg).total * sizeof(float), 256);
+    const size_t plan = ws_bytes < pbytes ? 0 : net_train_plan_bytes(cfg, B, ws_bytes - pbytes);
+    if (!ws || !plan) return NDF_E_WORKSPACE;
+    float *grad = (float *)((char *)ws + plan);
+    s = launch_net_grad(cfg, params, pairs, nullptr, targets, B, grad, loss_out, ws, plan, S(stream));
     if (s != NDF_OK) return s;
     return launch_adam(cfg, params, opt_state, grad, step, lr, (const int32_t *)ws, S(stream));
 }
@@ -327,11 +331,11 @@ int ndf_train_step_at(const ndf_net_config *cfg, float *params, float *opt_state
     if (!params || !opt_state || !pos || !targets || !loss_out || B < 1 || step < 1 ||
         !(lr >= 0.f) || !isfinite(lr))
         return NDF_E_ARG;
-    const size_t pbytes = (size_t)net_offsets(cfg).total * sizeof(float);
-    if (!ws || ws_bytes < net_train_ws_bytes(cfg, B) + align_up(pbytes, 256))
-        return NDF_E_WORKSPACE;
-    float *grad = (float *)((char *)ws + net_train_ws_bytes(cfg, B));
-    s = launch_net_grad(cfg, params, nullptr, pos, targets, B, grad, loss_out, ws, S(stream));
+    const size_t pbytes = align_up((size_t)net_offsets(cfg).total * sizeof(float), 256);
+    const size_t plan = ws_bytes < pbytes ? 0 : net_train_plan_bytes(cfg, B, ws_bytes - pbytes);
+    if (!ws || !plan) return NDF_E_WORKSPACE;
+    float *grad = (float *)((char *)ws + plan);
+    s = launch_net_grad(cfg, params, nullptr, pos, targets, B, grad, loss_out, ws, plan, S(stream));
     if (s != NDF_OK) return s;
     return launch_adam(cfg, params, opt_state, grad, step, lr, (const int32_t *)ws, S(stream));
 }

@@ -321,6 +321,9 @@ __device__ __forceinline__ void stage_lds(T *__restrict__ dst, const T *__restri
 }
 
 size_t net_train_ws_bytes(const ndf_net_config *c, int64_t B);
+// Bytes of a workspace of `avail` that a training call lays out: net_train_ws_bytes where
+// they are there, else (two encoders) the layer-by-layer rows, else 0 (too small).
+size_t net_train_plan_bytes(const ndf_net_config *c, int64_t B, size_t avail);
 size_t net_infer_ws_bytes(const ndf_net_config *c, int64_t n_ref, int prec);
 size_t net_infer_lat_ws_bytes(int64_t n_ref);
 size_t net_qparam_bytes(const ndf_net_config *c, int prec);
@@ -328,12 +331,13 @@ size_t net_qparam_bytes(const ndf_net_config *c, int prec);
 int launch_net_init(const ndf_net_config *c, float *params, float *opt, uint64_t seed,
                     hipStream_t st);
 // Rows come from vertex pairs int64[B][2] (pos null) or from continuous
-// position pairs float[B][2][3] in [-1, 1]^3 (pairs null).
+// position pairs float[B][2][3] in [-1, 1]^3 (pairs null).  plan: net_train_plan_bytes.
 int launch_net_grad(const ndf_net_config *c, const float *params, const int64_t *pairs,
                     const float *pos, const float *targets, int64_t B, float *grad, float *loss,
-                    void *ws, hipStream_t st);
+                    void *ws, size_t plan, hipStream_t st);
 int launch_net_forward(const ndf_net_config *c, const float *params, const int64_t *pairs,
-                       const float *pos, int64_t B, float *y, void *ws, hipStream_t st);
+                       const float *pos, int64_t B, float *y, void *ws, size_t plan,
+                       hipStream_t st);
 int launch_adam(const ndf_net_config *c, float *params, float *opt, const float *grad,
                 int64_t step, float lr, const int32_t *status, hipStream_t st);
 int launch_net_quantize(const ndf_net_config *c, const float *params, int prec, void *q,

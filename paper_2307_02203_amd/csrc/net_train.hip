@@ -10,10 +10,13 @@
 // and weights are rounded to bf16 as they enter the MFMA; latents, parameters, parameter
 // gradients and Adam moments are FP32.
 //
-// Networks with an encoder MLP run in the fused kernels below ("fused step").  A
-// grid-only network (no encoder MLP) runs row-wise, layer by layer: the R = 2B positions
-// (all first endpoints, then all second endpoints) go through the grid lookup, the two
-// feature rows of a pair are multiplied, and the decoder gives Phi:
+// Networks with an encoder MLP run in the fused kernels below ("fused step").  Two kinds of
+// call run row-wise, layer by layer: a grid-only network (no encoder MLP), and a
+// two-encoder network whose caller brings a workspace that is too small for the fused
+// step's slabs and packed weights but holds the layers' rows (few pairs: 8 KB against
+// 0.6 MB for one; fewer bytes below 224 pairs and at some counts up to 293).  The R = 2B
+// positions (all first endpoints, then all second endpoints) go through the grid lookup (and
+// the encoders), the two feature rows of a pair are multiplied, and the decoder gives Phi:
 //  rows_mma_kernel  Y[rows][NOUT] = epilogue(X[rows][KIN] A^T), A staged once per
 //                   workgroup in LDS in MFMA operand order (A = W forward,
 //                   A = W^T for the data adjoint); 64 rows per wave and tile.
@@ -554,7 +557,7 @@ __global__ __launch_bounds__(64 * kL) void grid_tile_kernel(
 }
 
 // ----------------------------------------------------- row-wise MFMA ----
-enum { EPI_BIAS_RELU = 0, EPI_MASK = 1, EPI_PLAIN = 2 };
+enum { EPI_BIAS = 0, EPI_BIAS_RELU = 1, EPI_MASK = 2, EPI_PLAIN = 3 };
 
 __device__ __forceinline__ bf16x8 load_row8(const float *__restrict__ X, int64_t rows, int64_t r,
                                             int ld, int k0) {
@@ -589,7 +592,7 @@ __global__ __launch_bounds__(kThreads) void rows_mma_kernel(
         const int ob = i >> 5, il = i & 31, kb = k >> 4, hh = (k >> 3) & 1, e = k & 7;
         sa[((ob * KB + kb) * 64 + hh * 32 + il) * 8 + e] = f2bf(wv);
     }
-    if (EPI == EPI_BIAS_RELU)
+    if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU)
         for (int i = threadIdx.x; i < NOUT; i += kThreads) s_bias[i] = bias[i];
     __syncthreads();
 
@@ -626,7 +629,7 @@ __global__ __launch_bounds__(kThreads) void rows_mma_kernel(
                     f32x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = acc[ob][jb][4 * gq + e];
-                    if (EPI == EPI_BIAS_RELU) {
+                    if (EPI == EPI_BIAS || EPI == EPI_BIAS_RELU) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) v[e] += s_bias[i0 + e];
                     }
@@ -935,7 +938,21 @@ GridOffs grid_offs(const NetOffsets &o) {
     return g;
 }
 
-// Forward pass of a grid-only network into the workspace; with targets also the loss and gy.
+// Y = X A^T of one layer over `rows` rows (rows_mma_kernel).
+template <int KIN, int NOUT, int EPI>
+void rows_layer(const float *X, int64_t rows, const float *W, int w_si, int w_sk,
+                const float *bias, const float *mask, float *Y, hipStream_t st) {
+    hipLaunchKernelGGL((rows_mma_kernel<KIN, NOUT, EPI>), dim3(mma_blocks(rows)), dim3(kThreads),
+                       0, st, X, rows, W, w_si, w_sk, bias, mask, Y);
+}
+template <int KIN>
+void rows_wgrad(const float *G, const float *X, int64_t rows, float *dW, float *db,
+                hipStream_t st) {
+    hipLaunchKernelGGL(wgrad_kernel<KIN>, dim3(wgrad_blocks(rows)), dim3(kThreads), 0, st, G, X,
+                       rows, dW, db);
+}
+
+// Forward pass, layer by layer, into the workspace; with targets also the loss and gy.
 void forward(const ndf_net_config *c, const NetOffsets &o, const float *P, const int64_t *pairs,
              const float *pos, const float *targets, int64_t B, const TrainWS &t,
              hipStream_t st) {
@@ -944,13 +961,26 @@ void forward(const ndf_net_config *c, const NetOffsets &o, const float *P, const
     const GridOffs go = grid_offs(o);
     hipLaunchKernelGGL(grid_fwd_kernel, dim3((unsigned)ceil_div(R * kL, kThreads)), dim3(kThreads),
                        0, st, P, go, g, c->n_enc, pairs, pos, B, t.H0);
-    // the grid features are the latents: merge them and decode (W4 is [128][32])
-    hipLaunchKernelGGL(merge_fwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st, t.H0,
-                       B, t.M, kK0);
-    hipLaunchKernelGGL((rows_mma_kernel<kK0, kH, EPI_BIAS_RELU>), dim3(mma_blocks(B)),
-                       dim3(kThreads), 0, st, t.M, B, P + o.W4, kK0, 1, P + o.b4, nullptr, t.D1);
-    hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_BIAS_RELU>), dim3(mma_blocks(B)),
-                       dim3(kThreads), 0, st, t.D1, B, P + o.W5, kH, 1, P + o.b5, nullptr, t.D2);
+    if (c->grid_only) {
+        // the grid features are the latents: merge them and decode (W4 is [128][32])
+        hipLaunchKernelGGL(merge_fwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st,
+                           t.H0, B, t.M, kK0);
+        rows_layer<kK0, kH, EPI_BIAS_RELU>(t.M, B, P + o.W4, kK0, 1, P + o.b4, nullptr, t.D1, st);
+    } else {  // two encoders
+        for (int e = 0; e < 2; ++e) {
+            const int64_t r0 = e * B;
+            rows_layer<kK0, kH, EPI_BIAS_RELU>(t.H0 + r0 * kK0, B, P + o.W1[e], kK0, 1, P + o.b1[e],
+                                               nullptr, t.H1 + r0 * kH, st);
+            rows_layer<kH, kH, EPI_BIAS_RELU>(t.H1 + r0 * kH, B, P + o.W2[e], kH, 1, P + o.b2[e],
+                                              nullptr, t.H2 + r0 * kH, st);
+            rows_layer<kH, kH, EPI_BIAS>(t.H2 + r0 * kH, B, P + o.W3[e], kH, 1, P + o.b3[e],
+                                         nullptr, t.E + r0 * kH, st);
+        }
+        hipLaunchKernelGGL(merge_fwd_kernel, dim3(gs_blocks(B * kH / 4)), dim3(kThreads), 0, st,
+                           t.E, B, t.M, kH);
+        rows_layer<kH, kH, EPI_BIAS_RELU>(t.M, B, P + o.W4, kH, 1, P + o.b4, nullptr, t.D1, st);
+    }
+    rows_layer<kH, kH, EPI_BIAS_RELU>(t.D1, B, P + o.W5, kH, 1, P + o.b5, nullptr, t.D2, st);
     hipLaunchKernelGGL(head_fwd_kernel, dim3((unsigned)ceil_div(B, kThreads)), dim3(kThreads), 0,
                        st, t.D2, P + o.w6, P + o.b6, targets, B, t.y, t.gy, t.partial);
 }
@@ -2340,6 +2370,18 @@ size_t net_train_ws_bytes(const ndf_net_config *c, int64_t B) {
     return fused_path(c) ? carve_fused(c, nullptr, B).bytes : carve(nullptr, B).bytes;
 }
 
+size_t net_train_plan_bytes(const ndf_net_config *c, int64_t B, size_t avail) {
+    const size_t asked = net_train_ws_bytes(c, B);
+    if (avail >= asked) return asked;
+    const size_t rows = carve(nullptr, B).bytes;
+    return c->n_enc == 2 && avail >= rows ? rows : 0;
+}
+
+// Whether a call with net_train_plan_bytes = plan runs the fused step.
+static bool runs_fused(const ndf_net_config *c, int64_t B, size_t plan) {
+    return fused_path(c) && plan >= net_train_ws_bytes(c, B);
+}
+
 int launch_net_init(const ndf_net_config *c, float *params, float *opt, uint64_t seed,
                     hipStream_t st) {
     const NetOffsets o = net_offsets(c);
@@ -2367,9 +2409,10 @@ int launch_net_init(const ndf_net_config *c, float *params, float *opt, uint64_t
 }
 
 int launch_net_forward(const ndf_net_config *c, const float *params, const int64_t *pairs,
-                       const float *pos, int64_t B, float *y, void *ws, hipStream_t st) {
+                       const float *pos, int64_t B, float *y, void *ws, size_t plan,
+                       hipStream_t st) {
     const NetOffsets o = net_offsets(c);
-    if (fused_path(c)) {
+    if (runs_fused(c, B, plan)) {
         const FusedWS t = carve_fused(c, ws, B);
         fused_forward(c, o, fused_args(c, o, params, pairs, pos, nullptr, B, t, y), t, nullptr,
                       nullptr, st);
@@ -2383,11 +2426,10 @@ int launch_net_forward(const ndf_net_config *c, const float *params, const int64
 
 int launch_net_grad(const ndf_net_config *c, const float *P, const int64_t *pairs,
                     const float *pos, const float *targets, int64_t B, float *G, float *loss,
-                    void *ws, hipStream_t st) {
-    if (fused_path(c)) return fused_grad(c, P, pairs, pos, targets, B, G, loss, ws, st);
+                    void *ws, size_t plan, hipStream_t st) {
+    if (runs_fused(c, B, plan)) return fused_grad(c, P, pairs, pos, targets, B, G, loss, ws, st);
     const NetOffsets o = net_offsets(c);
     const TrainWS t = carve(ws, B);
-    const int64_t R = 2 * B;
     launch_status_clear(t.status, st);
     hipLaunchKernelGGL(fill_kernel, dim3(gs_blocks(o.total)), dim3(kThreads), 0, st, G, o.total,
                        0.f);
@@ -2401,20 +2443,35 @@ int launch_net_grad(const ndf_net_config *c, const float *P, const int64_t *pair
         hipLaunchKernelGGL(head_bwd_kernel, dim3((unsigned)(hb < 1024 ? hb : 1024)), dim3(kThreads),
                            0, st, t.D2, t.gy, P + o.w6, B, t.dA, G + o.w6, G + o.b6);
     }
-    hipLaunchKernelGGL(wgrad_kernel<kH>, dim3(wgrad_blocks(B)), dim3(kThreads), 0, st, t.dA, t.D1, B,
-                       G + o.W5, G + o.b5);
-    hipLaunchKernelGGL((rows_mma_kernel<kH, kH, EPI_MASK>), dim3(mma_blocks(B)), dim3(kThreads), 0,
-                       st, t.dA, B, P + o.W5, 1, kH, nullptr, t.D1, t.dB);
+    rows_wgrad<kH>(t.dA, t.D1, B, G + o.W5, G + o.b5, st);
+    rows_layer<kH, kH, EPI_MASK>(t.dA, B, P + o.W5, 1, kH, nullptr, t.D1, t.dB, st);
     const GridGeom g = grid_geom(c);
     const GridOffs go = grid_offs(o);
-    // W4 [128][32] on the merged grid features; the product rule gives the
-    // grid features' gradient directly
-    hipLaunchKernelGGL(wgrad_kernel<kK0>, dim3(wgrad_blocks(B)), dim3(kThreads), 0, st, t.dB, t.M,
-                       B, G + o.W4, G + o.b4);
-    hipLaunchKernelGGL((rows_mma_kernel<kH, kK0, EPI_PLAIN>), dim3(mma_blocks(B)), dim3(kThreads),
-                       0, st, t.dB, B, P + o.W4, 1, kK0, nullptr, nullptr, t.dA);
-    hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st, t.dA,
-                       t.H0, B, t.dH0, kK0);
+    if (c->grid_only) {
+        // W4 [128][32] on the merged grid features; the product rule gives the
+        // grid features' gradient directly
+        rows_wgrad<kK0>(t.dB, t.M, B, G + o.W4, G + o.b4, st);
+        rows_layer<kH, kK0, EPI_PLAIN>(t.dB, B, P + o.W4, 1, kK0, nullptr, nullptr, t.dA, st);
+        hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kK0 / 4)), dim3(kThreads), 0, st,
+                           t.dA, t.H0, B, t.dH0, kK0);
+    } else {
+        rows_wgrad<kH>(t.dB, t.M, B, G + o.W4, G + o.b4, st);
+        rows_layer<kH, kH, EPI_PLAIN>(t.dB, B, P + o.W4, 1, kH, nullptr, nullptr, t.dA, st);
+        // product rule across the merge: dE[b] = dM[b] * E[B+b], dE[B+b] = dM[b] * E[b]
+        hipLaunchKernelGGL(merge_bwd_kernel, dim3(gs_blocks(B * kH / 4)), dim3(kThreads), 0, st,
+                           t.dA, t.E, B, t.dB, kH);
+        for (int e = 0; e < 2; ++e) {  // encoder adjoints
+            const int64_t r0 = e * B;
+            float *dE = t.dB + r0 * kH, *dP2 = t.dA + r0 * kH, *dP1 = t.dB + r0 * kH;
+            rows_wgrad<kH>(dE, t.H2 + r0 * kH, B, G + o.W3[e], G + o.b3[e], st);
+            rows_layer<kH, kH, EPI_MASK>(dE, B, P + o.W3[e], 1, kH, nullptr, t.H2 + r0 * kH, dP2, st);
+            rows_wgrad<kH>(dP2, t.H1 + r0 * kH, B, G + o.W2[e], G + o.b2[e], st);
+            rows_layer<kH, kH, EPI_MASK>(dP2, B, P + o.W2[e], 1, kH, nullptr, t.H1 + r0 * kH, dP1, st);
+            rows_wgrad<kK0>(dP1, t.H0 + r0 * kK0, B, G + o.W1[e], G + o.b1[e], st);
+            rows_layer<kH, kK0, EPI_PLAIN>(dP1, B, P + o.W1[e], 1, kK0, nullptr, nullptr,
+                                           t.dH0 + r0 * kK0, st);
+        }
+    }
     scatter_direct(G, go, g, c->n_enc, pairs, pos, B, t.dH0, st);
     return status_of_launch();
 }

@@ -42,3 +42,72 @@ def test_prepare_of_very_many_vertices(dims):
         assert np.array_equal(e.mean[0, rows].cpu().numpy(), (c[0] + c[1]) / 2)
     del e, x
     torch.cuda.empty_cache()
+
+
+def _layered_ws_bytes(B):
+    """Workspace of the layer-by-layer step of two encoders (as ndf.h states it)."""
+    per_pair = [256, 1024, 1024, 1024, 512, 512, 512, 4, 4, 1024, 1024, 256]
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    return 256 + sum(up(n * B) for n in per_pair) + up(8 * ((B + 255) // 256))
+
+
+# pair counts at which the layers' rows need less than the fused step's plan, around a 64-row
+# tile and up to the last such count
+@pytest.mark.parametrize("B", [1, 31, 64, 65, 224, 225, 257, 293])
+@pytest.mark.parametrize("at", [False, True])
+def test_two_encoder_step_in_the_smaller_workspace(B, at):
+    cfg = gen.CONFIGS["tiny"]
+    dims = (cfg.nx, cfg.ny, cfg.nz)
+    lay = gen.NetLayout.for_grid(*dims, n_enc=2)
+    flat = gen.make_net_params(lay, seed=2340, grid_scale=0.5, bias_scale=0.1)
+    c = ndf.net_config(*dims, lay.res, n_enc=2)
+    net = nn.Net(flat, dims, lay.res, 8, 128, 2)
+    P = torch.from_numpy(flat).cuda()
+    need = _layered_ws_bytes(B)
+    pairs = gen.random_pairs(cfg.n_vertices, B, seed=B)
+    if at:
+        where = gen.random_positions(2 * B, seed=B).reshape(B, 2, 3).astype(np.float32)
+        y = nn.forward_points(net, where)
+        loss_and_grad = lambda t, *o: nn.loss_and_grad_points(net, where, t, *o)  # noqa: E731
+        fwd, grad, step = ndf.ndf_net_forward_at, ndf.ndf_net_grad_at, ndf.ndf_train_step_at
+    else:
+        where = pairs
+        y, _ = nn.forward(net, pairs[:, 0], pairs[:, 1])
+        loss_and_grad = lambda t, *o: nn.loss_and_grad(  # noqa: E731
+            net, pairs[:, 0], pairs[:, 1], t, *o)
+        fwd, grad, step = ndf.ndf_net_forward, ndf.ndf_net_grad, ndf.ndf_train_step
+    t = y + 1.0  # residual -1 everywhere, far from the L1 kink
+    g_o = loss_and_grad(t)[1]
+    g_e = loss_and_grad(t, TRAIN_OPS)[1]
+    w = torch.as_tensor(where, device="cuda")
+    tt = torch.as_tensor(t, dtype=torch.float32, device="cuda")
+    pbytes = (P.numel() * 4 + 255) // 256 * 256
+    ws = torch.full((need + pbytes + 256,), 0x5a, dtype=torch.uint8, device="cuda")
+    g, loss, out = torch.full_like(P, 7.0), torch.empty(1, device="cuda"), torch.empty(B, device="cuda")
+    grad(c, P, w, tt, g, loss, ws[:need])
+    assert ndf.status_word(ws) == ndf.NDF_OK
+    assert bool((ws[need:] == 0x5a).all())  # nothing past the bytes that were given
+    assert abs(loss.item() - 1.0) <= 1e-2
+    check_grad_floor(lay, g.cpu().numpy().astype(np.float64), g_o.flat, g_e.flat,
+                     f"grad at={at} B={B}")
+    fwd(c, P, w, out, ws[:need])
+    assert bool((ws[need:] == 0x5a).all())
+    # the fused step rounds the same operands; the head's FP32 sum of 128 terms, whose
+    # absolute values add up to at most 64 times the largest output, runs in another order
+    big = torch.empty(ndf.train_ws_bytes(c, B), dtype=torch.uint8, device="cuda")
+    ref = torch.empty(B, device="cuda")
+    fwd(c, P, w, ref, big)
+    assert torch.allclose(out, ref, rtol=0, atol=136 * 2.0 ** -24 * 64 * np.abs(y).max())
+    least = min(need, ndf.train_ws_bytes(c, B))  # the fused plan is the smaller one at 224
+    with pytest.raises(ndf.NdfError, match="workspace"):
+        grad(c, P, w, tt, g, loss, ws[:least - 256])
+    # a step leaves its gradient right behind the bytes it lays out
+    P1, opt = P.clone(), torch.zeros(2 * P.numel(), device="cuda")
+    step(c, P1, opt, 1, w, tt, 1e-3, loss, ws[:need + pbytes])
+    left = ws[least:least + 4 * P.numel()].view(torch.float32)
+    d = (left - g).double().norm() / g.double().norm()
+    assert d <= 1e-6  # the scatter's atomics add in any order
+    assert bool((ws[need + pbytes:] == 0x5a).all())
+    assert not torch.equal(P1, P) and bool(torch.isfinite(P1).all())
+    with pytest.raises(ndf.NdfError, match="workspace"):
+        step(c, P1, opt, 1, w, tt, 1e-3, loss, ws[:least + pbytes - 256])
