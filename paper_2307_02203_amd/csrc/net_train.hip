@@ -1200,13 +1200,15 @@ __device__ __forceinline__ bf16x8 gather_h0(const FusedArgs &A, const int64_t (&
     // A corner of weight 0 adds nothing, and on a level of the vertex grid's size only one
     // corner of eight has weight.  With many waves in flight the others are skipped; a
     // branch around each read waits for it before the next is issued, so with few waves
-    // (`few`, uniform) they read the last weighted corner's cell instead.
+    // (`few`, uniform) they read the last weighted corner's cell instead and leave it out of
+    // the sum (0 times an infinite feature is not 0).
     f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
     auto add = [&](float wc, const f32x4 &c0, const f32x4 &c1) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            s0[i] = fmaf(wc, c0[i], s0[i]);
-            s1[i] = fmaf(wc, c1[i], s1[i]);
+            const float a0 = fmaf(wc, c0[i], s0[i]), a1 = fmaf(wc, c1[i], s1[i]);
+            s0[i] = wc != 0.f ? a0 : s0[i];
+            s1[i] = wc != 0.f ? a1 : s1[i];
         }
     };
     if (few) {

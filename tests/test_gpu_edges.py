@@ -111,3 +111,34 @@ def test_two_encoder_step_in_the_smaller_workspace(B, at):
     assert not torch.equal(P1, P) and bool(torch.isfinite(P1).all())
     with pytest.raises(ndf.NdfError, match="workspace"):
         step(c, P1, opt, 1, w, tt, 1e-3, loss, ws[:least + pbytes - 256])
+
+
+# a batch of few waves (which reads every corner's cell) and one of many (which skips corners of
+# weight 0), vertices and positions on cells of an infinite feature and beside them
+@pytest.mark.parametrize("n_enc", [1, 2])
+@pytest.mark.parametrize("at", [False, True])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_outputs_at_infinite_features_do_not_depend_on_the_batch(n_enc, at, value):
+    dims, n, B = (37, 29, 11), 64, 20000
+    V = dims[0] * dims[1] * dims[2]
+    lay = gen.NetLayout.for_grid(*dims, n_enc=n_enc)
+    flat = gen.make_net_params(lay, seed=2343, grid_scale=0.5, bias_scale=0.1)
+    lay.view(flat, "grid0_3").reshape(-1, 8)[V // 2, 3] = value
+    c = ndf.net_config(*dims, lay.res, n_enc=n_enc)
+    P = torch.from_numpy(flat).cuda()
+    v = gen.random_pairs(V, B, seed=5)
+    v[:8, 0] = V // 2
+    v[8:16, 0] = V // 2 + np.array([-1, 1, -37, 37, -37 * 29, 37 * 29, 38, -38])
+    if at:
+        ijk = np.stack([v % 37, v // 37 % 29, v // (37 * 29)], -1)
+        where = (2 * ijk / (np.array(dims) - 1) - 1).astype(np.float32)
+        where[64:] += 0.01
+    else:
+        where = v
+    w = torch.as_tensor(where, device="cuda")
+    fwd = ndf.ndf_net_forward_at if at else ndf.ndf_net_forward
+    ws = torch.empty(ndf.train_ws_bytes(c, B), dtype=torch.uint8, device="cuda")
+    few, many = torch.empty(n, device="cuda"), torch.empty(B, device="cuda")
+    fwd(c, P, w[:n].contiguous(), few, ws)
+    fwd(c, P, w, many, ws)
+    assert torch.equal(few.view(torch.int32), many[:n].view(torch.int32))
