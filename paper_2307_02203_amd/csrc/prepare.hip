@@ -480,12 +480,19 @@ int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStre
     // 1.30); with more the codes of a wave's four columns spill (1000 members 7.74 ms
     // against 6.08 with a kernel of its own).
     *sorted = false;
+    // Few members with neither orders nor the vertex-major copy: the two-read kernel, which
+    // holds them in one 64-member tile (its second read comes from the caches) and spends
+    // four threads instead of sixteen on a vertex.  1.76M vertices, us, one read against
+    // two: 2 members 156 / 118, 16 169 / 137, 32 189 / 144, 48 206 / 223, 56 218 / 267, 63
+    // 240 / 312, 64 (a whole tile) 227 / 208, 68 252 / 268; 65536 vertices: 2 members
+    // 8.5 / 7.0, 48 10.4 / 8.8, 56 10.6 / 10.0, 64 10.7 / 8.7, 68 11.8 / 12.1.
+    const bool two_reads = !e->order && !e->xt && (N <= 48 || N == 64);
 #define NDF_PREP_LAUNCH(E, OE)                                                                   \
     hipLaunchKernelGGL((prepare_kernel<E, OE>), rg, dim3(kRegThreads), 0, st, e->x, N, V, e->mean, \
                        e->inv_std, e->code, e->flags, status, e->xt, e->order)
 #define NDF_PREP_CASE(E, OE)                                                                     \
-    if (N < kRegPh * (E + 1)) {                                                                  \
-        *sorted = OE && e->order && N <= 64 * OE;                                                     \
+    if (!two_reads && N < kRegPh * (E + 1)) {                                                    \
+        *sorted = OE && e->order && N <= 64 * OE;                                                \
         if (*sorted)                                                                             \
             NDF_PREP_LAUNCH(E, OE);                                                              \
         else                                                                                     \

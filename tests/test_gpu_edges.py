@@ -142,3 +142,50 @@ def test_outputs_at_infinite_features_do_not_depend_on_the_batch(n_enc, at, valu
     fwd(c, P, w[:n].contiguous(), few, ws)
     fwd(c, P, w, many, ws)
     assert torch.equal(few.view(torch.int32), many[:n].view(torch.int32))
+
+
+def _check_prepare(n_members, dims, orders, transposed):
+    """ndf_prepare of an ensemble with constant, non-finite and far columns, against numpy."""
+    V = dims[0] * dims[1] * dims[2]
+    rng = np.random.default_rng(n_members + V)
+    x = (rng.standard_normal((n_members, V)) * 3.0 + 40.0).astype(np.float32)
+    x[:, 1] = -7.25
+    x[n_members // 2, 2] = np.nan
+    x[0, 3] = np.inf
+    x[-1, 4] = 1e6
+    x[:, 5] = rng.integers(0, 3, n_members)
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=orders, transposed=transposed)
+    ws = torch.empty(256, dtype=torch.uint8, device="cuda")
+    ndf.ndf_prepare(e, ws)
+    assert ndf.status_word(ws) == ndf.NDF_E_NONFINITE
+    fin = np.isfinite(x)
+    lo = np.where(np.isnan(x), np.inf, x).min(0)
+    hi = np.where(np.isnan(x), -np.inf, x).max(0)
+    flat = ~(hi > lo)
+    flags = ndf.NDF_FLAG_NONFINITE * ~fin.all(0) + ndf.NDF_FLAG_CONSTANT * flat
+    assert np.array_equal(e.flags[0].cpu().numpy(), flags)
+    if transposed:
+        assert np.array_equal(e.xt[0].cpu().numpy(), x.T, equal_nan=True)
+    code = e.code[0].cpu().numpy()
+    ok = flags == 0
+    d = x.T[ok].astype(np.float64)
+    l, h = d.min(1, keepdims=True), d.max(1, keepdims=True)
+    assert np.array_equal(code[ok], np.rint((d - l) * (8388608.0 / (h - l))))
+    assert np.all(code[flat] == 0) and np.all(e.inv_std[0].cpu().numpy()[flat] == 0.0)
+    if orders:
+        got = e.order[0].cpu().numpy().astype(np.int64) & 0xffff
+        assert np.array_equal(got, np.argsort(code, axis=1, kind="stable"))
+    # FP64 sums of N terms: (N + 2) 2^-53 of sum |x| on either side
+    tol = 2 * (n_members + 2) * 2.0 ** -53
+    assert np.max(np.abs(e.mean[0].cpu().numpy()[ok] - d.mean(1)) / np.abs(d).mean(1)) <= tol
+    var = ((d - d.mean(1, keepdims=True)) ** 2).mean(1)
+    assert np.max(np.abs(e.inv_std[0].cpu().numpy()[ok] * np.sqrt(var) - 1.0)) <= 4 * tol
+
+
+# member counts around the line between the one-read and the two-read kernel, with and without
+# the outputs that the rule asks for, vertex counts around a workgroup's 64
+@pytest.mark.parametrize("n_members", [2, 3, 16, 47, 48, 49, 63, 64, 65])
+@pytest.mark.parametrize("dims", [(7, 3, 3), (4, 4, 4), (5, 13, 2)])
+@pytest.mark.parametrize("orders,transposed", [(False, False), (False, True), (True, False)])
+def test_prepare_of_few_members(n_members, dims, orders, transposed):
+    _check_prepare(n_members, dims, orders, transposed)
