@@ -164,7 +164,8 @@ int ndf_prepare(const ndf_ensemble *ens, void *ws, size_t ws_bytes, void *stream
 /* Direct Pearson field (Sec. 3.1, Eq. 1; Table 1 "Pearson"):
  * out[r][v] = r(e^{var_ref}(ref_v[r]), e^{var_qry}(v)) for r < n_ref, v < V.
  * ref_v [host] int64[n_ref].  prec NDF_PREC_FP32 streams the ensemble once per
- * reference; NDF_PREC_SPLIT_BF16 runs all references as one MFMA contraction of
+ * eight references (the order of a field's sum over the members, and with it the
+ * last bits, follow the grid and the number of references); NDF_PREC_SPLIT_BF16 runs all references as one MFMA contraction of
  * standardised members (z = zhi + zlo, products hi*hi + hi*lo + lo*hi, FP32
  * accumulate).  r = 0 where either vertex has zero variance.  Needs ndf_prepare. */
 int ndf_pearson_field(const ndf_ensemble *ens, int32_t var_ref, int32_t var_qry,

@@ -177,14 +177,38 @@ static void launch_fp32(const Fp32Args &a, const RefList &refs, int n_ref, float
                        a.V, refs, n_ref, out);
 }
 
-// How the members are split: four vertices per lane fill the chip (eight waves on
-// each of 256 CUs) from 2^19 vertices on; below that 4 or 16 waves share a
-// workgroup's vertices, and under 2^15 vertices a lane also takes one vertex
-// instead of four.
+// How the members are split.  Four vertices per lane fill the chip (eight waves on each of
+// 256 CUs) from 2^19 vertices on; below that 4 or 16 waves share a workgroup's vertices, and
+// under 2^15 vertices a lane also takes one vertex instead of four.  Between 2^17 and 2^19
+// vertices one or two references are bound by the read of the ensemble, which is slower with
+// the members split (5 against 6.3 TB/s), unless the unsplit workgroups of 1024 vertices fill
+// less than 72 % of the CUs in their rounds; four references gain from the vertices of 440
+// such workgroups on, eight from 2^19 on.  1000 members, us, unsplit / four waves:
+//   vertices (workgroups)  162,540 (159)  201,960 (198)  261,800 (256)  286,720 (280)
+//   1 reference              114 / 118      127 / 162      160 / 176      219 / 184
+//   4 references             229 / 116      243 / 162      248 / 180      256 / 188
+//   8 references             339 / 145      346 / 169      360 / 200      376 / 290
+//   vertices (workgroups)  368,480 (360)  389,088 (380)  427,800 (418)  511,498 (500)
+//   1 reference              252 / 232      251 / 243      283 / 300      318 / 353
+//   4 references             280 / 237      281 / 244      305 / 311      329 / 420
+//   8 references             409 / 316      397 / 325      440 / 361      435 / 418
+// 100 members: the same order within 5 %, 194,020 vertices (190) 15.1 / 14.3.  At the other
+// lines, 1000 members, 1 and 8 references: 126,976 vertices 4 waves 77 and 122, 16 waves 78
+// and 105; 163,840 106 and 135 against 105 and 146; 31,744 vertices 16 waves of one vertex
+// a lane 22.7 and 41, of four 24.7 and 41; 38,400 30.6 and 57 against 27.3 and 45.
+constexpr int kUnsplitVerts = 1024;  // vertices of an unsplit workgroup
+template <int R>
+static bool fp32_unsplit(int64_t V) {
+    if (V >= (1 << 19)) return true;
+    if (V < (1 << 17)) return false;
+    const int64_t wgs = ceil_div(V, kUnsplitVerts), slots = 256 * ceil_div(wgs, 256);
+    return R <= 2 ? 100 * wgs > 72 * slots : R <= 4 && wgs > 440;
+}
+
 template <int R>
 static void launch_fp32_refs(const Fp32Args &a, const RefList &refs, int n_ref, float *out,
                              hipStream_t st) {
-    if (a.V >= (1 << 19))
+    if (fp32_unsplit<R>(a.V))
         launch_fp32<R, 4, 1>(a, refs, n_ref, out, st);
     else if (a.V >= (1 << 17))
         launch_fp32<R, 4, 4>(a, refs, n_ref, out, st);

@@ -189,3 +189,27 @@ def _check_prepare(n_members, dims, orders, transposed):
 @pytest.mark.parametrize("orders,transposed", [(False, False), (False, True), (True, False)])
 def test_prepare_of_few_members(n_members, dims, orders, transposed):
     _check_prepare(n_members, dims, orders, transposed)
+
+
+# vertex counts on both sides of the lines between split and unsplit members: 72 % of one and of
+# two rounds of 256 workgroups of 1024 vertices, one whole round, 440 workgroups, 2^19
+# vertices; 1, 2, 4 and 8 references take kernels of their own
+@pytest.mark.parametrize("dims", [(184, 128, 8), (189, 125, 8), (256, 128, 8), (257, 341, 3),
+                                  (367, 128, 8), (379, 125, 8), (440, 128, 8), (451, 500, 2),
+                                  (511, 341, 3), (512, 128, 8)])
+@pytest.mark.parametrize("n_ref", [1, 2, 4, 8])
+def test_pearson_fp32_at_the_split_lines(dims, n_ref):
+    n_members = 21
+    V = dims[0] * dims[1] * dims[2]
+    rng = np.random.default_rng(V + n_ref)
+    x = rng.standard_normal((n_members, V), dtype=np.float32)
+    x += rng.standard_normal((n_members, 1), dtype=np.float32)
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=False)
+    ndf.ndf_prepare(e)
+    refs = rng.integers(0, V, n_ref)
+    refs[-1] = V - 1
+    got = ndf.pearson_field(e, refs).cpu().numpy().astype(np.float64)
+    sub = np.unique(np.r_[0:600, np.arange(0, V, V // 2000), V - 600:V])
+    for i, r in enumerate(refs):
+        want = direct.pearson_field(np.ascontiguousarray(x[:, r]), np.ascontiguousarray(x[:, sub]))
+        assert np.max(np.abs(got[i, sub] - want)) <= 1e-5
