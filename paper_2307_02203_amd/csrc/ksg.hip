@@ -657,7 +657,7 @@ __global__ __launch_bounds__(kKsgThreads, order_waves(E)) void ksg_order_kernel(
     {
         uint32_t c[E];
         load_codes<E>(code + v * N, N, c);
-        wave_sort_codes<E>(c, N, order + v * N, s_lds[wave]);
+        wave_sort_codes<E, 1>(c, N, order + v * N, s_lds[wave]);
     }
 }
 

@@ -10,80 +10,86 @@ constexpr int log2_int(int n) { return n <= 1 ? 0 : 1 + log2_int(n / 2); }
 // merge of two sorted halves starts by comparing element i with its mirror
 // i ^ (size - 1): every comparator then puts the minimum at the lower index, so a
 // pair in one lane is one v_min and one v_max, and a pair across lanes one lane
-// shuffle plus a min or max.
+// shuffle plus a min or max.  The stages are template instances: a loop over them that
+// the compiler leaves rolled (E = 32) indexes the registers at run time (2048 members
+// 200 us a column).
 template <int E>
-__device__ __forceinline__ void wave_sort_regs32(uint32_t (&k)[E]) {
-    const int lane = threadIdx.x & 63;
-    constexpr int LE = log2_int(E);
-    constexpr int LPT = 6 + LE;  // log2 of the key count
+__device__ __forceinline__ void sort_in_lane(uint32_t (&k)[E], int mask) {
 #pragma unroll
-    for (int ls = 1; ls <= LPT; ++ls) {
-        const int size = 1 << ls;
-        if (size <= E) {
-#pragma unroll
-            for (int j = 0; j < E; ++j) {
-                const int jp = j ^ (size - 1);
-                if (jp > j) {
-                    const uint32_t a = k[j], b = k[jp];
-                    k[j] = min(a, b);
-                    k[jp] = max(a, b);
-                }
-            }
-        } else {
-            // partner of (lane, j) is (lane ^ (size / E - 1), E - 1 - j)
-            const bool lower = ((E * lane) & (size >> 1)) == 0;
-            uint32_t t[E];
-#pragma unroll
-            for (int j = 0; j < E; ++j) t[j] = __shfl_xor(k[E - 1 - j], size / E - 1, kWave);
-#pragma unroll
-            for (int j = 0; j < E; ++j) k[j] = lower ? min(k[j], t[j]) : max(k[j], t[j]);
-        }
-#pragma unroll
-        for (int ls2 = ls - 2; ls2 >= 0; --ls2) {
-            const int stride = 1 << ls2;
-            if (stride >= E) {
-                const bool lower = ((E * lane) & stride) == 0;
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const uint32_t o = __shfl_xor(k[j], stride / E, kWave);
-                    k[j] = lower ? min(k[j], o) : max(k[j], o);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const int jp = j ^ stride;
-                    if (jp > j) {
-                        const uint32_t a = k[j], b = k[jp];
-                        k[j] = min(a, b);
-                        k[jp] = max(a, b);
-                    }
-                }
-            }
+    for (int j = 0; j < E; ++j) {
+        const int jp = j ^ mask;
+        if (jp > j) {
+            const uint32_t a = k[j], b = k[jp];
+            k[j] = min(a, b);
+            k[jp] = max(a, b);
         }
     }
 }
+// Strides 2^LS2, 2^(LS2 - 1), ..., 1 of a merge.
+template <int E, int LS2>
+__device__ __forceinline__ void sort_strides(uint32_t (&k)[E]) {
+    constexpr int stride = 1 << LS2;
+    if constexpr (stride >= E) {
+        const bool lower = ((E * (threadIdx.x & 63)) & stride) == 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const uint32_t o = __shfl_xor(k[j], stride / E, kWave);
+            k[j] = lower ? min(k[j], o) : max(k[j], o);
+        }
+    } else {
+        sort_in_lane<E>(k, stride);
+    }
+    if constexpr (LS2 > 0) sort_strides<E, LS2 - 1>(k);
+}
+// Merges into sorted runs of 2^LS keys, then the longer ones.
+template <int E, int LS = 1>
+__device__ __forceinline__ void wave_sort_regs32(uint32_t (&k)[E]) {
+    constexpr int size = 1 << LS;
+    if constexpr (size <= E) {
+        sort_in_lane<E>(k, size - 1);
+    } else {
+        // partner of (lane, j) is (lane ^ (size / E - 1), E - 1 - j)
+        const bool lower = ((E * (threadIdx.x & 63)) & (size >> 1)) == 0;
+        uint32_t t[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) t[j] = __shfl_xor(k[E - 1 - j], size / E - 1, kWave);
+#pragma unroll
+        for (int j = 0; j < E; ++j) k[j] = lower ? min(k[j], t[j]) : max(k[j], t[j]);
+    }
+    if constexpr (LS >= 2) sort_strides<E, LS - 2>(k);
+    if constexpr (LS < 6 + log2_int(E)) wave_sort_regs32<E, LS + 1>(k);
+}
 
 // Sorted member order of one column of N <= 64 E members by one wave, as a bucket
-// sort in LDS.  Codes spread over [0, 2^23], so 2 E 64 buckets of equal width hold one
-// or two samples each: every sample takes a place in its bucket from an LDS counter,
-// a scan of the counters gives the bucket starts, and the samples go to LDS in bucket
-// order, where lane l then holds positions E l .. E l + E - 1.  Their 32-bit keys
+// sort in LDS.  Codes spread over [0, 2^23], so two (E = 32: four) buckets of equal width
+// per slot hold one or two samples each: every sample takes a place in its bucket from an
+// LDS counter, a scan of the counters gives the bucket starts, and the samples go to LDS in
+// bucket order, where lane l then holds positions E l .. E l + E - 1.  Their 32-bit keys
 //   (start of the bucket, code bits below the bucket, member)
-// order like (code, member), as the start grows with the bucket.  Odd-even passes
-// finish the buckets; a column with crowded buckets (repeated values, far outliers) is
-// still unsorted after kOddEven passes and goes through the full bitonic sort of the
-// same keys.
-constexpr int kOddEven = 8;  // passes (each both parities) before the full sort
+// order like (code, member), as the start grows with the bucket.  Odd-even passes finish
+// the buckets.
+// Repeated values crowd their buckets.  Code 0, the column's minimum (fields with many
+// zeros), has a bucket of its own, and the counters are taken in member order, so that
+// equal codes lie in order as they come; columns that are still far from sorted after
+// kLook passes (far outliers: many codes in few buckets) go through the full bitonic sort
+// of the same keys at once, the others after kOddEven.  ndf_prepare of 80,000 columns, us,
+// against a bitonic sort of every column: 200 members smooth 63 (130), 90 % zeros 90 (139),
+// lognormal 137 (141); 1000 members 293 (650), 450 (675), 602 (712); 2048 members 1414
+// (3803), 1694 (3639), 2398 (3822).  With one bucket sort for all codes, no early look and
+// members taken four by four, 90 % zeros took 173, 771 and 17,779.
+constexpr int kLook = 2;     // passes (each both parities) before the first look
+constexpr int kOddEven = 8;  // ... and before the full sort at the latest
+constexpr int kFarOff = 16;  // lanes with a pair out of order that end the passes at the look
 
 template <int E>
 struct ColumnSort {
     static constexpr int kLN = 6 + log2_int(E);          // log2 of the slots
-    // 2 buckets per slot; 8 at E = 32 so that start, code bits and member fit 32 bits
+    // 2 buckets per slot; 4 at E = 32 so that start, code bits and member fit 32 bits
     static constexpr int kLB = kLN <= 10 ? kLN + 1 : kLN + 2;
     static constexpr int kLow = 23 - kLB;                // code bits inside a bucket
     static constexpr int kWords = (1 << kLB) / 2;        // two 16-bit counters a word
     static constexpr int kPer = kWords / 64;             // counter words per lane
-    static constexpr int kLds = kWords + 4;              // + the bucket of code 2^23
+    static constexpr int kLds = kWords + 4;              // + the bucket of code 0
     static_assert(2 * kLN + kLow <= 32, "key bits");
     static_assert(kWords >= 64 * E, "the keys reuse the counters");
 };
@@ -99,48 +105,34 @@ typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x8u __attribute__((ext_vector_type(8), aligned(2)));
 
-template <int E>
-__device__ __forceinline__ int sort_member(int j, int lane) {
-    // members of a lane: four consecutive ones per load (E >= 4), else strided
-    return E >= 4 ? 256 * (j >> 2) + 4 * lane + (j & 3) : 64 * j + lane;
-}
+// Member of a lane's j-th code: a counter's places then follow the members (in a wave's
+// LDS operation the lanes come in order).
+__device__ __forceinline__ int sort_member(int j, int lane) { return 64 * j + lane; }
 
 // The codes of a column as wave_sort_codes takes them: code[j] of member sort_member(j).
 template <int E>
 __device__ __forceinline__ void load_codes(const int32_t *__restrict__ c, int N,
                                            uint32_t (&code)[E]) {
     const int lane = threadIdx.x & 63;
-    if constexpr (E >= 4) {
 #pragma unroll
-        for (int j = 0; j < E; j += 4) {
-            const int m = sort_member<E>(j, lane);
-            i32x4u q = {0, 0, 0, 0};
-            if (m + 3 < N) {
-                q = *reinterpret_cast<const i32x4u *>(c + m);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 3; ++e)
-                    if (m + e < N) q[e] = c[m + e];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) code[j + e] = (uint32_t)q[e];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < E; ++j) {
-            const int m = sort_member<E>(j, lane);
-            code[j] = m < N ? (uint32_t)c[m] : 0u;
-        }
+    for (int j = 0; j < E; ++j) {
+        const int m = sort_member(j, lane);
+        code[j] = m < N ? (uint32_t)c[m] : 0u;
     }
 }
 
-// The sort (codes past N are not read); lds: kLds words of the wave, 16-byte aligned.
-template <int E>
+// The sort (codes past N are not read); lds: kLds words of the wave, 16-byte aligned.  SUB: 1
+// where the codes come as they are, 0 where the caller has taken 1 off each (1 % less where
+// they come from LDS; off codes loaded from memory it made the compiler wait for one load
+// before the next, 1000 members 2.8 -> 4.1 ms).
+template <int E, uint32_t SUB>
 __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N,
                                                 uint16_t *__restrict__ o, uint32_t *lds) {
     typedef ColumnSort<E> C;
     const int lane = threadIdx.x & 63;
-    auto member = [&](int j) { return sort_member<E>(j, lane); };
+    auto member = [&](int j) { return sort_member(j, lane); };
+    // bucket of codes 1 .. 2^kLow, the next ones, ..., and last that of code 0
+    auto bucket = [](uint32_t c) { return min((c - SUB) >> C::kLow, 1u << C::kLB); };
     // counters to zero
     for (int i = lane; i < C::kLds / 4; i += 64)
         reinterpret_cast<u32x4v *>(lds)[i] = u32x4v{0u, 0u, 0u, 0u};
@@ -149,7 +141,7 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
     uint32_t place[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-        const uint32_t b = min(code[j] >> C::kLow, 1u << C::kLB);
+        const uint32_t b = bucket(code[j]);
         if (member(j) < N) {
             const uint32_t sh = (b & 1) * 16;
             place[j] = (atomicAdd(&lds[b >> 1], 1u << sh) >> sh) & 0xffffu;
@@ -169,8 +161,8 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
         const uint32_t t = __shfl_up(run, d, kWave);
         if (lane >= d) run += t;
     }
-    if (lane == 63) lds[C::kWords] = run;  // start of the bucket of code 2^23
-    run -= sum;
+    run += (lds[C::kWords] & 0xffffu) - sum;  // after the samples of code 0
+    if (lane == 0) lds[C::kWords] = 0;        // the start of theirs
 #pragma unroll
     for (int i = 0; i < C::kPer; ++i) {
         const uint32_t lo = w[i] & 0xffffu, hi = w[i] >> 16;
@@ -181,11 +173,11 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
     uint32_t k[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-        const uint32_t b = min(code[j] >> C::kLow, 1u << C::kLB);
+        const uint32_t b = bucket(code[j]);
         const uint32_t start = (lds[b >> 1] >> ((b & 1) * 16)) & 0xffffu;
         place[j] += start;
         k[j] = (start << (C::kLow + C::kLN)) |
-               ((code[j] & ((1u << C::kLow) - 1)) << C::kLN) | (uint32_t)member(j);
+               (((code[j] - SUB) & ((1u << C::kLow) - 1)) << C::kLN) | (uint32_t)member(j);
     }
     wave_lds_fence();  // every start is read: the keys reuse the counters' LDS
 #pragma unroll
@@ -204,8 +196,9 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
         bool bad = lane < 63 && k[E - 1] > nk;
 #pragma unroll
         for (int j = 0; j + 1 < E; ++j) bad |= k[j] > k[j + 1];
-        if (!__any(bad) || pass == kOddEven) {
-            if (__any(bad)) wave_sort_regs32<E>(k);
+        const int far = __popcll(__ballot(bad));
+        if (far == 0 || pass == kOddEven || (pass == kLook && far > kFarOff)) {
+            if (far) wave_sort_regs32<E>(k);
             break;
         }
 #pragma unroll

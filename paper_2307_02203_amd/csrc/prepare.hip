@@ -147,7 +147,7 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
         ss += d * d;
         return flat ? 0 : (int32_t)__builtin_rint(((double)q - dlo) * scale);
     };
-    uint32_t sc[kCols][OE ? OE : 1];  // the codes of this wave's columns, as they are sorted
+    uint32_t sc[kCols][OE ? OE : 1];  // this wave's columns: codes minus 1
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int m0 = kRegPh * J * k;
@@ -160,23 +160,15 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
         if (tail) row[kRegPh * (NF - J * k)] = encode(al);
         __syncthreads();
         prep_store<J>(s_tile, cv, N, V, v0, m0);
-        if constexpr (OE >= 4) {
-            if (4 * k < OE) {
-#pragma unroll
-                for (int c = 0; c < kCols; ++c) {
-                    const i32x4 q = *reinterpret_cast<const i32x4 *>(
-                        s_tile + (kCols * wave + c) * prep_row<J>() + 4 * lane);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) sc[c][4 * k + e] = (uint32_t)q[e];
-                }
-            }
-        } else if constexpr (OE > 0) {
-            if (k == 0) {
+        if constexpr (OE > 0) {
+            constexpr int kTileCodes = kRegPh * J / 64;  // of a lane
+            if (kTileCodes * k < OE) {
 #pragma unroll
                 for (int c = 0; c < kCols; ++c)
 #pragma unroll
-                    for (int j = 0; j < OE; ++j)
-                        sc[c][j] = (uint32_t)s_tile[(kCols * wave + c) * prep_row<J>() + 64 * j + lane];
+                    for (int e = 0; e < kTileCodes; ++e)
+                        sc[c][kTileCodes * k + e] =
+                            (uint32_t)s_tile[(kCols * wave + c) * prep_row<J>() + 64 * e + lane] - 1u;
             }
         }
         if (tv) {
@@ -211,7 +203,7 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
         for (int c = 0; c < kCols; ++c) {
             const int64_t vc = v0 + kCols * wave + c;
             if (vc >= V) break;  // uniform
-            wave_sort_codes<OE>(sc[c], N, ov + vc * N, lds);
+            wave_sort_codes<OE, 0>(sc[c], N, ov + vc * N, lds);
             wave_lds_fence();
         }
     }

@@ -213,3 +213,81 @@ def test_pearson_fp32_at_the_split_lines(dims, n_ref):
     for i, r in enumerate(refs):
         want = direct.pearson_field(np.ascontiguousarray(x[:, r]), np.ascontiguousarray(x[:, sub]))
         assert np.max(np.abs(got[i, sub] - want)) <= 1e-5
+
+
+def _crowded_columns(n_members, n_vertices, rng):
+    """Columns whose codes are the integers themselves (0 and 2^23 are always there): runs of
+    equal codes at both ends, bucket edges of every slot count, a few buckets for all."""
+    top = 1 << 23
+    x = np.empty((n_members, n_vertices), dtype=np.float32)
+    for v in range(n_vertices):
+        kind = v % 9
+        if kind == 0:      # many zeros
+            c = np.where(rng.random(n_members) < 0.7, 0, rng.integers(0, top + 1, n_members))
+        elif kind == 1:    # many maxima
+            c = np.where(rng.random(n_members) < 0.7, top, rng.integers(0, top + 1, n_members))
+        elif kind == 2:    # two values
+            c = rng.integers(0, 2, n_members) * top
+        elif kind == 3:    # four values
+            c = rng.integers(0, 4, n_members) * (top // 3)
+        elif kind == 4:    # edges of buckets of 2^10 .. 2^16 codes
+            c = np.clip((rng.integers(0, top >> 10, n_members) << rng.integers(10, 17, n_members))
+                        % (top + 1) + rng.integers(-1, 2, n_members), 0, top)
+        elif kind == 5:    # one far outlier above
+            c = rng.integers(0, 200, n_members)
+        elif kind == 6:    # ... and below
+            c = top - rng.integers(0, 200, n_members)
+        elif kind == 7:    # smallest codes
+            c = rng.integers(0, 3, n_members)
+        else:              # descending
+            c = np.sort(rng.integers(0, top + 1, n_members))[::-1].copy()
+        c[rng.integers(0, n_members)] = 0
+        at = rng.integers(0, n_members)
+        c[at] = top
+        if not (c == 0).any():
+            c[(at + 1) % n_members] = 0
+        x[:, v] = c
+    return x
+
+
+# slot counts of every sort (64 E, E = 1 .. 32) in ndf_prepare and in the kernel of its own
+@pytest.mark.parametrize("n_members", [2, 5, 63, 64, 65, 128, 129, 256, 257, 512, 513, 700, 1024,
+                                       1025, 1500, 2048, 2049])
+def test_stored_orders_of_crowded_columns(n_members):
+    dims = (5, 9, 3)
+    x = _crowded_columns(n_members, 135, np.random.default_rng(n_members))
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=True)
+    ndf.ndf_prepare(e)
+    code = e.code[0].cpu().numpy()
+    assert np.array_equal(code, x.T.astype(np.int64))
+    order = e.order[0].cpu().numpy().astype(np.int64) & 0xffff
+    assert np.array_equal(order, np.argsort(code, axis=1, kind="stable"))
+
+
+def _median_ms(run, n=5):
+    times = []
+    for _ in range(n + 1):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return float(np.median(times[1:]))
+
+
+# columns that the bucket sort leaves to the full sort: twice a smooth column's time (eleven
+# times it while the full sort of 2048 members indexed its registers at run time)
+@pytest.mark.parametrize("n_members", [200, 1000, 2048])
+def test_crowded_columns_take_no_multiple_of_a_smooth_one(n_members):
+    dims = (50, 50, 8)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n_members)
+    x = torch.randn((n_members, 20000), generator=g, device="cuda")
+    far = x.clone()
+    far[0] = 1e6
+    ms = []
+    for y in (x, far):
+        e = ndf.Ensemble(y, *dims, orders=True)
+        ms.append(_median_ms(lambda: ndf.ndf_prepare(e)))
+    assert ms[1] <= 5.0 * ms[0]
