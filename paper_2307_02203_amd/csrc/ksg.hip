@@ -15,7 +15,8 @@
 //    index), so no query sorts anything; without stored orders every column is
 //    sorted on the fly, which gives the same results;
 //  * for the neighbour search each order is split in two lists: the x order into the
-//    samples below and above the median y rank, the y order likewise by x rank;
+//    samples below and above the median y rank, the y order likewise by x rank (at the end
+//    of a run of equal codes where the median lies in one);
 //  * the k nearest neighbours of a sample are found by walking outwards from its
 //    own position in its list of one order, stopping on each side once the
 //    distance along that coordinate reaches the current k-th distance (under the
@@ -306,18 +307,18 @@ constexpr int kRefill = 16;  // idle lanes that start new walks together
 // Count phase: thread t takes samples t, t + kT, ... and counts the marginals
 // by bucket table and binary search; the partial sums are combined in a fixed
 // order, so the FP64 total is reproducible.
+// nx0: the x order's split_rank.
 template <int K, int W>
-__device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
+__device__ double ksg_pair(const PairLds &S, const Samples &s, int N, int nx0,
                            const uint16_t *__restrict__ perm, int32_t *__restrict__ cnt,
                            bool build_tx) {
     typedef Pair<W> G;
     constexpr int T = G::kT, C = G::kChunks;
     __shared__ double s_part[W];
     __shared__ int s_cy[C], s_cx[C];   // samples of the upper half per chunk of an order
-    __shared__ int s_edge[4];          // x at ranks n0 - 1, n0; y likewise
+    __shared__ int s_edge[4];          // x at ranks nx0 - 1, nx0; y at ny0 - 1, ny0
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n0 = N / 2, n1 = N - n0;
     const int LY = list_entries(N);    // first entry of the y order's lists
 
     // y codes in y order, y ranks, halves of the y order
@@ -328,12 +329,9 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
         if (j < N) {
             S.eps[j] = s.y[i];
             S.yrank[s.pj[i]] = (uint16_t)j;
-            if (j == n0 - 1 || j == n0) {
-                s_edge[j - n0 + 1] = s.x[i];  // here j is a rank of the x order
-                s_edge[j - n0 + 3] = s.y[i];
-            }
+            if (j == nx0 - 1 || j == nx0) s_edge[j - nx0 + 1] = s.x[i];  // j: rank of the x order
         }
-        my[i] = __ballot(j < N && s.pj[i] >= n0);
+        my[i] = __ballot(j < N && s.pj[i] >= nx0);
         if (lane == 0) s_cy[i * W + wave] = __popcll(my[i]);
     }
     tab_fill<W>(S.Ty, N);
@@ -341,6 +339,8 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
     __syncthreads();
 
     // the y order's lists; the x order's halves
+    const int ny0 = __builtin_amdgcn_readfirstlane(split_rank(S.eps, N));
+    if (tid < 2) s_edge[2 + tid] = S.eps[ny0 - 1 + tid];
     const int py = chunk_prefix<C>(s_cy);
     int yv[kPer], jr[kPer];
     uint64_t mx[kPer];
@@ -350,14 +350,14 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
         const int p = tid + T * i;
         const int q1 = __builtin_amdgcn_readlane(py, i * W + wave) + mask_below(my[i]);
         if (p < N) {  // here p is a rank of the y order
-            const int at = LY + list_place(s.pj[i] >= n0, p, q1, n0, n1);
+            const int at = LY + list_place(s.pj[i] >= nx0, p, q1, nx0, N - nx0);
             S.lists[kPad + at] = make_int2(s.y[i], s.xj[i]);
             S.other[s.pj[i]] = (uint16_t)at;
         }
         jr[i] = p < N ? min((int)S.yrank[p], N - 1) : 0;
         yv[i] = S.eps[jr[i]];
         if (p < N && spread_at(S.eps, jr[i], N) > s.sx[i]) in_y |= 1u << i;
-        mx[i] = __ballot(p < N && jr[i] >= n0);
+        mx[i] = __ballot(p < N && jr[i] >= ny0);
         if (lane == 0) s_cx[i * W + wave] = __popcll(mx[i]);
     }
     tab_scatter<W>(S.eps, S.Ty, N);
@@ -371,15 +371,15 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
         const int p = tid + T * i;
         const int q1 = __builtin_amdgcn_readlane(px, i * W + wave) + mask_below(mx[i]);
         if (p < N) {
-            const bool up = jr[i] >= n0;
-            const int at = list_place(up, p, q1, n0, n1);
+            const bool up = jr[i] >= ny0;
+            const int at = list_place(up, p, q1, ny0, N - ny0);
             S.lists[kPad + at] = make_int2(s.x[i], yv[i]);
-            int start = at, sum = place_sum(0, n0, p);
+            int start = at, sum = place_sum(0, ny0, p);
             int gap = up ? yv[i] - s_edge[2] : s_edge[3] - yv[i];
             if (in_y >> i & 1) {
                 start = S.other[p];
-                sum = place_sum(LY, n0, jr[i]);
-                gap = p >= n0 ? s.x[i] - s_edge[0] : s_edge[1] - s.x[i];
+                sum = place_sum(LY, nx0, jr[i]);
+                gap = p >= nx0 ? s.x[i] - s_edge[0] : s_edge[1] - s.x[i];
             }
             S.other[p] = (uint16_t)walk_other(sum - start, LY);
             S.eps[p] = (int)pack_start(start, gap);
@@ -388,7 +388,8 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
     if (tid < 8 * kPad) {
         // pads 0..3 of each order: left and right of the two lists
         const int pad = (tid >> 2) & 3, u = tid & 3;
-        const int at = pad_place(pad, tid >= 4 * kPad ? LY : 0, n0, n1) + u;
+        const int n0 = tid >= 4 * kPad ? nx0 : ny0;
+        const int at = pad_place(pad, tid >= 4 * kPad ? LY : 0, n0, N - n0) + u;
         S.lists[at] = make_int2(pad_code(pad), 0);
     }
     if (wave == 0) tab_scan<W>(S.Ty);
@@ -399,7 +400,7 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N,
     typedef __attribute__((address_space(3))) const i32x2 lds_int2;
     lds_int2 *const base = (lds_int2 *)reinterpret_cast<i32x2 *>(S.lists);
     lds_int2 *const endL = base;                  // four sentinels: a finished left side
-    lds_int2 *const endR = base + pad_place(3, 0, n0, n1);  // ... and right side
+    lds_int2 *const endR = base + pad_place(3, 0, ny0, N - ny0);  // ... and right side
     const int nchunks = (N + 63) >> 6;
     const int mine = 64 * ((nchunks - wave + W - 1) / W);  // this wave's share, whole chunks
     // first sample of the wave's ci-th chunk, from the middle outwards; the partial
@@ -712,6 +713,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
         tab_scatter<W>(xl, S.Tx, N);
 #pragma unroll
         for (int i = 0; i < kPer; ++i) s.sx[i] = spread_at(xl, min(tid + T * i, N - 1), N);
+        const int nx0 = __builtin_amdgcn_readfirstlane(split_rank(xl, N));
         __syncthreads();
         if (tid < 64) tab_scan<W>(S.Tx);
         __syncthreads();
@@ -735,7 +737,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
                 s.xj[i] = cr[m[i]];
                 s.pj[i] = min((int)invp[m[i]], N - 1);
             }
-            const double acc = ksg_pair<K, W>(S, s, N, perm, cnt, false);
+            const double acc = ksg_pair<K, W>(S, s, N, nx0, perm, cnt, false);
             if (tid == 0) out[(int64_t)r * V + q] = (float)(base - acc / (double)N);
         }
     }
@@ -800,7 +802,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) voi
             s.sx[i] = spread_at(xl, min(tid + T * i, N - 1), N);
             s.pj[i] = min((int)inv[mb[i]], N - 1);
         }
-        const double acc = ksg_pair<K, W>(S, s, N, perm, cnt, true);
+        const int nx0 = __builtin_amdgcn_readfirstlane(split_rank(xl, N));
+        const double acc = ksg_pair<K, W>(S, s, N, nx0, perm, cnt, true);
         if (tid == 0) out[b] = (float)(base - acc / (double)N);
     }
 }

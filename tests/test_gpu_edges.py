@@ -291,3 +291,76 @@ def test_crowded_columns_take_no_multiple_of_a_smooth_one(n_members):
         e = ndf.Ensemble(y, *dims, orders=True)
         ms.append(_median_ms(lambda: ndf.ndf_prepare(e)))
     assert ms[1] <= 5.0 * ms[0]
+
+
+def _runs_across_the_median(n_members, n_vertices, rng):
+    """Columns with a run of equal values across the middle of their order: at its lower end,
+    its upper end, inside, nearly all of it, a few values in all, and none."""
+    x = rng.standard_normal((n_members, n_vertices)).astype(np.float32)
+    for v in range(n_vertices):
+        c = x[:, v]
+        kind = v % 8
+        if kind == 0:
+            x[:, v] = np.maximum(c, np.quantile(c, 0.52))
+        elif kind == 1:
+            x[:, v] = np.minimum(c, np.quantile(c, 0.48))
+        elif kind == 2:
+            x[:, v] = np.clip(c, *np.quantile(c, [0.3, 0.9])) * np.where(
+                np.abs(c) < 2.0, 1.0, 1.5)
+        elif kind == 3:
+            x[:, v] = np.where(c > np.quantile(c, 0.9), c, 0.0)
+        elif kind == 4:
+            x[:, v] = c > 0
+        elif kind == 5:
+            x[:, v] = rng.integers(0, 4, n_members)
+        elif kind == 6:
+            lo, hi = np.quantile(c, [0.5 - 0.5 / 16, 0.5 + 0.5 / 16])  # about kLongRun
+            x[:, v] = np.where((c > lo) & (c < hi), 0.0, c)
+        if x[:, v].min() == x[:, v].max():
+            x[0, v] += 1.0
+    return x
+
+
+# members around a wave and every workgroup size, k from 1 to the most, stored orders and none
+@pytest.mark.parametrize("n_members,k", [(3, 1), (9, 8), (16, 4), (33, 3), (65, 8), (257, 4),
+                                         (1000, 8), (1025, 2), (2048, 4)])
+@pytest.mark.parametrize("orders", [True, False])
+def test_ksg_counts_with_runs_across_the_median(n_members, k, orders):
+    rng = np.random.default_rng(11 * n_members + k)
+    x = _runs_across_the_median(n_members, 16, rng)
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), 4, 2, 2, orders=orders)
+    ndf.ndf_prepare(e)
+    code = e.code[0].cpu().numpy().astype(np.int64)
+    refs = [0, 3, 4, 5, 7]
+    mi, cnt = ndf.ksg_field(e, refs, k=k, counts=True)
+    pairs = np.array([[a, b] for a in refs for b in range(16)])
+    pmi, pcnt = ndf.ksg_pairs(e, pairs, k=k, counts=True)
+    assert torch.equal(mi.reshape(-1), pmi)
+    assert torch.equal(cnt.reshape(-1, 2, n_members), pcnt)
+    cnt = cnt.cpu().numpy()
+    for i, r in enumerate(refs):
+        dx = np.abs(code[r][:, None] - code[r][None])
+        for v in range(16):
+            dy = np.abs(code[v][:, None] - code[v][None])
+            d = np.maximum(dx, dy)
+            np.fill_diagonal(d, 1 << 40)
+            eps = np.partition(d, k - 1, axis=1)[:, k - 1:k]
+            own = (eps[:, 0] > 0).astype(np.int64)
+            assert np.array_equal(cnt[i, v, 0], (dx < eps).sum(1) - own), (r, v)
+            assert np.array_equal(cnt[i, v, 1], (dy < eps).sum(1) - own), (r, v)
+
+
+# fields with many zeros: a run cut at the median took 1.5 times a smooth ensemble's time, kept
+# whole it takes 0.8 times
+def test_ksg_of_many_zeros_takes_no_longer_than_smooth():
+    dims = (50, 50, 8)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x = torch.randn((1000, 20000), generator=g, device="cuda")
+    zeros = torch.where(x > 1.28, x, torch.zeros_like(x))
+    ms = []
+    for y in (x, zeros):
+        e = ndf.Ensemble(y, *dims, orders=True)
+        ndf.ndf_prepare(e)
+        ms.append(_median_ms(lambda: ndf.ksg_field(e, [10000], k=8)))
+    assert ms[1] <= 1.2 * ms[0]

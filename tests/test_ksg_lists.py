@@ -42,8 +42,8 @@ static void walk(const std::vector<int> &lists, int me, int L, int R) {
 
 int main(int argc, char **argv) {
     const int N = atoi(argv[1]);
-    const int n0 = N / 2, n1 = N - n0, E = list_entries(N);
-    std::mt19937 rng(N);
+    const int n0 = atoi(argv[2]), n1 = N - n0, E = list_entries(N);
+    std::mt19937 rng(N + n0);
     // prepared orders: y ranks of the x order's samples
     std::vector<int> jr(N);
     for (int i = 0; i < N; ++i) jr[i] = i;
@@ -101,9 +101,10 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("n_members", [2, 3, 5, 64, 257, 1000, 2048])
-def test_walks_stay_in_the_lists(program, n_members):
-    r = subprocess.run([str(program), str(n_members)], capture_output=True, text=True, check=True,
+@pytest.mark.parametrize("n_members,n0", [(2, 1), (3, 1), (5, 2), (64, 32), (64, 63), (257, 128),
+                                          (257, 1), (1000, 500), (1000, 930), (2048, 1024)])
+def test_walks_stay_in_the_lists(program, n_members, n0):
+    r = subprocess.run([str(program), str(n_members), str(n0)], capture_output=True, text=True, check=True,
                        timeout=100)
     walks, reads_out, endless, changed = map(int, r.stdout.split())
     assert walks > 10000
