@@ -144,7 +144,9 @@ const char *ndf_status_string(int status);
 /* Workspace bytes for `op`.  `ens` is used by the PEARSON/KSG ops, `net` by
  * TRAIN/INFER; n = n_ref for the field ops, B (pairs per step) for TRAIN and
  * KSG_POINTS.
- * `prec` as the call will use it.  Returns 0 for an invalid request. */
+ * `prec` as the call will use it.  Returns 0 for an invalid request.
+ * The calls demand these sizes, of which FP32 PEARSON_FIELD and KSG_PAIRS use
+ * nothing any more, and KSG_FIELD, KSG_POINTS and INFER not all. */
 size_t ndf_workspace_bytes(int32_t op, const ndf_ensemble *ens, const ndf_net_config *net,
                            int64_t n, int32_t prec);
 

@@ -640,13 +640,15 @@ __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
 }
 
 // Waves per SIMD the registers are held to: of E = 16 four waves cover the LDS latencies
-// better than three of 144 registers (3.31 -> 2.95 ms); five and more spill (12 ms).
+// better than three of 144 registers (3.31 -> 2.95 ms before code 0 had its own bucket);
+// five and more spill (12 ms).
 constexpr int order_waves(int E) { return E == 16 ? 4 : 1; }
 
-// One column per wave, N <= 64 E.  Bound by VALU issue (779 per column of 1000 members)
-// and LDS beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 -> 2.95 ms
-// (3.6 TB/s) against a register bitonic sort of every column.  Holding the place in the
-// code's word and reading the counters twice took fewer registers, but more LDS: 3.3 ms.
+// One column per wave, N <= 64 E.  Bound by VALU issue (860 per column of 1000 members)
+// and LDS beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 -> 3.07 ms
+// (3.4 TB/s) against a register bitonic sort of every column, 704,000 of 2048 members (2040
+// VALU) 7.7 ms.  Holding the place in the code's word and reading the counters twice took
+// fewer registers, but more LDS: 3.3 against 2.95 ms then.
 template <int E>
 __global__ __launch_bounds__(kKsgThreads, order_waves(E)) void ksg_order_kernel(const int32_t *__restrict__ code,
                                                                 int N, int64_t ncol,
@@ -815,7 +817,8 @@ static int p2(int n) {
     return p;
 }
 
-// Workspace: FP64 [N + 1] (unused: the harmonic numbers are a constant) | refs |
+// Workspace: FP64 [N + 1] (unused: the harmonic numbers are a constant; the size stays what
+// callers have laid out) | refs |
 // x codes in x order [n_ref][N] | x-order members [n_ref][N] | inverse x permutation
 // [n_ref][N].
 size_t ksg_field_ws_bytes(int N, int n_ref) {

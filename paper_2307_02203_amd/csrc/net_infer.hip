@@ -98,7 +98,8 @@ size_t net_qparam_bytes(const ndf_net_config *c, int prec) {
 }
 
 // Workspace of the calls that decode from given or cached query latents: the
-// reference latents [n_ref][128] FP32 and the reference list.
+// reference latents [n_ref][128] FP32, and room for a reference list that no kernel uses any
+// more (the size stays what callers have laid out).
 size_t net_infer_lat_ws_bytes(int64_t n_ref) {
     return align_up((size_t)n_ref * kH * sizeof(float), 256) +
            align_up((size_t)n_ref * sizeof(int64_t), 256);

@@ -1098,7 +1098,6 @@ struct FusedArgs {
     const float *pos;
     const float *targets;
     int64_t B;
-    float inv_b;
     // slabs: enc = [2 T] (block 2 t + q), dec = [T]
     u32x4 *h0, *h1, *h2, *m, *d1, *d2, *da5, *da4, *dlat, *da2, *da1;
     f32x4 *lat;     // FP32 latents [2 T][4 ob][4 g][64]
@@ -2087,8 +2086,8 @@ static FusedWS carve_fused(const ndf_net_config *c, void *ws, int64_t B) {
 }
 
 // One workgroup per 32-pair tile up to one per CU (a workgroup's 140 KB of weights fill a
-// CU's LDS), then more tiles per workgroup, and two rounds of workgroups once every wave
-// of one round has two tiles.
+// CU's LDS), then a tile for each of its waves, and two rounds of workgroups once one
+// round's waves would have more than one.
 static unsigned fused_blocks(int64_t B) {
     const int64_t T = ceil_div(B, 32);
     return (unsigned)(T < 256 ? T : T <= 256 * kTW ? 256 : kFusedBlocksMax);
@@ -2105,11 +2104,21 @@ static size_t tile_scratch(int64_t rows, int64_t tiles, int rows_wg, size_t *lis
 // where it is the faster one by this model (us; measured on grids of 16 x 14 x 5 to
 // 400 x 400 x 11).  Directly, a level takes 0.25 ns per row (0.45 in tables far beyond the
 // L2s; 0.15 at vertices of a level of the data grid's size, where a row has one corner)
-// and, since adds to one cell follow each other, 150 ns per row and cell.  Sorted: the sort 12 us and 0.023 ns per row, a boxed row
-// 0.106 us in a workgroup's chain (512 workgroups run at once) and 1/32 ns per cell of
-// every workgroup's boxes, beside which the levels without boxes are added to.  Tiles of
-// three depths and nearly square footprints are tried for the one to three coarsest dense
-// levels, as far as their boxes stay within kTileLds and the lists within `scratch` bytes.
+// and, since adds to one cell follow each other, 150 ns per row and cell.  Sorted: the
+// sort 12 us and 0.023 ns per row, a boxed row 0.106 us in a workgroup's chain (512
+// workgroups run at once) and 1/32 ns per cell of every workgroup's boxes, beside which
+// the levels without boxes are added to.  Tiles of three depths and nearly square
+// footprints (of up to 400 vertices; a longer axis is cut) are tried for the one to three
+// coarsest dense levels, as far as the lists stay within `scratch` bytes and, in order of
+// growing edges, up to the first whose boxes exceed kTileLds.  The one smaller footprint
+// that may follow it is left out on purpose: on the 7 of 3000 random grids tried where the
+// model prefers it, its boxes nearly fill kTileLds and the step measured 2 to 11 % slower
+// (43 x 26 x 40 vertices, tables of 2^16, 195651 pairs: 634 -> 691 us; 544 x 260 x 11 at
+// 44623 pairs of positions: 246 -> 273).  The model spreads the rows evenly over the
+// tiles.  Rows crowded on a few cells are mostly still faster sorted (40000 pairs of one
+// vertex of 250 x 352 x 20: 1171 us directly, 392 sorted); slower were 40000 pairs of
+// positions in a twentieth of 37 x 29 x 11 (1190 directly, 1348 sorted) and 4000 pairs of
+// one vertex there (201 and 214).
 static bool tile_plan(const ndf_net_config *c, const GridGeom &g, int64_t rows, bool vertices,
                       size_t scratch, TilePlan &best) {
     if (rows < kMinSorted || rows >= (1ll << 31)) return false;
@@ -2256,7 +2265,6 @@ static FusedArgs fused_args(const ndf_net_config *c, const NetOffsets &o, const 
     a.pos = pos;
     a.targets = targets;
     a.B = B;
-    a.inv_b = 1.f / (float)B;
     a.h0 = t.h0; a.h1 = t.h1; a.h2 = t.h2; a.m = t.m; a.d1 = t.d1; a.d2 = t.d2;
     a.da5 = t.da5; a.da4 = t.da4; a.dlat = t.dlat; a.da2 = t.da2; a.da1 = t.da1;
     a.lat = t.lat;

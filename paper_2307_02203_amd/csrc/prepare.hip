@@ -7,9 +7,9 @@
 // multiply, divide) and round-half-even, so they are the same integers on any
 // conforming implementation; all later KSG distances are exact int32.
 //
-// Up to 1024 members (prepare_kernel) a workgroup reads its 32 vertices' members once
+// Up to 1039 members (prepare_kernel) a workgroup reads its 32 vertices' members once
 // and keeps them in registers for both passes (sum / min / max, then centred squares and
-// codes); more members are read twice (prepare_long_kernel).  The ensemble
+// codes); more members, and few ones alone, are read twice (prepare_long_kernel).  The ensemble
 // is member-major, so each member row contributes a coalesced segment; codes, and the
 // vertex-major copy of x where the caller wants one, leave through an LDS transpose.
 #include "order.hpp"
@@ -18,7 +18,7 @@
 
 namespace ndf {
 
-// ------------------------------------------------------- up to 1024 members ----
+// ------------------------------------------------------- up to 1039 members ----
 // Thread (vertex vl, phase ph) of eight waves holds members ph, ph + 16, ... (up to E, and
 // one of the last partial row) of vertex vl in registers, every load in flight at once;
 // two workgroups of eight waves per CU cover each other's load and coding phases.
@@ -209,17 +209,15 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
     }
 }
 
-// --------------------------------------------------- more than 1024 members ----
+// ------------------------------------- more than 1039 members, or few alone ----
 // One workgroup owns 64 consecutive vertices of one variable and reads their
 // members twice (sum / min / max, then centred squares and codes).  Each thread keeps 8
 // (first pass) or 16 (second pass) of its member loads in flight; one load at a time
 // left the kernel latency-bound at 3.3 TB/s.  (Two vertices per thread with 8-byte loads
 // measured slower: the larger tile cut the resident workgroups per CU.)
-constexpr int kPrepVW = 1;                    // consecutive vertices per thread (1 or 2)
-constexpr int kPrepG = 64;                    // vertex groups per workgroup
-constexpr int kPrepV = kPrepG * kPrepVW;      // vertices per workgroup
-constexpr int kPrepPh = 4;                    // member phases per vertex group
-constexpr int kPrepThreads = kPrepG * kPrepPh;
+constexpr int kPrepV = 64;                    // vertices per workgroup
+constexpr int kPrepPh = 4;                    // member phases per vertex
+constexpr int kPrepThreads = kPrepV * kPrepPh;
 
 __global__ __launch_bounds__(kPrepThreads) void prepare_long_kernel(
     const float *__restrict__ x, int N, int64_t V, double *__restrict__ mean,
@@ -228,12 +226,10 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_long_kernel(
     const int var = blockIdx.y;
     const float *xv = x + (int64_t)var * N * V;
     const int t = threadIdx.x;
-    const int vg = t % kPrepG;
-    const int ph = t / kPrepG;
+    const int vl = t % kPrepV;
+    const int ph = t / kPrepV;
     const int64_t v0 = (int64_t)blockIdx.x * kPrepV;
-    const int64_t vb = v0 + kPrepVW * vg;  // this thread's first vertex
-    // 8-byte loads need V even (every member row then starts 8-byte aligned)
-    const bool pairs = (V % 2) == 0;
+    const int64_t v = v0 + vl;
 
     __shared__ double s_sum[kPrepPh][kPrepV];
     __shared__ float s_lo[kPrepPh][kPrepV];
@@ -241,116 +237,73 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_long_kernel(
     __shared__ int s_bad[kPrepPh][kPrepV];
     __shared__ int32_t s_tile[64][kPrepV + 1];
 
-    auto load = [&](int m, float (&a)[kPrepVW]) {
-        const float *row = xv + (int64_t)m * V;
-        if (kPrepVW == 2 && pairs && vb + 1 < V) {
-            const f32x2 q = *reinterpret_cast<const f32x2 *>(row + vb);
-            a[0] = q[0];
-            a[1] = q[1];
-        } else {
-#pragma unroll
-            for (int j = 0; j < kPrepVW; ++j) a[j] = vb + j < V ? row[vb + j] : 0.f;
-        }
-    };
-
     // pass 1: sum, min, max, finiteness
-    double sum[kPrepVW];
-    float lo[kPrepVW], hi[kPrepVW];
-    int bad[kPrepVW];
-#pragma unroll
-    for (int j = 0; j < kPrepVW; ++j) {
-        sum[j] = 0.0;
-        lo[j] = INFINITY;
-        hi[j] = -INFINITY;
-        bad[j] = 0;
-    }
-    auto accumulate = [&](const float (&a)[kPrepVW]) {
-#pragma unroll
-        for (int j = 0; j < kPrepVW; ++j) {
-            sum[j] += (double)a[j];
-            lo[j] = fminf(lo[j], a[j]);
-            hi[j] = fmaxf(hi[j], a[j]);
-            bad[j] |= !isfinite(a[j]);
-        }
+    double sum = 0.0;
+    float lo = INFINITY, hi = -INFINITY;
+    int bad = 0;
+    auto accumulate = [&](float a) {
+        sum += (double)a;
+        lo = fminf(lo, a);
+        hi = fmaxf(hi, a);
+        bad |= !isfinite(a);
     };
-    if (vb < V) {
+    if (v < V) {
         // eight members' loads in flight at a time; the sums keep member order
         constexpr int U = 8;
         int m = ph;
         for (; m + kPrepPh * (U - 1) < N; m += kPrepPh * U) {
-            float a[U][kPrepVW];
+            float a[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) load(m + kPrepPh * u, a[u]);
+            for (int u = 0; u < U; ++u) a[u] = xv[(int64_t)(m + kPrepPh * u) * V + v];
 #pragma unroll
             for (int u = 0; u < U; ++u) accumulate(a[u]);
         }
-        for (; m < N; m += kPrepPh) {
-            float a[kPrepVW];
-            load(m, a);
-            accumulate(a);
-        }
+        for (; m < N; m += kPrepPh) accumulate(xv[(int64_t)m * V + v]);
     }
-#pragma unroll
-    for (int j = 0; j < kPrepVW; ++j) {
-        const int vl = kPrepVW * vg + j;
-        s_sum[ph][vl] = sum[j];
-        s_lo[ph][vl] = lo[j];
-        s_hi[ph][vl] = hi[j];
-        s_bad[ph][vl] = bad[j];
-    }
+    s_sum[ph][vl] = sum;
+    s_lo[ph][vl] = lo;
+    s_hi[ph][vl] = hi;
+    s_bad[ph][vl] = bad;
     __syncthreads();
-    double mu[kPrepVW], dlo[kPrepVW], scale[kPrepVW];
-    bool flat[kPrepVW];
-#pragma unroll
-    for (int j = 0; j < kPrepVW; ++j) {
-        const int vl = kPrepVW * vg + j;
-        double sm = 0.0;
-        float l = INFINITY, h = -INFINITY;
-        int b = 0;
-        for (int p = 0; p < kPrepPh; ++p) {
-            sm += s_sum[p][vl];
-            l = fminf(l, s_lo[p][vl]);
-            h = fmaxf(h, s_hi[p][vl]);
-            b |= s_bad[p][vl];
-        }
-        mu[j] = sm / (double)N;
-        flat[j] = !(h > l);
-        dlo[j] = (double)l;
-        scale[j] = flat[j] ? 0.0 : 8388608.0 / ((double)h - dlo[j]);
-        bad[j] = b;
+    sum = 0.0;
+    lo = INFINITY;
+    hi = -INFINITY;
+    bad = 0;
+    for (int p = 0; p < kPrepPh; ++p) {
+        sum += s_sum[p][vl];
+        lo = fminf(lo, s_lo[p][vl]);
+        hi = fmaxf(hi, s_hi[p][vl]);
+        bad |= s_bad[p][vl];
     }
+    const double mu = sum / (double)N;
+    const bool flat = !(hi > lo);
+    const double dlo = (double)lo;
+    const double scale = flat ? 0.0 : 8388608.0 / ((double)hi - dlo);
     __syncthreads();
 
     // pass 2: centred sum of squares and the codes, transposed through LDS into
     // vertex-major rows.  A thread visits members ph, ph + 4, ... in increasing
     // order, so its FP64 sum is the plain two-pass one.
     int32_t *cv = code + (int64_t)var * V * N;
-    double ss[kPrepVW];
-#pragma unroll
-    for (int j = 0; j < kPrepVW; ++j) ss[j] = 0.0;
+    double ss = 0.0;
     for (int m0 = 0; m0 < N; m0 += 64) {
         // the tile's 16 loads of this thread in flight together
-        float at[64 / kPrepPh][kPrepVW];
+        float a[64 / kPrepPh];
 #pragma unroll
         for (int i = 0; i < 64 / kPrepPh; ++i) {
             const int m = m0 + ph + kPrepPh * i;
-            if (vb < V && m < N) load(m, at[i]);
+            if (v < V && m < N) a[i] = xv[(int64_t)m * V + v];
         }
 #pragma unroll
         for (int i = 0; i < 64 / kPrepPh; ++i) {
             const int mm = ph + kPrepPh * i;
-            const int m = m0 + mm;
-            const float (&a)[kPrepVW] = at[i];
-#pragma unroll
-            for (int j = 0; j < kPrepVW; ++j) {
-                int32_t c = 0;
-                if (vb + j < V && m < N) {
-                    const double d = (double)a[j] - mu[j];
-                    ss[j] += d * d;
-                    if (!flat[j]) c = (int32_t)__builtin_rint(((double)a[j] - dlo[j]) * scale[j]);
-                }
-                s_tile[mm][kPrepVW * vg + j] = c;
+            int32_t c = 0;
+            if (v < V && m0 + mm < N) {
+                const double d = (double)a[i] - mu;
+                ss += d * d;
+                if (!flat) c = (int32_t)__builtin_rint(((double)a[i] - dlo) * scale);
             }
+            s_tile[mm][vl] = c;
         }
         __syncthreads();
         // kPrepV rows (vertices) of up to 64 members; 16 threads per row, 4 members each
@@ -376,24 +329,18 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_long_kernel(
         }
         __syncthreads();
     }
-#pragma unroll
-    for (int j = 0; j < kPrepVW; ++j) s_sum[ph][kPrepVW * vg + j] = ss[j];
+    s_sum[ph][vl] = ss;
     __syncthreads();
-    if (ph == 0) {
-#pragma unroll
-        for (int j = 0; j < kPrepVW; ++j) {
-            const int64_t v = vb + j;
-            if (v >= V) continue;
-            double s2 = 0.0;
-            for (int p = 0; p < kPrepPh; ++p) s2 += s_sum[p][kPrepVW * vg + j];
-            const double var_pop = s2 / (double)N;
-            mean[(int64_t)var * V + v] = mu[j];
-            inv_std[(int64_t)var * V + v] = (var_pop > 0.0 && !flat[j]) ? 1.0 / sqrt(var_pop) : 0.0;
-            flags[(int64_t)var * V + v] =
-                (bad[j] ? NDF_FLAG_NONFINITE : 0) | (flat[j] ? NDF_FLAG_CONSTANT : 0);
-            // every writer stores the same value, so the unordered stores agree
-            if (bad[j] && status) *status = NDF_E_NONFINITE;
-        }
+    if (ph == 0 && v < V) {
+        double s2 = 0.0;
+        for (int p = 0; p < kPrepPh; ++p) s2 += s_sum[p][vl];
+        const double var_pop = s2 / (double)N;
+        mean[(int64_t)var * V + v] = mu;
+        inv_std[(int64_t)var * V + v] = (var_pop > 0.0 && !flat) ? 1.0 / sqrt(var_pop) : 0.0;
+        flags[(int64_t)var * V + v] =
+            (bad ? NDF_FLAG_NONFINITE : 0) | (flat ? NDF_FLAG_CONSTANT : 0);
+        // every writer stores the same value, so the unordered stores agree
+        if (bad && status) *status = NDF_E_NONFINITE;
     }
 }
 
@@ -468,9 +415,9 @@ int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStre
                   (unsigned)ceil_div(tiles, kRegGridX));
     // the fewest registers that hold a thread's members: waves in flight against loads
     // past the last member.  Up to 512 members the columns are sorted here too, from codes
-    // kept in registers (450 members of 1.76M vertices 2.82 -> 2.62 ms, 250 members 1.40 ->
-    // 1.30); with more the codes of a wave's four columns spill (1000 members 7.74 ms
-    // against 6.08 with a kernel of its own).
+    // kept in registers (450 members of 1.76M vertices 2.87 -> 2.63 ms, 250 members 1.43 ->
+    // 1.35); with more the codes of a wave's four columns spill (1000 members 6.52 ms
+    // against 6.22 with a kernel of its own).
     *sorted = false;
     // Few members with neither orders nor the vertex-major copy: the two-read kernel, which
     // holds them in one 64-member tile (its second read comes from the caches) and spends
