@@ -364,3 +364,12 @@ def test_ksg_of_many_zeros_takes_no_longer_than_smooth():
         ndf.ndf_prepare(e)
         ms.append(_median_ms(lambda: ndf.ksg_field(e, [10000], k=8)))
     assert ms[1] <= 1.2 * ms[0]
+
+
+# member counts on both sides of every register count of the one-read kernel (16 E members and
+# up to 15 more: E = 4, 8, 16, 32, 48, 64) and of the kernel that reads twice
+@pytest.mark.parametrize("n_members", [79, 80, 143, 144, 271, 272, 527, 528, 783, 784, 1039, 1040])
+@pytest.mark.parametrize("dims", [(7, 3, 3), (4, 4, 5)])
+@pytest.mark.parametrize("orders,transposed", [(False, False), (False, True), (True, False)])
+def test_prepare_where_the_register_count_changes(n_members, dims, orders, transposed):
+    _check_prepare(n_members, dims, orders, transposed)
