@@ -373,3 +373,84 @@ def test_ksg_of_many_zeros_takes_no_longer_than_smooth():
 @pytest.mark.parametrize("orders,transposed", [(False, False), (False, True), (True, False)])
 def test_prepare_where_the_register_count_changes(n_members, dims, orders, transposed):
     _check_prepare(n_members, dims, orders, transposed)
+
+
+def _split_bf16_ensemble(n_members, dims):
+    """Members whose last vertex holds a NaN and the one before an infinity."""
+    V = dims[0] * dims[1] * dims[2]
+    rng = np.random.default_rng(n_members + V)
+    x = rng.standard_normal((n_members, V)).astype(np.float32)
+    x += rng.standard_normal((n_members, 1)).astype(np.float32) * rng.random(V, dtype=np.float32)
+    x[n_members // 2, V - 1] = np.nan
+    x[n_members - 1, V - 2] = -np.inf
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=False)
+    ndf.ndf_prepare(e)
+    return x, e
+
+
+def _split_bf16_field(e, refs):
+    return ndf.pearson_field(e, [int(r) for r in refs], prec=ndf.NDF_PREC_SPLIT_BF16)
+
+
+def _same_bits(a, b):
+    return torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+def _check_split_bf16(x, refs, got):
+    assert np.all(np.isnan(got[:, -2:]))
+    z = x[:, :-2].astype(np.float64)
+    z = (z - z.mean(0)) / z.std(0)
+    for r, v in enumerate(refs):
+        # hi + lo carries 2^-16 of |z| on either side and lo lo is dropped; FP32 sums of N
+        # terms and FP32 moments
+        tol = (3 * 2.0 ** -16 + (len(x) + 8) * 2.0 ** -24) * np.abs(z[:, v:v + 1] * z).mean(0)
+        assert np.all(np.abs(got[r, :-2] - (z[:, v:v + 1] * z).mean(0)) <= tol), v
+
+
+# 193 references on 185 64-vertex tiles take the one-pass kernel; its k-steps (16 members) run six
+# to an iteration with the rest behind it: 1 to 5 k-steps alone, and 6 to 12 for every rest.
+# Its bits are those of calls of 64, which take the kernel for few waves.
+@pytest.mark.parametrize("n_members", [2, 11, 16, 17, 40, 60, 75, 96, 100, 120, 140, 150, 170,
+                                       192])
+def test_pearson_one_pass_kernel_at_every_kstep_count(n_members):
+    dims, n_ref = (37, 29, 11), 193
+    x, e = _split_bf16_ensemble(n_members, dims)
+    refs = np.linspace(0, x.shape[1] - 3, n_ref).astype(np.int64)
+    got = _split_bf16_field(e, refs)
+    for r0 in range(0, n_ref, 64):
+        assert _same_bits(_split_bf16_field(e, refs[r0:r0 + 64]), got[r0:r0 + 64]), r0
+    at = [0, 63, 64, 127, 128, 191, 192]
+    _check_split_bf16(x, refs[at], got[at].cpu().numpy())
+
+
+# odd and even vertex counts just past the kernel for few waves (1088 waves of 32 references x
+# 64 vertices): 65 references take the one-pass kernel, 64 and 32 the kernels of two and of one
+# block of 32.  One ensemble's fields have the same bits from each, and on the first vertices
+# alone from the kernel for few waves.
+@pytest.mark.parametrize("n_members", [2, 15, 33, 75])
+@pytest.mark.parametrize("dims,part", [((257, 91, 3), (7, 13, 257)), ((256, 91, 3), (8, 32, 91))])
+def test_pearson_split_bf16_kernels_agree(dims, part, n_members):
+    x, e = _split_bf16_ensemble(n_members, dims)
+    n = part[0] * part[1] * part[2]
+    refs = np.linspace(0, n - 1, 65).astype(np.int64)
+    got = _split_bf16_field(e, refs)
+    for m in (1, 32, 33, 64):
+        assert _same_bits(_split_bf16_field(e, refs[:m]), got[:m]), m
+    e2 = ndf.Ensemble(torch.from_numpy(x[:, :n].copy()).cuda(), *part, orders=False)
+    ndf.ndf_prepare(e2)
+    assert _same_bits(_split_bf16_field(e2, refs[:32]), got[:32, :n].contiguous())
+    at = [0, 31, 32, 64]
+    _check_split_bf16(x, refs[at], got[at].cpu().numpy())
+
+
+# 33 to 64 references where calls of 32 still take the kernel for few waves
+@pytest.mark.parametrize("dims", [(129, 91, 3), (130, 90, 3)])
+@pytest.mark.parametrize("n_ref", [33, 64])
+def test_pearson_split_bf16_of_two_blocks(dims, n_ref):
+    x, e = _split_bf16_ensemble(50, dims)
+    refs = np.linspace(0, x.shape[1] - 3, n_ref).astype(np.int64)
+    got = _split_bf16_field(e, refs)
+    for r0 in range(0, n_ref, 32):
+        assert _same_bits(_split_bf16_field(e, refs[r0:r0 + 32]), got[r0:r0 + 32]), r0
+    at = [0, 31, 32, n_ref - 1]
+    _check_split_bf16(x, refs[at], got[at].cpu().numpy())
