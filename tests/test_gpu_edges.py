@@ -454,3 +454,44 @@ def test_pearson_split_bf16_of_two_blocks(dims, n_ref):
         assert _same_bits(_split_bf16_field(e, refs[r0:r0 + 32]), got[r0:r0 + 32]), r0
     at = [0, 31, 32, n_ref - 1]
     _check_split_bf16(x, refs[at], got[at].cpu().numpy())
+
+
+# pair counts past which a training launch changes: more than two encoder tiles per workgroup
+# (16384 pairs of two encoders), two rounds of workgroups (65536) and more than one tile per
+# wave (131072); the last tile half full
+@pytest.mark.parametrize("n_enc,B", [(2, 16400), (2, 65552), (2, 131088), (1, 65552), (1, 131088)])
+@pytest.mark.parametrize("at", [False, True])
+def test_training_of_large_batches(n_enc, B, at):
+    dims = (37, 29, 11)
+    rng = np.random.default_rng(B)
+    lay = gen.NetLayout.for_grid(*dims, n_enc=n_enc)
+    flat = gen.make_net_params(lay, seed=2343, grid_scale=0.5, bias_scale=0.1)
+    c = ndf.net_config(*dims, lay.res, n_enc=n_enc)
+    P = torch.from_numpy(flat).cuda()
+    w = (rng.uniform(-1.0, 1.0, (B, 2, 3)).astype(np.float32) if at
+         else rng.integers(0, dims[0] * dims[1] * dims[2], (B, 2)))
+    where = torch.as_tensor(w, device="cuda")
+    fwd, grad = ((ndf.ndf_net_forward_at, ndf.ndf_net_grad_at) if at
+                 else (ndf.ndf_net_forward, ndf.ndf_net_grad))
+    ws = torch.empty(ndf.train_ws_bytes(c, B), dtype=torch.uint8, device="cuda")
+
+    def run(w):
+        g, y = torch.full_like(P, 7.0), torch.full((len(w),), 7.0, device="cuda")
+        loss = torch.empty(1, device="cuda")
+        t = torch.full((len(w),), 1e3, device="cuda")  # one residual sign for every pair
+        fwd(c, P, w, y, ws)
+        grad(c, P, w, t, g, loss, ws)
+        return g.double(), y, loss.item()
+
+    got, y, loss = run(where)
+    # sixteen batches of equal size: their BF16 operands are scaled by a power of two, so the
+    # rows' outputs and gradients are the same numbers and only the order of the sums differs
+    parts = [run(p.contiguous()) for p in where.chunk(16)]
+    assert torch.equal(y, torch.cat([p[1] for p in parts]))
+    assert abs(loss - np.mean([p[2] for p in parts])) <= 2.0 ** -22 * loss
+    want = sum(p[0] for p in parts) / 16
+    for name, _shape in lay.tensors():
+        a, b = (lay.view(v.cpu().numpy(), name).ravel() for v in (got, want))
+        # at most 2^18 adds to a sum, rounding errors that add up at random (sqrt(2^18) 2^-24
+        # of sum |x|) and sum |x| up to three times |sum x|
+        assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b), name
