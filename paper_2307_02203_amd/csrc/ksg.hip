@@ -644,10 +644,10 @@ __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
 // five and more spill (12 ms).
 constexpr int order_waves(int E) { return E == 16 ? 4 : 1; }
 
-// One column per wave, N <= 64 E.  Bound by VALU issue (860 per column of 1000 members)
-// and LDS beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 -> 3.07 ms
-// (3.4 TB/s) against a register bitonic sort of every column, 704,000 of 2048 members (2040
-// VALU) 7.7 ms.  Holding the place in the code's word and reading the counters twice took
+// One column per wave, N <= 64 E.  Bound by VALU issue (787 per column of 1000 members)
+// and LDS beside 6 B/sample of HBM: 1.76M columns of 1000 members 9.56 -> 3.1 ms
+// (3.4 TB/s) against a register bitonic sort of every column, 704,000 of 2048 members (1966
+// VALU) 7.8 ms.  Holding the place in the code's word and reading the counters twice took
 // fewer registers, but more LDS: 3.3 against 2.95 ms then.
 template <int E>
 __global__ __launch_bounds__(kKsgThreads, order_waves(E)) void ksg_order_kernel(const int32_t *__restrict__ code,
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(kKsgThreads, order_waves(E)) void ksg_order_kernel(
     {
         uint32_t c[E];
         load_codes<E>(code + v * N, N, c);
-        wave_sort_codes<E, 1>(c, N, order + v * N, s_lds[wave]);
+        wave_sort_codes<E, ColumnSort<E>::kLowMask>(c, N, order + v * N, s_lds[wave]);
     }
 }
 

@@ -87,9 +87,10 @@ struct ColumnSort {
     // 2 buckets per slot; 4 at E = 32 so that start, code bits and member fit 32 bits
     static constexpr int kLB = kLN <= 10 ? kLN + 1 : kLN + 2;
     static constexpr int kLow = 23 - kLB;                // code bits inside a bucket
+    static constexpr uint32_t kLowMask = (1u << kLow) - 1;
     static constexpr int kWords = (1 << kLB) / 2;        // two 16-bit counters a word
     static constexpr int kPer = kWords / 64;             // counter words per lane
-    static constexpr int kLds = kWords + 4;              // + the bucket of code 0
+    static constexpr int kLds = kWords + 4;              // + the last bucket
     static_assert(2 * kLN + kLow <= 32, "key bits");
     static_assert(kWords >= 64 * E, "the keys reuse the counters");
 };
@@ -121,18 +122,20 @@ __device__ __forceinline__ void load_codes(const int32_t *__restrict__ c, int N,
     }
 }
 
-// The sort (codes past N are not read); lds: kLds words of the wave, 16-byte aligned.  SUB: 1
-// where the codes come as they are, 0 where the caller has taken 1 off each (1 % less where
-// they come from LDS; off codes loaded from memory it made the compiler wait for one load
-// before the next, 1000 members 2.8 -> 4.1 ms).
-template <int E, uint32_t SUB>
+// The sort (codes past N are not read); lds: kLds words of the wave, 16-byte aligned.  ADD:
+// kLowMask where the codes come as they are, 0 where the caller has added it.  (Without the
+// opaque values below the compiler adds beside every load and waits for one before the
+// next: 1000 members 2.8 -> 4.1 ms.  With the bucket formed again at its second use, each
+// time in three operations, ndf_prepare of 100 to 1000 members took 1 to 3 % more.)
+template <int E, uint32_t ADD>
 __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N,
                                                 uint16_t *__restrict__ o, uint32_t *lds) {
     typedef ColumnSort<E> C;
     const int lane = threadIdx.x & 63;
     auto member = [&](int j) { return sort_member(j, lane); };
-    // bucket of codes 1 .. 2^kLow, the next ones, ..., and last that of code 0
-    auto bucket = [](uint32_t c) { return min((c - SUB) >> C::kLow, 1u << C::kLB); };
+    // codes with kLowMask added: bucket 0 is that of code 0, the next that of codes 1 ..
+    // 2^kLow, the last one ends at 2^23
+    uint32_t t[E];
     // counters to zero
     for (int i = lane; i < C::kLds / 4; i += 64)
         reinterpret_cast<u32x4v *>(lds)[i] = u32x4v{0u, 0u, 0u, 0u};
@@ -141,7 +144,12 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
     uint32_t place[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-        const uint32_t b = bucket(code[j]);
+        // opaque: the addition is not moved up to its load, and t is formed once
+        uint32_t c = code[j];
+        asm volatile("" : "+v"(c));
+        t[j] = min(c + ADD, (1u << 23) + C::kLowMask);
+        asm volatile("" : "+v"(t[j]));
+        const uint32_t b = t[j] >> C::kLow;
         if (member(j) < N) {
             const uint32_t sh = (b & 1) * 16;
             place[j] = (atomicAdd(&lds[b >> 1], 1u << sh) >> sh) & 0xffffu;
@@ -161,8 +169,8 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
         const uint32_t t = __shfl_up(run, d, kWave);
         if (lane >= d) run += t;
     }
-    run += (lds[C::kWords] & 0xffffu) - sum;  // after the samples of code 0
-    if (lane == 0) lds[C::kWords] = 0;        // the start of theirs
+    if (lane == 63) lds[C::kWords] = run;  // start of the last bucket
+    run -= sum;
 #pragma unroll
     for (int i = 0; i < C::kPer; ++i) {
         const uint32_t lo = w[i] & 0xffffu, hi = w[i] >> 16;
@@ -173,11 +181,11 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
     uint32_t k[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-        const uint32_t b = bucket(code[j]);
+        const uint32_t b = t[j] >> C::kLow;
         const uint32_t start = (lds[b >> 1] >> ((b & 1) * 16)) & 0xffffu;
         place[j] += start;
         k[j] = (start << (C::kLow + C::kLN)) |
-               (((code[j] - SUB) & ((1u << C::kLow) - 1)) << C::kLN) | (uint32_t)member(j);
+               ((t[j] & C::kLowMask) << C::kLN) | (uint32_t)member(j);
     }
     wave_lds_fence();  // every start is read: the keys reuse the counters' LDS
 #pragma unroll

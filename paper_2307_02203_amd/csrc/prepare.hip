@@ -147,7 +147,7 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
         ss += d * d;
         return flat ? 0 : (int32_t)__builtin_rint(((double)q - dlo) * scale);
     };
-    uint32_t sc[kCols][OE ? OE : 1];  // this wave's columns: codes minus 1
+    uint32_t sc[kCols][OE ? OE : 1];  // this wave's columns, for wave_sort_codes<OE, 0>
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int m0 = kRegPh * J * k;
@@ -168,7 +168,8 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
 #pragma unroll
                     for (int e = 0; e < kTileCodes; ++e)
                         sc[c][kTileCodes * k + e] =
-                            (uint32_t)s_tile[(kCols * wave + c) * prep_row<J>() + 64 * e + lane] - 1u;
+                            (uint32_t)s_tile[(kCols * wave + c) * prep_row<J>() + 64 * e + lane] +
+                            ColumnSort<OE>::kLowMask;
             }
         }
         if (tv) {
@@ -415,8 +416,8 @@ int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStre
                   (unsigned)ceil_div(tiles, kRegGridX));
     // the fewest registers that hold a thread's members: waves in flight against loads
     // past the last member.  Up to 512 members the columns are sorted here too, from codes
-    // kept in registers (450 members of 1.76M vertices 2.87 -> 2.63 ms, 250 members 1.43 ->
-    // 1.35); with more the codes of a wave's four columns spill (1000 members 6.52 ms
+    // kept in registers (450 members of 1.76M vertices 2.86 -> 2.59 ms, 250 members 1.44 ->
+    // 1.33); with more the codes of a wave's four columns spill (1000 members 6.52 ms
     // against 6.22 with a kernel of its own).
     *sorted = false;
     // Few members with neither orders nor the vertex-major copy: the two-read kernel, which
