@@ -70,16 +70,19 @@ __device__ __forceinline__ void wave_sort_regs32(uint32_t (&k)[E]) {
 // the buckets.
 // Repeated values crowd their buckets.  Code 0, the column's minimum (fields with many
 // zeros), has a bucket of its own, and the counters are taken in member order, so that
-// equal codes lie in order as they come; columns that are still far from sorted after
-// kLook passes (far outliers: many codes in few buckets) go through the full bitonic sort
-// of the same keys at once, the others after kOddEven.  ndf_prepare of 80,000 columns, us,
-// against a bitonic sort of every column: 200 members smooth 63 (130), 90 % zeros 90 (139),
-// lognormal 137 (141); 1000 members 293 (650), 450 (675), 602 (712); 2048 members 1414
-// (3803), 1694 (3639), 2398 (3822).  With one bucket sort for all codes, no early look and
-// members taken four by four, 90 % zeros took 173, 771 and 17,779.
-constexpr int kLook = 2;     // passes (each both parities) before the first look
-constexpr int kOddEven = 8;  // ... and before the full sort at the latest
-constexpr int kFarOff = 16;  // lanes with a pair out of order that end the passes at the look
+// equal codes lie in order as they come.  A column with more than 70 % of its lanes still out
+// of order after kLook passes (far outliers: many codes in few buckets) goes through the full
+// bitonic sort of the same keys at once, others that need more than odd_even_passes (a full
+// sort costs 11 passes at E = 4, 17 to 30 above) then.  ndf_prepare of 80,000 columns, us,
+// against a bitonic sort of every column: 200 members smooth 60 (132), 90 % zeros 88 (139),
+// lognormal 70 (134), Cauchy 132 (140), one member at 10^4 deviations 164 (147); 1000
+// members 284 (659), 447 (681), 351 (672), 606 (732), 740 (720); 2000 members 1491 (3820),
+// 1714 (3665), 1734 (3819), 2542 (3818), 2643 (3830).  A look after two passes at more than 16
+// lanes, and eight passes, sorted many skewed columns in full that a few passes more
+// finish: lognormal 72, 546 and 2435; with no look 2000 members Cauchy took 17,552.
+constexpr int kLook = 3;  // passes (each both parities) before the look
+// ... and before the full sort at the latest
+constexpr int odd_even_passes(int E) { return E <= 4 ? 8 : 12; }
 
 template <int E>
 struct ColumnSort {
@@ -205,7 +208,8 @@ __device__ __forceinline__ void wave_sort_codes(const uint32_t (&code)[E], int N
 #pragma unroll
         for (int j = 0; j + 1 < E; ++j) bad |= k[j] > k[j + 1];
         const int far = __popcll(__ballot(bad));
-        if (far == 0 || pass == kOddEven || (pass == kLook && far > kFarOff)) {
+        if (far == 0 || pass == odd_even_passes(E) ||
+            (pass == kLook && 10 * E * far > 7 * (N + E - 1))) {
             if (far) wave_sort_regs32<E>(k);
             break;
         }
