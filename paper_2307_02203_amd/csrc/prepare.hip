@@ -9,7 +9,7 @@
 //
 // Up to 1039 members (prepare_kernel) a workgroup reads its 32 vertices' members once
 // and keeps them in registers for both passes (sum / min / max, then centred squares and
-// codes); more members, and few ones alone, are read twice (prepare_long_kernel).  The ensemble
+// codes); more members, and few without orders, are read twice (prepare_long_kernel).  The ensemble
 // is member-major, so each member row contributes a coalesced segment; codes, and the
 // vertex-major copy of x where the caller wants one, leave through an LDS transpose.
 #include "order.hpp"
@@ -210,7 +210,7 @@ prepare_kernel(const float *__restrict__ x, int N, int64_t V, double *__restrict
     }
 }
 
-// ------------------------------------- more than 1039 members, or few alone ----
+// ------------------------------------- more than 1039 members, or few ----------
 // One workgroup owns 64 consecutive vertices of one variable and reads their
 // members twice (sum / min / max, then centred squares and codes).  Each thread keeps 8
 // (first pass) or 16 (second pass) of its member loads in flight; one load at a time
@@ -426,7 +426,14 @@ int launch_prepare(const ndf_ensemble *e, int32_t *status, bool *sorted, hipStre
     // two: 2 members 156 / 118, 16 169 / 137, 32 189 / 144, 48 206 / 223, 56 218 / 267, 63
     // 240 / 312, 64 (a whole tile) 227 / 208, 68 252 / 268; 65536 vertices: 2 members
     // 8.5 / 7.0, 48 10.4 / 8.8, 56 10.6 / 10.0, 64 10.7 / 8.7, 68 11.8 / 12.1.
-    const bool two_reads = !e->order && !e->xt && (N <= 48 || N == 64);
+    // With the copy, which the two-read kernel leaves to a launch of its own, up to 16 members
+    // and 32 (whole rows of both kernels' stores) from 2^17 vertices on.  1.76M vertices: 2
+    // members 179 / 129, 4 169 / 110, 15 216 / 204, 16 198 / 177, 17 205 / 225, 20 203 /
+    // 210, 31 256 / 317, 32 226 / 202, 40 239 / 260; 131,072: 2 members 15.9 / 14.6, 16 17.3
+    // / 14.7, 20 17.8 / 15.7, 28 19.0 / 18.2, 32 19.7 / 17.3, 40 20.9 / 20.3; 65536: 2 members
+    // 9.3 / 9.9, 8 9.0 / 8.8; 11,803: 6.4 / 8.6.
+    const bool two_reads =
+        !e->order && (e->xt ? V >= 1 << 17 && (N <= 16 || N == 32) : N <= 48 || N == 64);
 #define NDF_PREP_LAUNCH(E, OE)                                                                   \
     hipLaunchKernelGGL((prepare_kernel<E, OE>), rg, dim3(kRegThreads), 0, st, e->x, N, V, e->mean, \
                        e->inv_std, e->code, e->flags, status, e->xt, e->order)

@@ -366,6 +366,13 @@ def test_ksg_of_many_zeros_takes_no_longer_than_smooth():
     assert ms[1] <= 1.2 * ms[0]
 
 
+# member counts and vertex counts around the line between both kernels with the copy
+@pytest.mark.parametrize("n_members", [2, 15, 16, 17, 31, 32, 33])
+@pytest.mark.parametrize("dims", [(127, 129, 8), (128, 128, 8), (257, 255, 2)])
+def test_prepare_of_few_members_with_the_copy(n_members, dims):
+    _check_prepare(n_members, dims, False, True)
+
+
 # member counts on both sides of every register count of the one-read kernel (16 E members and
 # up to 15 more: E = 4, 8, 16, 32, 48, 64) and of the kernel that reads twice
 @pytest.mark.parametrize("n_members", [79, 80, 143, 144, 271, 272, 527, 528, 783, 784, 1039, 1040])
