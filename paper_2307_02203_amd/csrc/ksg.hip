@@ -501,7 +501,7 @@ __device__ double ksg_pair(const PairLds &S, const Samples &s, int N, int nx0,
         ny = min(max(ny, 0), N - 1);
         acc += kHarmonic.v[nx] + kHarmonic.v[ny];
         if (cnt) {
-            const int m = perm[pp];
+            const int m = order_member(perm[pp], N);
             cnt[m] = nx;
             cnt[N + m] = ny;
         }
@@ -573,9 +573,9 @@ __device__ __forceinline__ void sorted_members(const int32_t *__restrict__ c,
     constexpr int T = Pair<W>::kT;
     if (order) {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) {  // in bounds even if never prepared
+        for (int i = 0; i < kPer; ++i) {
             const int r = tid + T * i;
-            m[i] = r < N ? min((int)order[r], N - 1) : 0;
+            m[i] = r < N ? order_member(order[r], N) : 0;
         }
         return;
     }
@@ -620,7 +620,7 @@ __global__ void ksg_sort_ref_kernel(const int32_t *__restrict__ code,
     if (order) {  // the column's stored order
         const uint16_t *o = order + v * N;
         for (int p = threadIdx.x; p < N; p += kKsgThreads) {
-            const int m = min((int)o[p], N - 1);  // in bounds even if never prepared
+            const int m = order_member(o[p], N);
             xs[(int64_t)r * N + p] = c[m];
             perm[(int64_t)r * N + p] = (uint16_t)m;
             invp[(int64_t)r * N + m] = (uint16_t)p;

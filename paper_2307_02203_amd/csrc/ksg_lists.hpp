@@ -98,6 +98,9 @@ __host__ __device__ constexpr int walk_other(int at, int entries) {
 // from which every sentinel is far.
 __host__ __device__ constexpr int walk_code(int c) { return clamp_int(c, 0, kTopCode); }
 
+// The member at an entry of a stored order: a no-op on prepared orders, else in bounds.
+__host__ __device__ constexpr int order_member(uint16_t m, int N) { return m < N ? m : N - 1; }
+
 // A walk start as one word: place (13 bits) and the distance to the other list in units of
 // 32, rounded down (a list visited for nothing changes no result).
 __host__ __device__ constexpr uint32_t pack_start(int place, int gap) {

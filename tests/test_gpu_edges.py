@@ -502,3 +502,36 @@ def test_training_of_large_batches(n_enc, B, at):
         # at most 2^18 adds to a sum, rounding errors that add up at random (sqrt(2^18) 2^-24
         # of sum |x|) and sum |x| up to three times |sum x|
         assert np.linalg.norm(a - b) <= 1e-4 * np.linalg.norm(b), name
+
+
+# stored orders that were never prepared: the calls end, the counts of a pair stay its own
+# (behind the last pair there is room for any 16-bit member) and the outputs are numbers
+@pytest.mark.parametrize("n_members", [2, 200, 256, 1000, 2048])
+@pytest.mark.parametrize("fill", ["top", "random"])
+def test_ksg_counts_of_unprepared_orders_stay_in_place(n_members, fill):
+    dims, B = (4, 4, 4), 3
+    rng = np.random.default_rng(n_members)
+    x = rng.standard_normal((n_members, 64)).astype(np.float32)
+    e = ndf.Ensemble(torch.from_numpy(x).cuda(), *dims, orders=True)
+    ndf.ndf_prepare(e)
+    bad = (np.full(e.order.shape, -1) if fill == "top"
+           else rng.integers(-32768, 32768, tuple(e.order.shape))).astype(np.int16)
+    e.order.copy_(torch.from_numpy(bad).view(e.order.dtype))
+    pairs = torch.tensor([[0, 1], [5, 5], [63, 2]], device="cuda")
+    out = torch.empty(B, device="cuda")
+    ws = torch.empty(ndf.ndf_workspace_bytes(5, e, None, 1, 0), dtype=torch.uint8, device="cuda")
+    flat = torch.full((B * 2 * n_members + 70000,), 77, dtype=torch.int32, device="cuda")
+    cnt = flat[:B * 2 * n_members].view(B, 2, n_members)
+    ndf.ndf_ksg_mi_pairs(e, 0, 0, pairs, 1, out, cnt, ws)
+    assert torch.all(flat[B * 2 * n_members:] == 77)
+    assert torch.all((cnt >= 0) & (cnt < max(n_members, 78)))
+    assert torch.all(torch.isfinite(out))
+    refs = [0, 63]
+    flat = torch.full((2 * 64 * 2 * n_members + 70000,), 77, dtype=torch.int32, device="cuda")
+    cnt = flat[:2 * 64 * 2 * n_members].view(2, 64, 2, n_members)
+    out = torch.empty((2, 64), device="cuda")
+    ws = torch.empty(ndf.ndf_workspace_bytes(2, e, None, 2, 0), dtype=torch.uint8, device="cuda")
+    ndf.ndf_ksg_mi_field(e, 0, 0, refs, 1, out, cnt, ws)
+    assert torch.all(flat[2 * 64 * 2 * n_members:] == 77)
+    assert torch.all((cnt >= 0) & (cnt < max(n_members, 78)))
+    assert torch.all(torch.isfinite(out))

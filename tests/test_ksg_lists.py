@@ -85,6 +85,10 @@ int main(int argc, char **argv) {
             walk(lists, me, there - kPad, there);
         }
     }
+    for (int m = 0; m < 65536; ++m) {
+        const int got = order_member((uint16_t)m, N);
+        if (got < 0 || got >= N || (m < N && got != m)) ++changed;
+    }
     printf("%ld %ld %ld %ld\n", walks, reads_out, endless, changed);
     return 0;
 }
